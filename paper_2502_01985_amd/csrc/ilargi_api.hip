@@ -71,7 +71,7 @@ struct SourcePlan {
 };
 
 struct Layout {
-  size_t o_gslot = 0, o_gj0 = 0, o_ct_slot = 0, o_ct_j = 0, o_ones = 0, o_tmp_a = 0, o_tmp_b = 0, o_rmm = 0;
+  size_t o_gslot = 0, o_gj0 = 0, o_ones = 0, o_tmp_a = 0, o_tmp_b = 0, o_rmm = 0;
   size_t o_eye = 0;                          // sparse crossprod: a block of identity columns, c_T x min(max_cx, 16)
   size_t o_cn = 0, o_counts = 0, o_rr = 0;   // KMeans / NMF: centroid norms, cluster sizes, two small square matrices
   int64_t max_entries = 0;       // most stored entries of a sparse source (0: every source is dense)
@@ -117,9 +117,8 @@ struct ilargi_plan {
   int star_k = -1;  // two-table star join: the dimension table every target row joins (else -1)
   bool cover_disjoint = false;  // no target column is fed by two sources
   bool cover_full = false;      // every target column is fed and every source reaches every target row
-  bool mat_vec4 = false;  // the grouped column tables of the vectorized join-gather are valid
-  bool mat_flat = false;  // ... and every group is an aligned float4 of its source
-  bool mat_cols = false;  // the per-column feeder tables (at most two feeders per column) are valid
+  bool mat_flat = false;  // every aligned group of four target columns is an aligned float4 of one source, or unfed
+  bool cover_columns = false;   // every target column is fed by some source
   int npairs = 0;
   int64_t pairlist_n[kMaxPairLists] = {};   // entries of the pair lists of the layout
   bool small_gd = false;  // the schema is small enough for the single-workgroup gradient-descent iteration
@@ -253,8 +252,6 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
   lay.o_pairs = take(sizeof(GramAsmPair) * n * (n + 1) / 2);
   lay.o_gslot = take(sizeof(int32_t) * c_T);
   lay.o_gj0 = take(sizeof(int32_t) * c_T);
-  lay.o_ct_slot = take(sizeof(int32_t) * 2 * c_T);
-  lay.o_ct_j = take(sizeof(int32_t) * 2 * c_T);
   lay.o_ones = take(sizeof(float) * c_T);
   lay.o_rmm = take(sizeof(float) * c_T * max_cx);
   lay.o_cn = take(sizeof(float) * max_cx);
@@ -1244,11 +1241,12 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
   {
     pl->cover_disjoint = true;
     pl->cover_full = true;
+    pl->cover_columns = true;
     for (int64_t t = 0; t < c_T; ++t) {
       int feeders = 0;
       for (int k = 0; k < n; ++k) feeders += (!pl->src[k].empty && tcol[k][(size_t)t] >= 0) ? 1 : 0;
       if (feeders > 1) pl->cover_disjoint = false;
-      if (feeders == 0) pl->cover_full = false;
+      if (feeders == 0) pl->cover_full = pl->cover_columns = false;
     }
     for (int k = 0; k < n; ++k)
       if (!pl->src[k].empty && pl->src[k].nnz != r_T) pl->cover_full = false;
@@ -1324,10 +1322,10 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     }
     pl->rowjoin_gd = ok && live >= 2 && r_T >= 1 && bytes_join <= 0.85 * bytes_fact;
   }
-  // join-gather tables: groups of four target columns fed by four consecutive columns of one source
+  // join-gather tables: groups of four target columns fed by four consecutive columns of one source, 16-byte aligned
   if (c_T % 4 == 0) {
     std::vector<int32_t> gslot((size_t)c_T / 4, -1), gj0((size_t)c_T / 4, 0);
-    bool regular = true, flat = true;
+    bool regular = true;
     for (int64_t g = 0; g < c_T / 4 && regular; ++g) {
       int slot = 0;
       for (int k = 0; k < n && regular; ++k) {
@@ -1338,42 +1336,17 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
             tcol[k][4 * g + 2] == tcol[k][4 * g] + 2 && tcol[k][4 * g + 3] == tcol[k][4 * g] + 3) {
           gslot[g] = slot;
           gj0[g] = tcol[k][4 * g];
-          if (gj0[g] % 4 != 0 || pl->src[k].cols % 4 != 0 || reinterpret_cast<uintptr_t>(pl->src[k].D) % 16 != 0) flat = false;
+          if (gj0[g] % 4 != 0 || pl->src[k].cols % 4 != 0 || reinterpret_cast<uintptr_t>(pl->src[k].D) % 16 != 0) regular = false;
         } else if (hits != 0) {
           regular = false;
         }
         ++slot;
       }
     }
-    pl->mat_vec4 = regular;
-    pl->mat_flat = regular && flat;
+    pl->mat_flat = regular;
     if (regular) {
       HIP_TRY(hipMemcpyAsync(pl->at<int32_t>(lay.o_gslot), gslot.data(), sizeof(int32_t) * gslot.size(), hipMemcpyHostToDevice, st));
       HIP_TRY(hipMemcpyAsync(pl->at<int32_t>(lay.o_gj0), gj0.data(), sizeof(int32_t) * gj0.size(), hipMemcpyHostToDevice, st));
-      HIP_TRY(hipStreamSynchronize(st));
-    }
-  }
-  // join-gather tables, general form: the first two feeders of every target column, in source order
-  {
-    std::vector<int32_t> cs((size_t)2 * c_T, -1), cj((size_t)2 * c_T, 0);
-    bool ok = true;
-    for (int64_t t = 0; t < c_T && ok; ++t) {
-      int found = 0, slot = 0;
-      for (int k = 0; k < n; ++k) {
-        if (pl->src[k].empty) continue;
-        if (tcol[k][t] >= 0) {
-          if (found == 2) { ok = false; break; }
-          cs[2 * t + found] = slot;
-          cj[2 * t + found] = tcol[k][t];
-          ++found;
-        }
-        ++slot;
-      }
-    }
-    pl->mat_cols = ok;
-    if (ok) {
-      HIP_TRY(hipMemcpyAsync(pl->at<int32_t>(lay.o_ct_slot), cs.data(), sizeof(int32_t) * cs.size(), hipMemcpyHostToDevice, st));
-      HIP_TRY(hipMemcpyAsync(pl->at<int32_t>(lay.o_ct_j), cj.data(), sizeof(int32_t) * cj.size(), hipMemcpyHostToDevice, st));
       HIP_TRY(hipStreamSynchronize(st));
     }
   }
@@ -1988,14 +1961,33 @@ ilargi_status_t ilargi_materialize(ilargi_plan_t* plan, float* T, void* stream) 
     ++a.n;
   }
   a.T = T; a.r_T = plan->r_T; a.c_T = (int)plan->c_T;
-  a.gslot = plan->mat_vec4 ? plan->at<int32_t>(plan->lay.o_gslot) : nullptr;
-  a.gj0 = plan->mat_vec4 ? plan->at<int32_t>(plan->lay.o_gj0) : nullptr;
-  a.flat_ok = plan->mat_flat ? 1 : 0;
-  a.ct_slot = plan->mat_cols ? plan->at<int32_t>(plan->lay.o_ct_slot) : nullptr;
-  a.ct_j = plan->mat_cols ? plan->at<int32_t>(plan->lay.o_ct_j) : nullptr;
+  a.gslot = plan->mat_flat ? plan->at<int32_t>(plan->lay.o_gslot) : nullptr;
+  a.gj0 = plan->mat_flat ? plan->at<int32_t>(plan->lay.o_gj0) : nullptr;
+  MatTileArgs t;
+  memset(&t, 0, sizeof(t));
+  t.T = T; t.r_T = plan->r_T; t.c_T = (int)plan->c_T;
+  t.add = plan->cover_disjoint ? 0 : 1;
+  t.zero = plan->cover_disjoint && plan->cover_columns ? 0 : 1;
+  for (int k = 0; k < plan->n; ++k) {
+    const SourcePlan& p = plan->src[k];
+    if (p.empty) continue;
+    MatTileSource& q = t.s[t.n++];
+    q.D = p.D; q.idx = p.ident ? nullptr : p.idx; q.rows = p.rows; q.ck = (int)p.cols;
+    q.colmap = plan->at<int32_t>(p.o_colmap);
+    q.c0 = p.colmap_h[0];
+    for (int64_t j = 1; j < p.cols && q.c0 >= 0; ++j)
+      if (p.colmap_h[(size_t)j] != q.c0 + j) q.c0 = -1;
+    q.vec = q.c0 < 0 ? 1 : p.vec;
+    q.nv = (unsigned)(q.ck / q.vec);
+    q.magic = (unsigned)(((1ull << 32) + q.nv - 1) / q.nv);
+  }
   {
     TraceScope ts(plan, "materialize", -1, static_cast<hipStream_t>(stream));
-    HIP_TRY(launch_materialize(a, static_cast<hipStream_t>(stream)));
+    // the flat stream and the LDS tiles run level where both apply (1,000,000 x 220: 281 and 277 microseconds, 100,000 x
+    // 100: 11.9 and 12.5); beyond kMatTileMaxCols a tile of four rows no longer fits
+    if (materialize_flat_supported(a)) HIP_TRY(launch_materialize_flat(a, static_cast<hipStream_t>(stream)));
+    else if (materialize_tile_supported(t)) HIP_TRY(launch_materialize_tile(t, static_cast<hipStream_t>(stream)));
+    else HIP_TRY(launch_materialize(a, static_cast<hipStream_t>(stream)));
   }
   return ILARGI_OK;
 }

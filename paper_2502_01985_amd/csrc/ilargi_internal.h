@@ -235,16 +235,32 @@ struct MatArgs {
   float* T;
   int64_t r_T;
   int c_T;
-  // optional tables for the vectorized form: per group of four target columns the feeding source slot
-  // (-1: nobody) and its first source column; NULL when some group is fed irregularly
+  // optional tables for the flat form: per group of four target columns the feeding source slot (-1: nobody) and
+  // its first source column; NULL unless every fed group is four 16-byte-aligned values of one source
   const int32_t* gslot;
   const int32_t* gj0;
-  int flat_ok;   // every fed group is four 16-byte-aligned values of its source (tables narrower than 4096 columns)
-  // optional tables for the column form: for target column t the (up to two) feeding source slots
-  // ct_slot[2t], ct_slot[2t+1] (-1: none) in source order and their source columns ct_j[2t], ct_j[2t+1];
-  // NULL when some column has more than two feeders
-  const int32_t* ct_slot;
-  const int32_t* ct_j;
+};
+
+// Join-gather through tiles of whole target rows in LDS (kernels_mat.hip): any column map, any alignment.
+constexpr int kMatTileFloats = 5120;     // floats of a tile aimed at (20 KiB)
+constexpr int kMatTileMaxCols = 3584;    // four rows of so many columns, and their row numbers, fit 64 KiB of LDS
+struct MatTileSource {
+  const float* D;
+  const int32_t* idx;      // NULL: identity on the first `rows` target rows
+  const int32_t* colmap;   // device int32[ck], read when c0 < 0
+  int64_t rows;
+  int ck, c0;              // c0 >= 0: column j feeds target column c0 + j
+  int vec;                 // floats per load (1 when c0 < 0)
+  unsigned nv, magic;      // ck / vec and ceil(2^32 / nv): e / nv = mulhi(e, magic) for e * nv < 2^32
+};
+struct MatTileArgs {
+  int n;
+  MatTileSource s[kMaxSources];
+  float* T;
+  int64_t r_T;
+  int c_T, rt;             // rt: rows per tile (set by the launcher)
+  int zero;                // some column has no feeder, or several: tiles start from zero
+  int add;                 // some column has several feeders: sources are added one after the other
 };
 
 // Transposed reduction  C = sum_t w_t a_t^T b_t  on the matrix cores (see kernels_tred.hip).
@@ -403,6 +419,10 @@ int colred_step_rows(int ck, int vec);
 bool tmm_part_supported(const ColredArgs& c, const SegArgs* s);
 hipError_t launch_tmm_parts(const TmmParts& t, hipStream_t st);
 hipError_t launch_materialize(const MatArgs& a, hipStream_t st);
+bool materialize_flat_supported(const MatArgs& a);
+hipError_t launch_materialize_flat(const MatArgs& a, hipStream_t st);
+bool materialize_tile_supported(const MatTileArgs& a);
+hipError_t launch_materialize_tile(MatTileArgs a, hipStream_t st);
 hipError_t launch_gram_assemble(const GramAsmPair* pairs_dev, int npairs, const int32_t* const* tcol2src_dev,
                                 int c_T, float* out, hipStream_t st);
 bool tmm_join_supported(int ck, int c);

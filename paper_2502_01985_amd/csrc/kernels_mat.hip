@@ -35,173 +35,123 @@ __global__ __launch_bounds__(kBlock) void materialize_kernel(MatArgs a) {
   }
 }
 
-// General form for tables whose columns have at most two feeding sources each (ct_slot / ct_j tables, built
-// with the plan, list them in source order).  A wavefront writes four rows per step; its 64 lanes first fetch
-// the 4 x 16 row indices (row u, source slot s) in one coalesced-by-source load and park them in LDS, then
-// every lane copies its columns t = lane, lane + 64, ... of the four rows.
-constexpr int kColBlock = 4;   // columns per lane held in registers (target tables up to 256 columns per pass)
+// General form: a workgroup builds a tile of whole target rows in LDS, one source after the other, and writes it out
+// as one contiguous run of float4.  Bound by the write of T.  The rows are built in LDS because a schema whose column
+// blocks start anywhere (10 + 50 + 100 + 40 columns) leaves no aligned float4 a lane could move from a source to T by
+// itself: every source is read in the widest vectors its own rows allow, and the stores fill whole 128-byte lines
+// whatever the alignment of the column blocks.  The tile is small enough for eight workgroups on a compute unit, which
+// overlap one another's gathers and stores (20 KiB; 10 KiB measures 18 % slower, 40 KiB 3 %; non-temporal stores 9 %
+// faster than plain ones).  5,000,000 x 200 from tables of 10, 50, 100 and 40 columns: 1280 microseconds (a lane per
+// target column, as before: 2726); 3,400,000 x 96 from two overlapping tables: 400 (1333).  What is left in the first
+// is the gathered rows, 2.6 GB of lines beside the 4 GB written.
+constexpr int kTileU = 4;      // vectors in flight per lane
 
-__global__ __launch_bounds__(kBlock) void materialize_cols_kernel(MatArgs a) {
-  __shared__ const float* sD[kMaxSources];
-  __shared__ const int32_t* sIdx[kMaxSources];
-  __shared__ int64_t sRows[kMaxSources];
-  __shared__ int sCk[kMaxSources];
-  __shared__ int sJ[kBlock / kWave][4][kMaxSources];
-  if (threadIdx.x < kMaxSources) {
-    int k = threadIdx.x;
-    sD[k] = k < a.n ? a.D[k] : nullptr;
-    sIdx[k] = k < a.n ? a.idx[k] : nullptr;
-    sRows[k] = k < a.n ? a.rows[k] : 0;
-    sCk[k] = k < a.n ? a.ck[k] : 0;
-  }
-  __syncthreads();
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const int64_t wave0 = ((int64_t)blockIdx.x * (kBlock / kWave) + wave) * 4;
-  const int64_t stride = (int64_t)gridDim.x * (kBlock / kWave) * 4;
-  const int ru = lane / kMaxSources, rs = lane % kMaxSources;   // (row of the step, source slot) this lane fetches
-  for (int cb = 0; cb < a.c_T; cb += kWave * kColBlock) {
-    // this lane's columns of the pass and their feeders
-    const float* dp[kColBlock][2];
-    int ck[kColBlock][2], slot[kColBlock][2];
+template <int V> struct TileVec;
+template <> struct TileVec<1> { typedef float T; };
+template <> struct TileVec<2> { typedef float T __attribute__((ext_vector_type(2))); };
+template <> struct TileVec<4> { typedef float T __attribute__((ext_vector_type(4))); };
+
+// Source s into the tile.  MAP: the target column of every source column is looked up (V = 1), else the columns form
+// the block [c0, c0 + ck).  Without `add` the source is the only feeder of its columns and writes their cells.
+template <int V, bool MAP>
+__device__ void tile_source(const MatTileSource& s, float* tile, const int* jrow, int nrow, int c_T, bool add) {
+  typedef typename TileVec<V>::T VT;
+  const unsigned total = (unsigned)nrow * s.nv;
+  const bool whole = (c_T % V == 0) && (s.c0 % V == 0);    // the tile's vectors are aligned as well
+  for (unsigned e0 = threadIdx.x; e0 < total; e0 += kBlock * kTileU) {
+    VT v[kTileU];
+    int dst[kTileU];
+    bool fed[kTileU];
 #pragma unroll
-    for (int q = 0; q < kColBlock; ++q) {
-      const int t = cb + lane + q * kWave;
-#pragma unroll
-      for (int f = 0; f < 2; ++f) {
-        slot[q][f] = t < a.c_T ? a.ct_slot[2 * t + f] : -1;
-        dp[q][f] = nullptr; ck[q][f] = 0;
-        if (slot[q][f] >= 0) { dp[q][f] = sD[slot[q][f]] + a.ct_j[2 * t + f]; ck[q][f] = sCk[slot[q][f]]; }
-      }
+    for (int u = 0; u < kTileU; ++u) {
+      const unsigned e = min(e0 + u * kBlock, total - 1);
+      const unsigned row = s.nv == 1 ? e : __umulhi(e, s.magic);     // e / nv
+      const unsigned j = (e - row * s.nv) * V;
+      const int r = jrow[row];
+      fed[u] = r >= 0;
+      v[u] = *reinterpret_cast<const VT*>(s.D + (int64_t)max(r, 0) * s.ck + j);   // (a source here has rows)
+      int t = s.c0 + (int)j;
+      if (MAP) t = s.colmap[j];
+      dst[u] = t < 0 ? -1 : (int)row * c_T + t;
     }
-    for (int64_t i0 = wave0; i0 < a.r_T; i0 += stride) {
-      {
-        const int64_t i = i0 + ru;
-        int r = -1;
-        if (rs < a.n && i < a.r_T) r = sIdx[rs] != nullptr ? sIdx[rs][i] : (i < sRows[rs] ? (int)i : -1);
-        __builtin_amdgcn_wave_barrier();
-        sJ[wave][ru][rs] = r;
-        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int u = 0; u < kTileU; ++u) {
+      if (e0 + u * kBlock >= total || dst[u] < 0 || (add && !fed[u])) continue;
+      float x[V];
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        if constexpr (V == 1) x[i] = fed[u] ? v[u] : 0.0f;
+        else x[i] = fed[u] ? v[u][i] : 0.0f;
       }
-      float v[4][kColBlock][2];
+      float* out = tile + dst[u];
+      if (add) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+        for (int i = 0; i < V; ++i) out[i] += x[i];
+      } else if (V > 1 && whole) {
+        VT o;
+        if constexpr (V > 1) {
 #pragma unroll
-        for (int q = 0; q < kColBlock; ++q)
-#pragma unroll
-          for (int f = 0; f < 2; ++f) {
-            v[u][q][f] = 0.0f;
-            if (slot[q][f] >= 0) {
-              const int r = sJ[wave][u][slot[q][f]];
-              if (r >= 0) v[u][q][f] = dp[q][f][(int64_t)r * ck[q][f]];
-            }
-          }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int64_t i = i0 + u;
-        if (i >= a.r_T) break;
-#pragma unroll
-        for (int q = 0; q < kColBlock; ++q) {
-          const int t = cb + lane + q * kWave;
-          if (t < a.c_T) {
-            float acc = 0.0f + v[u][q][0];
-            if (slot[q][1] >= 0 && sJ[wave][u][slot[q][1]] >= 0) acc += v[u][q][1];
-            __builtin_nontemporal_store(acc, a.T + i * a.c_T + t);
-          }
+          for (int i = 0; i < V; ++i) o[i] = 0.0f + x[i];
         }
+        *reinterpret_cast<VT*>(out) = o;
+      } else {
+        // 0.0f + x: a source cell holding -0.0 becomes +0.0, as in the sum that defines the cell
+#pragma unroll
+        for (int i = 0; i < V; ++i) out[i] = 0.0f + x[i];
       }
     }
   }
 }
 
-// Fast form for the usual schema: every aligned group of four target columns is either fed by four
-// consecutive columns of one source or by nobody (gslot / gj0 tables, built with the plan).  A lane owns
-// column groups lane, lane + 64, ... of its wavefront's row and stores them as float4.
-constexpr int kMatRows = 4;   // rows in flight per wavefront
-constexpr int kMatGroups = 4; // column groups per lane (target tables up to 1024 columns)
-
-__global__ __launch_bounds__(kBlock) void materialize_vec4_kernel(MatArgs a) {
-  __shared__ const float* sD[kMaxSources];
-  __shared__ const int32_t* sIdx[kMaxSources];
-  __shared__ int64_t sRows[kMaxSources];
-  __shared__ int sCk[kMaxSources];
-  if (threadIdx.x < kMaxSources) {
-    int k = threadIdx.x;
-    sD[k] = k < a.n ? a.D[k] : nullptr;
-    sIdx[k] = k < a.n ? a.idx[k] : nullptr;
-    sRows[k] = k < a.n ? a.rows[k] : 0;
-    sCk[k] = k < a.n ? a.ck[k] : 0;
+__global__ __launch_bounds__(kBlock) void materialize_tile_kernel(MatTileArgs a) {
+  extern __shared__ float tile_lds[];
+  float* tile = tile_lds;                                            // rt x c_T, flat
+  int* srow = reinterpret_cast<int*>(tile_lds + a.rt * a.c_T);       // [source][rt]: the row each target row takes
+  const int64_t i0 = (int64_t)blockIdx.x * a.rt;
+  const int nrow = (int)min((int64_t)a.rt, a.r_T - i0);
+  for (int e = threadIdx.x; e < a.n * a.rt; e += kBlock) {
+    const int k = e / a.rt, u = e - k * a.rt;
+    const int64_t i = i0 + u;
+    int r = -1;
+    if (u < nrow) r = a.s[k].idx != nullptr ? a.s[k].idx[i] : (i < a.s[k].rows ? (int)i : -1);
+    srow[e] = r;
   }
+  if (a.zero)
+    for (int e = threadIdx.x; e < nrow * a.c_T; e += kBlock) tile[e] = 0.0f;
   __syncthreads();
-  const int lane = threadIdx.x % kWave;
-  const int ngroups = a.c_T / 4;
-  const float* dp[kMatGroups];
-  const int32_t* ip[kMatGroups];
-  int64_t rows[kMatGroups];
-  int ck[kMatGroups];
-  bool vec[kMatGroups];
-#pragma unroll
-  for (int q = 0; q < kMatGroups; ++q) {
-    int g = lane + q * kWave;
-    dp[q] = nullptr; ip[q] = nullptr; rows[q] = 0; ck[q] = 0; vec[q] = false;
-    if (g < ngroups) {
-      int slot = a.gslot[g];
-      if (slot >= 0) {
-        int j0 = a.gj0[g];
-        dp[q] = sD[slot] + j0;
-        ip[q] = sIdx[slot];
-        rows[q] = sRows[slot];
-        ck[q] = sCk[slot];
-        vec[q] = (j0 % 4 == 0) && (ck[q] % 4 == 0) && (reinterpret_cast<uintptr_t>(sD[slot]) % 16 == 0);
-      }
-    }
+  for (int k = 0; k < a.n; ++k) {
+    const MatTileSource& s = a.s[k];
+    const int* jrow = srow + k * a.rt;
+    if (s.c0 < 0) tile_source<1, true>(s, tile, jrow, nrow, a.c_T, a.add != 0);
+    else if (s.vec == 4) tile_source<4, false>(s, tile, jrow, nrow, a.c_T, a.add != 0);
+    else if (s.vec == 2) tile_source<2, false>(s, tile, jrow, nrow, a.c_T, a.add != 0);
+    else tile_source<1, false>(s, tile, jrow, nrow, a.c_T, a.add != 0);
+    if (a.add) __syncthreads();          // cells with several feeders receive them in source order
   }
-  const int64_t wave0 = ((int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave) * kMatRows;
-  const int64_t stride = (int64_t)gridDim.x * (kBlock / kWave) * kMatRows;
-  for (int64_t i0 = wave0; i0 < a.r_T; i0 += stride) {
-    float4 v[kMatRows][kMatGroups];
-#pragma unroll
-    for (int u = 0; u < kMatRows; ++u) {
-      int64_t i = i0 + u;
-#pragma unroll
-      for (int q = 0; q < kMatGroups; ++q) {
-        v[u][q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (dp[q] != nullptr && i < a.r_T) {
-          int64_t r = ip[q] != nullptr ? (int64_t)ip[q][i] : (i < rows[q] ? i : -1);
-          if (r >= 0) {
-            const float* src = dp[q] + r * ck[q];
-            if (vec[q]) v[u][q] = *reinterpret_cast<const float4*>(src);
-            else v[u][q] = make_float4(src[0], src[1], src[2], src[3]);
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kMatRows; ++u) {
-      int64_t i = i0 + u;
-      if (i >= a.r_T) break;
-#pragma unroll
-      for (int q = 0; q < kMatGroups; ++q) {
-        int g = lane + q * kWave;
-        if (g < ngroups) {
-          // 0.0f + x: a source cell holding -0.0 becomes +0.0, as in the sum that defines the cell
-          typedef float f4 __attribute__((ext_vector_type(4)));
-          f4 o = {0.0f + v[u][q].x, 0.0f + v[u][q].y, 0.0f + v[u][q].z, 0.0f + v[u][q].w};
-          // the table is written once and not read back here: keep it out of the caches' way
-          __builtin_nontemporal_store(o, reinterpret_cast<f4*>(a.T + i * a.c_T + 4 * g));
-        }
-      }
-    }
+  if (!a.add) __syncthreads();
+  const int64_t base = i0 * a.c_T;
+  const int count = nrow * a.c_T;
+  if (reinterpret_cast<uintptr_t>(a.T + base) % 16 == 0) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    const f4* src = reinterpret_cast<const f4*>(tile);
+    f4* out = reinterpret_cast<f4*>(a.T + base);
+    // the table is written once and not read back here: keep it out of the caches' way
+    for (int e = threadIdx.x; e < count / 4; e += kBlock) __builtin_nontemporal_store(src[e], out + e);
+    for (int e = count / 4 * 4 + threadIdx.x; e < count; e += kBlock) a.T[base + e] = tile[e];
+  } else {
+    for (int e = threadIdx.x; e < count; e += kBlock) __builtin_nontemporal_store(tile[e], a.T + base + e);
   }
 }
 
-// The same table written as one flat stream of float4: element e is column group e % (c_T / 4) of row
-// e / (c_T / 4).  A wavefront stores kFlatU runs of 64 consecutive float4, so every store instruction fills whole
+// Fast form for schemas whose every aligned group of four target columns is an aligned float4 of one source, or fed by
+// nobody (gslot / gj0 tables, built with the plan): the table is written as one flat stream of float4, element e is
+// column group e % (c_T / 4) of row e / (c_T / 4).  A wavefront stores kFlatU runs of 64 consecutive float4, so every store instruction fills whole
 // 128-byte lines whatever the row length (880-byte rows otherwise leave partial lines at both ends of each row).
-// Needs every fed group to be four 16-byte-aligned source values (flat_ok).  The loop body has no branches: all
+// The loop body has no branches: all
 // row indices of a step are requested, then all source values, then all stores go out; elements nobody feeds
 // read a dummy location and are replaced by zero.
 constexpr int kFlatU = 4;
-constexpr int kFlatMaxGroups = 1024;
+constexpr int kFlatMaxCols = 1024;
 typedef const int32_t __attribute__((address_space(1)))* GIntPtr;
 typedef float mf4 __attribute__((ext_vector_type(4)));
 typedef const mf4 __attribute__((address_space(1)))* GVecPtr;
@@ -211,8 +161,8 @@ __global__ __launch_bounds__(kBlock) void materialize_flat_kernel(MatArgs a, int
   __shared__ const int32_t* sIdx[kMaxSources];
   __shared__ int64_t sRows[kMaxSources];
   __shared__ int sCk[kMaxSources];
-  __shared__ short gS[kFlatMaxGroups];
-  __shared__ short gJ[kFlatMaxGroups];
+  __shared__ short gS[kFlatMaxCols / 4];
+  __shared__ short gJ[kFlatMaxCols / 4];
   const int ngroups = a.c_T / 4;
   if (threadIdx.x < kMaxSources) {
     int k = threadIdx.x;
@@ -273,31 +223,51 @@ __global__ __launch_bounds__(kBlock) void materialize_flat_kernel(MatArgs a, int
 
 }  // namespace
 
+bool materialize_tile_supported(const MatTileArgs& a) { return a.c_T <= kMatTileMaxCols; }
+
+hipError_t launch_materialize_tile(MatTileArgs a, hipStream_t st) {
+  if (a.r_T <= 0 || a.c_T <= 0) return hipSuccess;
+  // Rows per tile: about 20 KiB of LDS, and tiles of whole 128-byte lines where the row length allows it in that space.
+  int line = 32;                                     // rows whose cells fill whole lines: 32 / gcd(32, c_T)
+  while (line > 1 && (line / 2) * a.c_T % 32 == 0) line /= 2;
+  line = line < 4 ? 4 : line;                        // (tiles start on float4s)
+  int rt = kMatTileFloats / a.c_T;
+  if (rt >= line) rt = rt / line * line;
+  else rt = rt / 4 * 4;
+  rt = rt < 4 ? 4 : (rt > 256 ? 256 : rt);
+  if (a.r_T < (int64_t)rt * 1024) {
+    // fewer tiles than four per compute unit: smaller ones, so that every unit has some
+    int64_t want = (a.r_T + 1023) / 1024;
+    want = (want + line - 1) / line * line;
+    rt = (int)(want < rt ? want : rt);
+  }
+  a.rt = rt;
+  const size_t lds = sizeof(float) * (size_t)rt * a.c_T + sizeof(int) * (size_t)rt * a.n;
+  const int64_t grid = (a.r_T + rt - 1) / rt;
+  materialize_tile_kernel<<<(unsigned)grid, kBlock, lds, st>>>(a);
+  return hipGetLastError();
+}
+
 hipError_t launch_materialize(const MatArgs& a, hipStream_t st) {
   if (a.r_T <= 0 || a.c_T <= 0) return hipSuccess;
-  bool fast = a.gslot != nullptr && a.c_T % 4 == 0 && a.c_T <= 4 * kWave * kMatGroups &&
-              reinterpret_cast<uintptr_t>(a.T) % 16 == 0;
+  int64_t grid = (a.r_T + (kBlock / kWave) - 1) / (kBlock / kWave);
+  if (grid > 8192) grid = 8192;
+  materialize_kernel<<<(int)grid, kBlock, 0, st>>>(a);
+  return hipGetLastError();
+}
+
+bool materialize_flat_supported(const MatArgs& a) {
+  return a.gslot != nullptr && a.c_T % 4 == 0 && a.c_T <= kFlatMaxCols && reinterpret_cast<uintptr_t>(a.T) % 16 == 0 &&
+         reinterpret_cast<uintptr_t>(a.gslot) % 16 == 0;
+}
+
+hipError_t launch_materialize_flat(const MatArgs& a, hipStream_t st) {
+  if (a.r_T <= 0 || a.c_T <= 0) return hipSuccess;
   const int64_t total = a.r_T * (a.c_T / 4);
-  if (fast && a.flat_ok && a.c_T / 4 <= kFlatMaxGroups && reinterpret_cast<uintptr_t>(a.gslot) % 16 == 0) {
-    int64_t waves = (total + kWave * kFlatU - 1) / (kWave * kFlatU);
-    int64_t grid = (waves + (kBlock / kWave) - 1) / (kBlock / kWave);
-    if (grid > 65536) grid = 65536;
-    materialize_flat_kernel<<<(int)grid, kBlock, 0, st>>>(a, total);
-  } else if (fast) {
-    int64_t waves = (a.r_T + kMatRows - 1) / kMatRows;
-    int64_t grid = (waves + (kBlock / kWave) - 1) / (kBlock / kWave);
-    if (grid > 65536) grid = 65536;
-    materialize_vec4_kernel<<<(int)grid, kBlock, 0, st>>>(a);
-  } else if (a.ct_slot != nullptr) {
-    int64_t waves = (a.r_T + 3) / 4;
-    int64_t grid = (waves + (kBlock / kWave) - 1) / (kBlock / kWave);
-    if (grid > 65536) grid = 65536;
-    materialize_cols_kernel<<<(int)grid, kBlock, 0, st>>>(a);
-  } else {
-    int64_t grid = (a.r_T + (kBlock / kWave) - 1) / (kBlock / kWave);
-    if (grid > 8192) grid = 8192;
-    materialize_kernel<<<(int)grid, kBlock, 0, st>>>(a);
-  }
+  int64_t waves = (total + kWave * kFlatU - 1) / (kWave * kFlatU);
+  int64_t grid = (waves + (kBlock / kWave) - 1) / (kBlock / kWave);
+  if (grid > 65536) grid = 65536;
+  materialize_flat_kernel<<<(int)grid, kBlock, 0, st>>>(a, total);
   return hipGetLastError();
 }
 
