@@ -60,6 +60,9 @@ struct SourcePlan {
          o_long_seg = 0, o_long_first = 0, o_chunk_partial = 0, o_pz = 0, o_partial = 0, o_g = 0, o_cnt = 0;
   int64_t nch_max = 0, nl_max = 0;
   int n_chunks = 0, n_long = 0;
+  int long_thr = kLongSeg;        // segments of the inverse index longer than this are summed in chunks of this length
+  bool very_long = false;         // some segment has more than kLongSeg entries: no join-order paths
+  int max_row = 0, max_col = 0;   // sparse: most entries of a row, of a column
   size_t o_join_first = 0;        // join-order column reduce: first source row of every workgroup
   int n_join_blocks = 0;
   bool sliced = false;            // the inverse index is also split by slice of target rows (large target tables)
@@ -265,8 +268,8 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
     if (p.has_idx) {
       p.o_rowptr = take(sizeof(int32_t) * (p.rows + 1));
       p.o_perm = take(sizeof(int32_t) * std::max<int64_t>(r_T, 1));
-      p.nl_max = r_T / kLongSeg + 1;
-      p.nch_max = r_T / kSegChunk + p.nl_max + 1;
+      p.nl_max = r_T / kSegCut + 1;
+      p.nch_max = r_T / (kLongSeg / 4) + 2;
       p.o_chunk_seg = take(sizeof(int32_t) * p.nch_max);
       p.o_chunk_beg = take(sizeof(int32_t) * p.nch_max);
       p.o_chunk_end = take(sizeof(int32_t) * p.nch_max);
@@ -318,8 +321,6 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
   lay.o_eye = take(sizeof(float) * (lay.max_entries > 0 && c_T <= kSparseGramMaxCols ? c_T * std::min<int64_t>(max_cx, kSparseGramWidth) : 1));
   lay.o_loss = take(sizeof(float) * std::max<int64_t>(32768 * kNarrowCT, 1024 * max_cx));
   const int64_t sort_n = std::max<int64_t>(std::max<int64_t>(r_T, 1), lay.max_entries);
-  lay.o_sort = take(sizeof(int32_t) * 4 * sort_n);
-  lay.o_hist = take(sizeof(int32_t) * sort_hist_ints(sort_n));
   // Gram scratch: summed rows for the "via sums" route, chunk partials, the (k,l) blocks
   lay.zc_floats = 1;
   lay.gpartial_floats = kGramPartialFloats;
@@ -344,7 +345,11 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
     }
   for (int i = 0; i < lay.n_pairlists; ++i) lay.o_pairlist[i] = take(sizeof(int32_t) * 2 * r_T);
   lay.o_zc = take(sizeof(float) * lay.zc_floats);
-  lay.o_gpartial = take(sizeof(float) * lay.gpartial_floats);
+  // (the sort that builds the inverse indices is over before the first partial block is written: same space)
+  const size_t sort_bytes = align_up(sizeof(int32_t) * 4 * sort_n), hist_bytes = sizeof(int32_t) * sort_hist_ints(sort_n);
+  lay.o_gpartial = take(std::max(sizeof(float) * lay.gpartial_floats, sort_bytes + hist_bytes));
+  lay.o_sort = lay.o_gpartial;
+  lay.o_hist = lay.o_gpartial + sort_bytes;
   lay.o_blocks = take(sizeof(float) * std::max<int64_t>(lay.blocks_floats, 1));
   lay.total = off;
   return ILARGI_OK;
@@ -363,19 +368,19 @@ int pick_logL(int64_t cols, int vec) {
   return l > 6 ? 6 : l;
 }
 
-// Splits the segments longer than kLongSeg into chunks (host side, once per plan).
-void build_long_tables(const std::vector<int32_t>& rowptr, std::vector<int32_t>& chunk_seg,
+// Splits the segments longer than thr into chunks of thr entries (host side, once per plan).
+void build_long_tables(const std::vector<int32_t>& rowptr, int32_t thr, std::vector<int32_t>& chunk_seg,
                        std::vector<int32_t>& chunk_beg, std::vector<int32_t>& chunk_end,
                        std::vector<int32_t>& long_seg, std::vector<int32_t>& long_first) {
   long_first.push_back(0);
   for (size_t j = 0; j + 1 < rowptr.size(); ++j) {
     int32_t b = rowptr[j], e = rowptr[j + 1];
-    if (e - b <= kLongSeg) continue;
+    if (e - b <= thr) continue;
     long_seg.push_back((int32_t)j);
-    for (int32_t c = b; c < e; c += kSegChunk) {
+    for (int32_t c = b; c < e; c += thr) {
       chunk_seg.push_back((int32_t)j);
       chunk_beg.push_back(c);
-      chunk_end.push_back(std::min(e, c + kSegChunk));
+      chunk_end.push_back(std::min(e, c + thr));
     }
     long_first.push_back((int32_t)chunk_seg.size());
   }
@@ -394,6 +399,7 @@ SegArgs seg_args(const ilargi_plan* pl, int k) {
   a.long_first = pl->at<int32_t>(p.o_long_first);
   a.n_chunks = p.n_chunks;
   a.n_long = p.n_long;
+  a.long_thr = p.long_thr;
   a.r_k = p.rows;
   a.gidx = nullptr;
   a.g_rows = -1;
@@ -411,6 +417,23 @@ SegArgs seg_args(const ilargi_plan* pl, int k) {
   return a;
 }
 
+// Lanes (log2) that share a row or column of a sparse table in the lane-group products: about four entries each.
+int sparse_lanes(int64_t entries, int64_t n) {
+  const int64_t avg = n > 0 ? (entries + n - 1) / n : 1;
+  return std::min(6, ilog2_ceil(std::max<int64_t>((avg + 3) / 4, 1)));
+}
+
+// Which of its two forms a sparse product takes.  The lane-group kernel wins while the table is too small for the
+// staged kernels (a workgroup per 2048 entries, per column) to fill the chip and no row or column keeps its lanes for
+// more than four rounds; beyond, staging reads the operand once per workgroup instead of once per entry.
+constexpr int64_t kSparseLaneEntries = 512 * 2048;
+bool sparse_rows_by_lanes(const SourcePlan& p) {
+  return p.entries <= kSparseLaneEntries && p.max_row <= (16 << sparse_lanes(p.entries, p.rows));
+}
+bool sparse_cols_by_lanes(const SourcePlan& p) {
+  return p.entries <= kSparseLaneEntries && p.max_col <= (16 << sparse_lanes(p.entries, p.cols));
+}
+
 SparseArgs sparse_args(const ilargi_plan* pl, int k) {
   const SourcePlan& p = pl->src[k];
   SparseArgs a;
@@ -426,6 +449,9 @@ SparseArgs sparse_args(const ilargi_plan* pl, int k) {
   a.chunk_end = pl->at<int32_t>(p.o_tchunk_end);
   a.col_first_chunk = pl->at<int32_t>(p.o_col_first);
   a.n_chunks = p.n_tchunks;
+  a.colptr = pl->at<int32_t>(p.o_colptr);
+  a.logR = sparse_lanes(p.entries, p.rows);
+  a.logC = sparse_lanes(p.entries, p.cols);
   return a;
 }
 
@@ -457,28 +483,48 @@ ilargi_status_t lmm_pass(ilargi_plan* pl, const float* X, int ldx, int col0, int
     a.scratch = pl->at<float>(pl->lay.o_gpartial); a.scratch_floats = pl->lay.gpartial_floats;   // free until the assembly
     return a;
   };
-  // Narrow operands: when two or more dense sources can take the streaming product kernel, their products share
-  // one launch (a plan with several dimension tables otherwise pays a launch per table for a few microseconds of work).
+  // Narrow operands: the products of the sources that take the same kernel share one launch (a plan with several
+  // dimension tables otherwise pays a launch per table for a few microseconds of work): dense tables with aligned rows
+  // the streaming kernel, the other dense ones the tile kernel, small sparse ones the lane-group kernel.
   bool product_done[kMaxSources] = {};
   if (!wide) {
-    int ks[kMaxSources], nk = 0;
+    int by[3][kMaxSources], nby[3] = {0, 0, 0};
     for (int k = 0; k < pl->n; ++k) {
       const SourcePlan& p = pl->src[k];
-      if (p.empty || k == pl->fused || p.sparse) continue;
-      if (rowdot_supported(product_args(k), p.vec)) ks[nk++] = k;
+      if (p.empty || k == pl->fused) continue;
+      int form = -1;
+      if (p.sparse) form = sparse_rows_by_lanes(p) ? 2 : -1;
+      else if (rowdot_supported(product_args(k), p.vec)) form = 0;
+      else if (prod_tile_supported(product_args(k), p.vec)) form = 1;
+      if (form < 0) continue;
+      by[form][nby[form]++] = k;
+      product_done[k] = true;
     }
-    for (int i0 = 0; nk >= 2 && i0 < nk; i0 += kRowdotMulti) {
-      LmmArgs multi[kRowdotMulti];
-      int vecs[kRowdotMulti];
-      const int cnt = std::min(kRowdotMulti, nk - i0);
-      for (int i = 0; i < cnt; ++i) {
-        multi[i] = product_args(ks[i0 + i]);
-        vecs[i] = pl->src[ks[i0 + i]].vec;
-        product_done[ks[i0 + i]] = true;
+    static_assert(kRowdotMulti == kTileParts && kTileParts == kSparseMulti, "one group size");
+    for (int form = 0; form < 3; ++form)
+      for (int i0 = 0; i0 < nby[form]; i0 += kTileParts) {
+        const int cnt = std::min(kTileParts, nby[form] - i0);
+        LmmArgs multi[kTileParts];
+        SparsePart sparse[kTileParts];
+        int vecs[kTileParts];
+        for (int i = 0; i < cnt; ++i) {
+          const int k = by[form][i0 + i];
+          if (form == 2) {
+            SparsePart& sp = sparse[i];
+            memset(&sp, 0, sizeof(sp));
+            sp.a = sparse_args(pl, k);
+            sp.X = X; sp.ldx = ldx; sp.col0 = col0; sp.ncols = ncols;
+            sp.out = pl->at<float>(pl->src[k].o_pz); sp.ldo = ldx;
+          } else {
+            multi[i] = product_args(k);
+            vecs[i] = pl->src[k].vec;
+          }
+        }
+        TraceScope ts(pl, "lmm_rows", by[form][i0], st);
+        if (form == 0) HIP_TRY(launch_rowdot_multi(multi, vecs, cnt, st));
+        else if (form == 1) HIP_TRY(launch_prod_tile(multi, cnt, st));
+        else HIP_TRY(launch_spmm_lanes_rows(sparse, cnt, st));
       }
-      TraceScope ts(pl, "lmm_rows", ks[i0], st);
-      HIP_TRY(launch_rowdot_multi(multi, vecs, cnt, st));
-    }
   }
   for (int k = 0; k < pl->n; ++k) {
     SourcePlan& p = pl->src[k];
@@ -507,13 +553,14 @@ ilargi_status_t lmm_pass(ilargi_plan* pl, const float* X, int ldx, int col0, int
   a.X = X; a.ldx = ldx; a.col0 = col0; a.ncols = ncols;
   a.out = out; a.ldo = ldo; a.r_out = pl->r_T;
   // results (and residuals) larger than the caches are streamed out past them
+  a.nt_in = stream_past_caches(a.d_rows * a.ck);
   a.nt_out = (int64_t)pl->r_T * ldo * (int64_t)sizeof(float) >= (64ll << 20);
   a.g = g;
   a.y = y;
   a.loss_partial = pl->at<float>(pl->lay.o_loss);
   a.ld_loss = ldx;
   if (!wide && mode != 0 && fused_gradient != nullptr && pl->fused >= 0 &&
-      lmm_can_fuse_gradient(a.ck, vec, a.logL)) {
+      (lmm_can_fuse_gradient(a.ck, vec, a.logL) || asm_tile_supported(a, vec, true))) {
     // the fused source's share of the gradient comes out of the same pass over its rows
     a.grad_partial = pl->at<float>(pl->src[pl->fused].o_partial);
     *fused_gradient = true;
@@ -580,22 +627,23 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
     parts_first_k = -1; parts_joins = 0;
     return ILARGI_OK;
   };
-  // Large target table: the per-slice sums over the sliced indices of all such sources run as one launch (and the
-  // sums over the slices as another); the sources then take part in the column reduce with Z_k as a plain operand.
+  // Segment sums of the sources that do not take the join-order form, as one launch per kind of index: a large target
+  // table's are summed by slice (and then over the slices).  The sources then take part in the column reduce with Z_k
+  // as a plain operand.
   bool z_ready[kMaxSources] = {};
-  {
+  for (const bool sliced : {true, false}) {
     SegArgs multi[kSegMulti];
     int nm = 0, first_k = -1;
     auto flush_multi = [&]() -> ilargi_status_t {
       if (nm == 0) return ILARGI_OK;
       TraceScope ts(pl, "segsum", first_k, st);
-      HIP_TRY(launch_segsum_sliced(multi, nm, st));
+      HIP_TRY(sliced ? launch_segsum_sliced(multi, nm, st) : launch_segsum_narrow(multi, nm, st));
       nm = 0; first_k = -1;
       return ILARGI_OK;
     };
     for (int k = 0; k < pl->n && Y != nullptr; ++k) {
       const SourcePlan& p = pl->src[k];
-      if (p.empty || k == done_k || p.ident || !p.sliced) continue;
+      if (p.empty || k == done_k || p.ident || p.sliced != sliced) continue;
       if (!p.sparse) {
         SegArgs sg = segsum_args(k);
         if (tmm_part_supported(colred_args(k, nullptr, 0, 0), &sg)) continue;      // join-order form: no Z_k
@@ -611,6 +659,59 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
     ilargi_status_t rc = flush_multi();
     if (rc != ILARGI_OK) return rc;
   }
+  // Column reduces that share a launch: dense tables without aligned float4 rows (tiles), small sparse tables.
+  int tile_blocks[kMaxSources] = {};                   // partial blocks the tile kernel left for source k (0: not its)
+  bool sparse_done[kMaxSources] = {};
+  {
+    ColredArgs tiles[kTileParts];
+    SparsePart sparse[kSparseMulti];
+    int tk[kTileParts], nt = 0, ns = 0, first_sparse = -1;
+    auto flush_tiles = [&]() -> ilargi_status_t {
+      if (nt == 0) return ILARGI_OK;
+      int nblocks[kTileParts];
+      TraceScope ts(pl, "colred", tk[0], st);
+      HIP_TRY(launch_colred_tile(tiles, nt, nblocks, st));
+      for (int i = 0; i < nt; ++i) tile_blocks[tk[i]] = nblocks[i];
+      nt = 0;
+      return ILARGI_OK;
+    };
+    auto flush_sparse = [&]() -> ilargi_status_t {
+      if (ns == 0) return ILARGI_OK;
+      TraceScope ts(pl, "colred", first_sparse, st);
+      HIP_TRY(launch_spmm_lanes_cols(sparse, ns, st));
+      ns = 0;
+      return ILARGI_OK;
+    };
+    for (int k = 0; k < pl->n; ++k) {
+      const SourcePlan& p = pl->src[k];
+      if (p.empty || k == done_k) continue;
+      const ColredArgs c = Y == nullptr ? colred_args(k, pl->at<float>(p.o_cnt), 1, 0)
+                                        : (p.ident ? colred_args(k, Y, ldy, col0) : colred_args(k, pl->at<float>(p.o_pz), ldy, col0));
+      if (Y != nullptr && !p.ident && !z_ready[k]) continue;              // join-order form
+      if (p.sparse && sparse_cols_by_lanes(p)) {
+        if (ns == kSparseMulti) {
+          ilargi_status_t rc = flush_sparse();
+          if (rc != ILARGI_OK) return rc;
+        }
+        if (ns == 0) first_sparse = k;
+        SparsePart& sp = sparse[ns++];
+        memset(&sp, 0, sizeof(sp));
+        sp.a = sparse_args(pl, k);
+        sp.X = c.Z; sp.ldx = c.ldz; sp.col0 = c.col0; sp.ncols = ncols; sp.out = c.partial;
+        sparse_done[k] = true;
+      } else if (!p.sparse && !tmm_part_supported(c, nullptr) && colred_tile_supported(c)) {
+        if (nt == kTileParts) {
+          ilargi_status_t rc = flush_tiles();
+          if (rc != ILARGI_OK) return rc;
+        }
+        tk[nt] = k;
+        tiles[nt++] = c;
+      }
+    }
+    ilargi_status_t rc = flush_tiles();
+    if (rc == ILARGI_OK) rc = flush_sparse();
+    if (rc != ILARGI_OK) return rc;
+  }
   for (int k = 0; k < pl->n; ++k) {
     SourcePlan& p = pl->src[k];
     if (p.empty) continue;
@@ -624,9 +725,12 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
       continue;
     }
     int nb = colred_nblocks(p.rows, p.cols, p.vec);
-    ColredArgs c;
+    ColredArgs c = colred_args(k, nullptr, 0, 0);
     bool merged = false;
-    if (!p.sparse) {
+    if (tile_blocks[k] > 0 || sparse_done[k]) {
+      nb = sparse_done[k] ? 1 : tile_blocks[k];
+      merged = true;
+    } else if (!p.sparse) {
       const bool direct = Y == nullptr || p.ident || z_ready[k];
       c = direct ? (Y == nullptr ? colred_args(k, pl->at<float>(p.o_cnt), 1, 0)
                                  : (z_ready[k] ? colred_args(k, pl->at<float>(p.o_pz), ldy, col0) : colred_args(k, Y, ldy, col0)))
@@ -656,14 +760,8 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
         c = colred_args(k, pl->at<float>(p.o_cnt), 1, 0);
       } else if (p.ident) {
         c = colred_args(k, Y, ldy, col0);
-      } else if (z_ready[k]) {
-        c = colred_args(k, pl->at<float>(p.o_pz), ldy, col0);
       } else {
-        {
-          TraceScope ts(pl, "segsum", k, st);
-          HIP_TRY(launch_segsum(segsum_args(k), st));
-        }
-        c = colred_args(k, pl->at<float>(p.o_pz), ldy, col0);
+        c = colred_args(k, pl->at<float>(p.o_pz), ldy, col0);              // (every source left here has its Z_k)
       }
       if (p.sparse) {
         // D_k^T Z_k over the column-sorted view; the result takes the place of a single block of partials
@@ -767,7 +865,7 @@ ilargi_status_t tmm_wide(ilargi_plan* pl, const float* Y, int cx, float* out, in
   memset(&c, 0, sizeof(c));
   // which kernel serves a source: 1 join-order pass, 2 flat column reduce, 0 segment sums + matrix-core reduce
   auto route = [&](const SourcePlan& p) {
-    if (!p.ident && !bf16 && p.n_long == 0 && cx % 4 == 0 && tmm_join_supported((int)p.cols, cx) &&
+    if (!p.ident && !bf16 && !p.very_long && cx % 4 == 0 && tmm_join_supported((int)p.cols, cx) &&
         p.cols * cx <= pl->lay.gpartial_floats)
       return 1;
     if (p.ident && !bf16 && cx % 4 == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0 && colred_flat_supported(p.D, p.cols, cx) &&
@@ -1109,8 +1207,25 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     HIP_TRY(hipMemcpyAsync(rowptr.data(), pl->at<int32_t>(p.o_rowptr), sizeof(int32_t) * (p.rows + 1), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     p.nnz = rowptr[(size_t)p.rows];
+    const int64_t avg = p.rows > 0 ? (p.nnz + p.rows - 1) / p.rows : 1;
+    // lanes per segment of the narrow segment sum: about four entries each, which a lane keeps in flight together; a
+    // segment is cut when its lanes would need more than four such rounds, later if the tables have no room for that
+    // (a lane per entry while that leaves the chip room)
+    p.logG = std::min(6, ilog2_ceil(std::max<int64_t>((avg + 3) / 4, 1)));
+    const int one_each = std::min(6, ilog2_ceil(std::max<int64_t>(avg, 1)));
+    while (p.logG < one_each && p.rows << (p.logG + 1) <= 256 * 1024) ++p.logG;
+    // (with hundreds of entries per segment on average, whole wavefronts serve the segments as they are: cutting a part
+    // of them costs a launch, 48 against 39 microseconds for 1,000,000 rows over 1,000 uniform keys)
+    p.long_thr = std::max(kSegCut, 16 << p.logG);
+    if (2 * avg > p.long_thr) p.long_thr = kLongSeg;
+    for (size_t j = 0; j + 1 < rowptr.size(); ++j) p.very_long = p.very_long || rowptr[j + 1] - rowptr[j] > kLongSeg;
     std::vector<int32_t> cs, cb, ce, ls, lf;
-    build_long_tables(rowptr, cs, cb, ce, ls, lf);
+    for (;;) {
+      build_long_tables(rowptr, p.long_thr, cs, cb, ce, ls, lf);
+      if ((int64_t)cs.size() <= p.nch_max || p.long_thr >= kLongSeg) break;
+      p.long_thr *= 2;
+      cs.clear(); cb.clear(); ce.clear(); ls.clear(); lf.clear();
+    }
     p.n_chunks = (int)cs.size();
     p.n_long = (int)ls.size();
     if (p.n_chunks > p.nch_max || p.n_long > p.nl_max) return fail(ILARGI_ERR_WORKSPACE, "internal: long-segment tables overflow");
@@ -1122,8 +1237,6 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
       HIP_TRY(hipMemcpyAsync(pl->at<int32_t>(p.o_long_first), lf.data(), sizeof(int32_t) * lf.size(), hipMemcpyHostToDevice, st));
       HIP_TRY(hipStreamSynchronize(st));
     }
-    int64_t avg = p.rows > 0 ? (p.nnz + p.rows - 1) / p.rows : 1;
-    p.logG = std::min(6, ilog2_ceil(std::max<int64_t>(avg, 1)));
     if (p.sliced) {
       int64_t slice_rows = (r_T + kSegSlices - 1) / kSegSlices;
       slice_rows = (slice_rows + 63) / 64 * 64;
@@ -1142,7 +1255,7 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
       // lanes per (slice, source row) run: about four entries per lane, which it keeps in flight together
       p.sl_logG = std::min(6, ilog2_ceil(std::max<int64_t>((avg + 4 * kSegSlices - 1) / (4 * kSegSlices), 1)));
     }
-    if (p.n_long == 0 && p.rows > 0 && !p.sparse && p.nnz <= 32 * p.rows && p.nnz >= 4 * p.rows) {
+    if (!p.very_long && p.rows > 0 && !p.sparse && p.nnz <= 32 * p.rows && p.nnz >= 4 * p.rows) {
       // (with more index entries per row the gathers dominate and the segment-sum kernel, which spreads a
       // segment over a group of lanes, serves them better; with about one entry per row the gathers of a round
       // are too few to hide behind the other workgroups' streaming, and segment sums followed by a plain
@@ -1189,6 +1302,7 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
           if (rp[(size_t)r + 1] - rp[(size_t)r] > cap)
             return fail(ILARGI_ERR_UNSUPPORTED, "source %d: a row of a table wider than %d columns holds more than %d entries", k,
                         kMaxLdsFloats, cap);
+      for (int64_t r = 0; r < p.rows; ++r) p.max_row = std::max(p.max_row, rp[(size_t)r + 1] - rp[(size_t)r]);
       std::vector<int32_t> rb;
       rb.push_back(0);
       int64_t r = 0;
@@ -1214,6 +1328,7 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     if (colptr[(size_t)p.cols] != p.entries) return fail(ILARGI_ERR_DEVICE, "internal: column view of source %d lost entries", k);
     std::vector<int32_t> cb, ce, first((size_t)p.cols + 1, 0);
     for (int64_t j = 0; j < p.cols; ++j) {
+      p.max_col = std::max(p.max_col, colptr[(size_t)j + 1] - colptr[(size_t)j]);
       first[(size_t)j] = (int32_t)cb.size();
       for (int32_t b = colptr[(size_t)j]; b < colptr[(size_t)j + 1]; b += kSparseChunk) {
         cb.push_back(b);
@@ -1271,7 +1386,7 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     if (live == 2 && pl->fused >= 0 && dim >= 0 && !pl->any_sparse) {
       const SourcePlan& f = pl->src[pl->fused];
       const SourcePlan& d = pl->src[dim];
-      if (f.rows == r_T && d.has_idx && !d.ident && d.nnz == r_T && d.n_long == 0) pl->star_k = dim;
+      if (f.rows == r_T && d.has_idx && !d.ident && d.nnz == r_T && !d.very_long) pl->star_k = dim;
     }
   }
   // a small two-table star join (or a small single table): one gradient-descent iteration then runs as a
@@ -1291,7 +1406,7 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     }
     if (ok && live == 2) {
       const SourcePlan& d = pl->src[kj];
-      ok = !d.ident && d.vec == 4 && d.cols <= 16 && d.rows <= 1024 && d.n_long == 0 && d.nnz <= 16384;
+      ok = !d.ident && d.vec == 4 && d.cols <= 16 && d.rows <= 1024 && !d.very_long && d.nnz <= 16384;
     }
     if (ok) {
       SmallStarArgs probe;

@@ -21,8 +21,9 @@ constexpr int kSparseChunk = 4096;   // entries of a column one workgroup sums
 constexpr int kSegSlices = 8;        // slices of target rows of the sliced segment sum (one per XCD and its L2)
 constexpr int kSlLong = 256;         // ... runs of a (slice, source row) longer than this are cut into chunks
 constexpr int kSlChunk = 1024;       // ... of this many entries, each summed by a whole workgroup
-constexpr int kLongSeg = 2048;       // inverse-index segments longer than this are split ...
-constexpr int kSegChunk = 2048;      // ... into chunks of this many entries
+constexpr int kLongSeg = 2048;       // inverse-index segments longer than this keep a plan off the join-order paths, and
+                                     // the most entries of a segment that the segment sums leave uncut
+constexpr int kSegCut = 256;         // the least (a plan picks its own threshold between the two)
 constexpr int kSortChunk = 2048;     // keys per workgroup in one radix pass
 constexpr int kMaxLdsFloats = 4096;  // 16 KiB of LDS for the staged operand rows (also the column limit of a source)
 constexpr int64_t kGramPartialFloats = 16ll << 20;
@@ -52,6 +53,7 @@ struct LmmArgs {
   const float* y;         // labels, r_out
   float* loss_partial;    // narrow kernel: [gridDim.x][kNarrowCT]; matrix-core kernel: [gridDim.x][ld_loss]
   int ld_loss;
+  int nt_in;              // read the table past the caches (see stream_past_caches)
   int nt_out;             // store the output with non-temporal stores (large results nobody re-reads soon)
   float* scratch;         // optional device scratch of scratch_floats floats (the caller's, free for the launch)
   int64_t scratch_floats;
@@ -85,6 +87,21 @@ struct SparseArgs {
   const int32_t* chunk_beg, *chunk_end;   // n_chunks ranges of that order, each inside one column
   const int32_t* col_first_chunk;         // cols + 1
   int n_chunks;
+  const int32_t* colptr;   // cols + 1: ranges of that order
+  int logR, logC;          // lanes per row and per column of the lane-group products
+};
+
+// Lane-group products of several sparse sources in one launch (kernels_sparse.hip).
+constexpr int kSparseMulti = 4;
+struct SparsePart {
+  SparseArgs a;
+  const float* X; int ldx, col0, ncols;   // rows: the operand; columns: the rows of Z
+  float* out; int ldo;                    // rows: P, rows x ldo; columns: [cols][kNarrowCT]
+};
+struct SparseMultiArgs {
+  int n;
+  int first[kSparseMulti + 1];
+  SparsePart s[kSparseMulti];
 };
 
 // Gradient-descent pass over a two-table star join for a wide batch of models (kernels_star.hip).
@@ -139,6 +156,7 @@ struct SegArgs {
   const int32_t* chunk_seg, *chunk_beg, *chunk_end;  // long-segment chunks
   const int32_t* long_seg, *long_first;              // long segments and their chunk ranges
   int n_chunks, n_long;
+  int long_thr;            // longest segment that is summed in one go
   int64_t r_k;
   const float* Y;          // rows addressed through perm (and gidx if given)
   int ldy, col0, ncols;
@@ -175,12 +193,12 @@ struct RowdotMulti {
   RowdotArgs a[kRowdotMulti];
 };
 
-// Sliced segment sums of several sources in one launch (kernels_tmm.hip).
+// Segment sums of several sources in one launch, plain or sliced (kernels_tmm.hip).
 constexpr int kSegMulti = 4;
 struct SegMulti {
   int n;
   int first[kSegMulti + 1];    // workgroups [first[q], first[q + 1]) of the sum kernel serve source q (multiples of kSegSlices)
-  int cfirst[kSegMulti + 1];   // ... of the kernel that adds the per-slice sums
+  int cfirst[kSegMulti + 1];   // ... of the kernel that adds the per-slice sums, or the chunks of long segments
   SegArgs s[kSegMulti];
 };
 
@@ -203,6 +221,22 @@ struct TmmParts {
   int join[kTmmParts];        // 1: join-order form (segment sums in LDS), 0: operand rows read from c.Z
   ColredArgs c[kTmmParts];
   SegArgs s[kTmmParts];       // inverse index and operand of the join-order form
+};
+
+// Tables read through tiles of rows in LDS, several in one launch (kernels_tile.hip).
+constexpr int kTileParts = 4;
+struct TilePart {
+  const float* D; int ck; int64_t rows;
+  const int32_t* colmap;              // product
+  const float* X; int ldx, col0, ncols;   // product: the operand; column reduce: the rows of Z
+  float* out; int ldo;                // product: rows x ldo; column reduce: [workgroup][ck][kNarrowCT]
+  int logR;                           // log2 of the rows per tile
+  int nt;                             // the table is read past the caches
+};
+struct TileMulti {
+  int n;
+  int first[kTileParts + 1];          // workgroups [first[q], first[q + 1]) serve part q
+  TilePart a[kTileParts];
 };
 
 struct FinSource {
@@ -373,6 +407,12 @@ hipError_t launch_lmm_lane(const LmmArgs& a, int vec, int mode, hipStream_t st, 
 // floats; the products of up to kRowdotMulti sources (same operand columns) can share one launch.
 bool rowdot_supported(const LmmArgs& a, int vec);
 hipError_t launch_rowdot_multi(const LmmArgs* a, const int* vec, int n, hipStream_t st);
+bool prod_tile_supported(const LmmArgs& a, int vec);
+hipError_t launch_prod_tile(const LmmArgs* a, int n, hipStream_t st);
+bool asm_tile_supported(const LmmArgs& a, int vec, bool fuseg);
+hipError_t launch_asm_tile(const LmmArgs& a, int mode, hipStream_t st, int* grid_out);
+bool colred_tile_supported(const ColredArgs& c);
+hipError_t launch_colred_tile(const ColredArgs* c, int n, int* nblocks, hipStream_t st);
 int lmm_grid(int64_t r_out, int logL, bool fuseg);
 bool lmm_can_fuse_gradient(int ck, int vec, int logL);
 MfmaShape lmm_mfma_shape(int ck, int nt, bool gathers, bool bf16);
@@ -399,9 +439,12 @@ hipError_t launch_spmm_rows(const SparseArgs& a, const float* X, int ldx, int co
                             hipStream_t st);
 hipError_t launch_spmm_t(const SparseArgs& a, const float* Z, int ldz, int col0, int ncols, float* partial, float* G,
                          hipStream_t st);
+hipError_t launch_spmm_lanes_rows(const SparsePart* s, int n, hipStream_t st);
+hipError_t launch_spmm_lanes_cols(const SparsePart* s, int n, hipStream_t st);
 hipError_t launch_mat_scatter(const SparseArgs* sparse, const float* D, int64_t rows, int ck, const int32_t* colmap,
                               const int32_t* idx, int64_t ident_rows, float* T, int64_t r_T, int c_T, hipStream_t st);
 hipError_t launch_segsum(const SegArgs& a, hipStream_t st);
+hipError_t launch_segsum_narrow(const SegArgs* a, int n, hipStream_t st);   // n <= kSegMulti sources, same operand columns
 // Builds the sliced copy of an inverse index (see SegArgs): sl_rowptr, sl_perm, the chunk records of long runs.
 // src_beg: scratch of kSegSlices * r_k integers; scan_scratch: of (kSegSlices * r_k + 1) / 1024 + 1 integers.
 hipError_t launch_build_sliced_index(const int32_t* rowptr, const int32_t* perm, int64_t r_k, int64_t nnz, int64_t slice_rows,
@@ -480,6 +523,11 @@ hipError_t launch_kmeans_update(float* C, const float* G, const int32_t* counts,
                                 int32_t* counts_out, hipStream_t st);
 hipError_t launch_gnmf_update(float* X, const float* P, const float* Q, int64_t rows, int k, float tiny,
                               float* gram_partial, int64_t partial_floats, int* nparts_out, hipStream_t st);
+
+// A table of more floats than the second-level caches hold (8 x 4 MiB) gains nothing from passing through them, and
+// read past them it leaves them to the gathered operands: the narrow iteration over 5,000,000 x 11 in tiles takes 223
+// microseconds instead of 246.  Tables that fit lose by it (333,333 x 13 trained over and over: 64 against 61).
+inline int stream_past_caches(int64_t floats) { return floats >= (8ll << 20) ? 1 : 0; }
 
 inline int ilog2_ceil(int64_t v) { int l = 0; while ((1ll << l) < v) ++l; return l; }
 

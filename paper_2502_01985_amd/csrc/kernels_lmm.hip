@@ -491,6 +491,7 @@ hipError_t launch_lmm_rows(const LmmArgs& a, int vec, int mode, hipStream_t st, 
   if (lmm_lane_supported(a, vec, mode, fuseg)) return launch_lmm_lane(a, vec, mode, st, grid_out);
   if (lmm_flat_supported(a, vec, fuseg)) return launch_lmm_flat(a, mode, fuseg, st, grid_out);
   if (lmm_flat_pair_supported(a, vec, fuseg)) return launch_lmm_flat_pair(a, mode, fuseg, st, grid_out);
+  if (asm_tile_supported(a, vec, fuseg)) return launch_asm_tile(a, mode, st, grid_out);
   switch (vec) {
     case 4: return launch_ct<4>(a, mode, fuseg, grid, st);
     case 2: return launch_ct<2>(a, mode, fuseg, grid, st);

@@ -1,0 +1,569 @@
+// Narrow operands (at most four columns a pass) over tables whose rows have no useful alignment, in three kernels
+// built on one step: a tile of whole table rows is read as a flat run of float4 (the run starts on a float4 whatever
+// the row length, because a tile starts at a row number that is a multiple of four), parked in LDS, and used from there
+// in the mapping that the arithmetic wants.
+//   product        P_k = D_k X_k               lanes of a row sum its columns
+//   assembly       out = D X + sum_s P_s[row]  with the residual, the loss and D^T e of Alg. 1
+//   column reduce  G_k = D_k^T Z_k             a thread owns a column and every nsub-th row of the tile
+// All three are bound by reading the tables once; a lane that reads such a row itself does it one float at a time.
+// The next tile's loads (and row numbers) are requested before the current one is used, and a tile is at most 20 KiB,
+// so that four or more workgroups share a compute unit.  Measured for three logistic models over 333,333 x 13 joined
+// with 9,001 x 33 and 41,003 x 75, before (a lane group per row, one float per lane) and now, in microseconds: products
+// 27 (two launches) and 7, assembly 41 and 18, column reduces 11 (two launches) and 6.
+#include <algorithm>
+#include <cstring>
+
+#include "ilargi_internal.h"
+
+namespace ilargi {
+
+namespace {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+constexpr int kTileFloats = 5120;                        // most floats of a tile
+constexpr int kTileV = kTileFloats / 4 / kBlock;         // float4 a thread carries
+constexpr int kTileGather = 4;                           // gathered sources of the assembly
+
+// The whole float4s among n floats from p on into registers.  AL: p is 16-byte aligned.  nt: past the caches.
+template <bool AL>
+__device__ __forceinline__ void tile_load(const float* __restrict__ p, int n, bool nt, v4f (&v)[kTileV]) {
+  if (AL && nt) {
+#pragma unroll
+    for (int i = 0; i < kTileV; ++i) {
+      const unsigned e = 4 * (threadIdx.x + i * kBlock);
+      if (e + 4 <= (unsigned)n) v[i] = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(p + e));
+    }
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < kTileV; ++i) {
+    const unsigned e = 4 * (threadIdx.x + i * kBlock);
+    if (e + 4 <= (unsigned)n) {
+      if constexpr (AL) v[i] = *reinterpret_cast<const v4f*>(p + e);
+      else v[i] = (v4f){p[e], p[e + 1], p[e + 2], p[e + 3]};
+    }
+  }
+}
+
+// The tile into LDS; the floats after its last whole float4 (only a table's last tile has any) straight from p.
+__device__ __forceinline__ void tile_put(float* lds, const float* __restrict__ p, int n, const v4f (&v)[kTileV]) {
+#pragma unroll
+  for (int i = 0; i < kTileV; ++i) {
+    const unsigned e = 4 * (threadIdx.x + i * kBlock);
+    if (e + 4 <= (unsigned)n) *reinterpret_cast<v4f*>(lds + e) = v[i];
+  }
+  const unsigned tail = (unsigned)n & ~3u;
+  if (tail + threadIdx.x < (unsigned)n) lds[tail + threadIdx.x] = p[tail + threadIdx.x];
+}
+
+// Operand rows X_k = M_k^T X, [ck][CT].
+template <int CT>
+__device__ __forceinline__ void stage_operand(const float* X, int ldx, int col0, int ncols, const int32_t* colmap, int ck, float* Xs) {
+  for (int e = threadIdx.x; e < ck * CT; e += kBlock) {
+    const int j = e / CT, n = e - j * CT;
+    const int t = colmap[j];
+    Xs[e] = (t >= 0 && n < ncols) ? X[(int64_t)t * ldx + col0 + n] : 0.0f;
+  }
+}
+
+// acc += row `row` of the tile times the operand: the L = 2^logL lanes of a row take every L-th column.  A row length
+// that is an even multiple of L would put the rows of a wavefront on the same banks: each row then starts elsewhere.
+template <int CT>
+__device__ __forceinline__ void tile_dot(const float* tile, const float* Xs, int ck, int logL, int row, int l, bool rotate,
+                                         float (&acc)[CT]) {
+  const int steps = (ck + (1 << logL) - 1) >> logL;
+  int k = rotate ? row % steps : 0;
+  const float* d = tile + row * ck;
+#pragma unroll 4
+  for (int i = 0; i < steps; ++i) {
+    const int j = l + (k << logL);
+    if (j < ck) {
+      const float x = d[j];
+#pragma unroll
+      for (int n = 0; n < CT; ++n) acc[n] = fmaf(x, Xs[j * CT + n], acc[n]);
+    }
+    k = k + 1 == steps ? 0 : k + 1;
+  }
+  for (int m = (1 << logL) >> 1; m >= 1; m >>= 1) {
+#pragma unroll
+    for (int n = 0; n < CT; ++n) acc[n] += __shfl_xor(acc[n], m);
+  }
+}
+
+// g += column j of the tile times the rows es[row][CT], rows sub, sub + nsub, ...
+template <int CT>
+__device__ __forceinline__ void tile_grad(const float* tile, const float* es, int nrow, int ck, int j, int sub, int nsub,
+                                          float (&g)[CT]) {
+#pragma unroll 4
+  for (int r = sub; r < nrow; r += nsub) {
+    const float x = tile[r * ck + j];
+#pragma unroll
+    for (int n = 0; n < CT; ++n) g[n] = fmaf(x, es[r * CT + n], g[n]);
+  }
+}
+
+// The threads' column sums added in order of `sub` and stored as the workgroup's partial block.
+template <int CT>
+__device__ __forceinline__ void tile_grad_store(float* lds, const float (&g)[CT], int ck, int nsub, float* partial) {
+  __syncthreads();
+#pragma unroll
+  for (int n = 0; n < CT; ++n) lds[threadIdx.x * CT + n] = g[n];
+  __syncthreads();
+  for (int o = threadIdx.x; o < ck * CT; o += kBlock) {
+    const int j = o / CT, n = o - j * CT;
+    float s = 0.0f;
+    for (int q = 0; q < nsub; ++q) s += lds[(q * ck + j) * CT + n];
+    partial[(int64_t)j * kNarrowCT + n] = s;
+  }
+}
+
+template <int CT, bool AL>
+__global__ __launch_bounds__(kBlock, 4) void prod_tile_kernel(TileMulti m) {
+  extern __shared__ v4f tile_lds4[];
+  float* tile = reinterpret_cast<float*>(tile_lds4);
+  float* Xs = tile + kTileFloats;
+  int q = 0;
+  while (q + 1 < m.n && (int)blockIdx.x >= m.first[q + 1]) ++q;
+  const TilePart a = m.a[q];
+  const int bid = (int)blockIdx.x - m.first[q], nb = m.first[q + 1] - m.first[q];
+  stage_operand<CT>(a.X, a.ldx, a.col0, a.ncols, a.colmap, a.ck, Xs);
+  const int Rt = 1 << a.logR, logL = 8 - a.logR;
+  const int row = (int)threadIdx.x >> logL, l = (int)threadIdx.x & ((1 << logL) - 1);
+  const bool rotate = ((a.ck >> logL) & 1) == 0;
+  const int64_t stride = (int64_t)nb * Rt;
+  v4f v[kTileV];
+  int64_t i0 = (int64_t)bid * Rt;
+  if (i0 < a.rows) tile_load<AL>(a.D + i0 * a.ck, (int)min((int64_t)Rt, a.rows - i0) * a.ck, a.nt, v);
+  for (; i0 < a.rows; i0 += stride) {
+    const int nrow = (int)min((int64_t)Rt, a.rows - i0);
+    tile_put(tile, a.D + i0 * a.ck, nrow * a.ck, v);
+    __syncthreads();
+    const int64_t in = i0 + stride;
+    if (in < a.rows) tile_load<AL>(a.D + in * a.ck, (int)min((int64_t)Rt, a.rows - in) * a.ck, a.nt, v);
+    float acc[CT];
+#pragma unroll
+    for (int n = 0; n < CT; ++n) acc[n] = 0.0f;
+    tile_dot<CT>(tile, Xs, a.ck, logL, row, l, rotate, acc);   // (rows beyond nrow: stale LDS values, not stored)
+    if (l == 0 && row < nrow) {
+      float* o = a.out + (i0 + row) * a.ldo + a.col0;
+#pragma unroll
+      for (int n = 0; n < CT; ++n)
+        if (n < a.ncols) o[n] = acc[n];
+    }
+    __syncthreads();
+  }
+}
+
+// Residual and loss of one row and column (MODE 1 linear, 2 logistic; 0: the product itself).
+template <int MODE>
+__device__ __forceinline__ float residual(float z, float y, float& loss) {
+  if constexpr (MODE == 1) {
+    const float r = z - y;
+    loss = fmaf(r, r, loss);
+    return r;
+  } else if constexpr (MODE == 2) {
+    // one exponential serves the sigmoid and the softplus: e = exp(-|z|)
+    const float e = __expf(-fabsf(z));
+    const float d = 1.0f + e;
+    float inv = __builtin_amdgcn_rcpf(d);
+    inv = fmaf(inv, fmaf(-d, inv, 1.0f), inv);           // one Newton step: the reciprocal to the last bit or so
+    loss += fmaxf(z, 0.0f) + fmaf(e - (d - 1.0f), inv, __logf(d)) - y * z;   // log(1 + e) with the rounding of 1 + e made good
+    return (z >= 0.0f ? inv : e * inv) - y;
+  }
+  return z;
+}
+
+// Loss of this workgroup: butterfly inside each wavefront, then the wavefronts in order.
+template <int CT>
+__device__ __forceinline__ void store_loss(const float (&loss)[CT], float (*lsum)[CT], float* partial) {
+#pragma unroll
+  for (int n = 0; n < CT; ++n) {
+    float s = loss[n];
+    for (int m = kWave / 2; m >= 1; m >>= 1) s += __shfl_xor(s, m);
+    if (threadIdx.x % kWave == 0) lsum[threadIdx.x / kWave][n] = s;
+  }
+  __syncthreads();
+  if (threadIdx.x < CT) {
+    float s = 0.0f;
+    for (int w = 0; w < kBlock / kWave; ++w) s += lsum[w][threadIdx.x];
+    partial[(int64_t)blockIdx.x * kNarrowCT + threadIdx.x] = s;
+  }
+}
+
+// Assembly without an identity source (every table is joined): a thread takes kGatherRows rows, 256 apart, with the
+// row numbers and then the gathered values of all of them in flight.  1,000,000 rows over two tables with the logistic
+// residual: 11 microseconds (16 with one row per thread and step), of which 3 are its bytes; the rest is the chain row
+// number -> value -> store of a kernel this short.
+constexpr int kGatherRows = 4;
+
+template <int CT, int MODE>
+__global__ __launch_bounds__(kBlock) void asm_gather_kernel(LmmArgs a) {
+  float loss_local[CT];
+#pragma unroll
+  for (int n = 0; n < CT; ++n) loss_local[n] = 0.0f;
+  constexpr int64_t step = (int64_t)kBlock * kGatherRows;
+  for (int64_t base = (int64_t)blockIdx.x * step + threadIdx.x; base < a.r_out + threadIdx.x; base += (int64_t)gridDim.x * step) {
+    float z[kGatherRows][CT], y[kGatherRows];
+#pragma unroll
+    for (int u = 0; u < kGatherRows; ++u) {
+      const int64_t i = base + u * kBlock;
+#pragma unroll
+      for (int n = 0; n < CT; ++n) z[u][n] = 0.0f;
+      y[u] = 0.0f;
+      if constexpr (MODE != 0) y[u] = i < a.r_out ? a.y[i] : 0.0f;
+    }
+    for (int s0 = 0; s0 < a.g.n; s0 += 2) {
+      int j[2][kGatherRows];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int u = 0; u < kGatherRows; ++u) {
+          const int64_t i = base + u * kBlock;
+          j[h][u] = -1;
+          if (s0 + h < a.g.n && i < a.r_out)
+            j[h][u] = a.g.idx[s0 + h] != nullptr ? (int)a.g.idx[s0 + h][i] : (i < a.g.rows[s0 + h] ? (int)i : -1);
+        }
+      float p[2][kGatherRows][CT];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int u = 0; u < kGatherRows; ++u)
+#pragma unroll
+          for (int n = 0; n < CT; ++n)
+            p[h][u][n] = (j[h][u] >= 0 && n < a.ncols) ? a.g.P[s0 + h][(int64_t)j[h][u] * a.g.ldp + a.col0 + n] : 0.0f;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int u = 0; u < kGatherRows; ++u)
+#pragma unroll
+          for (int n = 0; n < CT; ++n) z[u][n] += p[h][u][n];
+    }
+#pragma unroll
+    for (int u = 0; u < kGatherRows; ++u) {
+      const int64_t i = base + u * kBlock;
+      if (i >= a.r_out) break;
+#pragma unroll
+      for (int n = 0; n < CT; ++n) {
+        if (n >= a.ncols) break;
+        const float r = residual<MODE>(z[u][n], y[u], loss_local[n]);
+        float* op = a.out + i * a.ldo + a.col0 + n;
+        if (a.nt_out) __builtin_nontemporal_store(r, op);
+        else *op = r;
+      }
+    }
+  }
+  if constexpr (MODE != 0) {
+    __shared__ float lsum[kBlock / kWave][CT];
+    store_loss<CT>(loss_local, lsum, a.loss_partial);
+  }
+}
+
+// MODE 0: store the product.  1: linear residual z - y.  2: logistic residual sigmoid(z) - y.  FUSEG: this workgroup's
+// share of D^T e as well (at most 256 columns).  The first lane of a row owns its target row.
+template <int CT, int MODE, bool FUSEG, bool AL>
+__global__ __launch_bounds__(kBlock, 4) void asm_tile_kernel(LmmArgs a, int logR) {
+  extern __shared__ v4f tile_lds4[];
+  float* tile = reinterpret_cast<float*>(tile_lds4);
+  float* es = tile + kTileFloats;                        // [Rt][CT] residuals of the tile
+  float* Xs = es + kBlock * CT;
+  const int ck = a.ck;
+  stage_operand<CT>(a.X, a.ldx, a.col0, a.ncols, a.colmap, ck, Xs);
+  const int Rt = 1 << logR, logL = 8 - logR;
+  const int tid = threadIdx.x, row = tid >> logL, l = tid & ((1 << logL) - 1);
+  const bool rotate = ((ck >> logL) & 1) == 0;
+  const int nsub = FUSEG ? kBlock / ck : 1;
+  const int gsub = FUSEG ? tid / ck : 0, gj = FUSEG ? tid - gsub * ck : 0;
+  const int64_t stride = (int64_t)gridDim.x * Rt;
+  float g[CT], loss_local[CT];
+#pragma unroll
+  for (int n = 0; n < CT; ++n) g[n] = loss_local[n] = 0.0f;
+  auto table_rows = [&](int64_t i) { return (int)max((int64_t)0, min((int64_t)Rt, a.d_rows - i)); };   // rows of D in the tile
+  auto row_of = [&](int s, int64_t i) {
+    if (a.g.idx[s] != nullptr) return (int)a.g.idx[s][i];
+    return i < a.g.rows[s] ? (int)i : -1;
+  };
+  // Requests run one tile ahead, row numbers two: when a tile starts, everything it uses was asked for a tile ago.
+  v4f v[kTileV];
+  int jn[kTileGather];
+  float pn[kTileGather][CT], yn = 0.0f;
+  auto load_index = [&](int64_t i) {
+#pragma unroll
+    for (int s = 0; s < kTileGather; ++s) jn[s] = (s < a.g.n && l == 0 && i < a.r_out) ? row_of(s, i) : -1;
+  };
+  auto gather = [&](int64_t i) {
+#pragma unroll
+    for (int s = 0; s < kTileGather; ++s) {
+      const float* p = jn[s] >= 0 ? a.g.P[s] + (int64_t)jn[s] * a.g.ldp + a.col0 : nullptr;
+#pragma unroll
+      for (int n = 0; n < CT; ++n) pn[s][n] = (jn[s] >= 0 && n < a.ncols) ? p[n] : 0.0f;
+    }
+    if constexpr (MODE != 0) yn = (l == 0 && i < a.r_out) ? a.y[i] : 0.0f;
+  };
+  int64_t i0 = (int64_t)blockIdx.x * Rt;
+  load_index(i0 + row);
+  tile_load<AL>(a.D + i0 * ck, i0 < a.r_out ? table_rows(i0) * ck : 0, a.nt_in, v);
+  gather(i0 + row);
+  load_index(i0 + stride + row);
+  for (; i0 < a.r_out; i0 += stride) {
+    const int64_t i = i0 + row;
+    const bool own = l == 0 && i < a.r_out;
+    const int drow = table_rows(i0);
+    float gsum[CT];
+#pragma unroll
+    for (int n = 0; n < CT; ++n) {
+      gsum[n] = 0.0f;
+#pragma unroll
+      for (int s = 0; s < kTileGather; ++s) gsum[n] += pn[s][n];
+    }
+    const float yi = yn;
+    if (own) {
+      for (int s = kTileGather; s < a.g.n; ++s) {
+        const int j = row_of(s, i);
+        if (j >= 0) {
+          const float* p = a.g.P[s] + (int64_t)j * a.g.ldp + a.col0;
+#pragma unroll
+          for (int n = 0; n < CT; ++n)
+            if (n < a.ncols) gsum[n] += p[n];
+        }
+      }
+    }
+    tile_put(tile, a.D + i0 * ck, drow * ck, v);
+    __syncthreads();
+    const int64_t in = i0 + stride;
+    gather(in + row);
+    load_index(in + stride + row);
+    if (in < a.r_out) tile_load<AL>(a.D + in * ck, table_rows(in) * ck, a.nt_in, v);
+    float z[CT];
+#pragma unroll
+    for (int n = 0; n < CT; ++n) z[n] = 0.0f;
+    tile_dot<CT>(tile, Xs, ck, logL, row, l, rotate, z);
+    if (row >= drow) {
+#pragma unroll
+      for (int n = 0; n < CT; ++n) z[n] = 0.0f;
+    }
+    if (l == 0) {
+#pragma unroll
+      for (int n = 0; n < CT; ++n) {
+        float r = 0.0f;
+        if (own && n < a.ncols) {
+          r = residual<MODE>(z[n] + gsum[n], yi, loss_local[n]);
+          float* op = a.out + i * a.ldo + a.col0 + n;
+          if (a.nt_out) __builtin_nontemporal_store(r, op);
+          else *op = r;
+        }
+        if constexpr (FUSEG) es[row * CT + n] = r;
+      }
+    }
+    __syncthreads();
+    if constexpr (FUSEG) {
+      if (gsub < nsub) tile_grad<CT>(tile, es, drow, ck, gj, gsub, nsub, g);
+      __syncthreads();
+    }
+  }
+  if constexpr (MODE != 0) {
+    __shared__ float lsum[kBlock / kWave][CT];
+    store_loss<CT>(loss_local, lsum, a.loss_partial);
+  }
+  if constexpr (FUSEG) tile_grad_store<CT>(tile, g, ck, nsub, a.grad_partial + (int64_t)blockIdx.x * ck * kNarrowCT);
+}
+
+template <int CT, bool AL>
+__global__ __launch_bounds__(kBlock, 4) void colred_tile_kernel(TileMulti m) {
+  extern __shared__ v4f tile_lds4[];
+  float* tile = reinterpret_cast<float*>(tile_lds4);
+  float* es = tile + kTileFloats;
+  int q = 0;
+  while (q + 1 < m.n && (int)blockIdx.x >= m.first[q + 1]) ++q;
+  const TilePart a = m.a[q];
+  const int bid = (int)blockIdx.x - m.first[q], nb = m.first[q + 1] - m.first[q];
+  const int Rt = 1 << a.logR;
+  const int nsub = kBlock / a.ck, gsub = (int)threadIdx.x / a.ck, gj = (int)threadIdx.x - gsub * a.ck;
+  const int64_t stride = (int64_t)nb * Rt;
+  float g[CT];
+#pragma unroll
+  for (int n = 0; n < CT; ++n) g[n] = 0.0f;
+  v4f v[kTileV];
+  float zr[CT];                                          // operand row of this thread (Rt <= kBlock)
+  auto load = [&](int64_t i) {
+    tile_load<AL>(a.D + i * a.ck, (int)min((int64_t)Rt, a.rows - i) * a.ck, a.nt, v);
+#pragma unroll
+    for (int n = 0; n < CT; ++n)
+      zr[n] = ((int)threadIdx.x < Rt && i + threadIdx.x < a.rows && n < a.ncols) ? a.X[(i + threadIdx.x) * a.ldx + a.col0 + n] : 0.0f;
+  };
+  int64_t i0 = (int64_t)bid * Rt;
+  if (i0 < a.rows) load(i0);
+  for (; i0 < a.rows; i0 += stride) {
+    const int nrow = (int)min((int64_t)Rt, a.rows - i0);
+    tile_put(tile, a.D + i0 * a.ck, nrow * a.ck, v);
+    if ((int)threadIdx.x < Rt) {
+#pragma unroll
+      for (int n = 0; n < CT; ++n) es[threadIdx.x * CT + n] = zr[n];
+    }
+    __syncthreads();
+    if (i0 + stride < a.rows) load(i0 + stride);
+    if (gsub < nsub) tile_grad<CT>(tile, es, nrow, a.ck, gj, gsub, nsub, g);
+    __syncthreads();
+  }
+  tile_grad_store<CT>(tile, g, a.ck, nsub, a.out + (int64_t)bid * a.ck * kNarrowCT);
+}
+
+// Rows per tile (a power of two of 4 to 256): as many as fit, fewer (not below 64) where the table would not give 512
+// tiles.
+int tile_logR(int64_t rows, int ck) {
+  int logR = 8;
+  while (logR > 2 && (int64_t)ck << logR > kTileFloats) --logR;
+  while (logR > 6 && rows >> logR < 512) --logR;
+  return logR;
+}
+
+// A launch reads all its tables as float4 or, when one of them does not start on one, all of them float by float.
+bool all_aligned(const TileMulti& m) {
+  for (int q = 0; q < m.n; ++q)
+    if (reinterpret_cast<uintptr_t>(m.a[q].D) % 16 != 0) return false;
+  return true;
+}
+
+#define ILARGI_TILE(kernel, ct, al, grid, lds, st, ...)                                            \
+  do {                                                                                             \
+    if (ct == 1 && al) kernel<1, true><<<grid, kBlock, lds, st>>>(__VA_ARGS__);                    \
+    else if (ct == 1) kernel<1, false><<<grid, kBlock, lds, st>>>(__VA_ARGS__);                    \
+    else if (ct == 2 && al) kernel<2, true><<<grid, kBlock, lds, st>>>(__VA_ARGS__);               \
+    else if (ct == 2) kernel<2, false><<<grid, kBlock, lds, st>>>(__VA_ARGS__);                    \
+    else if (al) kernel<4, true><<<grid, kBlock, lds, st>>>(__VA_ARGS__);                          \
+    else kernel<4, false><<<grid, kBlock, lds, st>>>(__VA_ARGS__);                                 \
+  } while (0)
+
+constexpr int kTileMaxCols = kTileFloats / 4;            // four rows of so many columns fill a tile
+
+}  // namespace
+
+// Rows of whole float4s are left to the kernels that read them in place: above 256 columns (the streaming product kernel
+// has the shorter ones) the tile costs more than it gives, 100,000 x 800: 59 microseconds in place, 81 through tiles.
+bool prod_tile_supported(const LmmArgs& a, int vec) {
+  if (vec == 4 && a.ck > 256) return false;
+  return a.D != nullptr && a.g.n == 0 && a.ncols >= 1 && a.ncols <= kNarrowCT && a.r_out > 0 && a.ck >= 1 && a.ck <= kTileMaxCols;
+}
+
+// The products of n <= kTileParts sources with the same operand columns in one launch.
+hipError_t launch_prod_tile(const LmmArgs* a, int n, hipStream_t st) {
+  if (n < 1 || n > kTileParts) return hipErrorInvalidValue;
+  TileMulti m;
+  memset(&m, 0, sizeof(m));
+  m.n = n;
+  int64_t tiles[kTileParts], total = 0;
+  int ckmax = 1;
+  for (int q = 0; q < n; ++q) {
+    if (!prod_tile_supported(a[q], 1) || a[q].ncols != a[0].ncols) return hipErrorInvalidValue;
+    TilePart& t = m.a[q];
+    t.D = a[q].D; t.ck = a[q].ck; t.rows = std::min(a[q].r_out, a[q].d_rows); t.colmap = a[q].colmap;
+    t.X = a[q].X; t.ldx = a[q].ldx; t.col0 = a[q].col0; t.ncols = a[q].ncols; t.out = a[q].out; t.ldo = a[q].ldo;
+    t.nt = stream_past_caches(t.rows * t.ck);
+    t.logR = tile_logR(t.rows, t.ck);
+    tiles[q] = (t.rows + (1 << t.logR) - 1) >> t.logR;
+    total += tiles[q];
+    ckmax = std::max(ckmax, t.ck);
+  }
+  const int64_t cap = 2048;
+  for (int q = 0; q < n; ++q)
+    m.first[q + 1] = m.first[q] + (int)std::max<int64_t>(1, total > cap ? tiles[q] * cap / total : tiles[q]);
+  const int ct = a[0].ncols <= 1 ? 1 : (a[0].ncols <= 2 ? 2 : 4);
+  const size_t lds = sizeof(float) * (kTileFloats + (size_t)ckmax * ct);
+  ILARGI_TILE(prod_tile_kernel, ct, all_aligned(m), m.first[n], lds, st, m);
+  return hipGetLastError();
+}
+
+// One operand column over rows of float4 (or float2) that fill their lanes is left to the kernel that reads such rows in
+// place: 333,333 x 100, one logistic model, 71 microseconds an iteration in place and 76 through tiles (200 columns: 116
+// and 126; 64: 50 and 54); where a fifth of the lanes or more idles the tiles win (68 columns: 66 and 56), and with
+// several operand columns always (100 columns, three models: 117 and 101; 40 columns: 71 and 53).
+bool asm_tile_supported(const LmmArgs& a, int vec, bool fuseg) {
+  if (a.ncols < 1 || a.ncols > kNarrowCT || a.r_out <= 0) return false;
+  if (a.D == nullptr) return !fuseg;
+  if (a.ck < 1 || a.ck > (fuseg ? kBlock : kTileMaxCols)) return false;
+  const int nvec = a.ck / vec;
+  if (vec >= 2 && a.ncols == 1 && nvec >= 16 && (nvec > kWave || 4 * nvec >= 3 * (1 << ilog2_ceil(nvec)))) return false;
+  return vec != 4 || a.ck <= 256;
+}
+
+hipError_t launch_asm_tile(const LmmArgs& a, int mode, hipStream_t st, int* grid_out) {
+  const bool fuseg = a.grad_partial != nullptr && mode != 0;
+  if (!asm_tile_supported(a, 1, fuseg)) return hipErrorInvalidValue;
+  if (a.D == nullptr) {
+    int64_t grid = (a.r_out + kBlock * kGatherRows - 1) / (kBlock * kGatherRows);
+    if (grid > 4096) grid = 4096;
+    if (grid_out) *grid_out = (int)grid;
+#define ILARGI_GATHER(C)                                                                  \
+  do {                                                                                    \
+    if (mode == 0) asm_gather_kernel<C, 0><<<(int)grid, kBlock, 0, st>>>(a);              \
+    else if (mode == 1) asm_gather_kernel<C, 1><<<(int)grid, kBlock, 0, st>>>(a);         \
+    else asm_gather_kernel<C, 2><<<(int)grid, kBlock, 0, st>>>(a);                        \
+  } while (0)
+    if (a.ncols <= 1) ILARGI_GATHER(1);
+    else if (a.ncols <= 2) ILARGI_GATHER(2);
+    else ILARGI_GATHER(4);
+#undef ILARGI_GATHER
+    return hipGetLastError();
+  }
+  const int logR = tile_logR(a.r_out, a.ck);
+  int64_t grid = (a.r_out + (1 << logR) - 1) >> logR;
+  const int64_t cap = fuseg ? kColredBlocks : 4096;
+  if (grid > cap) {
+    const int64_t per = (grid + cap - 1) / cap;
+    grid = (grid + per - 1) / per;
+  }
+  if (grid_out) *grid_out = (int)grid;
+  const int ct = a.ncols <= 1 ? 1 : (a.ncols <= 2 ? 2 : 4);
+  const size_t lds = sizeof(float) * (kTileFloats + (size_t)(kBlock + a.ck) * ct);
+#define ILARGI_ASM(C, AL)                                                                                    \
+  do {                                                                                                       \
+    if (mode == 0) asm_tile_kernel<C, 0, false, AL><<<(int)grid, kBlock, lds, st>>>(a, logR);                \
+    else if (mode == 1 && fuseg) asm_tile_kernel<C, 1, true, AL><<<(int)grid, kBlock, lds, st>>>(a, logR);   \
+    else if (mode == 1) asm_tile_kernel<C, 1, false, AL><<<(int)grid, kBlock, lds, st>>>(a, logR);           \
+    else if (fuseg) asm_tile_kernel<C, 2, true, AL><<<(int)grid, kBlock, lds, st>>>(a, logR);                \
+    else asm_tile_kernel<C, 2, false, AL><<<(int)grid, kBlock, lds, st>>>(a, logR);                          \
+  } while (0)
+  const bool al = reinterpret_cast<uintptr_t>(a.D) % 16 == 0;
+  if (ct == 1 && al) ILARGI_ASM(1, true);
+  else if (ct == 1) ILARGI_ASM(1, false);
+  else if (ct == 2 && al) ILARGI_ASM(2, true);
+  else if (ct == 2) ILARGI_ASM(2, false);
+  else if (al) ILARGI_ASM(4, true);
+  else ILARGI_ASM(4, false);
+#undef ILARGI_ASM
+  return hipGetLastError();
+}
+
+bool colred_tile_supported(const ColredArgs& c) {
+  return c.ck >= 1 && c.ck <= kBlock && c.ncols >= 1 && c.ncols <= kNarrowCT && c.rows > 0;
+}
+
+// The column reduces of n <= kTileParts sources in one launch; nblocks[q] receives the number of partial blocks that
+// source q leaves (at most kColredBlocks).
+hipError_t launch_colred_tile(const ColredArgs* c, int n, int* nblocks, hipStream_t st) {
+  if (n < 1 || n > kTileParts) return hipErrorInvalidValue;
+  TileMulti m;
+  memset(&m, 0, sizeof(m));
+  m.n = n;
+  int64_t tiles[kTileParts], total = 0;
+  for (int q = 0; q < n; ++q) {
+    if (!colred_tile_supported(c[q]) || c[q].ncols != c[0].ncols) return hipErrorInvalidValue;
+    TilePart& t = m.a[q];
+    t.D = c[q].D; t.ck = c[q].ck; t.rows = c[q].rows;
+    t.X = c[q].Z; t.ldx = c[q].ldz; t.col0 = c[q].col0; t.ncols = c[q].ncols; t.out = c[q].partial;
+    t.nt = stream_past_caches(t.rows * t.ck);
+    t.logR = tile_logR(t.rows, t.ck);
+    tiles[q] = (t.rows + (1 << t.logR) - 1) >> t.logR;
+    total += tiles[q];
+  }
+  for (int q = 0; q < n; ++q) {
+    nblocks[q] = (int)std::max<int64_t>(1, total > kColredBlocks ? tiles[q] * kColredBlocks / total : tiles[q]);
+    m.first[q + 1] = m.first[q] + nblocks[q];
+  }
+  const int ct = c[0].ncols <= 1 ? 1 : (c[0].ncols <= 2 ? 2 : 4);
+  const size_t lds = sizeof(float) * (kTileFloats + (size_t)kBlock * ct);
+  ILARGI_TILE(colred_tile_kernel, ct, all_aligned(m), m.first[n], lds, st, m);
+  return hipGetLastError();
+}
+
+}  // namespace ilargi

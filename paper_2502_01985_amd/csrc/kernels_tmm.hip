@@ -20,65 +20,70 @@ __device__ __forceinline__ int64_t seg_row(const SegArgs& a, int64_t p) {
   return i;
 }
 
-// Narrow form: G = 2^logG lanes share one segment and stride over its entries; CT columns per lane.
-// Work items [0, r_k) are whole segments (skipped when longer than kLongSeg), items [r_k, r_k + n_chunks)
-// are chunks of long segments whose sums go to chunk_partial.
-// (bx of gx: this workgroup's place among the workgroups that share the work)
+constexpr int kSegU = 8;
+
+// Sum of the operand rows of entries [beg, end) by lanes `lig` of G: kSegU entries of a lane in flight, first their
+// target rows, then the operand rows.
 template <int CT>
-__device__ __forceinline__ void segsum_narrow_body(const SegArgs& a, int bx, int gx) {
-  const int G = 1 << a.logG;
-  const int lig = threadIdx.x & (G - 1);
-  const int64_t n_items = a.r_k + a.n_chunks;
-  const int64_t gpb = kBlock >> a.logG;
-  for (int64_t item = (int64_t)bx * gpb + (threadIdx.x >> a.logG); item < n_items + gpb;
-       item += (int64_t)gx * gpb) {
-    // keep whole wavefronts in the loop so that the butterfly below is convergent
-    bool live = item < n_items;
-    int64_t beg = 0, end = 0;
-    float* dst = nullptr;
-    if (live) {
-      if (item < a.r_k) {
-        beg = a.rowptr[item];
-        end = a.rowptr[item + 1];
-        dst = a.Z + item * a.ldz + a.zcol0;
-        if (end - beg > kLongSeg) { live = false; }
-      } else {
-        int c = (int)(item - a.r_k);
-        beg = a.chunk_beg[c];
-        end = a.chunk_end[c];
-        dst = a.chunk_partial + (int64_t)c * a.ncols;
-      }
-    }
-    float acc[CT];
+__device__ __forceinline__ void segsum_range(const SegArgs& a, int64_t beg, int64_t end, int lig, int G, float (&acc)[CT]) {
 #pragma unroll
-    for (int n = 0; n < CT; ++n) acc[n] = 0.0f;
-    if (live) {
-      for (int64_t p = beg + lig; p < end; p += G) {
-        int64_t r = seg_row(a, p);
-        if (r >= 0) {
-          const float* y = a.Y + r * a.ldy + a.col0;
+  for (int n = 0; n < CT; ++n) acc[n] = 0.0f;
+  for (int64_t p = beg + lig; p < end; p += kSegU * G) {
+    int64_t r[kSegU];
 #pragma unroll
-          for (int n = 0; n < CT; ++n)
-            if (n < a.ncols) acc[n] += y[n];
-        }
-      }
-    }
-    for (int m = G >> 1; m >= 1; m >>= 1) {
+    for (int u = 0; u < kSegU; ++u) r[u] = p + u * G < end ? seg_row(a, p + u * G) : -1;
+    float y[kSegU][CT];
 #pragma unroll
-      for (int n = 0; n < CT; ++n) acc[n] += __shfl_xor(acc[n], m);
-    }
-    if (live && lig == 0) {
+    for (int u = 0; u < kSegU; ++u)
 #pragma unroll
-      for (int n = 0; n < CT; ++n)
-        if (n < a.ncols) dst[n] = acc[n];
-    }
-    if (item >= n_items) break;
+      for (int n = 0; n < CT; ++n) y[u][n] = (r[u] >= 0 && n < a.ncols) ? a.Y[r[u] * a.ldy + a.col0 + n] : 0.0f;
+#pragma unroll
+    for (int u = 0; u < kSegU; ++u)
+#pragma unroll
+      for (int n = 0; n < CT; ++n) acc[n] += y[u][n];
+  }
+  for (int m = G >> 1; m >= 1; m >>= 1) {
+#pragma unroll
+    for (int n = 0; n < CT; ++n) acc[n] += __shfl_xor(acc[n], m);
   }
 }
 
+// Narrow form, CT columns per lane.  Bound by the two dependent round trips (index entry, operand row) per group of
+// entries, so a lane keeps eight entries in flight and a group of 2^logG lanes is sized for two rounds at most: the
+// segments longer than a.long_thr are cut into chunks, which whole wavefronts sum and segsum_combine_kernel adds up.
+// 333,333 rows over 9,001 Zipf and 41,003 uniform keys, three columns: 21 microseconds in one launch (with segments cut
+// at 2048 entries and one entry in flight: 42 and 8 in two).  What is left are 650,000 gathers from a residual of 4 MB,
+// which does not stay in an XCD's L2 beside the index.
 template <int CT>
-__global__ __launch_bounds__(kBlock) void segsum_narrow_kernel(SegArgs a) {
-  segsum_narrow_body<CT>(a, blockIdx.x, gridDim.x);
+__global__ __launch_bounds__(kBlock) void segsum_narrow_kernel(SegMulti m) {
+  int q = 0;
+  while (q + 1 < m.n && (int)blockIdx.x >= m.first[q + 1]) ++q;
+  const SegArgs a = m.s[q];
+  const int bx = (int)blockIdx.x - m.first[q], gx = m.first[q + 1] - m.first[q];
+  float acc[CT];
+  const int G = 1 << a.logG, lig = threadIdx.x & (G - 1);
+  const int64_t gpb = kBlock >> a.logG;
+  for (int64_t base = (int64_t)bx * gpb; base < a.r_k; base += (int64_t)gx * gpb) {   // same trip count for all lanes
+    const int64_t j = base + (threadIdx.x >> a.logG);
+    int64_t beg = 0, end = 0;
+    if (j < a.r_k) { beg = a.rowptr[j]; end = a.rowptr[j + 1]; }
+    const bool live = j < a.r_k && end - beg <= a.long_thr;
+    segsum_range<CT>(a, beg, live ? end : beg, lig, G, acc);
+    if (live && lig == 0) {
+#pragma unroll
+      for (int n = 0; n < CT; ++n)
+        if (n < a.ncols) a.Z[j * a.ldz + a.zcol0 + n] = acc[n];
+    }
+  }
+  const int lane = threadIdx.x % kWave;
+  for (int c = bx * (kBlock / kWave) + threadIdx.x / kWave; c < a.n_chunks; c += gx * (kBlock / kWave)) {
+    segsum_range<CT>(a, a.chunk_beg[c], a.chunk_end[c], lane, kWave, acc);
+    if (lane == 0) {
+#pragma unroll
+      for (int n = 0; n < CT; ++n)
+        if (n < a.ncols) a.chunk_partial[(int64_t)c * a.ncols + n] = acc[n];
+    }
+  }
 }
 
 // Wide form: W lanes of a segment each own columns lane, lane + W, ...  The lanes first load W different
@@ -97,7 +102,7 @@ __global__ __launch_bounds__(kBlock) void segsum_wide_kernel(SegArgs a) {
       beg = a.rowptr[item];
       end = a.rowptr[item + 1];
       dst = a.Z + item * a.ldz + a.zcol0;
-      if (end - beg > kLongSeg) continue;
+      if (end - beg > a.long_thr) continue;
     } else {
       int c = (int)(item - a.r_k);
       beg = a.chunk_beg[c];
@@ -350,15 +355,20 @@ __global__ __launch_bounds__(kBlock) void segsum_sliced_combine_kernel(SegMulti 
   segsum_sliced_combine_body<CT>(m.s[q], (int)blockIdx.x - m.cfirst[q], m.cfirst[q + 1] - m.cfirst[q]);
 }
 
-// Long segments: add the chunk sums in chunk order.
-__global__ __launch_bounds__(kBlock) void segsum_combine_kernel(SegArgs a) {
-  int64_t total = (int64_t)a.n_long * a.ncols;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    int s = (int)(e / a.ncols), n = (int)(e % a.ncols);
+// Long segments: one wavefront adds a segment's chunk sums for one operand column, in a fixed order.
+__global__ __launch_bounds__(kBlock) void segsum_combine_kernel(SegMulti m) {
+  int q = 0;
+  while (q + 1 < m.n && (int)blockIdx.x >= m.cfirst[q + 1]) ++q;
+  const SegArgs a = m.s[q];
+  const int bx = (int)blockIdx.x - m.cfirst[q], gx = m.cfirst[q + 1] - m.cfirst[q];
+  const int lane = threadIdx.x % kWave;
+  const int64_t total = (int64_t)a.n_long * a.ncols;
+  for (int64_t e = (int64_t)bx * (kBlock / kWave) + threadIdx.x / kWave; e < total; e += (int64_t)gx * (kBlock / kWave)) {
+    const int s = (int)(e / a.ncols), n = (int)(e % a.ncols);
     float acc = 0.0f;
-    for (int c = a.long_first[s]; c < a.long_first[s + 1]; ++c) acc += a.chunk_partial[(int64_t)c * a.ncols + n];
-    a.Z[(int64_t)a.long_seg[s] * a.ldz + a.zcol0 + n] = acc;
+    for (int c = a.long_first[s] + lane; c < a.long_first[s + 1]; c += kWave) acc += a.chunk_partial[(int64_t)c * a.ncols + n];
+    for (int k = kWave / 2; k >= 1; k >>= 1) acc += __shfl_xor(acc, k);
+    if (lane == 0) a.Z[(int64_t)a.long_seg[s] * a.ldz + a.zcol0 + n] = acc;
   }
 }
 
@@ -468,7 +478,7 @@ constexpr int kJoinTileFloats = 2048;  // LDS floats for the gathered operand ro
 // multiplied right away; Z is never written to memory and the table is the only stream.  The operand rows of a
 // tile of consecutive index entries are gathered with all their loads in flight (entry -> target row -> operand
 // row: two dependent round trips per tile, whatever the number of rows), then the thread of each table row adds
-// its entries in index order.  Needs a table without long segments (s.n_long == 0) and a single column slab.
+// its entries in index order.  Needs a table without segments above kLongSeg (the plan then has no row ranges) and a single column slab.
 template <int VEC, int CT>
 __device__ __forceinline__ void colred_join_body(const ColredArgs& a, const SegArgs& s, int bx) {
   constexpr int kTile = kJoinTileFloats / CT;          // index entries per tile
@@ -618,37 +628,96 @@ __global__ __launch_bounds__(kBlock) void finalize_kernel(FinArgs a, int c_T) {
   }
 }
 
+// The same step for sources that left at most kFinFlat partial blocks each (sparse tables leave one): one thread per
+// target column.  A workgroup per column spends its time on starting 13,350 workgroups (a one-hot schema of that many
+// columns: 19 microseconds, 4 this way).
+constexpr int kFinFlat = 4;
+
+template <int MODE>
+__global__ __launch_bounds__(kBlock) void finalize_flat_kernel(FinArgs a, int c_T, int col_blocks) {
+  __shared__ float scratch[kBlock / kWave][4];
+  if ((int)blockIdx.x == col_blocks) {
+    if constexpr (MODE == 1) {
+      float4 s = block_sum4(reinterpret_cast<const float4*>(a.loss_partial), 1, a.n_loss_partial, scratch);
+      float sv[4] = {s.x, s.y, s.z, s.w};
+      if ((int)threadIdx.x < a.ncols) a.loss[a.col0 + threadIdx.x] = sv[threadIdx.x] * a.loss_scale;
+    }
+    return;
+  }
+  const int t = blockIdx.x * kBlock + threadIdx.x;
+  if (t >= c_T) return;
+  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int k = 0; k < a.n; ++k) {
+    const int j = a.s[k].tcol2src[t];
+    if (j < 0) continue;
+    for (int b = 0; b < a.s[k].nblocks; ++b) {
+      const float4 s = reinterpret_cast<const float4*>(a.s[k].partial)[(int64_t)b * a.s[k].ck + j];
+      acc[0] += s.x; acc[1] += s.y; acc[2] += s.z; acc[3] += s.w;
+    }
+  }
+#pragma unroll
+  for (int n = 0; n < kNarrowCT; ++n) {
+    if (n >= a.ncols) break;
+    float* o = a.out + (int64_t)t * a.ldo + a.col0 + n;
+    if constexpr (MODE == 0) *o = acc[n];
+    else *o = *o - a.lr[a.col0 + n] * (acc[n] * a.inv_rT);
+  }
+}
+
 }  // namespace
 
-hipError_t launch_segsum(const SegArgs& a, hipStream_t st) {
-  int64_t n_items = a.r_k + a.n_chunks;
-  if (n_items <= 0 || a.ncols <= 0) return hipSuccess;
-  if (a.ncols <= kNarrowCT) {
-    int64_t gpb = kBlock >> a.logG;
-    int64_t grid = (n_items + gpb - 1) / gpb;
-    if (grid > 65536) grid = 65536;
-    if (a.ncols == 1) segsum_narrow_kernel<1><<<(int)grid, kBlock, 0, st>>>(a);
-    else if (a.ncols == 2) segsum_narrow_kernel<2><<<(int)grid, kBlock, 0, st>>>(a);
-    else segsum_narrow_kernel<4><<<(int)grid, kBlock, 0, st>>>(a);
-  } else {
-    int W = a.ncols <= 16 ? 16 : (a.ncols <= 32 ? 32 : 64);
-    int64_t gpb = kBlock / W;
-    int64_t grid = (n_items + gpb - 1) / gpb;
-    if (grid > 65536) grid = 65536;
-    if (W == 16) segsum_wide_kernel<16><<<(int)grid, kBlock, 0, st>>>(a);
-    else if (W == 32) segsum_wide_kernel<32><<<(int)grid, kBlock, 0, st>>>(a);
-    else segsum_wide_kernel<64><<<(int)grid, kBlock, 0, st>>>(a);
+namespace {
+
+hipError_t launch_combine(SegMulti& m, hipStream_t st) {
+  for (int q = 0; q < m.n; ++q) {
+    const int64_t items = (int64_t)m.s[q].n_long * m.s[q].ncols;
+    m.cfirst[q + 1] = m.cfirst[q] + (int)std::min<int64_t>((items + kBlock / kWave - 1) / (kBlock / kWave), 2048);
   }
+  if (m.cfirst[m.n] > 0) segsum_combine_kernel<<<m.cfirst[m.n], kBlock, 0, st>>>(m);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_segsum_narrow(const SegArgs* a, int n, hipStream_t st) {
+  if (n < 1 || n > kSegMulti) return hipErrorInvalidValue;
+  SegMulti m;
+  memset(&m, 0, sizeof(m));
+  m.n = n;
+  for (int q = 0; q < n; ++q) {
+    if (a[q].ncols < 1 || a[q].ncols > kNarrowCT || a[q].ncols != a[0].ncols || a[q].r_k <= 0) return hipErrorInvalidValue;
+    m.s[q] = a[q];
+    const int64_t gpb = kBlock >> a[q].logG;
+    const int64_t grid = std::max<int64_t>((a[q].r_k + gpb - 1) / gpb, (a[q].n_chunks + kBlock / kWave - 1) / (kBlock / kWave));
+    m.first[q + 1] = m.first[q] + (int)std::min<int64_t>(grid, 65536);
+  }
+  const unsigned grid = (unsigned)m.first[n];
+  if (a[0].ncols == 1) segsum_narrow_kernel<1><<<grid, kBlock, 0, st>>>(m);
+  else if (a[0].ncols == 2) segsum_narrow_kernel<2><<<grid, kBlock, 0, st>>>(m);
+  else segsum_narrow_kernel<4><<<grid, kBlock, 0, st>>>(m);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (a.n_long > 0) {
-    int64_t total = (int64_t)a.n_long * a.ncols;
-    int grid = (int)((total + kBlock - 1) / kBlock);
-    if (grid > 1024) grid = 1024;
-    segsum_combine_kernel<<<grid, kBlock, 0, st>>>(a);
-    e = hipGetLastError();
-  }
-  return e;
+  return launch_combine(m, st);
+}
+
+hipError_t launch_segsum(const SegArgs& a, hipStream_t st) {
+  if (a.r_k <= 0 || a.ncols <= 0) return hipSuccess;
+  if (a.ncols <= kNarrowCT) return launch_segsum_narrow(&a, 1, st);
+  const int64_t n_items = a.r_k + a.n_chunks;
+  int W = a.ncols <= 16 ? 16 : (a.ncols <= 32 ? 32 : 64);
+  int64_t gpb = kBlock / W;
+  int64_t grid = (n_items + gpb - 1) / gpb;
+  if (grid > 65536) grid = 65536;
+  if (W == 16) segsum_wide_kernel<16><<<(int)grid, kBlock, 0, st>>>(a);
+  else if (W == 32) segsum_wide_kernel<32><<<(int)grid, kBlock, 0, st>>>(a);
+  else segsum_wide_kernel<64><<<(int)grid, kBlock, 0, st>>>(a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.n_long <= 0) return e;
+  SegMulti m;
+  memset(&m, 0, sizeof(m));
+  m.n = 1;
+  m.s[0] = a;
+  return launch_combine(m, st);
 }
 
 hipError_t launch_build_sliced_index(const int32_t* rowptr, const int32_t* perm, int64_t r_k, int64_t nnz, int64_t slice_rows,
@@ -717,6 +786,14 @@ hipError_t launch_colred(const ColredArgs& a, int nblocks, hipStream_t st) {
 
 hipError_t launch_finalize(const FinArgs& a, int c_T, int mode, hipStream_t st) {
   if (c_T <= 0 || a.ncols <= 0) return hipSuccess;
+  bool flat = true;
+  for (int k = 0; k < a.n; ++k) flat = flat && a.s[k].nblocks <= kFinFlat;
+  if (flat) {
+    const int blocks = (c_T + kBlock - 1) / kBlock;
+    if (mode == 0) finalize_flat_kernel<0><<<blocks, kBlock, 0, st>>>(a, c_T, blocks);
+    else finalize_flat_kernel<1><<<blocks + (a.loss != nullptr ? 1 : 0), kBlock, 0, st>>>(a, c_T, blocks);
+    return hipGetLastError();
+  }
   if (mode == 0) finalize_kernel<0><<<c_T, kBlock, 0, st>>>(a, c_T);
   else finalize_kernel<1><<<c_T + (a.loss != nullptr ? 1 : 0), kBlock, 0, st>>>(a, c_T);
   return hipGetLastError();
@@ -732,7 +809,7 @@ int colred_step_rows(int ck, int vec) {
 // A part of the merged launch: float4 rows, one column slab, and for the join-order form no long segments.
 bool tmm_part_supported(const ColredArgs& c, const SegArgs* s) {
   if (c.vec != 4 || c.ck <= 0 || c.ck > kWave * 4 || c.ncols < 1 || c.ncols > kNarrowCT || c.rows <= 0) return false;
-  if (s != nullptr && (s->n_long != 0 || s->ncols != c.ncols || s->r_k != c.rows || s->block_first == nullptr)) return false;
+  if (s != nullptr && (s->ncols != c.ncols || s->r_k != c.rows || s->block_first == nullptr)) return false;
   return true;
 }
 

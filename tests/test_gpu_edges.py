@@ -63,3 +63,124 @@ def test_materialize_any_column_block(il, r_T, widths, kw, shift):
     want = oracle.Target(sch).T32
     assert np.array_equal(T.cpu().numpy().view(np.uint32), want.view(np.uint32))
     assert torch.all(flat[:shift] == 7.0) and torch.all(flat[shift + sch.r_T * sch.c_T:] == 7.0)
+
+
+OP_TOL, GD_TOL = 1e-5, 1e-4     # float32 operators and weights against the float64 oracle
+
+
+def rel(a, b):
+    a, b = np.asarray(a, dtype=np.float64), np.asarray(b, dtype=np.float64)
+    nb = np.linalg.norm(b)
+    return float(np.linalg.norm(a - b) / (nb if nb > 0 else 1.0))
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+@pytest.mark.parametrize("cx", [1, 2, 3, 4])
+@pytest.mark.parametrize("r_T,widths,rows,missing", [
+    (1, (1, 1), 1, 0.0),                      # one row of one column
+    (3, (5, 3), 2, 0.5),                      # less than a tile of four rows
+    (255, (13, 75), 100, 0.1),                # one tile, not full
+    (70_001, (7, 33, 75), 9_001, 0.1),        # several tiles, last one ragged
+    (20_003, (256, 9), 4_000, 0.0),           # widest table whose gradient the assembly forms
+    (5_001, (257, 1_281), 301, 0.0),          # just beyond it, and beyond the widest tile
+    (5_001, (31, 1_279), 301, 0.2),           # rows of four to a tile
+    (4_099, (64, 96), 129, 0.0),              # row lengths on the same LDS banks
+    (9_000, (68, 300), 500, 0.0),             # aligned rows that leave a good part of the lanes idle, a wide aligned table
+])
+def test_narrow_operators_over_unaligned_rows(il, r_T, widths, rows, missing, cx):
+    sch = _blocks(5 + r_T, r_T, widths, rows=rows, missing=missing)
+    tg = oracle.Target(sch)
+    plan = il.ilargi_plan_create(il.schema_to_device(sch), sch.r_T, sch.c_T, max_cx=4)
+    rng = datagen.rng_for(3)
+    X = rng.standard_normal((sch.c_T, cx)).astype(np.float32)
+    Y = rng.standard_normal((sch.r_T, cx)).astype(np.float32)
+    assert rel(il.ilargi_lmm(plan, dev(X)).cpu().numpy(), oracle.lmm(tg, X)) < OP_TOL
+    assert rel(il.ilargi_tmm(plan, dev(Y)).cpu().numpy(), oracle.tmm(tg, Y)) < OP_TOL
+    for code, kind in ((il.LINEAR, "linear"), (il.LOGISTIC, "logistic")):
+        y = (rng.random(sch.r_T) < 0.5).astype(np.float32)
+        lr = [0.05] * cx
+        W = torch.zeros((sch.c_T, cx), device="cuda")
+        loss = torch.zeros(cx, device="cuda")
+        for _ in range(3):
+            il.ilargi_gd_step(plan, code, W, dev(y), dev(np.array(lr, dtype=np.float32)), loss)
+        W_ref, L_ref = oracle.gd(tg, kind, y, np.zeros((sch.c_T, cx)), lr, 3)
+        assert rel(W.cpu().numpy(), W_ref) < GD_TOL
+        assert np.allclose(loss.cpu().numpy(), L_ref[-1], rtol=1e-4)
+
+
+def test_tables_that_start_on_any_float(il):
+    """Tables that are views at an odd offset: rows and tiles without 16-byte alignment."""
+    rng = datagen.rng_for(9)
+    r_T, r_R = 3_001, 207
+    S, R = rng.standard_normal((r_T, 12)).astype(np.float32), rng.standard_normal((r_R, 20)).astype(np.float32)
+    fk = rng.integers(0, r_R, r_T).astype(np.int32)
+    sch = datagen.Schema([datagen.Source(S, None, np.arange(12, dtype=np.int32)),
+                          datagen.Source(R, fk, np.arange(12, 32, dtype=np.int32))], r_T, 32)
+
+    def shifted(a):
+        flat = torch.empty(a.size + 1, device="cuda")
+        flat[1:] = dev(a).reshape(-1)
+        return flat[1:].view(a.shape)
+
+    plan = il.ilargi_plan_create([(shifted(S), None, np.arange(12)), (shifted(R), dev(fk), np.arange(12, 32))], r_T, 32, max_cx=3)
+    tg = oracle.Target(sch)
+    X, Y = rng.standard_normal((32, 3)).astype(np.float32), rng.standard_normal((r_T, 3)).astype(np.float32)
+    assert rel(il.ilargi_lmm(plan, dev(X)).cpu().numpy(), oracle.lmm(tg, X)) < OP_TOL
+    assert rel(il.ilargi_tmm(plan, dev(Y)).cpu().numpy(), oracle.tmm(tg, Y)) < OP_TOL
+
+
+@pytest.mark.parametrize("cx", [1, 3, 5])
+@pytest.mark.parametrize("counts", [
+    [0, 256, 257, 0, 1, 0],                   # at the shortest cut, just above it, empty segments
+    [2_048, 2_049, 4_096, 7],                 # at the longest uncut segment and above
+    [40_000, 3, 0, 600],                      # one segment of many chunks
+    [9] * 3_000,                              # none cut
+])
+def test_segment_sums_around_the_cuts(il, counts, cx):
+    rng = datagen.rng_for(sum(counts))
+    fk = np.repeat(np.arange(len(counts), dtype=np.int32), counts)
+    rng.shuffle(fk)
+    r_T = fk.size
+    R = rng.standard_normal((len(counts), 5)).astype(np.float32)
+    plan = il.ilargi_plan_create([(dev(R), dev(fk), np.arange(5))], r_T, 5, max_cx=5)
+    Y = rng.standard_normal((r_T, cx)).astype(np.float32)
+    want = np.zeros((len(counts), cx))
+    np.add.at(want, fk, Y.astype(np.float64))
+    got = il.ilargi_segment_sum(plan, 0, dev(Y)).cpu().numpy()
+    bound = np.zeros((len(counts), cx))
+    np.add.at(bound, fk, np.abs(Y.astype(np.float64)))
+    assert np.all(np.abs(got - want) <= OP_TOL * bound + 1e-30)
+    assert rel(il.ilargi_tmm(plan, dev(Y)).cpu().numpy(), R.astype(np.float64).T @ want) < OP_TOL
+
+
+@pytest.mark.parametrize("cx", [1, 2, 4])
+@pytest.mark.parametrize("rows,cols,per_row,long_row", [
+    (1, 1, 1, 0), (37, 9, 3, 0), (3_001, 513, 20, 0),
+    (3_001, 5_000, 6, 0),                     # wider than the operand that fits LDS
+    (2_003, 700, 4, 650),                     # a row too long for its lanes: the staged kernel
+    (20_011, 30, 12, 0),                      # columns too long for theirs
+])
+def test_sparse_products_by_lane_groups(il, rows, cols, per_row, long_row, cx):
+    rng = datagen.rng_for(rows + cols)
+    D = np.zeros((rows, cols), dtype=np.float32)
+    for i in range(rows):
+        k = long_row if i == 5 and long_row else int(rng.integers(0, min(per_row, cols) + 1))
+        D[i, rng.choice(cols, k, replace=False)] = rng.standard_normal(k)
+    D[0, 0] = 1.0
+    r_T = 2 * rows + 3
+    fk = rng.integers(-1, rows, r_T).astype(np.int32)
+    sch = datagen.Schema([datagen.Source(D, fk, np.arange(cols, dtype=np.int32))], r_T, cols)
+    tg = oracle.Target(sch)
+    plan = il.ilargi_plan_create(il.schema_to_device(sch, sparse=True), r_T, cols, max_cx=4)
+    X, Y = rng.standard_normal((cols, cx)).astype(np.float32), rng.standard_normal((r_T, cx)).astype(np.float32)
+    assert rel(il.ilargi_lmm(plan, dev(X)).cpu().numpy(), oracle.lmm(tg, X)) < OP_TOL
+    assert rel(il.ilargi_tmm(plan, dev(Y)).cpu().numpy(), oracle.tmm(tg, Y)) < OP_TOL
+    W, y = torch.zeros((cols, 1), device="cuda"), (rng.random(r_T) < 0.5).astype(np.float32)
+    loss = torch.zeros(1, device="cuda")
+    for _ in range(2):
+        il.ilargi_gd_step(plan, il.LOGISTIC, W, dev(y), dev(np.array([0.5], dtype=np.float32)), loss)
+    W_ref, L_ref = oracle.gd(tg, "logistic", y, np.zeros((cols, 1)), [0.5], 2)
+    assert rel(W.cpu().numpy(), W_ref) < GD_TOL and np.allclose(loss.cpu().numpy(), L_ref[-1], rtol=1e-4)
