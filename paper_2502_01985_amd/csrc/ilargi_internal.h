@@ -231,7 +231,6 @@ struct TilePart {
   const float* X; int ldx, col0, ncols;   // product: the operand; column reduce: the rows of Z
   float* out; int ldo;                // product: rows x ldo; column reduce: [workgroup][ck][kNarrowCT]
   int logR;                           // log2 of the rows per tile
-  int nt;                             // the table is read past the caches
 };
 struct TileMulti {
   int n;
@@ -524,11 +523,23 @@ hipError_t launch_kmeans_update(float* C, const float* G, const int32_t* counts,
 hipError_t launch_gnmf_update(float* X, const float* P, const float* Q, int64_t rows, int k, float tiny,
                               float* gram_partial, int64_t partial_floats, int* nparts_out, hipStream_t st);
 
-// A table of more floats than the second-level caches hold (8 x 4 MiB) gains nothing from passing through them, and
-// read past them it leaves them to the gathered operands: the narrow iteration over 5,000,000 x 11 in tiles takes 223
-// microseconds instead of 246.  Tables that fit lose by it (333,333 x 13 trained over and over: 64 against 61).
-inline int stream_past_caches(int64_t floats) { return floats >= (8ll << 20) ? 1 : 0; }
+// An entity table of more than half the last-level cache (256 MiB) is not there any more when the next iteration asks
+// for it.  Read past the caches it leaves them to the gathered operands: the assembly over 5,000,000 x 10 with three
+// joined tables takes 72 microseconds instead of 102, the iteration over 5,000,000 x 11 in tiles 221 instead of 246.
+// A table that stays between calls loses by it (1,000,000 x 20, trained: 68.7 against 67.5 an iteration with three copies
+// in turn, 67.9 against 65.2 with one), and so does a joined table, which an iteration reads twice.  Kernels take it as
+// a template argument: of two branches with the same loads the compiler makes one.
+inline int stream_past_caches(int64_t floats) { return floats >= (32ll << 20) ? 1 : 0; }
 
+// A float4 read past the caches, or through them.
+template <bool NT>
+__device__ __forceinline__ float4 load4(const float* p) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  f4 t;
+  if constexpr (NT) t = __builtin_nontemporal_load(reinterpret_cast<const f4*>(p));
+  else t = *reinterpret_cast<const f4*>(p);
+  return make_float4(t.x, t.y, t.z, t.w);
+}
 inline int ilog2_ceil(int64_t v) { int l = 0; while ((1ll << l) < v) ++l; return l; }
 
 }  // namespace ilargi

@@ -33,7 +33,7 @@ constexpr int kFlatGather = 3;                 // gathered sources (their row in
 constexpr int kFlatWaves = kBlock / kWave;
 
 // NVT: compile-time bound of nvec = ck / 4.  wave_floats: LDS floats of one wavefront.
-template <int NVT, int CT, int MODE, bool FUSEG>
+template <int NVT, int CT, int MODE, bool FUSEG, bool NT>
 __global__ __launch_bounds__(kBlock) void lmm_flat_kernel(LmmArgs a, int wave_floats) {
   extern __shared__ float lds[];
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kBlock) void lmm_flat_kernel(LmmArgs a, int wave_fl
 #pragma unroll
     for (int u = 0; u < NVT; ++u) {
       dst[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      if (u < nvec && ch < nchunks && r0 + row_u[u] < a.d_rows) dst[u] = b4[u * kWave + lane];
+      if (u < nvec && ch < nchunks && r0 + row_u[u] < a.d_rows) dst[u] = load4<NT>(reinterpret_cast<const float*>(b4 + u * kWave + lane));
     }
   };
   load_chunk(chunk, vn);
@@ -269,13 +269,18 @@ __global__ __launch_bounds__(kBlock) void lmm_flat_kernel(LmmArgs a, int wave_fl
 
 typedef void (*FlatFn)(LmmArgs, int);
 
-template <int NVT, int CT>
-FlatFn pick_flat(int mode, bool fuseg) {
+template <int NVT, int CT, bool NT>
+FlatFn pick_flat_nt(int mode, bool fuseg) {
   if constexpr (NVT * CT <= 8) {
-    if (fuseg) return mode == 1 ? lmm_flat_kernel<NVT, CT, 1, true> : lmm_flat_kernel<NVT, CT, 2, true>;
+    if (fuseg) return mode == 1 ? lmm_flat_kernel<NVT, CT, 1, true, NT> : lmm_flat_kernel<NVT, CT, 2, true, NT>;
   }
-  if (mode == 0) return lmm_flat_kernel<NVT, CT, 0, false>;
-  return mode == 1 ? lmm_flat_kernel<NVT, CT, 1, false> : lmm_flat_kernel<NVT, CT, 2, false>;
+  if (mode == 0) return lmm_flat_kernel<NVT, CT, 0, false, NT>;
+  return mode == 1 ? lmm_flat_kernel<NVT, CT, 1, false, NT> : lmm_flat_kernel<NVT, CT, 2, false, NT>;
+}
+
+template <int NVT, int CT>
+FlatFn pick_flat(int mode, bool fuseg, bool nt) {
+  return nt ? pick_flat_nt<NVT, CT, true>(mode, fuseg) : pick_flat_nt<NVT, CT, false>(mode, fuseg);
 }
 
 // Compile-time bound of the float4 per row that serves a table (5 = the 20-column entity table of the benchmark).
@@ -331,10 +336,10 @@ hipError_t launch_lmm_flat(const LmmArgs& a, int mode, bool fuseg, hipStream_t s
   const int64_t nchunks = (a.r_out + kWave - 1) / kWave;
   int64_t grid = (nchunks + kFlatWaves - 1) / kFlatWaves;
   FlatFn fn = nullptr;
-  if (nvt == 4) fn = ct == 1 ? pick_flat<4, 1>(mode, fuseg) : (ct == 2 ? pick_flat<4, 2>(mode, fuseg) : pick_flat<4, 4>(mode, fuseg));
-  else if (nvt == 5) fn = ct == 1 ? pick_flat<5, 1>(mode, fuseg) : pick_flat<5, 2>(mode, fuseg);
-  else if (nvt == 8) fn = ct == 1 ? pick_flat<8, 1>(mode, fuseg) : pick_flat<8, 2>(mode, fuseg);
-  else fn = pick_flat<16, 1>(mode, fuseg);
+  if (nvt == 4) fn = ct == 1 ? pick_flat<4, 1>(mode, fuseg, a.nt_in != 0) : (ct == 2 ? pick_flat<4, 2>(mode, fuseg, a.nt_in != 0) : pick_flat<4, 4>(mode, fuseg, a.nt_in != 0));
+  else if (nvt == 5) fn = ct == 1 ? pick_flat<5, 1>(mode, fuseg, a.nt_in != 0) : pick_flat<5, 2>(mode, fuseg, a.nt_in != 0);
+  else if (nvt == 8) fn = ct == 1 ? pick_flat<8, 1>(mode, fuseg, a.nt_in != 0) : pick_flat<8, 2>(mode, fuseg, a.nt_in != 0);
+  else fn = pick_flat<16, 1>(mode, fuseg, a.nt_in != 0);
   // one round of resident workgroups (every wavefront walks its share of the chunks), within the partial buffers
   int64_t cap = flat_slots(fn, lds_bytes);
   if (fuseg || mode != 0) cap = std::min<int64_t>(cap, kColredBlocks);

@@ -43,7 +43,7 @@ __device__ __forceinline__ float lane_uniform(float x) {
 }
 
 // RPL rows per lane (1: rows of whole float4, 2: rows of an odd number of float2), NV float4 per unit.
-template <int RPL, int NV, int MODE>
+template <int RPL, int NV, int MODE, bool NT>
 __global__ __launch_bounds__(kBlock) void lmm_lane_kernel(LmmArgs a) {
   constexpr int CK = 4 * NV / RPL;                              // columns of the table
   extern __shared__ v4f lds4[];
@@ -75,7 +75,11 @@ __global__ __launch_bounds__(kBlock) void lmm_lane_kernel(LmmArgs a) {
   auto load_rows = [&](int64_t ch, v4f (&dst)[NV]) {
     const int64_t base = ch * (kWave * NV) + lane;
 #pragma unroll
-    for (int u = 0; u < NV; ++u) dst[u] = D4[min(base + u * kWave, last_f4)];
+    for (int u = 0; u < NV; ++u) {
+      const v4f* p = D4 + min(base + u * kWave, last_f4);
+      if constexpr (NT) dst[u] = __builtin_nontemporal_load(p);
+      else dst[u] = *p;
+    }
   };
   auto load_idx = [&](int64_t ch, int (&j)[kLaneGather][RPL]) {
     const int64_t unit = min(ch * kWave + lane, nunits - 1);
@@ -235,20 +239,20 @@ __global__ __launch_bounds__(kBlock) void lmm_lane_kernel(LmmArgs a) {
 
 typedef void (*LaneFn)(LmmArgs);
 
-template <int RPL, int NV>
+template <int RPL, int NV, bool NT>
 LaneFn pick_lane(int mode) {
-  return mode == 0 ? lmm_lane_kernel<RPL, NV, 0> : (mode == 1 ? lmm_lane_kernel<RPL, NV, 1> : lmm_lane_kernel<RPL, NV, 2>);
+  return mode == 0 ? lmm_lane_kernel<RPL, NV, 0, NT> : (mode == 1 ? lmm_lane_kernel<RPL, NV, 1, NT> : lmm_lane_kernel<RPL, NV, 2, NT>);
 }
 
 // Built for rows of 6, 10 and 14 columns (pairs of 8-byte aligned rows).  For rows of whole float4 the same kernel
 // (RPL = 1) measured 2 us faster than the flat-stream assembly on tables that sit in the last-level cache and 2 us
 // slower on tables that come from memory, so those keep the flat-stream kernel.
-LaneFn lane_fn(int rpl, int nv, int mode) {
+LaneFn lane_fn(int rpl, int nv, int mode, bool nt) {
   if (rpl != 2) return nullptr;
   switch (nv) {
-    case 3: return pick_lane<2, 3>(mode);
-    case 5: return pick_lane<2, 5>(mode);
-    case 7: return pick_lane<2, 7>(mode);
+    case 3: return nt ? pick_lane<2, 3, true>(mode) : pick_lane<2, 3, false>(mode);
+    case 5: return nt ? pick_lane<2, 5, true>(mode) : pick_lane<2, 5, false>(mode);
+    case 7: return nt ? pick_lane<2, 7, true>(mode) : pick_lane<2, 7, false>(mode);
     default: return nullptr;
   }
 }
@@ -291,7 +295,7 @@ bool lmm_lane_supported(const LmmArgs& a, int vec, int mode, bool fuseg) {
   if (!((vec == 4 && a.ck % 4 == 0) || (vec == 2 && a.ck % 4 == 2))) return false;
   int rpl, nv;
   lane_shape(a, vec, &rpl, &nv);
-  if (lane_fn(rpl, nv, mode) == nullptr || a.r_out % rpl != 0) return false;
+  if (lane_fn(rpl, nv, mode, a.nt_in != 0) == nullptr || a.r_out % rpl != 0) return false;
   for (int s = 0; s < a.g.n; ++s) {
     if (a.g.idx[s] == nullptr) return false;
     if (rpl == 2 && reinterpret_cast<uintptr_t>(a.g.idx[s]) % 8 != 0) return false;
@@ -306,7 +310,7 @@ hipError_t launch_lmm_lane(const LmmArgs& a, int vec, int mode, hipStream_t st, 
   if (!lmm_lane_supported(a, vec, mode, mode != 0)) return hipErrorInvalidValue;
   int rpl, nv;
   lane_shape(a, vec, &rpl, &nv);
-  LaneFn fn = lane_fn(rpl, nv, mode);
+  LaneFn fn = lane_fn(rpl, nv, mode, a.nt_in != 0);
   size_t lds_bytes = (size_t)kLaneWaves * kWave * nv * sizeof(v4f);
   lds_bytes = std::max(lds_bytes, (size_t)kLaneWaves * (a.ck + 1) * sizeof(float));
   const int64_t nchunks = (a.r_out / rpl + kWave - 1) / kWave;

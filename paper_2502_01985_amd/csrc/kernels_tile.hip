@@ -25,22 +25,15 @@ constexpr int kTileFloats = 5120;                        // most floats of a til
 constexpr int kTileV = kTileFloats / 4 / kBlock;         // float4 a thread carries
 constexpr int kTileGather = 4;                           // gathered sources of the assembly
 
-// The whole float4s among n floats from p on into registers.  AL: p is 16-byte aligned.  nt: past the caches.
-template <bool AL>
-__device__ __forceinline__ void tile_load(const float* __restrict__ p, int n, bool nt, v4f (&v)[kTileV]) {
-  if (AL && nt) {
-#pragma unroll
-    for (int i = 0; i < kTileV; ++i) {
-      const unsigned e = 4 * (threadIdx.x + i * kBlock);
-      if (e + 4 <= (unsigned)n) v[i] = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(p + e));
-    }
-    return;
-  }
+// The whole float4s among n floats from p on into registers.  AL: p is 16-byte aligned.  NT: past the caches.
+template <bool AL, bool NT>
+__device__ __forceinline__ void tile_load(const float* __restrict__ p, int n, v4f (&v)[kTileV]) {
 #pragma unroll
   for (int i = 0; i < kTileV; ++i) {
     const unsigned e = 4 * (threadIdx.x + i * kBlock);
     if (e + 4 <= (unsigned)n) {
-      if constexpr (AL) v[i] = *reinterpret_cast<const v4f*>(p + e);
+      if constexpr (AL && NT) v[i] = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(p + e));
+      else if constexpr (AL) v[i] = *reinterpret_cast<const v4f*>(p + e);
       else v[i] = (v4f){p[e], p[e + 1], p[e + 2], p[e + 3]};
     }
   }
@@ -134,13 +127,13 @@ __global__ __launch_bounds__(kBlock, 4) void prod_tile_kernel(TileMulti m) {
   const int64_t stride = (int64_t)nb * Rt;
   v4f v[kTileV];
   int64_t i0 = (int64_t)bid * Rt;
-  if (i0 < a.rows) tile_load<AL>(a.D + i0 * a.ck, (int)min((int64_t)Rt, a.rows - i0) * a.ck, a.nt, v);
+  if (i0 < a.rows) tile_load<AL, false>(a.D + i0 * a.ck, (int)min((int64_t)Rt, a.rows - i0) * a.ck, v);
   for (; i0 < a.rows; i0 += stride) {
     const int nrow = (int)min((int64_t)Rt, a.rows - i0);
     tile_put(tile, a.D + i0 * a.ck, nrow * a.ck, v);
     __syncthreads();
     const int64_t in = i0 + stride;
-    if (in < a.rows) tile_load<AL>(a.D + in * a.ck, (int)min((int64_t)Rt, a.rows - in) * a.ck, a.nt, v);
+    if (in < a.rows) tile_load<AL, false>(a.D + in * a.ck, (int)min((int64_t)Rt, a.rows - in) * a.ck, v);
     float acc[CT];
 #pragma unroll
     for (int n = 0; n < CT; ++n) acc[n] = 0.0f;
@@ -261,7 +254,7 @@ __global__ __launch_bounds__(kBlock) void asm_gather_kernel(LmmArgs a) {
 
 // MODE 0: store the product.  1: linear residual z - y.  2: logistic residual sigmoid(z) - y.  FUSEG: this workgroup's
 // share of D^T e as well (at most 256 columns).  The first lane of a row owns its target row.
-template <int CT, int MODE, bool FUSEG, bool AL>
+template <int CT, int MODE, bool FUSEG, bool AL, bool NT>
 __global__ __launch_bounds__(kBlock, 4) void asm_tile_kernel(LmmArgs a, int logR) {
   extern __shared__ v4f tile_lds4[];
   float* tile = reinterpret_cast<float*>(tile_lds4);
@@ -302,7 +295,7 @@ __global__ __launch_bounds__(kBlock, 4) void asm_tile_kernel(LmmArgs a, int logR
   };
   int64_t i0 = (int64_t)blockIdx.x * Rt;
   load_index(i0 + row);
-  tile_load<AL>(a.D + i0 * ck, i0 < a.r_out ? table_rows(i0) * ck : 0, a.nt_in, v);
+  tile_load<AL, NT>(a.D + i0 * ck, i0 < a.r_out ? table_rows(i0) * ck : 0, v);
   gather(i0 + row);
   load_index(i0 + stride + row);
   for (; i0 < a.r_out; i0 += stride) {
@@ -333,7 +326,7 @@ __global__ __launch_bounds__(kBlock, 4) void asm_tile_kernel(LmmArgs a, int logR
     const int64_t in = i0 + stride;
     gather(in + row);
     load_index(in + stride + row);
-    if (in < a.r_out) tile_load<AL>(a.D + in * ck, table_rows(in) * ck, a.nt_in, v);
+    if (in < a.r_out) tile_load<AL, NT>(a.D + in * ck, table_rows(in) * ck, v);
     float z[CT];
 #pragma unroll
     for (int n = 0; n < CT; ++n) z[n] = 0.0f;
@@ -386,7 +379,7 @@ __global__ __launch_bounds__(kBlock, 4) void colred_tile_kernel(TileMulti m) {
   v4f v[kTileV];
   float zr[CT];                                          // operand row of this thread (Rt <= kBlock)
   auto load = [&](int64_t i) {
-    tile_load<AL>(a.D + i * a.ck, (int)min((int64_t)Rt, a.rows - i) * a.ck, a.nt, v);
+    tile_load<AL, false>(a.D + i * a.ck, (int)min((int64_t)Rt, a.rows - i) * a.ck, v);
 #pragma unroll
     for (int n = 0; n < CT; ++n)
       zr[n] = ((int)threadIdx.x < Rt && i + threadIdx.x < a.rows && n < a.ncols) ? a.X[(i + threadIdx.x) * a.ldx + a.col0 + n] : 0.0f;
@@ -458,7 +451,6 @@ hipError_t launch_prod_tile(const LmmArgs* a, int n, hipStream_t st) {
     TilePart& t = m.a[q];
     t.D = a[q].D; t.ck = a[q].ck; t.rows = std::min(a[q].r_out, a[q].d_rows); t.colmap = a[q].colmap;
     t.X = a[q].X; t.ldx = a[q].ldx; t.col0 = a[q].col0; t.ncols = a[q].ncols; t.out = a[q].out; t.ldo = a[q].ldo;
-    t.nt = stream_past_caches(t.rows * t.ck);
     t.logR = tile_logR(t.rows, t.ck);
     tiles[q] = (t.rows + (1 << t.logR) - 1) >> t.logR;
     total += tiles[q];
@@ -515,21 +507,25 @@ hipError_t launch_asm_tile(const LmmArgs& a, int mode, hipStream_t st, int* grid
   if (grid_out) *grid_out = (int)grid;
   const int ct = a.ncols <= 1 ? 1 : (a.ncols <= 2 ? 2 : 4);
   const size_t lds = sizeof(float) * (kTileFloats + (size_t)(kBlock + a.ck) * ct);
-#define ILARGI_ASM(C, AL)                                                                                    \
-  do {                                                                                                       \
-    if (mode == 0) asm_tile_kernel<C, 0, false, AL><<<(int)grid, kBlock, lds, st>>>(a, logR);                \
-    else if (mode == 1 && fuseg) asm_tile_kernel<C, 1, true, AL><<<(int)grid, kBlock, lds, st>>>(a, logR);   \
-    else if (mode == 1) asm_tile_kernel<C, 1, false, AL><<<(int)grid, kBlock, lds, st>>>(a, logR);           \
-    else if (fuseg) asm_tile_kernel<C, 2, true, AL><<<(int)grid, kBlock, lds, st>>>(a, logR);                \
-    else asm_tile_kernel<C, 2, false, AL><<<(int)grid, kBlock, lds, st>>>(a, logR);                          \
+#define ILARGI_ASM(C, AL, NT)                                                                                   \
+  do {                                                                                                          \
+    if (mode == 0) asm_tile_kernel<C, 0, false, AL, NT><<<(int)grid, kBlock, lds, st>>>(a, logR);               \
+    else if (mode == 1 && fuseg) asm_tile_kernel<C, 1, true, AL, NT><<<(int)grid, kBlock, lds, st>>>(a, logR);  \
+    else if (mode == 1) asm_tile_kernel<C, 1, false, AL, NT><<<(int)grid, kBlock, lds, st>>>(a, logR);          \
+    else if (fuseg) asm_tile_kernel<C, 2, true, AL, NT><<<(int)grid, kBlock, lds, st>>>(a, logR);               \
+    else asm_tile_kernel<C, 2, false, AL, NT><<<(int)grid, kBlock, lds, st>>>(a, logR);                         \
+  } while (0)
+#define ILARGI_ASM_CT(C)                       \
+  do {                                         \
+    if (!al) ILARGI_ASM(C, false, false);      \
+    else if (a.nt_in) ILARGI_ASM(C, true, true); \
+    else ILARGI_ASM(C, true, false);           \
   } while (0)
   const bool al = reinterpret_cast<uintptr_t>(a.D) % 16 == 0;
-  if (ct == 1 && al) ILARGI_ASM(1, true);
-  else if (ct == 1) ILARGI_ASM(1, false);
-  else if (ct == 2 && al) ILARGI_ASM(2, true);
-  else if (ct == 2) ILARGI_ASM(2, false);
-  else if (al) ILARGI_ASM(4, true);
-  else ILARGI_ASM(4, false);
+  if (ct == 1) ILARGI_ASM_CT(1);
+  else if (ct == 2) ILARGI_ASM_CT(2);
+  else ILARGI_ASM_CT(4);
+#undef ILARGI_ASM_CT
 #undef ILARGI_ASM
   return hipGetLastError();
 }
@@ -551,7 +547,6 @@ hipError_t launch_colred_tile(const ColredArgs* c, int n, int* nblocks, hipStrea
     TilePart& t = m.a[q];
     t.D = c[q].D; t.ck = c[q].ck; t.rows = c[q].rows;
     t.X = c[q].Z; t.ldx = c[q].ldz; t.col0 = c[q].col0; t.ncols = c[q].ncols; t.out = c[q].partial;
-    t.nt = stream_past_caches(t.rows * t.ck);
     t.logR = tile_logR(t.rows, t.ck);
     tiles[q] = (t.rows + (1 << t.logR) - 1) >> t.logR;
     total += tiles[q];
