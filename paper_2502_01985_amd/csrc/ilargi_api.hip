@@ -455,6 +455,8 @@ SparseArgs sparse_args(const ilargi_plan* pl, int k) {
   return a;
 }
 
+constexpr int kWideMin = 8;   // operands with at least this many columns take the matrix-core kernels
+
 // Widest operand slice one narrow pass can stage in LDS for every source of the plan.
 int pass_width(const ilargi_plan* pl) {
   int64_t cmax = 1;
@@ -464,12 +466,10 @@ int pass_width(const ilargi_plan* pl) {
   return w >= 4 ? 4 : (w >= 2 ? 2 : 1);
 }
 
-// out (or the residual E) for operand columns [col0, col0 + ncols):  per-source products, then the assembly.
-ilargi_status_t lmm_pass(ilargi_plan* pl, const float* X, int ldx, int col0, int ncols, float* out, int ldo,
-                         int mode, const float* y, int* loss_grid, bool wide, hipStream_t st,
-                         bool* fused_gradient = nullptr, bool bf16 = false) {
-  if (fused_gradient) *fused_gradient = false;
-  GatherArgs g;
+// The products P_k = D_k (M_k^T X) of every source but the fused one, operand columns [col0, col0 + ncols), and the
+// gathers that add them up.
+ilargi_status_t lmm_products(ilargi_plan* pl, const float* X, int ldx, int col0, int ncols, bool wide, bool bf16, hipStream_t st,
+                             GatherArgs& g) {
   memset(&g, 0, sizeof(g));
   g.ldp = ldx;
   auto product_args = [&](int k) {
@@ -540,6 +540,19 @@ ilargi_status_t lmm_pass(ilargi_plan* pl, const float* X, int ldx, int col0, int
     g.P[g.n] = pl->at<float>(p.o_pz);
     g.rows[g.n] = p.rows;
     ++g.n;
+  }
+  return ILARGI_OK;
+}
+
+// out (or the residual E) for operand columns [col0, col0 + ncols):  per-source products, then the assembly.
+ilargi_status_t lmm_pass(ilargi_plan* pl, const float* X, int ldx, int col0, int ncols, float* out, int ldo,
+                         int mode, const float* y, int* loss_grid, bool wide, hipStream_t st,
+                         bool* fused_gradient = nullptr, bool bf16 = false) {
+  if (fused_gradient) *fused_gradient = false;
+  GatherArgs g;
+  {
+    const ilargi_status_t rc = lmm_products(pl, X, ldx, col0, ncols, wide, bf16, st, g);
+    if (rc != ILARGI_OK) return rc;
   }
   LmmArgs a;
   memset(&a, 0, sizeof(a));
@@ -1013,6 +1026,8 @@ ilargi_status_t tmm_wide(ilargi_plan* pl, const float* Y, int cx, float* out, in
   return ILARGI_OK;
 }
 
+constexpr int64_t kStarWideRows = 512 * 1024;   // target rows from which the shared-row pass is taken
+
 // Alg. 1 for a wide batch on a two-table star join: P = R W_R, the join-order pass (residual, S^T E, segment
 // sums), R^T Z, update.  The r_T x m residual is never stored.
 ilargi_status_t gd_star_step(ilargi_plan* pl, int mode, float* W, int m, const float* y, const float* lr,
@@ -1048,7 +1063,10 @@ ilargi_status_t gd_star_step(ilargi_plan* pl, int mode, float* W, int m, const f
   int grid = 0;
   {
     TraceScope ts(pl, "star_pass", -1, st);
-    HIP_TRY(launch_gd_star(s, f.vec, mode, bf16, (int)max_grid, st, &grid));
+    // (fewer target rows do not give every workgroup a run of tiles long enough to pay for its start: 250,000 rows, 256
+    // models, 160 microseconds an iteration in the other form and 184 in this one; 50,000: 61 and 66)
+    if (gd_star_wide_supported(s.cs, m) && pl->r_T >= kStarWideRows) HIP_TRY(launch_gd_star_wide(s, f.vec, mode, bf16, (int)max_grid, st, &grid));
+    else HIP_TRY(launch_gd_star(s, f.vec, mode, bf16, (int)max_grid, st, &grid));
   }
   HIP_TRY(launch_tred_reduce(s.grad_partial, grid, (int64_t)s.cs * m, pl->at<float>(f.o_g), st));
   TredArgs g;
@@ -1076,7 +1094,76 @@ ilargi_status_t gd_star_step(ilargi_plan* pl, int mode, float* W, int m, const f
   return ILARGI_OK;
 }
 
-constexpr int kWideMin = 8;   // operands with at least this many columns take the matrix-core kernels
+// One Lloyd iteration in one pass over the identity source (kernels_tile.hip): the assignments come out of the assembly
+// of T C, with the identity source's cluster sums; a joined source's sums are its table times the cluster counts of its
+// rows.  G (c_T x k) receives the per-cluster sums, cnt the cluster sizes.
+bool kmeans_fused_ok(const ilargi_plan* pl, int64_t k) {
+  if (pl->any_sparse || pl->fused < 0 || k > kKmeansTileK) return false;
+  const SourcePlan& f = pl->src[pl->fused];
+  if (!kmeans_tile_supported((int)f.cols, (int)k) || 2 * kColredBlocks * f.cols * k > pl->lay.gpartial_floats) return false;
+  for (int q = 0; q < pl->n; ++q) {
+    const SourcePlan& p = pl->src[q];
+    if (p.empty || q == pl->fused) continue;
+    if (p.ident || p.n_long > 0) return false;     // (a cut segment is spread over workgroups)
+  }
+  return true;
+}
+
+ilargi_status_t kmeans_fused(ilargi_plan* pl, const float* C, int k, const float* cn, int32_t* assign, float* G, int32_t* cnt,
+                             hipStream_t st) {
+  LmmArgs a;
+  memset(&a, 0, sizeof(a));
+  const SourcePlan& f = pl->src[pl->fused];
+  const int w = k >= kWideMin ? k : pass_width(pl);
+  for (int col0 = 0; col0 < k; col0 += w) {
+    const ilargi_status_t rc = lmm_products(pl, C, k, col0, std::min(w, k - col0), k >= kWideMin, false, st, a.g);
+    if (rc != ILARGI_OK) return rc;
+  }
+  a.D = f.D; a.d_rows = f.rows; a.ck = (int)f.cols; a.colmap = pl->at<int32_t>(f.o_colmap);
+  a.X = C; a.ldx = k; a.ncols = k; a.r_out = pl->r_T;
+  int logR = 0;
+  const int grid = kmeans_tile_grid(a, &logR);
+  float* sums = pl->at<float>(pl->lay.o_gpartial);
+  int32_t* sizes = pl->at<int32_t>(pl->lay.o_loss);
+  {
+    TraceScope ts(pl, "kmeans_assign", -1, st);
+    HIP_TRY(launch_kmeans_tile(a, cn, assign, sizes, sums, grid, logR, st));
+  }
+  HIP_TRY(launch_kmeans_counts(sizes, grid, k, cnt, st));
+  ColAsmArgs c;
+  memset(&c, 0, sizeof(c));
+  for (int q = 0; q < pl->n; ++q) {
+    SourcePlan& p = pl->src[q];
+    if (p.empty) continue;
+    c.tcol2src[c.n] = pl->at<int32_t>(p.o_tcol);
+    c.ck[c.n] = (int)p.cols;
+    if (q == pl->fused) {
+      c.G[c.n] = sums;
+      c.nparts[c.n] = grid;
+    } else {
+      {
+        TraceScope ts(pl, "segsum", q, st);
+        HIP_TRY(launch_kmeans_segcount(pl->at<int32_t>(p.o_rowptr), pl->at<int32_t>(p.o_perm), assign, p.rows, k, p.logG,
+                                       pl->at<float>(p.o_pz), st));
+      }
+      TredArgs g;
+      memset(&g, 0, sizeof(g));
+      g.A = p.D; g.lda = (int)p.cols; g.ca = (int)p.cols; g.a_rows = p.rows;
+      g.B = pl->at<float>(p.o_pz); g.ldb = k; g.cb = k; g.b_rows = p.rows;
+      g.n_rows = p.rows;
+      const int64_t room = (int64_t)grid * f.cols * k;
+      const ilargi_status_t rc = run_tred(pl, g, pl->at<float>(p.o_g), "colred", q, false, st, false, sums + room,
+                                          pl->lay.gpartial_floats - room);
+      if (rc != ILARGI_OK) return rc;
+      c.G[c.n] = pl->at<float>(p.o_g);
+    }
+    ++c.n;
+  }
+  c.c_T = (int)pl->c_T; c.cx = k; c.out = G;
+  TraceScope ts(pl, "finalize", -1, st);
+  HIP_TRY(launch_colasm(c, 0, st));
+  return ILARGI_OK;
+}
 
 // a: the c_T-row operand (never empty); b: the r_T-row one, which may be NULL when the target table has no rows.
 ilargi_status_t check_call(const ilargi_plan* pl, const void* a, const void* b, int64_t cx, const char* what) {
@@ -1896,21 +1983,27 @@ ilargi_status_t ilargi_kmeans_step(ilargi_plan_t* plan, float* C, int64_t k, int
   float* G = plan->at<float>(plan->lay.o_rmm);          // c_T x k: per-cluster sums
   float* cn = plan->at<float>(plan->lay.o_cn);
   int32_t* cnt = plan->at<int32_t>(plan->lay.o_counts);
-  HIP_TRY(launch_fill_zero(reinterpret_cast<float*>(cnt), k, st));   // all-zero bits are the integer 0
   if (plan->r_T > 0) {
     {
       TraceScope ts(plan, "centroid_norm", -1, st);
       HIP_TRY(launch_centroid_norm(C, plan->c_T, (int)k, cn, st));
     }
-    ilargi_status_t rc = ilargi_lmm(plan, C, k, P, ILARGI_F32, stream);
-    if (rc != ILARGI_OK) return rc;
-    {
-      TraceScope ts(plan, "kmeans_assign", -1, st);
-      HIP_TRY(launch_kmeans_assign(P, cn, plan->r_T, (int)k, assign, plan->at<int32_t>(plan->lay.o_loss),
-                                   std::max<int64_t>(32768 * kNarrowCT, 1024 * plan->max_cx), cnt, st));
+    if (kmeans_fused_ok(plan, k)) {
+      const ilargi_status_t rc = kmeans_fused(plan, C, (int)k, cn, assign != nullptr ? assign : reinterpret_cast<int32_t*>(P), G, cnt, st);
+      if (rc != ILARGI_OK) return rc;
+    } else {
+      ilargi_status_t rc = ilargi_lmm(plan, C, k, P, ILARGI_F32, stream);
+      if (rc != ILARGI_OK) return rc;
+      {
+        TraceScope ts(plan, "kmeans_assign", -1, st);
+        HIP_TRY(launch_kmeans_assign(P, cn, plan->r_T, (int)k, assign, plan->at<int32_t>(plan->lay.o_loss),
+                                     std::max<int64_t>(32768 * kNarrowCT, 1024 * plan->max_cx), cnt, st));
+      }
+      rc = ilargi_tmm(plan, P, k, G, ILARGI_F32, stream);
+      if (rc != ILARGI_OK) return rc;
     }
-    rc = ilargi_tmm(plan, P, k, G, ILARGI_F32, stream);
-    if (rc != ILARGI_OK) return rc;
+  } else {
+    HIP_TRY(launch_fill_zero(reinterpret_cast<float*>(cnt), k, st));   // all-zero bits are the integer 0
   }
   TraceScope ts(plan, "kmeans_update", -1, st);
   HIP_TRY(launch_kmeans_update(C, G, cnt, plan->c_T, (int)k, counts, st));

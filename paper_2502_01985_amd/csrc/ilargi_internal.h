@@ -427,6 +427,8 @@ bool lmm_prod_stream_supported(const LmmArgs& a, int vec, int mode);
 hipError_t launch_lmm_prod_stream(const LmmArgs& a, hipStream_t st);
 bool lmm_flat_wide_supported(const LmmArgs& a, int vec, int mode);
 hipError_t launch_lmm_flat_wide(const LmmArgs& a, hipStream_t st, int* grid_out);
+bool gd_star_wide_supported(int cs, int m);
+hipError_t launch_gd_star_wide(const StarArgs& a, int vec, int mode, bool bf16, int max_grid, hipStream_t st, int* grid_out);
 bool gd_star_supported(int cs, int m);
 hipError_t launch_gd_star(const StarArgs& a, int vec, int mode, bool bf16, int max_grid, hipStream_t st, int* grid_out);
 hipError_t launch_csr_check(const SparseArgs& a, int32_t* flags, hipStream_t st);
@@ -518,6 +520,14 @@ constexpr int kGnmfMaxRank = 64;
 hipError_t launch_centroid_norm(const float* C, int64_t c_T, int k, float* cn, hipStream_t st);
 hipError_t launch_kmeans_assign(float* P, const float* cn, int64_t r_T, int k, int32_t* assign, int32_t* counts_partial,
                                 int64_t partial_ints, int32_t* counts, hipStream_t st);
+constexpr int kKmeansTileK = 16;     // most centroids of the one-pass assignment (kernels_tile.hip)
+bool kmeans_tile_supported(int ck, int k);
+int kmeans_tile_grid(const LmmArgs& a, int* logR);
+hipError_t launch_kmeans_tile(const LmmArgs& a, const float* cn, int32_t* assign, int32_t* counts_partial, float* sum_partial,
+                              int grid, int logR, hipStream_t st);
+hipError_t launch_kmeans_counts(const int32_t* partial, int nparts, int k, int32_t* counts, hipStream_t st);
+hipError_t launch_kmeans_segcount(const int32_t* rowptr, const int32_t* perm, const int32_t* assign, int64_t r_k, int k,
+                                  int logG, float* Z, hipStream_t st);
 hipError_t launch_kmeans_update(float* C, const float* G, const int32_t* counts, int64_t c_T, int k,
                                 int32_t* counts_out, hipStream_t st);
 hipError_t launch_gnmf_update(float* X, const float* P, const float* Q, int64_t rows, int k, float tiny,
@@ -540,6 +550,17 @@ __device__ __forceinline__ float4 load4(const float* p) {
   else t = *reinterpret_cast<const f4*>(p);
   return make_float4(t.x, t.y, t.z, t.w);
 }
+// sigmoid(z) - y, and log(1 + exp(z)) - y z added to the loss.  One exponential, e = exp(-|z|), serves both; the
+// reciprocal takes a Newton step and the logarithm the rounding of 1 + e, so that both are right to the last bit or so.
+__device__ __forceinline__ float logistic_residual(float z, float y, float& loss) {
+  const float e = __expf(-fabsf(z));
+  const float d = 1.0f + e;
+  float inv = __builtin_amdgcn_rcpf(d);
+  inv = fmaf(inv, fmaf(-d, inv, 1.0f), inv);
+  loss += fmaxf(z, 0.0f) + fmaf(e - (d - 1.0f), inv, __logf(d)) - y * z;
+  return (z >= 0.0f ? inv : e * inv) - y;
+}
+
 inline int ilog2_ceil(int64_t v) { int l = 0; while ((1ll << l) < v) ++l; return l; }
 
 }  // namespace ilargi

@@ -149,6 +149,37 @@ __global__ __launch_bounds__(kBlock) void kmeans_assign_kernel(float* __restrict
   for (int j = tid; j < k; j += kBlock) counts_partial[(size_t)blockIdx.x * k + j] = hist[j];
 }
 
+// Z[j][c] = how many of the target rows that join row j of a source belong to cluster c: the segment sums of the 0/1
+// assignment matrix, counted from the assignments.  A group of 2^logG lanes per source row, four entries of a lane in
+// flight, integer counts in LDS.  (Sources without cut segments.)
+__global__ __launch_bounds__(kBlock) void kmeans_segcount_kernel(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ perm,
+                                                                 const int32_t* __restrict__ assign, int64_t r_k, int k, int logG,
+                                                                 float* __restrict__ Z) {
+  extern __shared__ float lds[];
+  int* hist = reinterpret_cast<int*>(lds);                     // [rows of the workgroup][k]
+  const int G = 1 << logG, rows = kBlock >> logG;
+  const int64_t r0 = (int64_t)blockIdx.x * rows;
+  const int nrow = (int)min((int64_t)rows, r_k - r0);
+  for (int e = threadIdx.x; e < nrow * k; e += kBlock) hist[e] = 0;
+  __syncthreads();
+  const int lr = threadIdx.x >> logG;
+  if (lr < nrow) {
+    const int end = rowptr[r0 + lr + 1];
+    for (int p = rowptr[r0 + lr] + (threadIdx.x & (G - 1)); p < end; p += 4 * G) {
+      int i[4], c[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) i[u] = p + u * G < end ? perm[p + u * G] : -1;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) c[u] = i[u] >= 0 ? assign[i[u]] : -1;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (c[u] >= 0) atomicAdd(&hist[lr * k + c[u]], 1);
+    }
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < nrow * k; e += kBlock) Z[r0 * k + e] = (float)hist[e];
+}
+
 // counts[j] = sum over the workgroups' shares, one workgroup per centroid.
 __global__ __launch_bounds__(kBlock) void kmeans_counts_kernel(const int32_t* __restrict__ partial, int nparts, int k,
                                                                int32_t* __restrict__ counts) {
@@ -326,6 +357,20 @@ hipError_t launch_kmeans_assign(float* P, const float* cn, int64_t r_T, int k, i
   if (grid < 1) return hipErrorInvalidValue;
   kmeans_assign_kernel<<<grid, kBlock, lds_bytes, st>>>(P, cn, r_T, k, rows_pb, vec4, assign, counts_partial);
   kmeans_counts_kernel<<<k, kBlock, 0, st>>>(counts_partial, grid, k, counts);
+  return hipGetLastError();
+}
+
+hipError_t launch_kmeans_counts(const int32_t* partial, int nparts, int k, int32_t* counts, hipStream_t st) {
+  kmeans_counts_kernel<<<k, kBlock, 0, st>>>(partial, nparts, k, counts);
+  return hipGetLastError();
+}
+
+hipError_t launch_kmeans_segcount(const int32_t* rowptr, const int32_t* perm, const int32_t* assign, int64_t r_k, int k,
+                                  int logG, float* Z, hipStream_t st) {
+  if (r_k <= 0) return hipSuccess;
+  const int rows = kBlock >> logG;
+  kmeans_segcount_kernel<<<(unsigned)((r_k + rows - 1) / rows), kBlock, sizeof(int) * (size_t)rows * k, st>>>(
+      rowptr, perm, assign, r_k, k, logG, Z);
   return hipGetLastError();
 }
 

@@ -26,16 +26,6 @@ namespace {
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-__device__ __forceinline__ float star_sigmoid(float z) {
-  if (z >= 0.0f) return 1.0f / (1.0f + __expf(-z));
-  float e = __expf(z);
-  return e / (1.0f + e);
-}
-
-__device__ __forceinline__ float star_softplus(float z) {
-  return fmaxf(z, 0.0f) + log1pf(__expf(-fabsf(z)));
-}
-
 // LDS writes of some lanes of a wavefront become visible to the others (one wavefront executes its LDS
 // instructions in order; the fences only keep the compiler from moving accesses across this point).
 __device__ __forceinline__ void wave_sync() {
@@ -79,7 +69,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(VEC4 ? (
     for (int e = tid; e < kp * NQ; e += kBlock) {
       const int k = e / NQ, nq = e - k * NQ;
       float4 xv = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      if (k < a.cs && 4 * nq < nw) {
+      if (k < a.cs && a.s_colmap[k] >= 0 && 4 * nq < nw) {
         const float* p = a.W + (int64_t)a.s_colmap[k] * a.ldw + n0 + 4 * nq;
         if (x_vec && 4 * nq + 3 < nw) {
           xv = *reinterpret_cast<const float4*>(p);
@@ -281,8 +271,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(VEC4 ? (
               ov[nt][r] = o;
               loss_local[nt] = fmaf(o, o, loss_local[nt]);
             } else {
-              ov[nt][r] = live ? star_sigmoid(z) - yi : 0.0f;
-              loss_local[nt] += live ? star_softplus(z) - yi * z : 0.0f;
+              float l = 0.0f;
+              const float o = logistic_residual(z, yi, l);
+              ov[nt][r] = live ? o : 0.0f;
+              loss_local[nt] += live ? l : 0.0f;
             }
           }
         }

@@ -184,3 +184,86 @@ def test_sparse_products_by_lane_groups(il, rows, cols, per_row, long_row, cx):
         il.ilargi_gd_step(plan, il.LOGISTIC, W, dev(y), dev(np.array([0.5], dtype=np.float32)), loss)
     W_ref, L_ref = oracle.gd(tg, "logistic", y, np.zeros((cols, 1)), [0.5], 2)
     assert rel(W.cpu().numpy(), W_ref) < GD_TOL and np.allclose(loss.cpu().numpy(), L_ref[-1], rtol=1e-4)
+
+
+@pytest.mark.parametrize("prec", ["f32", "bf16"])
+@pytest.mark.parametrize("model,r_T,c_S,r_R,m,drop", [
+    ("linear", 524_288, 1, 262, 129, False),  # the fewest rows, one column, one model of the third slab
+    ("logistic", 524_301, 20, 9_001, 256, False),
+    ("linear", 524_301, 20, 9_001, 257, True),
+    ("linear", 524_301, 32, 600_000, 130, False),   # mostly empty rows of R: tiles without a target row
+    ("logistic", 524_301, 17, 3_001, 132, True),
+    ("linear", 524_301, 4, 300, 320, False),
+    ("linear", 524_287, 20, 501, 256, True),  # one row too few for the shared rows
+    ("logistic", 20_001, 33, 501, 200, True), # a table too wide for them
+    ("linear", 20_001, 20, 501, 40, True),    # a batch too small for them
+])
+def test_star_join_sweep_with_shared_rows(il, prec, model, r_T, c_S, r_R, m, drop):
+    """Wide batches of models over a star join around the sizes where the shared-row pass takes over; `drop`: columns of
+    the entity table that no target column takes."""
+    rng = datagen.rng_for(c_S + m)
+    c_R = 12
+    S, R = rng.standard_normal((r_T, c_S)).astype(np.float32), rng.standard_normal((r_R, c_R)).astype(np.float32)
+    fk = rng.integers(0, r_R, r_T).astype(np.int32)
+    if r_R > r_T:
+        fk = fk // 300 * 300
+    cm = np.arange(c_S, dtype=np.int32)
+    if drop:
+        cm[0], cm[c_S // 2] = -1, -1
+    sch = datagen.Schema([datagen.Source(S, None, cm), datagen.Source(R, fk, np.arange(c_S, c_S + c_R, dtype=np.int32))],
+                         r_T, c_S + c_R)
+    plan = il.ilargi_plan_create(il.schema_to_device(sch), r_T, sch.c_T, max_cx=m)
+    y = (rng.random(r_T) < 0.5).astype(np.float32)
+    lr = np.logspace(-3, -0.5, m).astype(np.float32)
+    code = il.LINEAR if model == "linear" else il.LOGISTIC
+
+    def train(lr, precision):
+        W, loss = torch.zeros((sch.c_T, lr.size), device="cuda"), torch.zeros(lr.size, device="cuda")
+        for _ in range(2):
+            il.ilargi_gd_step(plan, code, W, dev(y), dev(lr), loss, precision=precision)
+        return W.cpu().numpy(), loss.cpu().numpy()
+
+    if prec == "f32":
+        W, loss = train(lr, il.F32)
+        W_ref, L_ref = oracle.gd(oracle.Target(sch), model, y, np.zeros((sch.c_T, m)), lr, 2)
+        assert rel(W, W_ref) < GD_TOL and np.allclose(loss, L_ref[-1], rtol=1e-4)
+    else:
+        # the same models in batches that keep a wavefront to themselves: the same values are rounded, the sums differ in
+        # order only, which moves a residual across a rounding step for a few rows in a million
+        W, loss = train(lr, il.BF16_IN_F32_ACC)
+        parts = [train(lr[j:j + 40], il.BF16_IN_F32_ACC) for j in range(0, m - m % 40, 40)]
+        n = 40 * len(parts)
+        assert rel(W[:, :n], np.concatenate([p[0] for p in parts], axis=1)) < 1e-4
+        assert np.allclose(loss[:n], np.concatenate([p[1] for p in parts]), rtol=1e-5)
+
+
+@pytest.mark.parametrize("k", [1, 3, 8, 10, 16, 17])
+@pytest.mark.parametrize("r_T,widths,rows,missing", [
+    (1, (1, 2), 1, 0.0), (300, (20, 40), 37, 0.0), (5_003, (13, 75, 9), 301, 0.2), (70_001, (20, 200), 9_001, 0.0),
+    (2_001, (256, 8), 100, 0.0), (2_001, (257, 8), 100, 0.0),          # the widest identity source of the one-pass form
+    (3_000, (8, 12), 2, 0.0),                                          # segments that are cut: the general form
+])
+def test_kmeans_in_one_pass_over_the_entity_table(il, r_T, widths, rows, missing, k):
+    """Against the oracle where no row lies between two centroids; rows close to the boundary may go either way."""
+    sch = _blocks(11 + r_T, r_T, widths, rows=rows, missing=missing)
+    tg = oracle.Target(sch)
+    T = tg.T32.astype(np.float64)
+    C = datagen.rng_for(k).standard_normal((sch.c_T, k)).astype(np.float32)
+    plan = il.ilargi_plan_create(il.schema_to_device(sch), sch.r_T, sch.c_T, max_cx=max(k, 1))
+    Cd, assign = dev(C.copy()), torch.full((r_T,), -7, device="cuda", dtype=torch.int32)
+    counts = torch.zeros(k, device="cuda", dtype=torch.int32)
+    il.ilargi_kmeans_step(plan, Cd, assign, counts)
+    a = assign.cpu().numpy()
+    assert a.min() >= 0 and a.max() < k and np.array_equal(np.bincount(a, minlength=k), counts.cpu().numpy())
+    C64 = C.astype(np.float64)
+    D = (C64 * C64).sum(0) - 2 * (T @ C64)
+    slack = 1e-5 * ((C64 * C64).sum(0).max() + 2 * (np.abs(T) @ np.abs(C64)).max(1))
+    assert np.all(D[np.arange(r_T), a] <= D.min(1) + slack)
+    want = C64.copy()                          # the centroids of the assignment that was made
+    for j in range(k):
+        if np.any(a == j):
+            want[:, j] = T[a == j].mean(0)
+    assert rel(Cd.cpu().numpy(), want) < OP_TOL
+    Cd2 = dev(C.copy())                        # without the optional outputs
+    il.ilargi_kmeans_step(plan, Cd2)
+    assert torch.equal(Cd, Cd2)
