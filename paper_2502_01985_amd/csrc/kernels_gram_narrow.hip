@@ -1,4 +1,4 @@
-// Gram blocks of tables with 36..64 columns (crossprod, the rewrite of Sec. 2.2 applied to both factors), on the
+// Gram blocks of tables with at most 64 columns (crossprod, the rewrite of Sec. 2.2 applied to both factors), on the
 // matrix cores, as streaming kernels without LDS staging or barriers in the loop:
 //   diagonal block   C = sum_t w_t d_t^T d_t          (D_k^T diag(fan-out) D_k; w = 1 for an identity source)
 //   pair block       C = sum_p a_{ia[p]}^T b_{ib[p]}  (D_k^T (I_k^T I_l) D_l over a list of (row of D_k, row of D_l)
@@ -22,13 +22,24 @@ namespace ilargi {
 namespace {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));   // a float4 that starts on any float
 
 constexpr int kGnUDiag = 8;          // quads of rows in a wavefront's run (diagonal block)
 constexpr int kGnUPairs = 4;         // ... pair block (two tables, sixteen tiles: twice the registers per quad)
 constexpr int kGnWaves = kBlock / kWave;
 
+// Components of a lane whose float4 was moved back by d columns to end with its row: the ones beyond the row are zero.
+__device__ __forceinline__ v4f shift_back(v4f v, int d) {
+  if (d & 1) v = (v4f){v[1], v[2], v[3], 0.0f};
+  if (d & 2) v = (v4f){v[2], v[3], 0.0f, 0.0f};
+  return v;
+}
+
 // PAIRS: rows through the index vectors ia / ib (both valid for every entry); else row t of A with weight w_t.
-template <bool PAIRS, bool WEIGHTED>
+// RAGGED: a table's rows are not whole aligned float4s.  The loads then start on any float, and the last one of a row is
+// moved back to end with it.  2,000,000 x 63 twice with 16 shared columns: 378 microseconds for the whole Gram matrix,
+// 1192 with the tiles staged element by element (37 columns: 343 and 703, 22: 333 and 349).
+template <bool PAIRS, bool WEIGHTED, bool RAGGED>
 __global__ __launch_bounds__(kBlock) void gram_narrow_kernel(TredArgs a) {
   __shared__ float red[64 * 64];
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
@@ -42,6 +53,11 @@ __global__ __launch_bounds__(kBlock) void gram_narrow_kernel(TredArgs a) {
   const int64_t t_hi = a.n_rows;
   const int cola = min(4 * s, a.ca - 4), colb = min(4 * s, a.cb - 4);     // clamped: lanes beyond the table are zeroed
   const bool ina = 4 * s < a.ca, inb = 4 * s < a.cb;
+  const int backa = RAGGED && ina ? 4 * s - cola : 0, backb = RAGGED && inb ? 4 * s - colb : 0;
+  auto load_row = [](const float* p) -> v4f {
+    if constexpr (RAGGED) return *reinterpret_cast<const v4f_any*>(p);
+    else return *reinterpret_cast<const v4f*>(p);
+  };
   // A wavefront takes runs of kGnU consecutive quads (4 kGnU rows: for the diagonal block 8 KiB of contiguous memory),
   // the four wavefronts of the workgroup neighbouring runs.  The rows of its next run are requested before the
   // products of the current one are issued (for a pair block the list entries of the run after that, too).
@@ -65,11 +81,11 @@ __global__ __launch_bounds__(kBlock) void gram_narrow_kernel(TredArgs a) {
 #pragma unroll
     for (int u = 0; u < kGnU; ++u) {
       if constexpr (PAIRS) {
-        va[u] = *reinterpret_cast<const v4f*>(a.A + (int64_t)ra[u] * a.lda + cola);
-        vb[u] = *reinterpret_cast<const v4f*>(a.B + (int64_t)rb[u] * a.ldb + a.bcol0 + colb);
+        va[u] = load_row(a.A + (int64_t)ra[u] * a.lda + cola);
+        vb[u] = load_row(a.B + (int64_t)rb[u] * a.ldb + a.bcol0 + colb);
       } else {
         const int64_t t = min(base + 4 * u + q, a.n_rows - 1);
-        va[u] = *reinterpret_cast<const v4f*>(a.A + t * a.lda + cola);
+        va[u] = load_row(a.A + t * a.lda + cola);
       }
     }
     if constexpr (WEIGHTED) {
@@ -89,6 +105,10 @@ __global__ __launch_bounds__(kBlock) void gram_narrow_kernel(TredArgs a) {
       const bool live = base + 4 * u + q < t_hi;
       xa[u] = (live && ina) ? va[u] : (v4f){0.0f, 0.0f, 0.0f, 0.0f};
       if constexpr (PAIRS) xb[u] = (live && inb) ? vb[u] : (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+      if constexpr (RAGGED) {
+        xa[u] = shift_back(xa[u], backa);
+        if constexpr (PAIRS) xb[u] = shift_back(xb[u], backb);
+      }
       if constexpr (WEIGHTED) wv[u] = (float)__shfl(wd, 4 * u + q);
       else wv[u] = 1.0f;
     }
@@ -188,18 +208,25 @@ hipError_t launch_pair_list(const int32_t* idx_a, int64_t rows_a, const int32_t*
   return hipGetLastError();
 }
 
-// Diagonal block: A == B without index vectors, 36..64 columns in whole aligned float4s.
-bool gram_narrow_supported(const TredArgs& a) {
-  return a.upper_only && a.A == a.B && a.ia == nullptr && a.ib == nullptr && a.ca == a.cb && a.lda == a.ldb && a.bcol0 == 0 &&
-         a.ca > 32 && a.ca <= 64 && a.ca % 4 == 0 && a.lda % 4 == 0 && reinterpret_cast<uintptr_t>(a.A) % 16 == 0 &&
-         a.n_rows >= 1 && a.a_rows >= a.n_rows;
+namespace {
+
+bool whole_rows(const float* p, int c, int ld, int col0) {
+  return c % 4 == 0 && ld % 4 == 0 && col0 % 4 == 0 && reinterpret_cast<uintptr_t>(p) % 16 == 0;
 }
 
-// Pair block: n_rows pairs (ia[p], ib[p]), every index valid; both tables with 4..64 columns in whole aligned float4s.
+}  // namespace
+
+// Diagonal block: A == B without index vectors, 33..64 columns; from 17 on where the rows are not whole float4s (the
+// kernel for those costs more than the products of empty columns do here).
+bool gram_narrow_supported(const TredArgs& a) {
+  return a.upper_only && a.A == a.B && a.ia == nullptr && a.ib == nullptr && a.ca == a.cb && a.lda == a.ldb && a.bcol0 == 0 &&
+         a.ca > (whole_rows(a.A, a.ca, a.lda, 0) ? 32 : 16) && a.ca <= 64 && a.n_rows >= 1 && a.a_rows >= a.n_rows;
+}
+
+// Pair block: n_rows pairs (ia[p], ib[p]), every index valid; both tables with 4..64 columns.
 bool gram_pairs_supported(const TredArgs& a) {
   return !a.upper_only && a.ia != nullptr && a.ib != nullptr && a.wptr == nullptr && a.n_rows >= 1 &&
-         a.ca >= 4 && a.ca <= 64 && a.ca % 4 == 0 && a.lda % 4 == 0 && reinterpret_cast<uintptr_t>(a.A) % 16 == 0 &&
-         a.cb >= 4 && a.cb <= 64 && a.cb % 4 == 0 && a.ldb % 4 == 0 && a.bcol0 % 4 == 0 && reinterpret_cast<uintptr_t>(a.B) % 16 == 0;
+         a.ca >= 4 && a.ca <= 64 && a.cb >= 4 && a.cb <= 64;
 }
 
 // At most four workgroups per compute unit and as many as partial_floats holds; *nch_out partial blocks of ca x cb
@@ -221,9 +248,16 @@ hipError_t launch_gram_narrow(TredArgs& a, float* partial, int64_t partial_float
   nch = std::min<int64_t>(nch, (a.n_rows + step_rows - 1) / step_rows);
   if (nch < 1) return hipErrorInvalidValue;
   a.partial = partial;
-  if (pairs) gram_narrow_kernel<true, false><<<(unsigned)nch, kBlock, 0, st>>>(a);
-  else if (a.wptr != nullptr) gram_narrow_kernel<false, true><<<(unsigned)nch, kBlock, 0, st>>>(a);
-  else gram_narrow_kernel<false, false><<<(unsigned)nch, kBlock, 0, st>>>(a);
+  const bool ragged = !whole_rows(a.A, a.ca, a.lda, 0) || (pairs && !whole_rows(a.B, a.cb, a.ldb, a.bcol0));
+#define ILARGI_GRAM(P, W)                                                                 \
+  do {                                                                                    \
+    if (ragged) gram_narrow_kernel<P, W, true><<<(unsigned)nch, kBlock, 0, st>>>(a);      \
+    else gram_narrow_kernel<P, W, false><<<(unsigned)nch, kBlock, 0, st>>>(a);            \
+  } while (0)
+  if (pairs) ILARGI_GRAM(true, false);
+  else if (a.wptr != nullptr) ILARGI_GRAM(false, true);
+  else ILARGI_GRAM(false, false);
+#undef ILARGI_GRAM
   *nch_out = (int)nch;
   return hipGetLastError();
 }

@@ -267,3 +267,25 @@ def test_kmeans_in_one_pass_over_the_entity_table(il, r_T, widths, rows, missing
     Cd2 = dev(C.copy())                        # without the optional outputs
     il.ilargi_kmeans_step(plan, Cd2)
     assert torch.equal(Cd, Cd2)
+
+
+@pytest.mark.parametrize("rows,cols,shared,overlap", [
+    (31, 17, 5, 0.5), (1, 33, 0, 1.0), (4_099, 37, 8, 0.3), (4_100, 63, 31, 0.6), (2_001, 62, 1, 0.1),
+    (3_003, 5, 2, 0.4), (3_003, 16, 0, 0.4), (2_050, 64, 32, 0.2), (2_050, 65, 3, 0.2),
+])
+def test_gram_of_stacked_tables_with_rows_on_any_float(il, rows, cols, shared, overlap):
+    rng = datagen.rng_for(rows + cols)
+    sch = datagen.config3(seed=rows + cols, rows=rows, cols=cols, shared=shared, overlap=overlap)
+    tg = oracle.Target(sch)
+    plan = il.ilargi_plan_create(il.schema_to_device(sch), sch.r_T, sch.c_T)
+    G = il.ilargi_crossprod(plan).cpu().numpy()
+    assert rel(G, oracle.crossprod(tg)) < OP_TOL
+    assert np.array_equal(G, G.T)
+    # the same tables at an odd offset in a larger buffer, filled with values that would show
+    flat = [torch.full((s.D.size + 9,), float("nan"), device="cuda") for s in sch.sources]
+    views = []
+    for f, s in zip(flat, sch.sources):
+        f[3:3 + s.D.size] = dev(s.D).reshape(-1)
+        views.append(f[3:3 + s.D.size].view(s.D.shape))
+    plan2 = il.ilargi_plan_create([(v, dev(s.row_idx), s.col_map) for v, s in zip(views, sch.sources)], sch.r_T, sch.c_T)
+    assert rel(il.ilargi_crossprod(plan2).cpu().numpy(), oracle.crossprod(tg)) < OP_TOL
