@@ -368,13 +368,16 @@ int pick_logL(int64_t cols, int vec) {
   return l > 6 ? 6 : l;
 }
 
-// Splits the segments longer than thr into chunks of thr entries (host side, once per plan).
-void build_long_tables(const std::vector<int32_t>& rowptr, int32_t thr, std::vector<int32_t>& chunk_seg,
+// Splits the segments longer than thr into chunks of thr entries (host side, once per plan).  Returns the length of the
+// longest segment.
+int32_t build_long_tables(const std::vector<int32_t>& rowptr, int32_t thr, std::vector<int32_t>& chunk_seg,
                        std::vector<int32_t>& chunk_beg, std::vector<int32_t>& chunk_end,
                        std::vector<int32_t>& long_seg, std::vector<int32_t>& long_first) {
   long_first.push_back(0);
+  int32_t longest = 0;
   for (size_t j = 0; j + 1 < rowptr.size(); ++j) {
     int32_t b = rowptr[j], e = rowptr[j + 1];
+    longest = std::max(longest, e - b);
     if (e - b <= thr) continue;
     long_seg.push_back((int32_t)j);
     for (int32_t c = b; c < e; c += thr) {
@@ -384,6 +387,7 @@ void build_long_tables(const std::vector<int32_t>& rowptr, int32_t thr, std::vec
     }
     long_first.push_back((int32_t)chunk_seg.size());
   }
+  return longest;
 }
 
 SegArgs seg_args(const ilargi_plan* pl, int k) {
@@ -1305,10 +1309,9 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     // of them costs a launch, 48 against 39 microseconds for 1,000,000 rows over 1,000 uniform keys)
     p.long_thr = std::max(kSegCut, 16 << p.logG);
     if (2 * avg > p.long_thr) p.long_thr = kLongSeg;
-    for (size_t j = 0; j + 1 < rowptr.size(); ++j) p.very_long = p.very_long || rowptr[j + 1] - rowptr[j] > kLongSeg;
     std::vector<int32_t> cs, cb, ce, ls, lf;
     for (;;) {
-      build_long_tables(rowptr, p.long_thr, cs, cb, ce, ls, lf);
+      p.very_long = build_long_tables(rowptr, p.long_thr, cs, cb, ce, ls, lf) > kLongSeg;
       if ((int64_t)cs.size() <= p.nch_max || p.long_thr >= kLongSeg) break;
       p.long_thr *= 2;
       cs.clear(); cb.clear(); ce.clear(); ls.clear(); lf.clear();
