@@ -7,9 +7,16 @@
 //   P = R (M_R^T w)                          thread per row of R                (Sec. 2.2, left multiply)
 //   z_i = S[i] . w_S + P[row_idx[i]],  e_i   thread per target row              (assembly, residual of Alg. 1)
 //   Z = I_R^T e                              thread per row of R, entries of the inverse index in order (LDS)
-//   G_R = R^T Z,  G_S = S^T e                per-thread products added in a fixed order: butterfly inside the
-//                                            wavefronts, wavefronts in order
+//   G_R = R^T Z,  G_S = S^T e                per-thread products added in a fixed order: a lane of a wavefront adds
+//                                            every 64th thread's, then a butterfly over the 64 lanes
 //   w  -= lr * (M_S G_S + M_R G_R) / r_T     thread per target column, sources in plan order
+//
+// Bound: latency, and what one compute unit can load (280 KB at 10,000 x 4 with 1000 x 8).  Launches back to back, linear
+// / logistic model: 10,000 x 4, 1000 x 8: 8.8 -> 8.4 us; 1000 rows of S to 100 of R: 6.3 -> 5.2; a fan-out of 100: 15.4
+// -> 9.5; 16,000 x 4, 1000 x 12: 12.2 / 23.2 -> 11.4 / 14.1; 8000 x 8, 1000 x 16: 10.1 / 15.5 -> 9.5 / 10.7, since a
+// row's index entries and residuals are in flight kSmallU at a time (before: one after the other), the last sums are a
+// butterfly (before: 64 values in turn, all on one LDS bank), the loads go out in the order of their use, and the sigmoid
+// and the loss share their exponential.  Labels requested after the index entries, which spares registers: 8.7.
 #include <algorithm>
 
 #include "ilargi_internal.h"
@@ -20,14 +27,7 @@ namespace {
 
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / kWave;
-
-__device__ __forceinline__ float small_sigmoid(float z) {
-  if (z >= 0.0f) return 1.0f / (1.0f + __expf(-z));
-  float e = __expf(z);
-  return e / (1.0f + e);
-}
-
-__device__ __forceinline__ float small_softplus(float z) { return fmaxf(z, 0.0f) + log1pf(__expf(-fabsf(z))); }
+constexpr int kSmallU = 8;                 // entries of a row of the joined table in flight
 
 constexpr int kSmallRowVecs = 16;          // float4 of the entity table a thread keeps in registers
 
@@ -54,11 +54,41 @@ __global__ __launch_bounds__(kSmallThreads) void small_star_kernel(SmallStarArgs
   extern __shared__ float lds[];
   float* wk = lds;                                   // [2][16] the weights in source-column order (S, then R)
   float* gl = wk + 32;                               // [2][16] gradient blocks
-  float* pz = gl + 32 + 33 * kWave;                  // [1024] products of R (after the [33][64] second-stage sums)
+  float* pz = gl + 32;                               // [1024] products of R
   float* es = pz + kSmallThreads;                    // [r_T] residual
   int* pl = reinterpret_cast<int*>(es + a.r_T);      // [nnz] inverse index entries
   const int tid = threadIdx.x;
 
+  // requested in the order of use: the products' operands and the index entries, then what the assembly needs
+  float wkv = 0.0f;
+  if (tid < 32) {
+    const int t = a.colmap[tid / 16][tid % 16];
+    if (t >= 0) wkv = a.W[(int64_t)t * a.ldw + a.col];
+  }
+  float4 rv[NR];
+  int rp0 = 0, rp1 = 0;
+  if constexpr (NVR > 0) {
+    const bool live = tid < a.r_R;
+#pragma unroll
+    for (int q = 0; q < NVR; ++q)
+      rv[q] = (live && q < a.cr / 4) ? reinterpret_cast<const float4*>(a.R + (int64_t)tid * a.cr)[q] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (live) { rp0 = a.rowptr[tid]; rp1 = a.rowptr[tid + 1]; }
+  }
+  float wold = 0.0f;
+  int tcs = -1, tcr = -1;
+  if (tid < a.c_T) {
+    wold = a.W[(int64_t)tid * a.ldw + a.col];
+    tcs = a.tcol_s[tid];
+    if constexpr (NVR > 0) tcr = a.tcol_r[tid];
+  }
+  int pv[16];
+  if constexpr (NVR > 0) {
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int p = tid + u * kSmallThreads;
+      pv[u] = p < a.nnz ? a.perm[p] : 0;
+    }
+  }
   float4 sv[UI][NVS];
   float yv[UI];
   int jr[UI];
@@ -72,38 +102,14 @@ __global__ __launch_bounds__(kSmallThreads) void small_star_kernel(SmallStarArgs
     yv[u] = live ? a.y[i] : 0.0f;
     jr[u] = (NVR > 0 && live) ? a.idx[i] : -1;
   }
-  float4 rv[NR];
-  int rp0 = 0, rp1 = 0;
   if constexpr (NVR > 0) {
-    const bool live = tid < a.r_R;
-#pragma unroll
-    for (int q = 0; q < NVR; ++q)
-      rv[q] = (live && q < a.cr / 4) ? reinterpret_cast<const float4*>(a.R + (int64_t)tid * a.cr)[q] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (live) { rp0 = a.rowptr[tid]; rp1 = a.rowptr[tid + 1]; }
-    int pv[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int p = tid + u * kSmallThreads;
-      pv[u] = p < a.nnz ? a.perm[p] : 0;
-    }
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const int p = tid + u * kSmallThreads;
       if (p < a.nnz) pl[p] = pv[u];
     }
   }
-  float wold = 0.0f;
-  int tcs = -1, tcr = -1;
-  if (tid < a.c_T) {
-    wold = a.W[(int64_t)tid * a.ldw + a.col];
-    tcs = a.tcol_s[tid];
-    if constexpr (NVR > 0) tcr = a.tcol_r[tid];
-  }
-  if (tid < 32) {
-    const int k = tid / 16, j = tid % 16;
-    const int t = a.colmap[k][j];
-    wk[tid] = t >= 0 ? a.W[(int64_t)t * a.ldw + a.col] : 0.0f;
-  }
+  if (tid < 32) wk[tid] = wkv;
   __syncthreads();
 
   // P = R w_R  (Sec. 2.2: the per-source product)
@@ -125,8 +131,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_star_kernel(SmallStarArgs
         ev[u] = z - yv[u];
         loss_local = fmaf(ev[u], ev[u], loss_local);
       } else {
-        ev[u] = small_sigmoid(z) - yv[u];
-        loss_local += small_softplus(z) - yv[u] * z;
+        ev[u] = logistic_residual(z, yv[u], loss_local);
       }
       es[i] = ev[u];
     }
@@ -151,7 +156,17 @@ __global__ __launch_bounds__(kSmallThreads) void small_star_kernel(SmallStarArgs
   }
   if constexpr (NVR > 0) {
     float zr = 0.0f;
-    for (int p = rp0; p < rp1; ++p) zr += es[pl[p]];
+    // kSmallU entries of the row in flight: their places, then their residuals, added in index order
+    for (int p = rp0; p < rp1; p += kSmallU) {
+      int at[kSmallU];
+      float e[kSmallU];
+#pragma unroll
+      for (int u = 0; u < kSmallU; ++u) at[u] = pl[p + u < rp1 ? p + u : p];
+#pragma unroll
+      for (int u = 0; u < kSmallU; ++u) e[u] = es[at[u]];
+#pragma unroll
+      for (int u = 0; u < kSmallU; ++u) zr += p + u < rp1 ? e[u] : 0.0f;
+    }
 #pragma unroll
     for (int q = 0; q < NVR; ++q) {
       vals[4 * (NVS + q)] = rv[q].x * zr; vals[4 * (NVS + q) + 1] = rv[q].y * zr;
@@ -160,10 +175,9 @@ __global__ __launch_bounds__(kSmallThreads) void small_star_kernel(SmallStarArgs
   }
   vals[NVALS - 1] = loss_local;
   __syncthreads();                                   // es, pz and pl are dead: their LDS serves the sums
-  // workgroup sums in a fixed order through LDS: red[v][t] <- value v of thread t; thread (v, part) adds the
-  // entries part, part + 64, ...; then thread v adds the 64 parts in order
+  // workgroup sums in a fixed order through LDS: red[v][t] <- value v of thread t; lane `part` of a wavefront adds
+  // the entries part, part + 64, ... of value v; then a butterfly over the 64 parts
   float* red = pz;                                   // [NVALS][1024]
-  float* red2 = gl + 32;                             // [NVALS][64]
 #pragma unroll
   for (int v = 0; v < NVALS; ++v) red[v * kSmallThreads + tid] = vals[v];
   __syncthreads();
@@ -172,15 +186,13 @@ __global__ __launch_bounds__(kSmallThreads) void small_star_kernel(SmallStarArgs
     float sum = 0.0f;
 #pragma unroll
     for (int k = 0; k < kSmallThreads / kWave; ++k) sum += red[v * kSmallThreads + part + kWave * k];
-    red2[v * kWave + part] = sum;
-  }
-  __syncthreads();
-  if (tid < NVALS) {
-    float sum = 0.0f;
-    for (int k = 0; k < kWave; ++k) sum += red2[tid * kWave + k];
-    if (tid < 4 * NVS) gl[tid] = sum;                                  // column tid of S
-    else if (tid < NVALS - 1) gl[16 + tid - 4 * NVS] = sum;            // column tid - 4 NVS of R
-    else if (a.loss != nullptr) a.loss[a.col] = sum * a.loss_scale;    // loss at the weights the iteration started from
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) sum += __shfl_xor(sum, d, kWave);
+    if (part == 0) {
+      if (v < 4 * NVS) gl[v] = sum;                                    // column v of S
+      else if (v < NVALS - 1) gl[16 + v - 4 * NVS] = sum;              // column v - 4 NVS of R
+      else if (a.loss != nullptr) a.loss[a.col] = sum * a.loss_scale;  // loss at the weights the iteration started from
+    }
   }
   __syncthreads();
   // column scatter through the maps, sources in their order in the plan, and the update of Alg. 1
@@ -214,11 +226,11 @@ SmallFn small_pick_r(int nvr, int mode) {
 int small_star_max_rows(int nvs) { return kSmallThreads * (kSmallRowVecs / nvs); }
 
 size_t small_star_lds_bytes(const SmallStarArgs& a) {
-  // weights and gradient blocks, second-stage sums, then the larger of (products, residual, index entries) and the
+  // weights and gradient blocks, then the larger of (products, residual, index entries) and the
   // per-thread terms of the final sums, which reuse that space
   const size_t work = (size_t)kSmallThreads + a.r_T + a.nnz;
   const size_t sums = (size_t)(a.cs + (a.R != nullptr ? a.cr : 0) + 1) * kSmallThreads;
-  return sizeof(float) * (64 + 33 * kWave + std::max(work, sums));
+  return sizeof(float) * (64 + std::max(work, sums));
 }
 
 hipError_t launch_small_star(const SmallStarArgs& a, int mode, hipStream_t st) {

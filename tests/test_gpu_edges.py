@@ -289,3 +289,35 @@ def test_gram_of_stacked_tables_with_rows_on_any_float(il, rows, cols, shared, o
         views.append(f[3:3 + s.D.size].view(s.D.shape))
     plan2 = il.ilargi_plan_create([(v, dev(s.row_idx), s.col_map) for v, s in zip(views, sch.sources)], sch.r_T, sch.c_T)
     assert rel(il.ilargi_crossprod(plan2).cpu().numpy(), oracle.crossprod(tg)) < OP_TOL
+
+
+@pytest.mark.parametrize("model", ["linear", "logistic"])
+@pytest.mark.parametrize("r_T,c_S,r_R,c_R,missing", [
+    (1, 4, 1, 4, 0.0),                # one row
+    (1_025, 4, 3, 8, 0.1),            # rows reached by hundreds of target rows, one row past the workgroup
+    (16_384, 4, 1_024, 16, 0.0),      # the most rows of both tables
+    (7_777, 8, 1_000, 12, 0.3),       # fan-outs around the entries in flight, some rows unmatched
+    (4_095, 16, 1_024, 16, 0.0),      # the longest rows
+    (5_000, 12, 600, 4, 1.0),         # no row matched
+])
+def test_small_star_join_in_one_launch(il, r_T, c_S, r_R, c_R, missing, model):
+    sch = _blocks(11 + r_T, r_T, (c_S, c_R), rows=r_R, missing=missing)
+    plan = il.ilargi_plan_create(il.schema_to_device(sch), sch.r_T, sch.c_T, max_cx=2)
+    rng = datagen.rng_for(4)
+    y = (rng.random(r_T) < 0.5).astype(np.float32)
+    lr = [0.05, 0.2]
+    W, loss = torch.zeros((sch.c_T, 2), device="cuda"), torch.zeros(2, device="cuda")
+    for _ in range(3):
+        il.ilargi_gd_step(plan, il.LINEAR if model == "linear" else il.LOGISTIC, W, dev(y),
+                          dev(np.array(lr, dtype=np.float32)), loss)
+    W_ref, L_ref = oracle.gd(oracle.Target(sch), model, y, np.zeros((sch.c_T, 2)), lr, 3)
+    assert rel(W.cpu().numpy(), W_ref) < GD_TOL
+    assert np.allclose(loss.cpu().numpy(), L_ref[-1], rtol=1e-4)
+
+
+def test_calls_take_the_current_stream_or_the_one_they_are_given(il):
+    s = torch.cuda.Stream()
+    assert il._stream_ptr() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(s):
+        assert il._stream_ptr() == s.cuda_stream
+    assert il._stream_ptr(s) == s.cuda_stream
