@@ -117,9 +117,12 @@ def _torch():
 
 
 def _stream_ptr(stream=None) -> int:
+    if stream is not None:
+        return int(stream.cuda_stream)
     torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    # The handle of the current stream without a torch.cuda.Stream object around it: 3.0 us of every call's host time,
+    # a third of an iteration on a small schema, which the host bounds.
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dev_f32(t, name: str):
