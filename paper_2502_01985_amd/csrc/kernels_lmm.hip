@@ -34,16 +34,6 @@ template <int VEC> __device__ __forceinline__ void load_vec(const float* p, floa
   }
 }
 
-__device__ __forceinline__ float sigmoidf_stable(float z) {
-  if (z >= 0.0f) return 1.0f / (1.0f + __expf(-z));
-  float e = __expf(z);
-  return e / (1.0f + e);
-}
-
-__device__ __forceinline__ float softplusf_stable(float z) {
-  return fmaxf(z, 0.0f) + log1pf(__expf(-fabsf(z)));
-}
-
 constexpr int kUnroll = 8;     // rows per lane group and step
 constexpr int kPrefetch = 3;   // gathered sources whose row indices are prefetched one step ahead
 
@@ -210,8 +200,7 @@ __global__ __launch_bounds__(kBlock) void lmm_rows_kernel(LmmArgs a) {
             r = z - yi;
             loss_local[n] = fmaf(r, r, loss_local[n]);
           } else if constexpr (MODE == 2) {
-            r = sigmoidf_stable(z) - yi;
-            loss_local[n] += softplusf_stable(z) - yi * z;
+            r = logistic_residual(z, yi, loss_local[n]);
           }
           float* op = a.out + irow * a.ldo + a.col0 + n;
           if (a.nt_out) __builtin_nontemporal_store(r, op);

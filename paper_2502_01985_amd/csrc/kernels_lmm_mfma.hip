@@ -20,16 +20,6 @@ namespace {
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-__device__ __forceinline__ float sigmoidf_stable(float z) {
-  if (z >= 0.0f) return 1.0f / (1.0f + __expf(-z));
-  float e = __expf(z);
-  return e / (1.0f + e);
-}
-
-__device__ __forceinline__ float softplusf_stable(float z) {
-  return fmaxf(z, 0.0f) + log1pf(__expf(-fabsf(z)));
-}
-
 // NT: 16-column tiles of the operand slab handled by one workgroup.  MODE as in the narrow kernel.
 // BF16: table and operand values are rounded to bfloat16 (nearest even) when they enter the MFMA
 // (16x16x32, eight K values per lane: lane 16 q + i holds columns 32 step + 8 q .. + 7), sums stay float32.
@@ -279,8 +269,7 @@ __global__ __launch_bounds__(kBlock) void lmm_mfma_kernel(LmmArgs a, MfmaShape s
                 o = z - yi;
                 loss_local[nt] = fmaf(o, o, loss_local[nt]);
               } else if constexpr (MODE == 2) {
-                o = sigmoidf_stable(z) - yi;
-                loss_local[nt] += softplusf_stable(z) - yi * z;
+                o = logistic_residual(z, yi, loss_local[nt]);
               }
               if constexpr (BF16 && JG > 0) ov[nt][r] = (float)(__bf16)o;
               else ov[nt][r] = o;
