@@ -345,11 +345,18 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
     }
   for (int i = 0; i < lay.n_pairlists; ++i) lay.o_pairlist[i] = take(sizeof(int32_t) * 2 * r_T);
   lay.o_zc = take(sizeof(float) * lay.zc_floats);
-  // (the sort that builds the inverse indices is over before the first partial block is written: same space)
+  // The sort that builds the inverse indices is over before the first partial block is written: same space.  Plans with
+  // sparse tables, whose workspace goes by the stored entries, keep room of their own for it.
   const size_t sort_bytes = align_up(sizeof(int32_t) * 4 * sort_n), hist_bytes = sizeof(int32_t) * sort_hist_ints(sort_n);
-  lay.o_gpartial = take(std::max(sizeof(float) * lay.gpartial_floats, sort_bytes + hist_bytes));
-  lay.o_sort = lay.o_gpartial;
-  lay.o_hist = lay.o_gpartial + sort_bytes;
+  const size_t partial_bytes = sizeof(float) * lay.gpartial_floats;
+  if (lay.max_entries > 0) {
+    lay.o_gpartial = take(partial_bytes);
+    lay.o_sort = take(sort_bytes + hist_bytes);
+  } else {
+    lay.o_gpartial = take(std::max(partial_bytes, sort_bytes + hist_bytes));
+    lay.o_sort = lay.o_gpartial;
+  }
+  lay.o_hist = lay.o_sort + sort_bytes;
   lay.o_blocks = take(sizeof(float) * std::max<int64_t>(lay.blocks_floats, 1));
   lay.total = off;
   return ILARGI_OK;
@@ -368,16 +375,20 @@ int pick_logL(int64_t cols, int vec) {
   return l > 6 ? 6 : l;
 }
 
-// Splits the segments longer than thr into chunks of thr entries (host side, once per plan).  Returns the length of the
-// longest segment.
-int32_t build_long_tables(const std::vector<int32_t>& rowptr, int32_t thr, std::vector<int32_t>& chunk_seg,
+// Length of the longest segment (host side, once per plan; a loop without branches, which the compiler vectorizes).
+int32_t longest_segment(const std::vector<int32_t>& rowptr) {
+  int32_t longest = 0;
+  for (size_t j = 1; j < rowptr.size(); ++j) longest = std::max(longest, rowptr[j] - rowptr[j - 1]);
+  return longest;
+}
+
+// Splits the segments longer than thr into chunks of thr entries (host side, once per plan).
+void build_long_tables(const std::vector<int32_t>& rowptr, int32_t thr, std::vector<int32_t>& chunk_seg,
                        std::vector<int32_t>& chunk_beg, std::vector<int32_t>& chunk_end,
                        std::vector<int32_t>& long_seg, std::vector<int32_t>& long_first) {
   long_first.push_back(0);
-  int32_t longest = 0;
   for (size_t j = 0; j + 1 < rowptr.size(); ++j) {
     int32_t b = rowptr[j], e = rowptr[j + 1];
-    longest = std::max(longest, e - b);
     if (e - b <= thr) continue;
     long_seg.push_back((int32_t)j);
     for (int32_t c = b; c < e; c += thr) {
@@ -387,7 +398,6 @@ int32_t build_long_tables(const std::vector<int32_t>& rowptr, int32_t thr, std::
     }
     long_first.push_back((int32_t)chunk_seg.size());
   }
-  return longest;
 }
 
 SegArgs seg_args(const ilargi_plan* pl, int k) {
@@ -1309,9 +1319,12 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     // of them costs a launch, 48 against 39 microseconds for 1,000,000 rows over 1,000 uniform keys)
     p.long_thr = std::max(kSegCut, 16 << p.logG);
     if (2 * avg > p.long_thr) p.long_thr = kLongSeg;
-    std::vector<int32_t> cs, cb, ce, ls, lf;
-    for (;;) {
-      p.very_long = build_long_tables(rowptr, p.long_thr, cs, cb, ce, ls, lf) > kLongSeg;
+    const int32_t longest = longest_segment(rowptr);
+    p.very_long = longest > kLongSeg;
+    std::vector<int32_t> cs, cb, ce, ls, lf(1, 0);
+    while (longest > p.long_thr) {
+      lf.clear();
+      build_long_tables(rowptr, p.long_thr, cs, cb, ce, ls, lf);
       if ((int64_t)cs.size() <= p.nch_max || p.long_thr >= kLongSeg) break;
       p.long_thr *= 2;
       cs.clear(); cb.clear(); ce.clear(); ls.clear(); lf.clear();
