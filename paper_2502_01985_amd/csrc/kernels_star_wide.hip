@@ -2,10 +2,10 @@
 // of at most 32 columns: four wavefronts walk the same tiles of R, each for its own 64 model columns, and share the
 // staged rows of S.  Gathered in join order, a row of S costs 1.5 cache lines on average, which one wavefront per tile
 // and slab of 64 models fetches again for every slab.
-// The workgroup owns a run of consecutive tiles of R and sees their target rows as one stream of batches of ST rows: a
-// batch ends at its tile's end, the next one starts there, and while batch k is computed the rows of S of batch k + 1
-// and the row list of batch k + 2 are on their way.  One barrier per batch.  Which row of the tile a target row joins
-// follows from its place between the tile's row pointers, without a look at its key.
+// The workgroup owns a run of consecutive tiles of R with its share of the target rows, and sees those as one stream of
+// batches of ST rows: a batch ends at its tile's end, the next one starts there, and while batch k is computed the rows of
+// S of batch k + 1 and the row list of batch k + 2 are on their way.  One barrier per batch.  Which row of the tile a
+// target row joins follows from its place between the tile's row pointers, without a look at its key.
 // In float32 the matrix cores bound it: 52 MFMAs of 32 cycles per 16 rows and 64 models are 180 microseconds of the
 // chip; with bfloat16 inputs the arithmetic of the residuals between the products.
 // 1,000,000 x 20 with 100,000 x 200, 256 linear models: 331 microseconds in float32 (367 with a wavefront per tile and
@@ -38,6 +38,7 @@ constexpr int SL = 4;         // wavefronts of the workgroup
 constexpr int ST = 64;        // target rows of a batch
 constexpr int JG = 2;         // 16-column tiles of S
 constexpr int KP = 16 * JG;
+constexpr int kTileCost = 32;  // what a tile of R costs beside its target rows, in target rows
 
 // MODE 1: linear, 2: logistic.  VEC4: rows of S are read as float4.  BF16: values of S, W and E are rounded
 // to bfloat16 (nearest even) where they enter a product.  lda: row stride of the staged rows (a constant: with a
@@ -106,8 +107,25 @@ void gd_star_wide_kernel(StarArgs a, int xfloats, int rtiles, int fold) {
   auto label_at = [&](int r) { return a.Sp == nullptr ? a.y[r] : (a.yp != nullptr ? a.yp[r] : a.y[a.perm[r]]); };
   auto tile_first = [&](int t) { return a.rowptr[min((int64_t)t * tr, a.r_R)]; };
 
+  // This workgroup's run of tiles: the tiles that start in its share of the work, where an index entry counts one and a
+  // tile kTileCost (by number of tiles alone, popular keys that lie side by side all fall to a few workgroups: half of
+  // 1,000,000 rows on the first 1 % of the keys, 256 models, 7078 microseconds an iteration).  A half wavefront looks for
+  // either end, 32 tiles at a time.
+  auto work_before = [&](int t) { return (int64_t)tile_first(t) + (int64_t)kTileCost * t; };
+  const int64_t want = work_before(rtiles) * ((int64_t)blockIdx.x + lane / 32) / gridDim.x;
+  int lo = 0, hi = rtiles;                                    // the end looked for lies in [lo, hi]
+  while (__any(lo < hi)) {
+    const int step = (hi - lo) / 32 + 1;
+    const int t = min(lo + (lane % 32 + 1) * step - 1, hi);
+    const unsigned reached = (unsigned)(__ballot(t == hi || work_before(t) >= want) >> (lane & 32));
+    const int f = __builtin_ctz(reached);                     // (the last lane's t is hi)
+    hi = min(lo + (f + 1) * step - 1, hi);
+    lo += f * step;
+  }
+  int t_lo = __builtin_amdgcn_readlane(lo, 0), t_hi = __builtin_amdgcn_readlane(lo, 32);
+  if (rtiles <= (int)gridDim.x) { t_lo = blockIdx.x; t_hi = t_lo + 1; }   // a workgroup per tile
+
   // Batches: tile t of R, index entries [p, min(p + ST, pe)) with pe the tile's end.  (An empty tile is a batch of none.)
-  const int t_lo = (int)((int64_t)rtiles * blockIdx.x / gridDim.x), t_hi = (int)((int64_t)rtiles * (blockIdx.x + 1) / gridDim.x);
   struct Batch { int t, p, pe; };
   Batch bc = {t_hi, 0, 0}, bs = {t_hi, 0, 0};                 // computed now; its rows of S are requested
   Batch bl = {t_lo, t_lo < t_hi ? tile_first(t_lo) : 0, t_lo < t_hi ? tile_first(t_lo + 1) : 0};   // its row list is requested

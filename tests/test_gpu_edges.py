@@ -321,3 +321,48 @@ def test_calls_take_the_current_stream_or_the_one_they_are_given(il):
     with torch.cuda.stream(s):
         assert il._stream_ptr() == s.cuda_stream
     assert il._stream_ptr(s) == s.cuda_stream
+
+
+def _star_sweep(il, r_T, r_R, m, keys, model, prec):
+    """A wide batch over a 20 + 12 column star join: its schema, its first iterations and the time of one."""
+    rng = datagen.rng_for(r_R + m)
+    S, R = rng.standard_normal((r_T, 20)).astype(np.float32), rng.standard_normal((r_R, 12)).astype(np.float32)
+    sch = datagen.Schema([datagen.Source(S, None, np.arange(20, dtype=np.int32)),
+                          datagen.Source(R, keys.astype(np.int32), np.arange(20, 32, dtype=np.int32))], r_T, 32)
+    plan = il.ilargi_plan_create(il.schema_to_device(sch), r_T, 32, max_cx=m)
+    y = (rng.random(r_T) < 0.5).astype(np.float32)
+    lr = np.logspace(-3, -0.5, m).astype(np.float32)
+    code, precision = (il.LINEAR if model == "linear" else il.LOGISTIC), (il.F32 if prec == "f32" else il.BF16_IN_F32_ACC)
+    yd, lrd, W, loss = dev(y), dev(lr), torch.zeros((32, m), device="cuda"), torch.zeros(m, device="cuda")
+
+    def step():
+        il.ilargi_gd_step(plan, code, W, yd, lrd, loss, precision=precision)
+
+    step()
+    step()
+    first = W.cpu().numpy(), loss.cpu().numpy()
+    times = []
+    for _ in range(5):
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        ev[0].record()
+        for _ in range(4):
+            step()
+        ev[1].record()
+        torch.cuda.synchronize()
+        times.append(ev[0].elapsed_time(ev[1]))
+    return sch, y, lr, first, sorted(times)[2]
+
+
+@pytest.mark.parametrize("prec", ["f32", "bf16"])
+def test_sweep_over_popular_keys_that_lie_side_by_side(il, prec):
+    """Half of the rows join the first 1 % of the joined table: right, and the work still spread over the device (it takes
+    1.7 times as long as with keys spread evenly; 12 times when the workgroups share the rows of R out by their number)."""
+    r_T, r_R, m = 600_000, 60_000, 256
+    rng = datagen.rng_for(1)
+    even = rng.integers(0, r_R, r_T)
+    popular = np.where(rng.random(r_T) < 0.5, rng.integers(0, r_R // 100, r_T), even)
+    sch, y, lr, (W, loss), t = _star_sweep(il, r_T, r_R, m, popular, "linear", prec)
+    if prec == "f32":
+        W_ref, L_ref = oracle.gd(oracle.Target(sch), "linear", y, np.zeros((32, m)), lr, 2)
+        assert rel(W, W_ref) < GD_TOL and np.allclose(loss, L_ref[-1], rtol=1e-4)
+    assert t < 4 * _star_sweep(il, r_T, r_R, m, even, "linear", prec)[4]
