@@ -38,7 +38,9 @@ constexpr int SL = 4;         // wavefronts of the workgroup
 constexpr int ST = 64;        // target rows of a batch
 constexpr int JG = 2;         // 16-column tiles of S
 constexpr int KP = 16 * JG;
-constexpr int kTileCost = 32;  // what a tile of R costs beside its target rows, in target rows
+constexpr int kTileCost = 48;  // weight of a tile of R beside its target rows.  1,000,000 rows, 256 linear models, float32: half
+                               // of them on the first 1 % of 600,000 keys 1031 microseconds an iteration with 32, 1050 with
+                               // 48, 1474 with 128; of 300,000 keys 825, 819, 1023; keys spread evenly level
 
 // MODE 1: linear, 2: logistic.  VEC4: rows of S are read as float4.  BF16: values of S, W and E are rounded
 // to bfloat16 (nearest even) where they enter a product.  lda: row stride of the staged rows (a constant: with a
@@ -107,20 +109,22 @@ void gd_star_wide_kernel(StarArgs a, int xfloats, int rtiles, int fold) {
   auto label_at = [&](int r) { return a.Sp == nullptr ? a.y[r] : (a.yp != nullptr ? a.yp[r] : a.y[a.perm[r]]); };
   auto tile_first = [&](int t) { return a.rowptr[min((int64_t)t * tr, a.r_R)]; };
 
-  // This workgroup's run of tiles: the tiles that start in its share of the work, where an index entry counts one and a
+  // This workgroup's run of tiles: the tiles that start in its share of the work, where an index entry weighs one and a
   // tile kTileCost (by number of tiles alone, popular keys that lie side by side all fall to a few workgroups: half of
-  // 1,000,000 rows on the first 1 % of the keys, 256 models, 7078 microseconds an iteration).  A half wavefront looks for
-  // either end, 32 tiles at a time.
+  // 1,000,000 rows on the first 1 % of 100,000 keys, 256 models, 7078 microseconds an iteration and 990 this way).  A half
+  // wavefront looks for either end, 32 tiles at a time: first around an even share of the tiles, where it mostly is.
   auto work_before = [&](int t) { return (int64_t)tile_first(t) + (int64_t)kTileCost * t; };
-  const int64_t want = work_before(rtiles) * ((int64_t)blockIdx.x + lane / 32) / gridDim.x;
+  const int64_t share = (int64_t)blockIdx.x + lane / 32, want = work_before(rtiles) * share / gridDim.x;
   int lo = 0, hi = rtiles;                                    // the end looked for lies in [lo, hi]
+  int first = max((int)(rtiles * share / gridDim.x) - 16, 0), step = 1;
   while (__any(lo < hi)) {
-    const int step = (hi - lo) / 32 + 1;
-    const int t = min(lo + (lane % 32 + 1) * step - 1, hi);
+    const int t = min(first + (lane % 32 + 1) * step - 1, hi);
     const unsigned reached = (unsigned)(__ballot(t == hi || work_before(t) >= want) >> (lane & 32));
-    const int f = __builtin_ctz(reached);                     // (the last lane's t is hi)
-    hi = min(lo + (f + 1) * step - 1, hi);
-    lo += f * step;
+    const int f = reached != 0 ? __builtin_ctz(reached) : 32; // tile first + (f + 1) step - 1 is the first one past the end
+    if (f < 32) hi = min(first + (f + 1) * step - 1, hi);
+    if (f > 0) lo = min(first + f * step, hi);
+    first = lo;
+    step = (hi - lo) / 32 + 1;
   }
   int t_lo = __builtin_amdgcn_readlane(lo, 0), t_hi = __builtin_amdgcn_readlane(lo, 32);
   if (rtiles <= (int)gridDim.x) { t_lo = blockIdx.x; t_hi = t_lo + 1; }   // a workgroup per tile
