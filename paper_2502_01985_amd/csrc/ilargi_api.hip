@@ -1040,7 +1040,10 @@ ilargi_status_t tmm_wide(ilargi_plan* pl, const float* Y, int cx, float* out, in
   return ILARGI_OK;
 }
 
-constexpr int64_t kStarWideRows = 512 * 1024;   // target rows from which the shared-row pass is taken
+// Target rows from which the shared-row pass may be taken.  Iterations of 256 models, ten target rows to a row of the
+// joined table, time with shared rows over the time without: 524,288 rows 0.84 to 0.99 in all modes and precisions, 250,000
+// 0.89 to 1.00, 50,000 0.87 to 1.09 (a workgroup's run of tiles no longer pays for its start).
+constexpr int64_t kStarWideRows = 512 * 1024;
 
 // Alg. 1 for a wide batch on a two-table star join: P = R W_R, the join-order pass (residual, S^T E, segment
 // sums), R^T Z, update.  The r_T x m residual is never stored.
@@ -1077,9 +1080,8 @@ ilargi_status_t gd_star_step(ilargi_plan* pl, int mode, float* W, int m, const f
   int grid = 0;
   {
     TraceScope ts(pl, "star_pass", -1, st);
-    // (fewer target rows do not give every workgroup a run of tiles long enough to pay for its start: 250,000 rows, 256
-    // models, 160 microseconds an iteration in the other form and 184 in this one; 50,000: 61 and 66)
-    if (gd_star_wide_supported(s.cs, m) && pl->r_T >= kStarWideRows) HIP_TRY(launch_gd_star_wide(s, f.vec, mode, bf16, (int)max_grid, st, &grid));
+    if (pl->r_T >= kStarWideRows && gd_star_wide_pays(s.cs, m, s.r_R, f.vec, mode, bf16))
+      HIP_TRY(launch_gd_star_wide(s, f.vec, mode, bf16, (int)max_grid, st, &grid));
     else HIP_TRY(launch_gd_star(s, f.vec, mode, bf16, (int)max_grid, st, &grid));
   }
   HIP_TRY(launch_tred_reduce(s.grad_partial, grid, (int64_t)s.cs * m, pl->at<float>(f.o_g), st));

@@ -428,6 +428,7 @@ hipError_t launch_lmm_prod_stream(const LmmArgs& a, hipStream_t st);
 bool lmm_flat_wide_supported(const LmmArgs& a, int vec, int mode);
 hipError_t launch_lmm_flat_wide(const LmmArgs& a, hipStream_t st, int* grid_out);
 bool gd_star_wide_supported(int cs, int m);
+bool gd_star_wide_pays(int cs, int m, int64_t r_R, int vec, int mode, bool bf16);
 hipError_t launch_gd_star_wide(const StarArgs& a, int vec, int mode, bool bf16, int max_grid, hipStream_t st, int* grid_out);
 bool gd_star_supported(int cs, int m);
 hipError_t launch_gd_star(const StarArgs& a, int vec, int mode, bool bf16, int max_grid, hipStream_t st, int* grid_out);

@@ -9,8 +9,10 @@
 // In float32 the matrix cores bound it: 52 MFMAs of 32 cycles per 16 rows and 64 models are 180 microseconds of the
 // chip; with bfloat16 inputs the arithmetic of the residuals between the products.
 // 1,000,000 x 20 with 100,000 x 200, 256 linear models: 331 microseconds in float32 (367 with a wavefront per tile and
-// slab), 161 with bfloat16 inputs (253).  With 128 models or fewer, or wider tables, too few wavefronts fit beside the
-// shared buffers and the one-wavefront form is the faster one (64 models: 246 microseconds an iteration against 317 with this scheme, 128: 358 and 375).
+// slab), 161 with bfloat16 inputs (253).  A wavefront without models of its own only stages rows, but its place on the
+// compute unit stays taken: gd_star_wide_pays says which counts of models and tiles come here.  With 128 models or fewer,
+// or wider tables, too few wavefronts fit beside the shared buffers and the one-wavefront form is the faster one
+// (64 models: 246 microseconds an iteration against 317 with this scheme, 128: 358 and 375).
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
@@ -60,7 +62,7 @@ void gd_star_wide_kernel(StarArgs a, int xfloats, int rtiles, int fold) {
   int* rS = reinterpret_cast<int*>(yS + 2 * ST);              // [2][20] first index entry of every row of a tile of R
   float* Xs = reinterpret_cast<float*>(rS + 40) + (size_t)wave * xfloats;   // [ceil(cs / 4)][64][4]  (bf16: [KP / 8][64][8])
   const int n0 = (blockIdx.y * SL + wave) * kN;
-  const int nw = max(0, min(kN, a.m - n0));
+  const int nw = __builtin_amdgcn_readfirstlane(max(0, min(kN, a.m - n0)));
   // fold: the table has 1..4 columns beyond whole groups of 16.  A tile of R then has 12 rows, and rows 12..15
   // of the segment-sum MFMA (whose A operand is the 0/1 indicator) carry those columns of S instead, so the
   // same MFMA forms their share of S^T E; they are collected in the last gacc slot by the lanes q == 3.
@@ -68,19 +70,39 @@ void gd_star_wide_kernel(StarArgs a, int xfloats, int rtiles, int fold) {
   const int full = a.cs / 16;
   const int njt = fold ? full : (a.cs + 15) / 16;             // 16-column groups of S that take their own MFMAs
 
-  // this wavefront's columns of W, one per lane, all requested together
-  {
-    float x[KP];
+  // this wavefront's columns of W, one per lane, all requested together (they travel while the run is looked for)
+  float x[KP];
 #pragma unroll
-    for (int k = 0; k < KP; ++k) {
-      const int t = k < a.cs ? a.s_colmap[k] : -1;
-      x[k] = (t >= 0 && lane < nw) ? a.W[(int64_t)t * a.ldw + n0 + lane] : 0.0f;
-    }
+  for (int k = 0; k < KP; ++k) {
+    const int t = k < a.cs ? a.s_colmap[k] : -1;
+    x[k] = (t >= 0 && lane < nw) ? a.W[(int64_t)t * a.ldw + n0 + lane] : 0.0f;
+  }
+
+  auto tile_first = [&](int t) { return a.rowptr[min((int64_t)t * tr, a.r_R)]; };
+  // This workgroup's run of tiles: the tiles that start in its share of the work, where an index entry weighs one and a
+  // tile kTileCost (by number of tiles alone, popular keys that lie side by side all fall to a few workgroups: half of
+  // 1,000,000 rows on the first 1 % of 100,000 keys, 256 models, 7078 microseconds an iteration and 990 this way).  A half
+  // wavefront looks for either end, 32 tiles at a time: first around an even share of the tiles, where it mostly is.
+  auto work_before = [&](int t) { return (int64_t)tile_first(t) + (int64_t)kTileCost * t; };
+  const int64_t share = (int64_t)blockIdx.x + lane / 32, want = work_before(rtiles) * share / gridDim.x;
+  int lo = 0, hi = rtiles;                                    // the end looked for lies in [lo, hi]
+  int first = max((int)(rtiles * share / gridDim.x) - 16, 0), step = 1;
+  while (__any(lo < hi)) {
+    const int t = min(first + (lane % 32 + 1) * step - 1, hi);
+    const unsigned reached = (unsigned)(__ballot(t == hi || work_before(t) >= want) >> (lane & 32));
+    const int f = reached != 0 ? __builtin_ctz(reached) : 32; // tile first + (f + 1) step - 1 is the first one past the end
+    if (f < 32) hi = min(first + (f + 1) * step - 1, hi);
+    if (f > 0) lo = min(first + f * step, hi);
+    first = lo;
+    step = (hi - lo) / 32 + 1;
+  }
+  int t_lo = __builtin_amdgcn_readlane(lo, 0), t_hi = __builtin_amdgcn_readlane(lo, 32);
+  if (rtiles <= (int)gridDim.x) { t_lo = blockIdx.x; t_hi = t_lo + 1; }   // a workgroup per tile
+
 #pragma unroll
-    for (int k = 0; k < KP; ++k) {
-      if constexpr (BF16) reinterpret_cast<__bf16*>(Xs)[((k >> 3) * kN + lane) * 8 + (k & 7)] = (__bf16)x[k];
-      else if (k < (a.cs + 3) / 4 * 4) Xs[((k >> 2) * kN + lane) * 4 + (k & 3)] = x[k];
-    }
+  for (int k = 0; k < KP; ++k) {
+    if constexpr (BF16) reinterpret_cast<__bf16*>(Xs)[((k >> 3) * kN + lane) * 8 + (k & 7)] = (__bf16)x[k];
+    else if (k < (a.cs + 3) / 4 * 4) Xs[((k >> 2) * kN + lane) * 4 + (k & 3)] = x[k];
   }
   wave_sync();
 
@@ -107,27 +129,6 @@ void gd_star_wide_kernel(StarArgs a, int xfloats, int rtiles, int fold) {
   // join-ordered copy of the table (and of the labels) when the plan keeps one
   auto row_at = [&](int p) { return a.Sp != nullptr ? p : a.perm[p]; };
   auto label_at = [&](int r) { return a.Sp == nullptr ? a.y[r] : (a.yp != nullptr ? a.yp[r] : a.y[a.perm[r]]); };
-  auto tile_first = [&](int t) { return a.rowptr[min((int64_t)t * tr, a.r_R)]; };
-
-  // This workgroup's run of tiles: the tiles that start in its share of the work, where an index entry weighs one and a
-  // tile kTileCost (by number of tiles alone, popular keys that lie side by side all fall to a few workgroups: half of
-  // 1,000,000 rows on the first 1 % of 100,000 keys, 256 models, 7078 microseconds an iteration and 990 this way).  A half
-  // wavefront looks for either end, 32 tiles at a time: first around an even share of the tiles, where it mostly is.
-  auto work_before = [&](int t) { return (int64_t)tile_first(t) + (int64_t)kTileCost * t; };
-  const int64_t share = (int64_t)blockIdx.x + lane / 32, want = work_before(rtiles) * share / gridDim.x;
-  int lo = 0, hi = rtiles;                                    // the end looked for lies in [lo, hi]
-  int first = max((int)(rtiles * share / gridDim.x) - 16, 0), step = 1;
-  while (__any(lo < hi)) {
-    const int t = min(first + (lane % 32 + 1) * step - 1, hi);
-    const unsigned reached = (unsigned)(__ballot(t == hi || work_before(t) >= want) >> (lane & 32));
-    const int f = reached != 0 ? __builtin_ctz(reached) : 32; // tile first + (f + 1) step - 1 is the first one past the end
-    if (f < 32) hi = min(first + (f + 1) * step - 1, hi);
-    if (f > 0) lo = min(first + f * step, hi);
-    first = lo;
-    step = (hi - lo) / 32 + 1;
-  }
-  int t_lo = __builtin_amdgcn_readlane(lo, 0), t_hi = __builtin_amdgcn_readlane(lo, 32);
-  if (rtiles <= (int)gridDim.x) { t_lo = blockIdx.x; t_hi = t_lo + 1; }   // a workgroup per tile
 
   // Batches: tile t of R, index entries [p, min(p + ST, pe)) with pe the tile's end.  (An empty tile is a batch of none.)
   struct Batch { int t, p, pe; };
@@ -153,7 +154,7 @@ void gd_star_wide_kernel(StarArgs a, int xfloats, int rtiles, int fold) {
 
   int tile_now = -1;
   for (int c = 0; bc.t < t_hi || bs.t < t_hi || bl.t < t_hi; c ^= 1) {
-    if (bc.t < t_hi) {
+    if (bc.t < t_hi && nw > 0) {                              // (a wavefront beyond the batch of models only stages rows)
       if (bc.t != tile_now) {
         // a new tile of R: its P into LDS (zero beyond the table and the slab)
         tile_now = bc.t;
@@ -463,7 +464,8 @@ StarFn pick_star(bool vec4, int lda) {
   return vec4 ? gd_star_wide_kernel<MODE, true, B, KP + 4> : gd_star_wide_kernel<MODE, false, B, KP + 4>;
 }
 
-int star_slots(StarFn fn, size_t lds_bytes) {
+// Workgroups resident at once, on the device and on one compute unit.
+int star_slots(StarFn fn, size_t lds_bytes, int* on_cu) {
   static std::mutex cache_mutex;   // the cache below is shared by every plan of the process
   std::lock_guard<std::mutex> lock(cache_mutex);
   static int cus = 0;
@@ -479,11 +481,12 @@ int star_slots(StarFn fn, size_t lds_bytes) {
       cus = prop.multiProcessorCount;
   }
   for (int i = 0; i < n_seen; ++i)
-    if (seen_fn[i] == fn && seen_lds[i] == lds_bytes) return seen_occ[i] * cus;
+    if (seen_fn[i] == fn && seen_lds[i] == lds_bytes) { *on_cu = seen_occ[i]; return seen_occ[i] * cus; }
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(fn), kWave * SL, lds_bytes) != hipSuccess || per_cu < 1)
     per_cu = 1;
   if (n_seen < 32) { seen_fn[n_seen] = fn; seen_lds[n_seen] = lds_bytes; seen_occ[n_seen] = per_cu; ++n_seen; }
+  *on_cu = per_cu;
   return per_cu * cus;
 }
 
@@ -491,36 +494,73 @@ int star_slots(StarFn fn, size_t lds_bytes) {
 
 bool gd_star_wide_supported(int cs, int m) { return cs > 0 && cs <= KP && m > 2 * kN; }
 
-// max_grid: the caller's bound on workgroups per slab of 256 models (sizes of the partial buffers).
-hipError_t launch_gd_star_wide(const StarArgs& a, int vec, int mode, bool bf16, int max_grid, hipStream_t st, int* grid_out) {
-  if (grid_out) *grid_out = 0;
-  if (!gd_star_wide_supported(a.cs, a.m) || (mode != 1 && mode != 2) || a.r_R <= 0 || max_grid < 1) return hipErrorInvalidValue;
-  const int tail = a.cs % 16;
-  const int fold = (tail >= 1 && tail <= 4) ? 1 : 0;   // see the kernel: 12-row tiles of R
-  const int tr = fold ? 12 : 16;
-  const int rtiles = (int)((a.r_R + tr - 1) / tr);
+namespace {
+
+struct WideShape {
+  StarFn fn;
+  int fold, rtiles, xfloats, gy;
+  size_t lds_bytes;
+  int64_t slots;                // workgroups resident at once
+  int per_cu;                   // ... on a compute unit
+};
+
+WideShape wide_shape(int cs, int m, int64_t r_R, int vec, int mode, bool bf16) {
+  WideShape w;
+  const int tail = cs % 16;
+  w.fold = (tail >= 1 && tail <= 4) ? 1 : 0;           // see the kernel: 12-row tiles of R
+  const int tr = w.fold ? 12 : 16;
+  w.rtiles = (int)((r_R + tr - 1) / tr);
   const bool vec4 = vec == 4;
   // Row stride of the staged rows, 4 modulo 8 floats: the 128-bit reads of 16 rows then fall on different banks.  The
   // bfloat16 product reads 32 columns of a row; in float32 the columns that are read are whole groups of four, or of 16
   // where such a group takes its own MFMAs, and up to 20 columns leave room for a third workgroup on a compute unit.
-  const int need = fold ? (a.cs + 3) / 4 * 4 : (a.cs + 15) / 16 * 16;
+  const int need = w.fold ? (cs + 3) / 4 * 4 : (cs + 15) / 16 * 16;
   const int lda = !bf16 && need <= 20 ? 20 : KP + 4;
-  StarFn fn;
-  if (bf16) fn = mode == 1 ? pick_star<1, true>(vec4, lda) : pick_star<2, true>(vec4, lda);
-  else fn = mode == 1 ? pick_star<1, false>(vec4, lda) : pick_star<2, false>(vec4, lda);
-  const int xfloats = bf16 ? KP * kN / 2 : (a.cs + 3) / 4 * 4 * kN;
-  const size_t lds_floats = 2 * (size_t)ST * lda + (size_t)SL * (16 * kN + xfloats) + 6 * (size_t)ST + 40;
-  const size_t lds_bytes = lds_floats * sizeof(float);
-  if (lds_bytes > 64 * 1024)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-  const int gy = (a.m + SL * kN - 1) / (SL * kN);
-  int64_t gx = rtiles;
-  const int64_t slots = star_slots(fn, lds_bytes);
+  if (bf16) w.fn = mode == 1 ? pick_star<1, true>(vec4, lda) : pick_star<2, true>(vec4, lda);
+  else w.fn = mode == 1 ? pick_star<1, false>(vec4, lda) : pick_star<2, false>(vec4, lda);
+  w.xfloats = bf16 ? KP * kN / 2 : (cs + 3) / 4 * 4 * kN;
+  w.lds_bytes = sizeof(float) * (2 * (size_t)ST * lda + (size_t)SL * (16 * kN + w.xfloats) + 6 * (size_t)ST + 40);
+  if (w.lds_bytes > 64 * 1024)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(w.fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)w.lds_bytes);
+  w.gy = (m + SL * kN - 1) / (SL * kN);
+  w.slots = star_slots(w.fn, w.lds_bytes, &w.per_cu);
+  return w;
+}
+
+}  // namespace
+
+// Whether the shared rows pay.  Iterations over 1,000,000 rows of 8, 20 and 32 columns, 1000 to 100,000 rows of R, 192,
+// 256, 320 and 384 models, time in this form over the time with a wavefront per tile and slab:
+//   linear models with bfloat16 inputs (bound by the staged rows): 0.49 to 0.87 everywhere
+//   no more tiles than compute units: 0.57 to 0.92 everywhere
+//   a last workgroup with two idle wavefronts of eight or one of four: 0.97 to 1.69; with none, or one of eight:
+//     logistic models with bfloat16 inputs: 0.85 to 0.96
+//     float32 logistic: 0.75 to 0.86, but 1.13 where the tiles fill 1.2 rounds of workgroups
+//     float32 linear (bound by the matrix cores): 0.94 to 0.95 with three workgroups on a compute unit and the last round
+//       nine tenths full, else 1.00 to 1.30
+bool gd_star_wide_pays(int cs, int m, int64_t r_R, int vec, int mode, bool bf16) {
+  if (!gd_star_wide_supported(cs, m)) return false;
+  if (bf16 && mode == 1) return true;
+  const WideShape w = wide_shape(cs, m, r_R, vec, mode, bf16);
+  const int64_t work = (int64_t)w.rtiles * w.gy;              // a tile and its 256 models
+  if (work <= w.slots / w.per_cu) return true;
+  if (2 * ((m + kN - 1) / kN) < 7 * w.gy) return false;
+  if (bf16) return true;
+  const int64_t rounds = (work + w.slots - 1) / w.slots;
+  return mode == 2 ? 10 * work >= 8 * rounds * w.slots : w.per_cu >= 3 && (rounds == 1 || 10 * work >= 9 * rounds * w.slots);
+}
+
+// max_grid: the caller's bound on workgroups per slab of 256 models (sizes of the partial buffers).
+hipError_t launch_gd_star_wide(const StarArgs& a, int vec, int mode, bool bf16, int max_grid, hipStream_t st, int* grid_out) {
+  if (grid_out) *grid_out = 0;
+  if (!gd_star_wide_supported(a.cs, a.m) || (mode != 1 && mode != 2) || a.r_R <= 0 || max_grid < 1) return hipErrorInvalidValue;
+  const WideShape w = wide_shape(a.cs, a.m, a.r_R, vec, mode, bf16);
+  int64_t gx = w.rtiles;
   // every workgroup walks its run of tiles: one round of resident workgroups
-  if (gx * gy > slots) gx = std::max<int64_t>(1, slots / gy);
+  if (gx * w.gy > w.slots) gx = std::max<int64_t>(1, w.slots / w.gy);
   gx = std::min<int64_t>(gx, max_grid);
   if (grid_out) *grid_out = (int)gx;
-  hipLaunchKernelGGL(fn, dim3((unsigned)gx, (unsigned)gy), dim3(kWave * SL), lds_bytes, st, a, xfloats, rtiles, fold);
+  hipLaunchKernelGGL(w.fn, dim3((unsigned)gx, (unsigned)w.gy), dim3(kWave * SL), w.lds_bytes, st, a, w.xfloats, w.rtiles, w.fold);
   return hipGetLastError();
 }
 

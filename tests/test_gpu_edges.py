@@ -366,3 +366,12 @@ def test_sweep_over_popular_keys_that_lie_side_by_side(il, prec):
         W_ref, L_ref = oracle.gd(oracle.Target(sch), "linear", y, np.zeros((32, m)), lr, 2)
         assert rel(W, W_ref) < GD_TOL and np.allclose(loss, L_ref[-1], rtol=1e-4)
     assert t < 4 * _star_sweep(il, r_T, r_R, m, even, "linear", prec)[4]
+
+
+def test_sweep_whose_models_do_not_fill_the_wavefronts(il):
+    """320 logistic models, a quarter more than 256: 1.49 times their time in wavefronts of 64 models each, 1.86 times in
+    groups of four wavefronts of which three are idle."""
+    r_T, r_R = 1_000_000, 100_000
+    keys = datagen.rng_for(2).integers(0, r_R, r_T)
+    t = [_star_sweep(il, r_T, r_R, m, keys, "logistic", "bf16")[4] for m in (256, 320)]
+    assert t[1] < 1.67 * t[0]
