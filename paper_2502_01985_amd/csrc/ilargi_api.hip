@@ -260,7 +260,41 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
   lay.o_cn = take(sizeof(float) * max_cx);
   lay.o_counts = take(sizeof(int32_t) * max_cx);
   lay.o_rr = take(sizeof(float) * 2 * kGnmfMaxRank * kGnmfMaxRank);
+  // Gram scratch: summed rows for the "via sums" route, chunk partials, the (k,l) blocks
+  lay.zc_floats = 1;
+  lay.gpartial_floats = kGramPartialFloats;
+  lay.blocks_floats = 0;
+  for (int k = 0; k < n && lay.max_entries == 0; ++k)    // (plans with sparse sources have no Gram matrix)
+    for (int l = k; l < n; ++l) {
+      int64_t cc = src[k].cols * src[l].cols;
+      lay.blocks_floats += cc;
+      lay.gpartial_floats = std::max(lay.gpartial_floats, cc);
+      lay.gpartial_floats = std::max(lay.gpartial_floats, src[k].cols * max_cx);
+      if (l > k) {
+        const bool via_l = src[l].has_idx && src[l].rows * 2 <= r_T, via_k = src[k].has_idx && src[k].rows * 2 <= r_T;
+        if (via_l) lay.zc_floats = std::max(lay.zc_floats, src[l].rows * src[k].cols);
+        if (via_k) lay.zc_floats = std::max(lay.zc_floats, src[k].rows * src[l].cols);
+        if (!via_l && !via_k && lay.n_pairlists < kMaxPairLists && src[k].cols >= 4 && src[k].cols <= 64 && src[l].cols >= 4 &&
+            src[l].cols <= 64 && src[k].rows > 0 && src[l].rows > 0 && r_T > 0) {
+          lay.pairlist_k[lay.n_pairlists] = k;
+          lay.pairlist_l[lay.n_pairlists] = l;
+          ++lay.n_pairlists;
+        }
+      }
+    }
+  // The sort that builds the inverse indices is over before the first partial block is written: same space.  Plans with
+  // sparse tables, whose workspace goes by the stored entries, keep room of their own for it.
+  const int64_t sort_n = std::max<int64_t>(std::max<int64_t>(r_T, 1), lay.max_entries);
+  const size_t sort_bytes = align_up(sizeof(int32_t) * 4 * sort_n), hist_bytes = sizeof(int32_t) * sort_hist_ints(sort_n);
+  const size_t partial_bytes = sizeof(float) * lay.gpartial_floats;
+  const int64_t shared_bytes = lay.max_entries > 0 ? 0 : (int64_t)std::min(partial_bytes, sort_bytes + hist_bytes);
+  // Chunks of long segments: what segments cut at kLongSeg entries leave, and more of them (shorter cuts) as far as the
+  // shared space pays for their sums, so that no plan asks for more workspace by them.
   const int64_t wmax = std::max<int64_t>(max_cx, cmax);
+  int64_t n_indexed = 0;
+  for (int k = 0; k < n; ++k) n_indexed += src[k].has_idx ? 1 : 0;
+  const int64_t chunks_long = 2 * (r_T / kLongSeg) + 2;
+  const int64_t more = std::max<int64_t>(shared_bytes / std::max<int64_t>(n_indexed, 1) - 6 * (int64_t)kAlign, 0) / (4 * wmax + 16);
   for (int k = 0; k < n; ++k) {
     SourcePlan& p = src[k];
     p.o_colmap = take(sizeof(int32_t) * std::max<int64_t>(p.cols, 1));
@@ -268,8 +302,8 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
     if (p.has_idx) {
       p.o_rowptr = take(sizeof(int32_t) * (p.rows + 1));
       p.o_perm = take(sizeof(int32_t) * std::max<int64_t>(r_T, 1));
-      p.nl_max = r_T / kSegCut + 1;
-      p.nch_max = r_T / (kLongSeg / 4) + 2;
+      p.nch_max = std::max(chunks_long, std::min(chunks_long + more, r_T / (kLongSeg / 4) + 2));
+      p.nl_max = p.nch_max / 2;                       // (a long segment is cut in two at least)
       p.o_chunk_seg = take(sizeof(int32_t) * p.nch_max);
       p.o_chunk_beg = take(sizeof(int32_t) * p.nch_max);
       p.o_chunk_end = take(sizeof(int32_t) * p.nch_max);
@@ -320,35 +354,8 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
   lay.o_E = take(sizeof(float) * std::max<int64_t>(r_T, 1) * max_cx);
   lay.o_eye = take(sizeof(float) * (lay.max_entries > 0 && c_T <= kSparseGramMaxCols ? c_T * std::min<int64_t>(max_cx, kSparseGramWidth) : 1));
   lay.o_loss = take(sizeof(float) * std::max<int64_t>(32768 * kNarrowCT, 1024 * max_cx));
-  const int64_t sort_n = std::max<int64_t>(std::max<int64_t>(r_T, 1), lay.max_entries);
-  // Gram scratch: summed rows for the "via sums" route, chunk partials, the (k,l) blocks
-  lay.zc_floats = 1;
-  lay.gpartial_floats = kGramPartialFloats;
-  lay.blocks_floats = 0;
-  for (int k = 0; k < n && lay.max_entries == 0; ++k)    // (plans with sparse sources have no Gram matrix)
-    for (int l = k; l < n; ++l) {
-      int64_t cc = src[k].cols * src[l].cols;
-      lay.blocks_floats += cc;
-      lay.gpartial_floats = std::max(lay.gpartial_floats, cc);
-      lay.gpartial_floats = std::max(lay.gpartial_floats, src[k].cols * max_cx);
-      if (l > k) {
-        const bool via_l = src[l].has_idx && src[l].rows * 2 <= r_T, via_k = src[k].has_idx && src[k].rows * 2 <= r_T;
-        if (via_l) lay.zc_floats = std::max(lay.zc_floats, src[l].rows * src[k].cols);
-        if (via_k) lay.zc_floats = std::max(lay.zc_floats, src[k].rows * src[l].cols);
-        if (!via_l && !via_k && lay.n_pairlists < kMaxPairLists && src[k].cols >= 4 && src[k].cols <= 64 && src[l].cols >= 4 &&
-            src[l].cols <= 64 && src[k].rows > 0 && src[l].rows > 0 && r_T > 0) {
-          lay.pairlist_k[lay.n_pairlists] = k;
-          lay.pairlist_l[lay.n_pairlists] = l;
-          ++lay.n_pairlists;
-        }
-      }
-    }
   for (int i = 0; i < lay.n_pairlists; ++i) lay.o_pairlist[i] = take(sizeof(int32_t) * 2 * r_T);
   lay.o_zc = take(sizeof(float) * lay.zc_floats);
-  // The sort that builds the inverse indices is over before the first partial block is written: same space.  Plans with
-  // sparse tables, whose workspace goes by the stored entries, keep room of their own for it.
-  const size_t sort_bytes = align_up(sizeof(int32_t) * 4 * sort_n), hist_bytes = sizeof(int32_t) * sort_hist_ints(sort_n);
-  const size_t partial_bytes = sizeof(float) * lay.gpartial_floats;
   if (lay.max_entries > 0) {
     lay.o_gpartial = take(partial_bytes);
     lay.o_sort = take(sort_bytes + hist_bytes);

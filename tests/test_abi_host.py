@@ -206,3 +206,25 @@ def test_choose_counts_stored_entries_for_sparse_tables():
     # Tab. 2: the factorized cost is counted in non-zero elements
     assert sparse["complexity_ratio"] > dense["complexity_ratio"]
     assert sparse["bytes_factorized"] < dense["bytes_factorized"]
+
+
+@pytest.mark.parametrize("r_T,max_cx,dense,sparse,most", [
+    # a program that keeps one buffer for its plans, sized once, keeps fitting: dense tables (rows, columns, joined), sparse
+    # ones (rows, columns, entries), the bytes that a plan asked for when segments were cut at 2048 entries only
+    (10_000, 1, [(10_000, 4, False), (1_000, 8, True)], [], 68_228_352),
+    (5_000_000, 1, [(5_000_000, 10, False), (100_000, 50, True), (50_000, 100, True), (10_000, 40, True)], [], 423_576_320),
+    (1_000_000, 1, [(1_000_000, 20, False), (1_000, 4_000, True), (1_000, 4_000, True)], [], 475_991_552),
+    (100_000_000, 4, [(100_000_000, 10, False), (100_000, 100, True), (100_000, 100, True)], [], 7_235_768_064),
+    (1_000_000, 1, [], [(6_040, 9_510, 120_800), (3_710, 3_840, 74_200)], 174_601_984),
+    (1_000_000, 64, [], [(50_000, 30, 200_000)], 360_864_000),
+    (1_000_000, 1, [], [(50_000, 1 << 20, 500_000)], 4_299_295_232),
+])
+def test_workspace_is_not_larger_for_shorter_segments(r_T, max_cx, dense, sparse, most):
+    tables, at = [], 0
+    for rows, cols, joined in dense:
+        tables.append(_src(rows, cols, not joined, np.arange(at, at + cols)))
+        at += cols
+    for rows, cols, entries in sparse:
+        tables.append((0, rows, cols, 8192, np.arange(at, at + cols, dtype=np.int32), 1, 1, 1, entries))
+        at += cols
+    assert il.ilargi_plan_workspace_bytes(tables, r_T, at, max_cx) <= most

@@ -375,3 +375,20 @@ def test_sweep_whose_models_do_not_fill_the_wavefronts(il):
     keys = datagen.rng_for(2).integers(0, r_R, r_T)
     t = [_star_sweep(il, r_T, r_R, m, keys, "logistic", "bf16")[4] for m in (256, 320)]
     assert t[1] < 1.67 * t[0]
+
+
+@pytest.mark.parametrize("sparse", [False, True])
+def test_segments_cut_as_far_as_the_chunk_tables_have_room(il, sparse):
+    """More segments above the shortest cut than chunks fit: the plan cuts longer ones."""
+    counts = [300] * 700 + [3_000, 0, 257] + [1_100] * 20
+    rng = datagen.rng_for(6)
+    fk = np.repeat(np.arange(len(counts), dtype=np.int32), counts)
+    rng.shuffle(fk)
+    R = rng.standard_normal((len(counts), 6)).astype(np.float32)
+    R[rng.random(R.shape) < 0.6] = 0.0
+    sch = datagen.Schema([datagen.Source(R, fk, np.arange(6, dtype=np.int32))], fk.size, 6)
+    tg = oracle.Target(sch)
+    plan = il.ilargi_plan_create(il.schema_to_device(sch, sparse=sparse), fk.size, 6, max_cx=12)
+    for cx in (1, 4, 12):
+        Y = rng.standard_normal((fk.size, cx)).astype(np.float32)
+        assert rel(il.ilargi_tmm(plan, dev(Y)).cpu().numpy(), oracle.tmm(tg, Y)) < OP_TOL
