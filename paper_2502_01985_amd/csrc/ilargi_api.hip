@@ -2188,7 +2188,6 @@ ilargi_status_t ilargi_materialize(ilargi_plan_t* plan, float* T, void* stream) 
     if (p.empty) continue;
     a.D[a.n] = p.D;
     a.idx[a.n] = p.ident ? nullptr : p.idx;
-    a.tcol2src[a.n] = plan->at<int32_t>(p.o_tcol);
     a.rows[a.n] = p.rows;
     a.ck[a.n] = (int)p.cols;
     ++a.n;
@@ -2206,7 +2205,7 @@ ilargi_status_t ilargi_materialize(ilargi_plan_t* plan, float* T, void* stream) 
     if (p.empty) continue;
     MatTileSource& q = t.s[t.n++];
     q.D = p.D; q.idx = p.ident ? nullptr : p.idx; q.rows = p.rows; q.ck = (int)p.cols;
-    q.colmap = plan->at<int32_t>(p.o_colmap);
+    q.colmap = plan->at<int32_t>(p.o_colmap); q.tcol = plan->at<int32_t>(p.o_tcol);
     q.c0 = p.colmap_h[0];
     for (int64_t j = 1; j < p.cols && q.c0 >= 0; ++j)
       if (p.colmap_h[(size_t)j] != q.c0 + j) q.c0 = -1;
@@ -2217,10 +2216,10 @@ ilargi_status_t ilargi_materialize(ilargi_plan_t* plan, float* T, void* stream) 
   {
     TraceScope ts(plan, "materialize", -1, static_cast<hipStream_t>(stream));
     // the flat stream and the LDS tiles run level where both apply (1,000,000 x 220: 281 and 277 microseconds, 100,000 x
-    // 100: 11.9 and 12.5); beyond kMatTileMaxCols a tile of four rows no longer fits
+    // 100: 11.9 and 12.5); wide tables go through slabs of columns
     if (materialize_flat_supported(a)) HIP_TRY(launch_materialize_flat(a, static_cast<hipStream_t>(stream)));
     else if (materialize_tile_supported(t)) HIP_TRY(launch_materialize_tile(t, static_cast<hipStream_t>(stream)));
-    else HIP_TRY(launch_materialize(a, static_cast<hipStream_t>(stream)));
+    else HIP_TRY(launch_materialize_slab(t, static_cast<hipStream_t>(stream)));
   }
   return ILARGI_OK;
 }

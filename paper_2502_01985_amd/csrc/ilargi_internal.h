@@ -262,7 +262,6 @@ struct MatArgs {
   int n;
   const float* D[kMaxSources];
   const int32_t* idx[kMaxSources];
-  const int32_t* tcol2src[kMaxSources];
   int64_t rows[kMaxSources];
   int ck[kMaxSources];
   float* T;
@@ -281,6 +280,7 @@ struct MatTileSource {
   const float* D;
   const int32_t* idx;      // NULL: identity on the first `rows` target rows
   const int32_t* colmap;   // device int32[ck], read when c0 < 0
+  const int32_t* tcol;     // device int32[c_T], column of D behind a target column (-1: none), read when c0 < 0
   int64_t rows;
   int ck, c0;              // c0 >= 0: column j feeds target column c0 + j
   int vec;                 // floats per load (1 when c0 < 0)
@@ -463,11 +463,11 @@ hipError_t launch_finalize(const FinArgs& a, int c_T, int mode, hipStream_t st);
 int colred_step_rows(int ck, int vec);
 bool tmm_part_supported(const ColredArgs& c, const SegArgs* s);
 hipError_t launch_tmm_parts(const TmmParts& t, hipStream_t st);
-hipError_t launch_materialize(const MatArgs& a, hipStream_t st);
 bool materialize_flat_supported(const MatArgs& a);
 hipError_t launch_materialize_flat(const MatArgs& a, hipStream_t st);
 bool materialize_tile_supported(const MatTileArgs& a);
 hipError_t launch_materialize_tile(MatTileArgs a, hipStream_t st);
+hipError_t launch_materialize_slab(const MatTileArgs& a, hipStream_t st);
 hipError_t launch_gram_assemble(const GramAsmPair* pairs_dev, int npairs, const int32_t* const* tcol2src_dev,
                                 int c_T, float* out, hipStream_t st);
 bool tmm_join_supported(int ck, int c);

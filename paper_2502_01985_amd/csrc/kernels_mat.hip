@@ -7,34 +7,6 @@ namespace ilargi {
 
 namespace {
 
-// One wavefront per target row, lanes across target columns.
-__global__ __launch_bounds__(kBlock) void materialize_kernel(MatArgs a) {
-  const int lane = threadIdx.x % kWave;
-  const int64_t wave0 = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
-  const int64_t nwaves = (int64_t)gridDim.x * (kBlock / kWave);
-  for (int64_t i = wave0; i < a.r_T; i += nwaves) {
-    int64_t jrow[kMaxSources];
-#pragma unroll
-    for (int k = 0; k < kMaxSources; ++k) {
-      if (k < a.n) {
-        if (a.idx[k] != nullptr) jrow[k] = a.idx[k][i];
-        else jrow[k] = (i < a.rows[k]) ? i : -1;
-      }
-    }
-    for (int t = lane; t < a.c_T; t += kWave) {
-      float acc = 0.0f;
-#pragma unroll
-      for (int k = 0; k < kMaxSources; ++k) {
-        if (k < a.n) {
-          int j = a.tcol2src[k][t];
-          if (j >= 0 && jrow[k] >= 0) acc += a.D[k][jrow[k] * a.ck[k] + j];
-        }
-      }
-      a.T[i * a.c_T + t] = acc;
-    }
-  }
-}
-
 // General form: a workgroup builds a tile of whole target rows in LDS, one source after the other, and writes it out
 // as one contiguous run of float4.  Bound by the write of T.  The rows are built in LDS because a schema whose column
 // blocks start anywhere (10 + 50 + 100 + 40 columns) leaves no aligned float4 a lane could move from a source to T by
@@ -143,6 +115,65 @@ __global__ __launch_bounds__(kBlock) void materialize_tile_kernel(MatTileArgs a)
   }
 }
 
+// Target tables too wide for a tile of whole rows: a wavefront builds kSlabCols columns of one row in LDS, one source after
+// the other, and writes them out.  The slab starts in LDS as far from a float4 as it does in T.  Bound by the write of T.
+// 100,000 rows of 4001 columns from four tables: 442 microseconds, 3.6 TB/s written (a lane per target column: 1100; a walk
+// over all sources for every column: 2281); scattered columns 1484 (3198, 4239).
+constexpr int kSlabCols = 1280;
+constexpr int kSlabU = 4;      // values in flight per lane
+constexpr int kSlabWaves = kBlock / kWave;
+
+__global__ __launch_bounds__(kBlock) void materialize_slab_kernel(MatTileArgs a) {
+  __shared__ __align__(16) float rows_lds[kSlabWaves][kSlabCols + 4];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int64_t i = (int64_t)blockIdx.x * kSlabWaves + wave;
+  if (i >= a.r_T) return;                                            // (no barrier below: wavefronts share nothing)
+  auto wave_sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  const int c_lo = (int)blockIdx.y * kSlabCols, cw = min(kSlabCols, a.c_T - c_lo);
+  float* out = a.T + i * a.c_T + c_lo;
+  const int lead = (int)((reinterpret_cast<uintptr_t>(out) / sizeof(float)) & 3);
+  float* row = rows_lds[wave] + lead;
+  if (a.zero)
+    for (int e = lane; e < cw; e += kWave) row[e] = 0.0f;
+  wave_sync();
+  for (int k = 0; k < a.n; ++k) {
+    const MatTileSource& s = a.s[k];
+    const int r = s.idx != nullptr ? s.idx[i] : (i < s.rows ? (int)i : -1);
+    if (r < 0 && a.add != 0) continue;
+    const float* d = s.D + (int64_t)max(r, 0) * s.ck;                // (a source here has rows)
+    // a block of columns: those of its own that fall in the slab; else every column of the slab by its place in the table
+    const bool block = s.c0 >= 0;
+    const int e_lo = block ? max(s.c0 - c_lo, 0) : 0, e_hi = block ? min(s.c0 + s.ck - c_lo, cw) : cw;
+    for (int e0 = e_lo + lane; e0 < e_hi; e0 += kWave * kSlabU) {
+      float v[kSlabU];
+      int j[kSlabU];
+#pragma unroll
+      for (int u = 0; u < kSlabU; ++u) {
+        const int e = min(e0 + u * kWave, e_hi - 1);
+        j[u] = block ? c_lo + e - s.c0 : s.tcol[c_lo + e];
+      }
+#pragma unroll
+      for (int u = 0; u < kSlabU; ++u) v[u] = r >= 0 && j[u] >= 0 ? d[j[u]] : 0.0f;
+#pragma unroll
+      for (int u = 0; u < kSlabU; ++u) {
+        const int e = e0 + u * kWave;
+        if (e < e_hi && j[u] >= 0) row[e] = (a.add != 0 ? row[e] : 0.0f) + v[u];   // 0.0f + x: no -0.0
+      }
+    }
+    wave_sync();                                                     // cells with several feeders receive them in source order
+  }
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  const int head = min((4 - lead) & 3, cw), quads = (cw - head) / 4, tail = head + 4 * quads;
+  if (lane < head) __builtin_nontemporal_store(row[lane], out + lane);
+  for (int e = lane; e < quads; e += kWave)
+    __builtin_nontemporal_store(*reinterpret_cast<const f4*>(row + head + 4 * e), reinterpret_cast<f4*>(out + head + 4 * e));
+  if (tail + lane < cw) __builtin_nontemporal_store(row[tail + lane], out + tail + lane);
+}
+
 // Fast form for schemas whose every aligned group of four target columns is an aligned float4 of one source, or fed by
 // nobody (gslot / gj0 tables, built with the plan): the table is written as one flat stream of float4, element e is
 // column group e % (c_T / 4) of row e / (c_T / 4).  A wavefront stores kFlatU runs of 64 consecutive float4, so every store instruction fills whole
@@ -223,7 +254,14 @@ __global__ __launch_bounds__(kBlock) void materialize_flat_kernel(MatArgs a, int
 
 }  // namespace
 
-bool materialize_tile_supported(const MatTileArgs& a) { return a.c_T <= kMatTileMaxCols; }
+// Above 2048 columns a tile of four rows leaves room for few workgroups, and blocks of columns go through slabs: 100,000
+// rows, tiles / slabs, microseconds: 1501 columns 153 / 168, 2001 210 / 210, 3001 344 / 319, 3501 610 / 377.  Scattered
+// columns, which a slab reads one by one, keep the tiles as long as four rows fit (2001: 270 / 507, 3501: 837 / 1366).
+bool materialize_tile_supported(const MatTileArgs& a) {
+  bool blocks = true;
+  for (int k = 0; k < a.n; ++k) blocks = blocks && a.s[k].c0 >= 0;
+  return a.c_T <= (blocks ? 2048 : kMatTileMaxCols);
+}
 
 hipError_t launch_materialize_tile(MatTileArgs a, hipStream_t st) {
   if (a.r_T <= 0 || a.c_T <= 0) return hipSuccess;
@@ -248,11 +286,10 @@ hipError_t launch_materialize_tile(MatTileArgs a, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_materialize(const MatArgs& a, hipStream_t st) {
+hipError_t launch_materialize_slab(const MatTileArgs& a, hipStream_t st) {
   if (a.r_T <= 0 || a.c_T <= 0) return hipSuccess;
-  int64_t grid = (a.r_T + (kBlock / kWave) - 1) / (kBlock / kWave);
-  if (grid > 8192) grid = 8192;
-  materialize_kernel<<<(int)grid, kBlock, 0, st>>>(a);
+  const dim3 grid((unsigned)((a.r_T + kSlabWaves - 1) / kSlabWaves), (unsigned)((a.c_T + kSlabCols - 1) / kSlabCols));
+  materialize_slab_kernel<<<grid, kBlock, 0, st>>>(a);
   return hipGetLastError();
 }
 

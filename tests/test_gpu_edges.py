@@ -392,3 +392,36 @@ def test_segments_cut_as_far_as_the_chunk_tables_have_room(il, sparse):
     for cx in (1, 4, 12):
         Y = rng.standard_normal((fk.size, cx)).astype(np.float32)
         assert rel(il.ilargi_tmm(plan, dev(Y)).cpu().numpy(), oracle.tmm(tg, Y)) < OP_TOL
+
+
+@pytest.mark.parametrize("r_T,widths,kw", [
+    (1, (2_000, 49), {}),                                         # one column more than block tables' tiles take
+    (203, (1_279, 2, 1_279, 1_500), {"missing": 0.2}),            # blocks across the ends of slabs
+    (203, (1_300, 1_300, 1_300), {"gap": 5}),                     # columns nobody feeds
+    (203, (1_300, 1_300, 1_300), {"overlap": 11, "missing": 0.2}),
+    (203, (1_300, 1_300, 1_300), {"shuffle": True, "missing": 0.2}),
+    (101, (900, 900, 900), {"shuffle": True}),                    # scattered columns in tiles
+    (17, (4_096, 4_096, 4_096), {"missing": 1.0}),                # the widest tables, no row matched
+])
+@pytest.mark.parametrize("shift", [0, 1, 2, 3])
+def test_materialize_wide_tables(il, r_T, widths, kw, shift):
+    test_materialize_any_column_block(il, r_T, widths, kw, shift)
+
+
+def test_materialize_keeps_its_rate_beyond_the_widest_tile(il):
+    """4001 columns from four tables: 1.0 to 1.4 times the time of 3001 a column, 4 times with a walk over all sources."""
+    times = []
+    for widths in ((501, 1_501, 999), (501, 1_501, 1_000, 999)):
+        sch = _blocks(3, 100_000, widths, rows=2_000)
+        plan = il.ilargi_plan_create(il.schema_to_device(sch), sch.r_T, sch.c_T)
+        T, t = torch.empty((sch.r_T, sch.c_T), device="cuda"), []
+        for _ in range(6):
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ev[0].record()
+            il.ilargi_materialize(plan, T)
+            ev[1].record()
+            torch.cuda.synchronize()
+            t.append(ev[0].elapsed_time(ev[1]) / sch.c_T)
+        times.append(sorted(t)[2])
+        del plan, T
+    assert times[1] < 2 * times[0]
