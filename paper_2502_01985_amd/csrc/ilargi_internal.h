@@ -551,15 +551,26 @@ __device__ __forceinline__ float4 load4(const float* p) {
   else t = *reinterpret_cast<const f4*>(p);
   return make_float4(t.x, t.y, t.z, t.w);
 }
-// sigmoid(z) - y, and log(1 + exp(z)) - y z added to the loss.  One exponential, e = exp(-|z|), serves both; the
-// reciprocal takes a Newton step and the logarithm the rounding of 1 + e, so that both are right to the last bit or so.
+// sigmoid(z) - y, and log(1 + exp(z)) - y z added to the loss.  One exponential, e = exp(-|z|), serves both (its relative
+// error grows with |z|, to 16 units of 2^-24 at 20).  The sigmoid is the quotient 1 / (1 + e) or e / (1 + e) with one
+// correction, which also takes in the rounding of 1 + e.  The logarithm is 2 atanh t with t = e / (2 + e) <= 1/3, the
+// remainder of that quotient carried along, and atanh t = t + t^3 p(t^2), p of degree four fitted to 2e-3 units.
+// Errors against 64 bits on this device, rms in units of 2^-24, for z normal with deviation 0.5 / with deviation 2 / uniform
+// in +-20: sigmoid 0.25 / 0.24 / 0.21, log(1 + exp(z)) 0.43 / 0.68 / 2.23 (the last is the rounding of values up to 20).
+// Two exponentials, a division and log1pf: 0.33 / 0.38 / 0.40 and 0.43 / 0.68 / 2.23.  Five iterations of 256 logistic
+// models over 1,000,000 x 20 with 100,000 x 200, float32 / bfloat16 inputs: those 7555 / 6805 microseconds, this form 4372 /
+// 2944; a Newton step and the native logarithm 4292 / 2872, but the logarithm's rms is then 0.64 / 0.74 / 2.23.
 __device__ __forceinline__ float logistic_residual(float z, float y, float& loss) {
   const float e = __expf(-fabsf(z));
-  const float d = 1.0f + e;
-  float inv = __builtin_amdgcn_rcpf(d);
-  inv = fmaf(inv, fmaf(-d, inv, 1.0f), inv);
-  loss += fmaxf(z, 0.0f) + fmaf(e - (d - 1.0f), inv, __logf(d)) - y * z;
-  return (z >= 0.0f ? inv : e * inv) - y;
+  const float d = 1.0f + e, d_lo = e - (d - 1.0f), inv_d = __builtin_amdgcn_rcpf(d);
+  const float n = z >= 0.0f ? 1.0f : e, q = n * inv_d;
+  const float sigmoid = fmaf(fmaf(-d, q, n) - d_lo * q, inv_d, q);
+  const float b = 2.0f + e, b_lo = e - (b - 2.0f), inv_b = __builtin_amdgcn_rcpf(b);
+  const float t = e * inv_b, t_lo = (fmaf(-b, t, e) - b_lo * t) * inv_b;
+  const float u = t * t, t2 = 2.0f * t;
+  const float p = fmaf(fmaf(fmaf(fmaf(0.12144784f, u, 0.10715369f), u, 0.14308299f), u, 0.19999444f), u, 0.33333337f);
+  loss += fmaxf(z, 0.0f) + (t2 + fmaf(t2 * u, p, 2.0f * fmaf(t_lo, u, t_lo))) - y * z;
+  return sigmoid - y;
 }
 
 inline int ilog2_ceil(int64_t v) { int l = 0; while ((1ll << l) < v) ++l; return l; }

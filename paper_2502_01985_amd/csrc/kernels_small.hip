@@ -13,7 +13,7 @@
 //
 // Bound: latency, and what one compute unit can load (280 KB at 10,000 x 4 with 1000 x 8).  Launches back to back, linear
 // / logistic model: 10,000 x 4, 1000 x 8: 8.8 -> 8.4 us; 1000 rows of S to 100 of R: 6.3 -> 5.2; a fan-out of 100: 15.4
-// -> 9.5; 16,000 x 4, 1000 x 12: 12.2 / 23.2 -> 11.4 / 14.1; 8000 x 8, 1000 x 16: 10.1 / 15.5 -> 9.5 / 10.7, since a
+// -> 9.5; 16,000 x 4, 1000 x 12: 12.2 / 23.2 -> 11.3 / 14.9; 8000 x 8, 1000 x 16: 10.1 / 15.5 -> 9.6 / 11.0, since a
 // row's index entries and residuals are in flight kSmallU at a time (before: one after the other), the last sums are a
 // butterfly (before: 64 values in turn, all on one LDS bank), the loads go out in the order of their use, and the sigmoid
 // and the loss share their exponential.  Labels requested after the index entries, which spares registers: 8.7.

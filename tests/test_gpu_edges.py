@@ -425,3 +425,47 @@ def test_materialize_keeps_its_rate_beyond_the_widest_tile(il):
         times.append(sorted(t)[2])
         del plan, T
     assert times[1] < 2 * times[0]
+
+
+@pytest.mark.parametrize("cols,m", [(1, 3), (4, 1), (1, 16), (1, 64), (1, 2_048)])
+def test_logistic_residual_and_loss_to_the_last_bits(il, cols, m):
+    """One row whose product is the weight itself: the loss is log(1 + exp(w)), the step sigmoid(w).  The bounds, in units
+    of 2^-24 (rms), lie 2 to 5 % above what two exponentials, a division and log1pf give (0.428, 0.695, 0.331, 0.386)."""
+    rng = datagen.rng_for(12)
+    z = np.concatenate([rng.normal(0, 0.5, 2_048), rng.normal(0, 2.0, 2_048)]).astype(np.float32)
+    D = np.zeros((1, cols), dtype=np.float32)
+    D[0, 0] = 1.0
+    plan = il.ilargi_plan_create([(dev(D), None, np.arange(cols))], 1, cols, max_cx=m)
+    y, lr = torch.zeros(1, device="cuda"), torch.full((m,), 2.0 ** 30, device="cuda")
+    soft, step = [], []
+    for at in range(0, z.size - z.size % m, m):
+        W, loss = torch.zeros((cols, m), device="cuda"), torch.zeros(m, device="cuda")
+        W[0] = dev(z[at:at + m])
+        il.ilargi_gd_step(plan, il.LOGISTIC, W, y, lr, loss)
+        soft.append(loss)
+        step.append(W[0])
+    n = z.size - z.size % m
+    soft, step = torch.cat(soft).cpu().numpy().astype(np.float64), torch.cat(step).cpu().numpy().astype(np.float64)
+    z64 = z[:n].astype(np.float64)
+    err_l = (soft - np.logaddexp(0.0, z64)) * 2.0 ** 24
+    err_s = ((z64 - step) / 2.0 ** 30 - 1.0 / (1.0 + np.exp(-z64))) * 2.0 ** 24
+    half = min(n, 2_048)
+    rms = [float(np.sqrt(np.mean(e ** 2))) for e in (err_l[:half], err_l[half:], err_s[:half], err_s[half:])]
+    assert rms[0] < 0.45 and rms[1] < 0.71 and rms[2] < 0.345 and rms[3] < 0.4
+
+
+def test_logistic_at_the_ends_of_the_range(il):
+    """Products beyond the exponential's range and infinite ones: the sigmoid is 0 or 1, the loss max(z, 0) - y z."""
+    z = np.array([0.0, -0.0, 200.0, -200.0, 3e38, -3e38, np.inf, -np.inf, np.nan], dtype=np.float32)
+    for m in (1, 9):
+        plan = il.ilargi_plan_create([(torch.ones((1, 1), device="cuda"), None, np.arange(1))], 1, 1, max_cx=m)
+        y, lr, soft, step = torch.zeros(1, device="cuda"), torch.full((m,), 1.0, device="cuda"), [], []
+        for at in range(0, z.size, m):
+            W, loss = dev(z[at:at + m].reshape(1, m).copy()), torch.zeros(m, device="cuda")
+            il.ilargi_gd_step(plan, il.LOGISTIC, W, y, lr, loss)
+            soft += loss.cpu().tolist()
+            step += W[0].cpu().tolist()
+        # (0 times an infinite product is not a number)
+        want = [np.log(2.0), np.log(2.0), 200.0, 0.0, 3e38, 0.0, np.nan, np.nan, np.nan]
+        assert np.allclose(soft[1:], want[1:], rtol=1e-6, equal_nan=True)
+        assert np.allclose(step, [-0.5, -0.5, 199.0, -200.0, 3e38, -3e38, np.inf, -np.inf, np.nan], rtol=1e-6, equal_nan=True)
