@@ -1120,10 +1120,22 @@ ilargi_status_t gd_star_step(ilargi_plan* pl, int mode, float* W, int m, const f
 // One Lloyd iteration in one pass over the identity source (kernels_tile.hip): the assignments come out of the assembly
 // of T C, with the identity source's cluster sums; a joined source's sums are its table times the cluster counts of its
 // rows.  G (c_T x k) receives the per-cluster sums, cnt the cluster sizes.
+// Widest identity source that the one pass serves faster than the separate ones.  Its operand and cluster sums grow with
+// columns times centroids in LDS, until three workgroups, then two, share a compute unit; the separate passes take operands
+// of 5 to 7 columns in two rounds.  Time of an iteration over 20,000 to 1,000,000 rows, one pass over separate passes:
+//   1 centroid     3 columns 1.01,           8 to 200 1.00 to 1.30
+//   2              to 16 0.89 to 0.98,       20 and 50 0.93 to 1.11,  100 and 200 1.14 and 1.19
+//   3, 4           to 64 0.75 to 1.07,       100 and 200 1.01 to 1.08
+//   5 to 7         to 200 0.48 to 0.67
+//   8 to 12        to 80 0.35 to 1.04,       100 1.00 to 1.08,        200 1.06 to 1.81
+//   13 to 16       to 32 0.38 to 1.05,       50 0.80 to 1.10,         64 1.00 to 1.40,  200 2.2 to 2.4
+int kmeans_tile_columns(int k) { return k < 2 ? 0 : k == 2 ? 16 : k <= 4 ? 64 : k <= 7 ? 256 : k <= 12 ? 96 : 48; }
+
 bool kmeans_fused_ok(const ilargi_plan* pl, int64_t k) {
   if (pl->any_sparse || pl->fused < 0 || k > kKmeansTileK) return false;
   const SourcePlan& f = pl->src[pl->fused];
   if (!kmeans_tile_supported((int)f.cols, (int)k) || 2 * kColredBlocks * f.cols * k > pl->lay.gpartial_floats) return false;
+  if (f.cols > kmeans_tile_columns((int)k)) return false;
   for (int q = 0; q < pl->n; ++q) {
     const SourcePlan& p = pl->src[q];
     if (p.empty || q == pl->fused) continue;

@@ -469,3 +469,29 @@ def test_logistic_at_the_ends_of_the_range(il):
         want = [np.log(2.0), np.log(2.0), 200.0, 0.0, 3e38, 0.0, np.nan, np.nan, np.nan]
         assert np.allclose(soft[1:], want[1:], rtol=1e-6, equal_nan=True)
         assert np.allclose(step, [-0.5, -0.5, 199.0, -200.0, 3e38, -3e38, np.inf, -np.inf, np.nan], rtol=1e-6, equal_nan=True)
+
+
+@pytest.mark.parametrize("k,cols", [(2, 16), (2, 17), (4, 64), (4, 65), (5, 256), (7, 255), (8, 96), (12, 96), (12, 97), (13, 48),
+                                    (16, 48), (16, 49)])
+def test_kmeans_on_both_sides_of_the_widest_table(il, k, cols):
+    test_kmeans_in_one_pass_over_the_entity_table(il, 5_003, (cols, 12), 301, 0.1, k)
+
+
+def test_kmeans_over_a_wide_entity_table_takes_separate_passes(il):
+    """16 centroids: 200 columns of the entity table take 4.3 times as long as 20, 9.9 times through one pass."""
+    times = []
+    for cols in (20, 200):
+        sch = _blocks(5, 500_000, (cols, 40), rows=50_000)
+        plan = il.ilargi_plan_create(il.schema_to_device(sch), sch.r_T, sch.c_T, max_cx=16)
+        C, t = dev(datagen.rng_for(1).standard_normal((sch.c_T, 16)).astype(np.float32)), []
+        for _ in range(9):
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ev[0].record()
+            for _ in range(3):
+                il.ilargi_kmeans_step(plan, C)
+            ev[1].record()
+            torch.cuda.synchronize()
+            t.append(ev[0].elapsed_time(ev[1]))
+        times.append(sorted(t)[4])
+        del plan
+    assert times[1] < 6.5 * times[0]
