@@ -840,7 +840,7 @@ ilargi_status_t run_tred(ilargi_plan* pl, TredArgs& g, float* block, const char*
   if (elems <= 0) return ILARGI_OK;
   if (part == nullptr) { part = pl->at<float>(pl->lay.o_gpartial); part_floats = pl->lay.gpartial_floats; }
   if (!bf16 && gram_narrow_supported(g) && elems <= part_floats) {
-    // diagonal Gram block of a table with 36..64 columns: streaming kernel over interleaved column tiles
+    // diagonal Gram block of a table with at most 64 columns: streaming kernel over interleaved column tiles
     int nch = 0;
     {
       TraceScope ts(pl, tag, tag_k, st);
@@ -2389,7 +2389,7 @@ ilargi_status_t ilargi_crossprod(ilargi_plan_t* plan, float* out, void* stream) 
               HIP_TRY(launch_fill_zero(block, (int64_t)g.ca * g.cb, st));
               continue;
             }
-            if (gram_pairs_supported(g) && (int64_t)g.ca * g.cb <= part_main_floats) {
+            if (gram_pairs_supported(g) && gram_pairs_pay(g, plan->r_T) && (int64_t)g.ca * g.cb <= part_main_floats) {
               int nch = 0;
               {
                 TraceScope ts(plan, "gram", k * n + l, st);

@@ -478,6 +478,7 @@ hipError_t launch_gram_star(const GramStarArgs& a, int vec, int max_grid, hipStr
 // diagonal block of a table with 36..64 columns, and the block of two tables over a list of row pairs.
 bool gram_narrow_supported(const TredArgs& a);
 bool gram_pairs_supported(const TredArgs& a);
+bool gram_pairs_pay(const TredArgs& a, int64_t r_T);
 hipError_t launch_gram_narrow(TredArgs& a, float* partial, int64_t partial_floats, hipStream_t st, int* nch_out);
 hipError_t launch_pair_list(const int32_t* idx_a, int64_t rows_a, const int32_t* idx_b, int64_t rows_b, int64_t r_T,
                             int32_t* scan, int32_t* totals, int32_t* list_a, int32_t* list_b, hipStream_t st);

@@ -38,7 +38,7 @@ __device__ __forceinline__ v4f shift_back(v4f v, int d) {
 // PAIRS: rows through the index vectors ia / ib (both valid for every entry); else row t of A with weight w_t.
 // RAGGED: a table's rows are not whole aligned float4s.  The loads then start on any float, and the last one of a row is
 // moved back to end with it.  2,000,000 x 63 twice with 16 shared columns: 378 microseconds for the whole Gram matrix,
-// 1192 with the tiles staged element by element (37 columns: 343 and 703, 22: 333 and 349).
+// 1192 with the tiles staged element by element (37 columns: 343 and 703).
 template <bool PAIRS, bool WEIGHTED, bool RAGGED>
 __global__ __launch_bounds__(kBlock) void gram_narrow_kernel(TredArgs a) {
   __shared__ float red[64 * 64];
@@ -216,17 +216,31 @@ bool whole_rows(const float* p, int c, int ld, int col0) {
 
 }  // namespace
 
-// Diagonal block: A == B without index vectors, 33..64 columns; from 17 on where the rows are not whole float4s (the
-// kernel for those costs more than the products of empty columns do here).
+// Diagonal block: A == B without index vectors, 33..64 columns.  Two column tiles or fewer are left to the general
+// kernel, whose products of empty columns cost less than the ragged loads here (the whole Gram matrix of two stacked tables
+// with 22 columns and 10 % of the rows in both, 2,000,000 rows: 237 microseconds with the general kernel, 300 with this one;
+// 320,000: 66 and 73; 100,000: 46 and 46); with fewer rows this one starts faster (20,000: 32 and 29).
+constexpr int64_t kGnFewRows = 64 * 1024;
 bool gram_narrow_supported(const TredArgs& a) {
+  const bool few = a.n_rows <= kGnFewRows && !whole_rows(a.A, a.ca, a.lda, 0);
   return a.upper_only && a.A == a.B && a.ia == nullptr && a.ib == nullptr && a.ca == a.cb && a.lda == a.ldb && a.bcol0 == 0 &&
-         a.ca > (whole_rows(a.A, a.ca, a.lda, 0) ? 32 : 16) && a.ca <= 64 && a.n_rows >= 1 && a.a_rows >= a.n_rows;
+         a.ca > (few ? 16 : 32) && a.ca <= 64 && a.n_rows >= 1 && a.a_rows >= a.n_rows;
 }
 
 // Pair block: n_rows pairs (ia[p], ib[p]), every index valid; both tables with 4..64 columns.
 bool gram_pairs_supported(const TredArgs& a) {
   return !a.upper_only && a.ia != nullptr && a.ib != nullptr && a.wptr == nullptr && a.n_rows >= 1 &&
          a.ca >= 4 && a.ca <= 64 && a.cb >= 4 && a.cb <= 64;
+}
+
+// Whether the block goes through the pairs, or by the general kernel's walk over all r_T target rows.  Tables in whole
+// aligned float4s keep the pairs; of the others narrow ones lose by them when they skip little.  Two tables of 2,000,000
+// rows, share of the target rows in the list, pairs / walk in microseconds for the whole matrix: 7 columns 18 % 182 / 205,
+// 31 % 211 / 198, 67 % 267 / 190; 22 columns 43 % 324 / 334, 67 % 358 / 327; 33 columns 43 % 396 / 557, 100 % 467 / 493.
+bool gram_pairs_pay(const TredArgs& a, int64_t r_T) {
+  if (whole_rows(a.A, a.ca, a.lda, 0) && whole_rows(a.B, a.cb, a.ldb, a.bcol0)) return true;
+  const int widest = std::max(a.ca, a.cb);
+  return widest > 32 || (widest > 16 ? 2 * a.n_rows <= r_T : 5 * a.n_rows <= r_T);
 }
 
 // At most four workgroups per compute unit and as many as partial_floats holds; *nch_out partial blocks of ca x cb
