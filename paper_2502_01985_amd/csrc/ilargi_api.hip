@@ -645,8 +645,8 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
   };
   // Every dense source with float4 rows of at most 256 columns takes part in a merged launch: an identity source
   // (and every source of colSum, whose operand is the fan-out vector) as a plain column reduce, a joined source in
-  // join-order form (segment sums in LDS, Z_k never written).  The other sources go through segment sum and
-  // column reduce as separate launches.
+  // join-order form (segment sums in LDS, Z_k never written).  The other sources go through segment sums, one launch for
+  // several of them, and column reduces, several to a launch as well where their rows go through tiles.
   TmmParts parts;
   memset(&parts, 0, sizeof(parts));
   int parts_first_k = -1, parts_joins = 0;
@@ -701,6 +701,7 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
     SparsePart sparse[kSparseMulti];
     int tk[kTileParts], nt = 0, ns = 0, first_sparse = -1;
     auto flush_tiles = [&]() -> ilargi_status_t {
+      if (nt == 1 && !colred_tile_pays(tiles[0])) nt = 0;                 // left to the launches below
       if (nt == 0) return ILARGI_OK;
       int nblocks[kTileParts];
       TraceScope ts(pl, "colred", tk[0], st);

@@ -411,6 +411,7 @@ hipError_t launch_prod_tile(const LmmArgs* a, int n, hipStream_t st);
 bool asm_tile_supported(const LmmArgs& a, int vec, bool fuseg);
 hipError_t launch_asm_tile(const LmmArgs& a, int mode, hipStream_t st, int* grid_out);
 bool colred_tile_supported(const ColredArgs& c);
+bool colred_tile_pays(const ColredArgs& c);
 hipError_t launch_colred_tile(const ColredArgs* c, int n, int* nblocks, hipStream_t st);
 int lmm_grid(int64_t r_out, int logL, bool fuseg);
 bool lmm_can_fuse_gradient(int ck, int vec, int logL);

@@ -703,6 +703,22 @@ bool colred_tile_supported(const ColredArgs& c) {
   return c.ck >= 1 && c.ck <= kBlock && c.ncols >= 1 && c.ncols <= kNarrowCT && c.rows > 0;
 }
 
+// Whether a table that shares its launch with no other goes through tiles (several always do: a launch costs more than any
+// of the differences below).  Time of the tiles over that of the kernel that reads rows in place:
+//   fewer than 65,536 rows                      20,000: 0.93 to 1.40
+//   rows of float2, 300,000 / 3,000,000         one column: 10 columns of the table 1.12 / 1.06, 30 1.10 / 1.05, 98 0.92 / 0.92
+//                                               two: 10 1.13 / 0.97, 46 1.01 / 0.81;  three: 10 1.07 / 0.89, 30 1.02 / 0.84
+//                                               four: 10 0.91 / 0.55, 98 0.71 / 0.69
+//   rows on any float, 300,000 / 3,000,000      one column: 3 1.12 / 1.32, 7 1.04 / 0.96, 13 1.01 / 0.67, 33 0.71 / 0.43
+//                                               four: 3 1.01 / 0.87, 13 0.76 / 0.37, 199 0.64
+bool colred_tile_pays(const ColredArgs& c) {
+  if (c.rows < 65536) return false;
+  const bool many = c.rows >= (1 << 20);
+  if (c.ncols == 4) return true;
+  if (c.vec == 1) return c.ck >= 12 || (many && c.ck >= 6);
+  return c.ck * c.ncols >= 64 || (many && c.ncols >= 2 && c.ck >= 6);
+}
+
 // The column reduces of n <= kTileParts sources in one launch; nblocks[q] receives the number of partial blocks that
 // source q leaves (at most kColredBlocks).
 hipError_t launch_colred_tile(const ColredArgs* c, int n, int* nblocks, hipStream_t st) {
@@ -724,9 +740,15 @@ hipError_t launch_colred_tile(const ColredArgs* c, int n, int* nblocks, hipStrea
     nblocks[q] = (int)std::max<int64_t>(1, total > kColredBlocks ? tiles[q] * kColredBlocks / total : tiles[q]);
     m.first[q + 1] = m.first[q] + nblocks[q];
   }
-  const int ct = c[0].ncols <= 1 ? 1 : (c[0].ncols <= 2 ? 2 : 4);
+  // (one operand column takes the kernel for two, as a kernel of its own measures slower: 3,000,000 x 50 149 microseconds
+  // and 112)
+  const int ct = c[0].ncols <= 2 ? 2 : 4;
   const size_t lds = sizeof(float) * (kTileFloats + (size_t)kBlock * ct);
-  ILARGI_TILE(colred_tile_kernel, ct, all_aligned(m), m.first[n], lds, st, m);
+  const bool al = all_aligned(m);
+  if (ct == 2 && al) colred_tile_kernel<2, true><<<m.first[n], kBlock, lds, st>>>(m);
+  else if (ct == 2) colred_tile_kernel<2, false><<<m.first[n], kBlock, lds, st>>>(m);
+  else if (al) colred_tile_kernel<4, true><<<m.first[n], kBlock, lds, st>>>(m);
+  else colred_tile_kernel<4, false><<<m.first[n], kBlock, lds, st>>>(m);
   return hipGetLastError();
 }
 

@@ -523,3 +523,33 @@ def test_gram_of_narrow_unaligned_tables_leaves_the_streaming_kernels_where_they
                                                (4_001, 31, 0.66), (4_001, 31, 0.67), (70_001, 33, 1.0)])
 def test_gram_on_both_sides_of_the_rules_for_narrow_unaligned_tables(il, rows, cols, overlap):
     test_gram_of_stacked_tables_with_rows_on_any_float(il, rows, cols, 3, overlap)
+
+
+@pytest.mark.parametrize("rows,cols", [(65_535, 7), (65_535, 130), (65_536, 5), (65_536, 11), (65_536, 13), (65_536, 22), (65_537, 62),
+                                       (65_537, 66), (1_048_576, 6), (1_048_577, 5)])
+def test_column_reduce_on_both_sides_of_the_rule_for_tiles(il, rows, cols):
+    sch = _blocks(rows, rows, (cols,))
+    tg = oracle.Target(sch)
+    plan = il.ilargi_plan_create(il.schema_to_device(sch), rows, cols, max_cx=4)
+    for cx in (1, 2, 3, 4):
+        Y = datagen.rng_for(cx).standard_normal((rows, cx)).astype(np.float32)
+        assert rel(il.ilargi_tmm(plan, dev(Y)).cpu().numpy(), oracle.tmm(tg, Y)) < OP_TOL
+    assert rel(il.ilargi_col_sum(plan).cpu().numpy().reshape(-1), tg.T32.astype(np.float64).sum(0)) < OP_TOL
+
+
+def test_column_reduce_of_one_column_costs_no_more_than_of_two(il):
+    """3,000,000 x 50: 1.0 to 1.07 times the time; 1.33 times in tiles with a single sum per thread."""
+    D = torch.randn((3_000_000, 50), device="cuda")
+    plan, times = il.ilargi_plan_create([(D, None, np.arange(50))], 3_000_000, 50, max_cx=2), []
+    for cx in (1, 2):
+        Y, out, t = torch.randn((3_000_000, cx), device="cuda"), torch.empty((50, cx), device="cuda"), []
+        for _ in range(9):
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ev[0].record()
+            for _ in range(4):
+                il.ilargi_tmm(plan, Y, out=out)
+            ev[1].record()
+            torch.cuda.synchronize()
+            t.append(ev[0].elapsed_time(ev[1]))
+        times.append(sorted(t)[4])
+    assert times[0] < 1.18 * times[1]
