@@ -634,16 +634,29 @@ hipError_t launch_prod_tile(const LmmArgs* a, int n, hipStream_t st) {
   return hipGetLastError();
 }
 
-// One operand column over rows of float4 (or float2) that fill their lanes is left to the kernel that reads such rows in
-// place: 333,333 x 100, one logistic model, 71 microseconds an iteration in place and 76 through tiles (200 columns: 116
-// and 126; 64: 50 and 54); where a fifth of the lanes or more idles the tiles win (68 columns: 66 and 56), and with
-// several operand columns always (100 columns, three models: 117 and 101; 40 columns: 71 and 53).
+// One operand column over rows of float4 or float2 is where the kernel that reads such rows in place, 2^k lanes to a row,
+// keeps up: the tiles win as far as its lanes idle and the table is long enough to fill the chip with them.  Time through
+// tiles over time in place at 300,000 / 2,000,000 rows joined with 8 columns:
+//   an iteration, rows of float4     36 and 40 columns (9 or 10 of 16 lanes at work) 1.06 / 0.93, 44 to 60 1.13 / 1.10,
+//                                    68 to 80 (17 to 20 of 32) 1.08 / 0.95, 84 to 92 (tiles of 32 rows) 1.28 / 1.25
+//                 rows of float2     18 (9 of 16) 0.97 / 0.79, 22 to 30 1.03 / 0.91 (700,000: 1.04 to 1.08), 34 to 42
+//                                    (17 to 21 of 32) 0.97 / 0.76, 46 1.02 / 0.88;  18 columns of 30,000 rows 1.10
+//   a product, rows of float4        68 to 80 0.91 / 0.81, 84 to 92 1.08 / 0.98;  rows of float2  34 to 46 0.82 / 0.61
+// With several operand columns the tiles win everywhere (300,000 rows, two models: 36 columns 0.80, 46 0.82, 52 0.86).
 bool asm_tile_supported(const LmmArgs& a, int vec, bool fuseg) {
   if (a.ncols < 1 || a.ncols > kNarrowCT || a.r_out <= 0) return false;
   if (a.D == nullptr) return !fuseg;
   if (a.ck < 1 || a.ck > (fuseg ? kBlock : kTileMaxCols)) return false;
   const int nvec = a.ck / vec;
-  if (vec >= 2 && a.ncols == 1 && nvec >= 16 && (nvec > kWave || 4 * nvec >= 3 * (1 << ilog2_ceil(nvec)))) return false;
+  if (vec >= 2 && a.ncols == 1 && nvec >= 9) {
+    const int lanes = 1 << ilog2_ceil(nvec);
+    const bool million = a.r_out >= (1 << 20);
+    if (nvec > kWave || (nvec >= 16 && 4 * nvec >= 3 * lanes)) return false;
+    if (fuseg && vec == 4) return million && 8 * nvec <= 5 * lanes && a.ck <= 80;
+    if (fuseg && nvec < 16) return million || (8 * nvec <= 5 * lanes && a.r_out >= 256 * 1024);
+    if (fuseg) return a.r_out >= (16 * nvec <= 11 * lanes ? 256 * 1024 : 512 * 1024);
+    if (vec == 4 && a.ck > 80 && !million) return false;
+  }
   return vec != 4 || a.ck <= 256;
 }
 

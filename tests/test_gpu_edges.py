@@ -553,3 +553,45 @@ def test_column_reduce_of_one_column_costs_no_more_than_of_two(il):
             t.append(ev[0].elapsed_time(ev[1]))
         times.append(sorted(t)[4])
     assert times[0] < 1.18 * times[1]
+
+
+@pytest.mark.parametrize("rows,cols", [(262_143, 18), (262_144, 18), (524_287, 46), (524_288, 46), (1_048_575, 30), (1_048_576, 30), (1_048_575, 40),
+                                       (1_048_576, 40), (1_048_577, 80), (1_048_577, 84), (1_048_576, 44)])
+def test_assembly_on_both_sides_of_the_rule_for_tiles(il, rows, cols):
+    """One column and one model: products exact on integers, the first step against the definition in 64 bits."""
+    rng = datagen.rng_for(cols)
+    S = rng.integers(-4, 5, (rows, cols)).astype(np.float32)
+    fk = rng.integers(0, 1_000, rows).astype(np.int32)
+    R = rng.integers(-4, 5, (1_000, 8)).astype(np.float32)
+    plan = il.ilargi_plan_create([(dev(S), None, np.arange(cols)), (dev(R), dev(fk), np.arange(cols, cols + 8))], rows, cols + 8)
+    X = rng.integers(-3, 4, (cols + 8, 1)).astype(np.float32)
+    z = S @ X[:cols] + (R @ X[cols:])[fk]
+    assert np.array_equal(il.ilargi_lmm(plan, dev(X)).cpu().numpy(), z)
+    y = rng.integers(0, 2, rows).astype(np.float32)
+    W, loss = dev(X.copy()), torch.zeros(1, device="cuda")
+    il.ilargi_gd_step(plan, il.LINEAR, W, dev(y), torch.full((1,), 0.5, device="cuda"), loss)
+    e = z[:, 0].astype(np.float64) - y
+    G = np.concatenate([S.astype(np.float64).T @ e, R.astype(np.float64).T @ np.bincount(fk, e, 1_000)])
+    assert rel(W.cpu().numpy()[:, 0], X[:, 0].astype(np.float64) - 0.5 * G / rows) < OP_TOL
+    assert np.isclose(loss.item(), (e * e).sum() / (2 * rows), rtol=1e-5)
+
+
+def test_iteration_over_rows_that_tiles_hold_badly(il):
+    """300,000 rows, one linear model: 88 columns take 0.98 times the time of 96, 1.25 times through tiles."""
+    rng, times = datagen.rng_for(1), []
+    fk = rng.integers(0, 15_000, 300_000).astype(np.int32)
+    y, lr, loss = torch.randn(300_000, device="cuda"), torch.full((1,), 0.01, device="cuda"), torch.zeros(1, device="cuda")
+    for cols in (88, 96):
+        plan = il.ilargi_plan_create([(torch.randn((300_000, cols), device="cuda"), None, np.arange(cols)),
+                                      (torch.randn((15_000, 8), device="cuda"), dev(fk), np.arange(cols, cols + 8))], 300_000, cols + 8)
+        W, t = torch.zeros((cols + 8, 1), device="cuda"), []
+        for _ in range(9):
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ev[0].record()
+            for _ in range(10):
+                il.ilargi_gd_step(plan, il.LINEAR, W, y, lr, loss)
+            ev[1].record()
+            torch.cuda.synchronize()
+            t.append(ev[0].elapsed_time(ev[1]))
+        times.append(sorted(t)[4])
+    assert times[0] < 1.12 * times[1]
