@@ -595,3 +595,107 @@ def test_iteration_over_rows_that_tiles_hold_badly(il):
             t.append(ev[0].elapsed_time(ev[1]))
         times.append(sorted(t)[4])
     assert times[0] < 1.12 * times[1]
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("r_T,widths,rows", [
+    (400_003, (7, 33), 200_001),              # products of 3,126 tiles, an assembly of 1,563
+    (700_003, (63, 9), 50_001),               # an assembly of 10,938 tiles, eleven to a workgroup
+])
+def test_tiles_that_walk_several_times(il, r_T, widths, rows, shift):
+    """Workgroups that take tile after tile, with row numbers requested two tiles ahead: products and sums exact on small
+    integers, tables that start on any float."""
+    rng = datagen.rng_for(r_T)
+    S, R = rng.integers(-3, 4, (r_T, widths[0])).astype(np.float32), rng.integers(-3, 4, (rows, widths[1])).astype(np.float32)
+    fk = rng.integers(-1, rows, r_T).astype(np.int32)
+    c_T = sum(widths)
+
+    def at(a):
+        flat = torch.full((a.size + 4,), float("nan"), device="cuda")
+        flat[shift:shift + a.size] = dev(a).reshape(-1)
+        return flat[shift:shift + a.size].view(a.shape)
+
+    plan = il.ilargi_plan_create([(at(S), None, np.arange(widths[0])), (at(R), dev(fk), np.arange(widths[0], c_T))], r_T, c_T, max_cx=16)
+    T = np.concatenate([S, np.where((fk >= 0)[:, None], R[fk], 0.0)], axis=1).astype(np.float64)
+    for cx in (1, 3, 4):
+        X, Y = rng.integers(-3, 4, (c_T, cx)).astype(np.float32), rng.integers(-2, 3, (r_T, cx)).astype(np.float32)
+        assert np.array_equal(il.ilargi_lmm(plan, dev(X)).cpu().numpy(), (T @ X).astype(np.float32))
+        assert np.array_equal(il.ilargi_tmm(plan, dev(Y)).cpu().numpy(), (T.T @ Y).astype(np.float32))     # sums below 2^24
+        W, loss = dev(X.copy()), torch.zeros(cx, device="cuda")
+        y = rng.integers(0, 2, r_T).astype(np.float32)
+        il.ilargi_gd_step(plan, il.LINEAR, W, dev(y), torch.full((cx,), 0.25, device="cuda"), loss)
+        e = T @ X - y[:, None]
+        assert rel(W.cpu().numpy(), X - 0.25 * (T.T @ e) / r_T) < OP_TOL
+        assert np.allclose(loss.cpu().numpy(), (e * e).sum(0) / (2 * r_T), rtol=1e-5)
+    for k in (3, 5, 12, 16):
+        if widths[0] > 48 and k > 12:
+            continue
+        C = rng.integers(-2, 3, (c_T, k)).astype(np.float32)
+        Cd, assign = dev(C.copy()), torch.zeros(r_T, device="cuda", dtype=torch.int32)
+        il.ilargi_kmeans_step(plan, Cd, assign)
+        D = (C.astype(np.float64) ** 2).sum(0) - 2 * (T @ C)          # whole numbers: ties go to the first centroid
+        want = D.argmin(1)
+        assert np.array_equal(assign.cpu().numpy(), want)
+        sums = np.stack([T[want == j].sum(0) if np.any(want == j) else C[:, j] for j in range(k)], axis=1)
+        n = np.maximum(np.bincount(want, minlength=k), 1)
+        assert rel(Cd.cpu().numpy(), sums / n) < 1e-6
+
+
+def test_entity_table_read_past_the_caches(il):
+    """Above 32 Mi floats of odd rows the assembly reads the table past the caches: products exact on small integers."""
+    r_T, c = 1_600_003, 21
+    rng = datagen.rng_for(8)
+    S = torch.randint(-3, 4, (r_T, c), device="cuda", generator=torch.Generator(device="cuda").manual_seed(1)).float()
+    R, fk = rng.integers(-3, 4, (1_000, 5)).astype(np.float32), rng.integers(0, 1_000, r_T).astype(np.int32)
+    plan = il.ilargi_plan_create([(S, None, np.arange(c)), (dev(R), dev(fk), np.arange(c, c + 5))], r_T, c + 5, max_cx=3)
+    for cx in (1, 3):
+        X = rng.integers(-3, 4, (c + 5, cx)).astype(np.float32)
+        z = S.double() @ dev(X[:c]).double() + (dev(R).double() @ dev(X[c:]).double())[dev(fk).long()]
+        assert torch.equal(il.ilargi_lmm(plan, dev(X)).double(), z)
+        y = torch.randint(0, 2, (r_T,), device="cuda").float()
+        W, loss = dev(X.copy()), torch.zeros(cx, device="cuda")
+        il.ilargi_gd_step(plan, il.LINEAR, W, y, torch.full((cx,), 0.25, device="cuda"), loss)
+        e = z - y.double()[:, None]
+        G = torch.cat([S.double().t() @ e, dev(R).double().t() @ torch.zeros((1_000, cx), device="cuda", dtype=torch.float64).index_add_(0, dev(fk).long(), e)])
+        assert rel(W.cpu().numpy(), X - 0.25 * G.cpu().numpy() / r_T) < OP_TOL
+        assert np.allclose(loss.cpu().numpy(), ((e * e).sum(0) / (2 * r_T)).cpu().numpy(), rtol=1e-5)
+
+
+@pytest.mark.parametrize("sparse", [False, True])
+@pytest.mark.parametrize("widths", [(13, 33), (12, 32), (20, 75, 9)])
+def test_values_that_are_not_finite_stay_in_their_rows_and_columns(il, widths, sparse):
+    """An infinity and a NaN in the tables: rows of a product and columns of a transposed product without them are what they
+    are without them, and the others are not finite; the join holds them as they are."""
+    r_T, rows = 3_001, 700
+    sch = _blocks(21, r_T, widths, rows=rows, missing=0.1)
+    sch.sources[0].D[17, 3], sch.sources[0].D[2_999, 5] = np.inf, np.nan
+    sch.sources[1].D[5, 2] = -np.inf
+    tg = oracle.Target(sch)
+    T = tg.T32.astype(np.float64)
+    bad_row, bad_col = ~np.isfinite(T).all(1), ~np.isfinite(T).all(0)
+    assert bad_row.sum() > 2 and bad_col.sum() == 3
+    T0 = np.where(np.isfinite(T), T, 0.0)
+    plan = il.ilargi_plan_create(il.schema_to_device(sch, sparse=sparse), r_T, sch.c_T, max_cx=16)
+    rng = datagen.rng_for(2)
+    for cx in (1, 3, 8, 16):
+        if sparse and cx > 4:
+            continue
+        X, Y = rng.standard_normal((sch.c_T, cx)).astype(np.float32), rng.standard_normal((r_T, cx)).astype(np.float32)
+        got = il.ilargi_lmm(plan, dev(X)).cpu().numpy()
+        assert not np.isfinite(got[bad_row]).any() and rel(got[~bad_row], (T0 @ X)[~bad_row]) < OP_TOL
+        got = il.ilargi_tmm(plan, dev(Y)).cpu().numpy()
+        assert not np.isfinite(got[bad_col]).any() and rel(got[~bad_col], (T0.T @ Y)[~bad_col]) < OP_TOL
+    got = il.ilargi_materialize(plan).cpu().numpy()
+    assert np.array_equal(got, tg.T32, equal_nan=True)
+    if not sparse:
+        got = il.ilargi_crossprod(plan).cpu().numpy()
+        ok = ~bad_col
+        assert rel(got[np.ix_(ok, ok)], (T0.T @ T0)[np.ix_(ok, ok)]) < OP_TOL
+        assert not np.isfinite(np.diag(got)[bad_col]).any()      # (a row that joins nothing adds nothing to cross cells)
+        C = rng.standard_normal((sch.c_T, 5)).astype(np.float32)
+        Cd, assign = dev(C.copy()), torch.zeros(r_T, device="cuda", dtype=torch.int32)
+        il.ilargi_kmeans_step(plan, Cd, assign)
+        a = assign.cpu().numpy()
+        for j in range(5):                       # centroids in the other columns: means of the rows that were assigned
+            if np.any(a == j):
+                assert rel(Cd.cpu().numpy()[ok, j], T0[a == j].mean(0)[ok]) < 1e-4
