@@ -1331,9 +1331,9 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     HIP_TRY(hipStreamSynchronize(st));
     p.nnz = rowptr[(size_t)p.rows];
     const int64_t avg = p.rows > 0 ? (p.nnz + p.rows - 1) / p.rows : 1;
-    // lanes per segment of the narrow segment sum: about four entries each, which a lane keeps in flight together; a
-    // segment is cut when its lanes would need more than four such rounds, later if the tables have no room for that
-    // (a lane per entry while that leaves the chip room)
+    // lanes per segment of the narrow segment sum: about four entries each, a lane per entry while that leaves the chip
+    // room.  A segment is cut when it is longer than 16 entries a lane and than kSegCut, later if the tables have no room
+    // for its chunks
     p.logG = std::min(6, ilog2_ceil(std::max<int64_t>((avg + 3) / 4, 1)));
     const int one_each = std::min(6, ilog2_ceil(std::max<int64_t>(avg, 1)));
     while (p.logG < one_each && p.rows << (p.logG + 1) <= 256 * 1024) ++p.logG;

@@ -49,8 +49,9 @@ __device__ __forceinline__ void segsum_range(const SegArgs& a, int64_t beg, int6
 }
 
 // Narrow form, CT columns per lane.  Bound by the two dependent round trips (index entry, operand row) per group of
-// entries, so a lane keeps eight entries in flight and a group of 2^logG lanes is sized for two rounds at most: the
-// segments longer than a.long_thr are cut into chunks, which whole wavefronts sum and segsum_combine_kernel adds up.
+// entries, so a lane keeps eight entries in flight.  Segments longer than a.long_thr, which the plan sets between 256 and
+// 2048 entries, are cut into chunks, which whole wavefronts sum and segsum_combine_kernel adds up; an uncut one takes a
+// group of 2^logG lanes up to long_thr / 8 / 2^logG rounds.
 // 333,333 rows over 9,001 Zipf and 41,003 uniform keys, three columns: 21 microseconds in one launch (with segments cut
 // at 2048 entries and one entry in flight: 42 and 8 in two).  What is left are 650,000 gathers from a residual of 4 MB,
 // which does not stay in an XCD's L2 beside the index.
