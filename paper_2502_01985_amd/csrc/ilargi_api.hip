@@ -69,6 +69,10 @@ struct SourcePlan {
   size_t o_sl_rowptr = 0, o_sl_perm = 0, o_sl_chunk0 = 0, o_sl_ch_beg = 0, o_sl_ch_end = 0, o_sl_nchunk = 0,
          o_sl_ch_partial = 0, o_zslice = 0;
   int sl_cap = 0, sl_logG = 0;
+  bool binned = false;            // the segment sums run in LDS over windows of target rows (large target tables)
+  size_t o_bin_entries = 0, o_bin_off = 0, o_bin_keyinfo = 0, o_bin_ranges = 0, o_bin_items = 0, o_bin_heavy = 0;
+  int bin_items = 0, bin_heavy = 0, bin_slots = 0;
+  int64_t bin_partial = 0;
   int64_t nnz = 0;
   int logG = 0;
 };
@@ -216,9 +220,9 @@ int colred_nblocks(int64_t rows, int64_t cols, int vec) {
   return (int)((rows + rpb - 1) / rpb);
 }
 
-// Shape-only part of a plan: fills the offsets of every workspace region.
+// Shape-only part of a plan: fills the offsets of every workspace region.  bins: with room for segment sums in LDS.
 ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_t c_T, int64_t max_cx,
-                            std::vector<SourcePlan>& src, Layout& lay) {
+                            std::vector<SourcePlan>& src, Layout& lay, bool bins) {
   if (s == nullptr) return fail(ILARGI_ERR_NULL, "sources is NULL");
   if (n < 1 || n > kMaxSources) return fail(ILARGI_ERR_SHAPE, "n = %d outside [1, %d]", n, kMaxSources);
   if (r_T < 0 || r_T > 2147483646ll) return fail(ILARGI_ERR_SHAPE, "r_T = %lld out of range", (long long)r_T);
@@ -290,11 +294,36 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
   const int64_t shared_bytes = lay.max_entries > 0 ? 0 : (int64_t)std::min(partial_bytes, sort_bytes + hist_bytes);
   // Chunks of long segments: what segments cut at kLongSeg entries leave, and more of them (shorter cuts) as far as the
   // shared space pays for their sums, so that no plan asks for more workspace by them.
-  const int64_t wmax = std::max<int64_t>(max_cx, cmax);
+  // (The widest operand of a segment sum is the call's own or, for Gram blocks, another table's columns; a plan with sparse
+  // tables forms its Gram matrix in blocks of the call's width.)
+  const int64_t widest = std::max<int64_t>(max_cx, cmax), wmax = lay.max_entries > 0 ? max_cx : widest;
   int64_t n_indexed = 0;
   for (int k = 0; k < n; ++k) n_indexed += src[k].has_idx ? 1 : 0;
   const int64_t chunks_long = 2 * (r_T / kLongSeg) + 2;
-  const int64_t more = std::max<int64_t>(shared_bytes / std::max<int64_t>(n_indexed, 1) - 6 * (int64_t)kAlign, 0) / (4 * wmax + 16);
+  // Segment sums in LDS (kernels_segbin.hip) for one operand column: their two launches cost about 20 microseconds before
+  // they gain.  Iterations with one model, gathering / in LDS: 5,000,000 rows and three tables 205 / 175, 2,000,000 121 / 101,
+  // 1,600,000 130 / 93; 1,000,000 and three tables 74 / 63, two sparse ones 39 / 34, one 37..45 / 39..45; 500,000 and three
+  // 58 / 53, one 33 / 36; 250,000 and three 50 / 51.  Several columns would take a pass each: 418 / 520 for three models.
+  // Their index takes the place of the sliced one, or of what the plan saves elsewhere: room that a caller set aside for
+  // its plans stays enough.
+  auto sliced = [&](int k) { return r_T >= 1500000 && src[k].rows > 0 && src[k].rows * kSegSlices <= r_T && s[k].csr_rowptr == nullptr; };
+  auto binnable = [&](int k) {
+    return bins && max_cx == 1 && src[k].has_idx && !src[k].empty && src[k].rows * kSegSlices <= r_T && segbin_ranges(src[k].rows) <= kBinMaxRanges;
+  };
+  int64_t n_binnable = 0, bin_bytes = 0;
+  for (int k = 0; k < n; ++k) {
+    if (!binnable(k)) continue;
+    ++n_binnable;
+    const int64_t n_ranges = segbin_ranges(src[k].rows);
+    if (!sliced(k))
+      bin_bytes += 4 * (r_T + kBinPad + n_ranges * kBinWaves * (segbin_windows(r_T, src[k].rows) + 1) + src[k].rows + n_ranges * kBinHeavyShare) +
+                   (int64_t)sizeof(BinRange) * n_ranges + (int64_t)sizeof(BinItem) * 2 * kBinPerXcd + 6 * (int64_t)kAlign;
+  }
+  const int64_t spare = lay.max_entries > 0 ? 4 * n_indexed * chunks_long * (widest - wmax) : shared_bytes;
+  const bool use_bins = bin_bytes <= spare &&
+                        (r_T >= 1500000 || (n_binnable >= 2 && r_T >= 500000 && n_binnable * r_T >= 1500000));
+  const int64_t chunk_bytes = shared_bytes - (use_bins && lay.max_entries == 0 ? bin_bytes : 0);
+  const int64_t more = std::max<int64_t>(chunk_bytes / std::max<int64_t>(n_indexed, 1) - 6 * (int64_t)kAlign, 0) / (4 * wmax + 16);
   for (int k = 0; k < n; ++k) {
     SourcePlan& p = src[k];
     p.o_colmap = take(sizeof(int32_t) * std::max<int64_t>(p.cols, 1));
@@ -313,7 +342,18 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
       p.o_join_first = take(sizeof(int32_t) * (kColredBlocks + 1));
       // a residual of 6 MB or more does not stay in an XCD's 4 MB of L2: segments are then also split by slice
       // of target rows (worth it when a source row still has entries in most slices)
-      p.sliced = r_T >= 1500000 && p.rows > 0 && p.rows * kSegSlices <= r_T && s[k].csr_rowptr == nullptr;
+      p.sliced = sliced(k);
+      p.binned = use_bins && binnable(k);
+      if (p.binned) {
+        p.sliced = false;
+        const int n_ranges = segbin_ranges(p.rows);
+        p.o_bin_entries = take(sizeof(uint32_t) * (r_T + kBinPad));
+        p.o_bin_off = take(sizeof(int32_t) * n_ranges * kBinWaves * (segbin_windows(r_T, p.rows) + 1));
+        p.o_bin_keyinfo = take(sizeof(uint32_t) * p.rows);
+        p.o_bin_ranges = take(sizeof(BinRange) * n_ranges);
+        p.o_bin_items = take(sizeof(BinItem) * 2 * kBinPerXcd);
+        p.o_bin_heavy = take(sizeof(int32_t) * kBinHeavyShare * n_ranges);
+      }
       if (p.sliced) {
         p.sl_cap = (int)segsum_sliced_chunk_cap(r_T);
         p.o_sl_rowptr = take(sizeof(int32_t) * (kSegSlices * p.rows + 1));
@@ -435,6 +475,21 @@ SegArgs seg_args(const ilargi_plan* pl, int k) {
     a.sl_cap = p.sl_cap; a.sl_logG = p.sl_logG;
     a.Zs = pl->at<float>(p.o_zslice);
   }
+  return a;
+}
+
+// Arguments of the segment sums in LDS of source k; the caller adds operand and result.
+SegBin bin_args(const ilargi_plan* pl, int k) {
+  const SourcePlan& p = pl->src[k];
+  SegBin a;
+  memset(&a, 0, sizeof(a));
+  a.entries = pl->at<uint32_t>(p.o_bin_entries); a.off = pl->at<int32_t>(p.o_bin_off);
+  a.ranges = pl->at<BinRange>(p.o_bin_ranges); a.items = pl->at<BinItem>(p.o_bin_items);
+  a.keyinfo = pl->at<uint32_t>(p.o_bin_keyinfo); a.heavy = pl->at<int32_t>(p.o_bin_heavy);
+  a.n_items = p.bin_items; a.n_heavy = p.bin_heavy; a.n_ranges = segbin_ranges(p.rows); a.max_slots = p.bin_slots;
+  a.n_win = (int)segbin_windows(pl->r_T, p.rows); a.win_log = segbin_win_log(pl->r_T, p.rows);
+  a.r_T = pl->r_T; a.r_k = p.rows;
+  a.partial_floats = p.bin_partial;
   return a;
 }
 
@@ -665,19 +720,22 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
   // table's are summed by slice (and then over the slices).  The sources then take part in the column reduce with Z_k
   // as a plain operand.
   bool z_ready[kMaxSources] = {};
-  for (const bool sliced : {true, false}) {
+  enum { kBinned, kSliced, kPlain };
+  for (const int kind : {kBinned, kSliced, kPlain}) {
     SegArgs multi[kSegMulti];
+    SegBin bins[kSegMulti];
     int nm = 0, first_k = -1;
     auto flush_multi = [&]() -> ilargi_status_t {
       if (nm == 0) return ILARGI_OK;
       TraceScope ts(pl, "segsum", first_k, st);
-      HIP_TRY(sliced ? launch_segsum_sliced(multi, nm, st) : launch_segsum_narrow(multi, nm, st));
+      if (kind == kBinned) HIP_TRY(launch_segbin(bins, nm, pl->at<float>(pl->lay.o_gpartial), pl->lay.gpartial_floats, st));
+      else HIP_TRY(kind == kSliced ? launch_segsum_sliced(multi, nm, st) : launch_segsum_narrow(multi, nm, st));
       nm = 0; first_k = -1;
       return ILARGI_OK;
     };
     for (int k = 0; k < pl->n && Y != nullptr; ++k) {
       const SourcePlan& p = pl->src[k];
-      if (p.empty || k == done_k || p.ident || p.sliced != sliced) continue;
+      if (p.empty || k == done_k || p.ident || kind != (p.binned ? kBinned : p.sliced ? kSliced : kPlain)) continue;
       if (!p.sparse) {
         SegArgs sg = segsum_args(k);
         if (tmm_part_supported(colred_args(k, nullptr, 0, 0), &sg)) continue;      // join-order form: no Z_k
@@ -687,7 +745,14 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
         if (rc != ILARGI_OK) return rc;
       }
       if (nm == 0) first_k = k;
-      multi[nm++] = segsum_args(k);
+      if (kind == kBinned) {
+        bins[nm] = bin_args(pl, k);
+        bins[nm].Y = Y; bins[nm].ldy = ldy; bins[nm].col0 = col0;
+        bins[nm].Z = pl->at<float>(p.o_pz); bins[nm].ldz = ldy; bins[nm].zcol0 = col0;
+      } else {
+        multi[nm] = segsum_args(k);
+      }
+      ++nm;
       z_ready[k] = true;
     }
     ilargi_status_t rc = flush_multi();
@@ -1224,7 +1289,7 @@ ilargi_status_t ilargi_plan_workspace_bytes(int n, const ilargi_source_t* source
   if (bytes == nullptr) return fail(ILARGI_ERR_NULL, "bytes is NULL");
   std::vector<SourcePlan> src;
   Layout lay;
-  ilargi_status_t st = make_layout(n, sources, r_T, c_T, max_cx, src, lay);
+  ilargi_status_t st = make_layout(n, sources, r_T, c_T, max_cx, src, lay, true);
   if (st != ILARGI_OK) return st;
   *bytes = lay.total;
   return ILARGI_OK;
@@ -1242,7 +1307,11 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
   if (plan == nullptr) return fail(ILARGI_ERR_NULL, "plan is NULL");
   std::vector<SourcePlan> src;
   Layout lay;
-  ilargi_status_t rc = make_layout(n, sources, r_T, c_T, max_cx, src, lay);
+  ilargi_status_t rc = make_layout(n, sources, r_T, c_T, max_cx, src, lay, true);
+  if (rc == ILARGI_OK && workspace_bytes < lay.total) {      // no room for every index: the plan works without
+    lay = Layout();
+    rc = make_layout(n, sources, r_T, c_T, max_cx, src, lay, false);
+  }
   if (rc != ILARGI_OK) return rc;
   // column maps (Def. 1): entries in [-1, c_T), no target column hit twice by one source
   std::vector<std::vector<int32_t>> tcol(n, std::vector<int32_t>((size_t)c_T, -1));
@@ -1318,6 +1387,7 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     if (p.ident) p.nnz = p.rows;
   }
   // inverse index of every non-identity source (Def. 2, transposed): stable sort by source row
+  std::vector<std::vector<BinRange>> bin_ranges((size_t)n);
   for (int k = 0; k < n; ++k) {
     SourcePlan& p = pl->src[k];
     if (p.ident) continue;
@@ -1362,6 +1432,22 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
       HIP_TRY(hipMemcpyAsync(pl->at<int32_t>(p.o_long_first), lf.data(), sizeof(int32_t) * lf.size(), hipMemcpyHostToDevice, st));
       HIP_TRY(hipStreamSynchronize(st));
     }
+    if (p.binned) {
+      std::vector<uint32_t> keyinfo;
+      std::vector<int32_t> heavy;
+      segbin_layout(rowptr, keyinfo, heavy, bin_ranges[k]);
+      p.bin_heavy = (int)heavy.size();
+      for (const BinRange& r : bin_ranges[k]) p.bin_slots = std::max(p.bin_slots, r.slots);
+      if (heavy.size() > kBinHeavyShare * bin_ranges[k].size() || p.bin_slots > kBinSlots)
+        return fail(ILARGI_ERR_WORKSPACE, "internal: tables of the segment sums overflow");
+      HIP_TRY(hipMemcpyAsync(pl->at<uint32_t>(p.o_bin_keyinfo), keyinfo.data(), sizeof(uint32_t) * keyinfo.size(), hipMemcpyHostToDevice, st));
+      if (!heavy.empty())
+        HIP_TRY(hipMemcpyAsync(pl->at<int32_t>(p.o_bin_heavy), heavy.data(), sizeof(int32_t) * heavy.size(), hipMemcpyHostToDevice, st));
+      HIP_TRY(launch_build_segbin(p.idx, r_T, p.nnz, (int)bin_ranges[k].size(), (int)segbin_windows(r_T, p.rows), segbin_win_log(r_T, p.rows),
+                                  pl->at<uint32_t>(p.o_bin_keyinfo), sortbuf, rr, pl->at<int32_t>(lay.o_hist), pl->at<int32_t>(p.o_bin_off),
+                                  pl->at<uint32_t>(p.o_bin_entries), st));
+      HIP_TRY(hipStreamSynchronize(st));
+    }
     if (p.sliced) {
       int64_t slice_rows = (r_T + kSegSlices - 1) / kSegSlices;
       slice_rows = (slice_rows + 63) / 64 * 64;
@@ -1403,6 +1489,24 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
         HIP_TRY(hipMemcpyAsync(pl->at<int32_t>(p.o_join_first), first.data(), sizeof(int32_t) * first.size(), hipMemcpyHostToDevice, st));
         HIP_TRY(hipStreamSynchronize(st));
       }
+    }
+  }
+  // the runs of windows of the segment sums in LDS: kSegMulti sources, in order, share a launch
+  for (int k = 0; k < n;) {
+    std::vector<BinRange>* shared[kSegMulti];
+    int64_t rows[kSegMulti];
+    int ks[kSegMulti], m = 0;
+    for (; k < n && m < kSegMulti; ++k)
+      if (!bin_ranges[k].empty()) { shared[m] = &bin_ranges[k]; rows[m] = pl->src[k].rows; ks[m] = k; ++m; }
+    segbin_share(r_T, shared, rows, m);
+    for (int i = 0; i < m; ++i) {
+      SourcePlan& p = pl->src[ks[i]];
+      std::vector<BinItem> items;
+      segbin_items(*shared[i], items, &p.bin_partial);
+      p.bin_items = (int)items.size();
+      HIP_TRY(hipMemcpyAsync(pl->at<BinRange>(p.o_bin_ranges), shared[i]->data(), sizeof(BinRange) * shared[i]->size(), hipMemcpyHostToDevice, st));
+      HIP_TRY(hipMemcpyAsync(pl->at<BinItem>(p.o_bin_items), items.data(), sizeof(BinItem) * items.size(), hipMemcpyHostToDevice, st));
+      HIP_TRY(hipStreamSynchronize(st));
     }
   }
   // column-sorted view of every sparse source: the same stable sort, keyed by column index

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "ilargi.h"
 
 namespace ilargi {
@@ -202,6 +204,45 @@ struct SegMulti {
   SegArgs s[kSegMulti];
 };
 
+// Segment sums in LDS over large target tables, one operand column (kernels_segbin.hip).
+constexpr int kBinWaves = 16;             // wavefronts of a workgroup
+constexpr int kBinKeys = 20480;           // most source rows of a range: 80 KB of sums ...
+constexpr int kBinHeavyShare = 128;       // ... and a slot per wavefront for keys with more than this part of its entries
+constexpr int kBinSlots = kBinKeys + kBinHeavyShare * kBinWaves;
+constexpr int kBinWinFloats = 16384;      // the longest window: 64 KB, so that one workgroup fills a compute unit's LDS
+constexpr int kBinMaxRanges = 15;         // ranges x wavefronts are one digit of the sort, 255 stands for no entry
+constexpr int kBinPerXcd = 32;            // workgroups an XCD holds
+constexpr int kBinPad = 512;              // index entries that may be read past the end
+constexpr int kBinRowBits = 14;           // an index entry: row within the window, above it the slot
+constexpr int kBinSlotBits = 15;          // keyinfo: (first) slot, above it the wavefront (range x 16 + wavefront) ...
+constexpr uint32_t kBinHeavy = 1u << 31;  // ... and whether the key has a slot in every wavefront
+static_assert(kBinSlots <= 1 << kBinSlotBits && kBinSlotBits + kBinRowBits <= 32 && kBinSlotBits + 8 < 31, "packed fields");
+struct BinRange { int key0, slots, nsub, partial0, entries; };   // first key, sums, runs of windows per XCD, first partial, index entries
+struct BinItem { int range, sub; };
+struct SegBin {
+  const uint32_t* entries;
+  const int32_t* off;        // [ranges x 16][n_win + 1]
+  const BinRange* ranges;
+  const BinItem* items;
+  const uint32_t* keyinfo;   // r_k
+  const int32_t* heavy;      // keys with a slot per wavefront
+  int n_items, n_heavy, n_ranges, n_win, win_log, max_slots;
+  int64_t r_T, r_k;
+  const float* Y;
+  int ldy, col0;
+  float* Z;
+  int ldz, zcol0;
+  float* partial;            // set by the launcher
+  int64_t partial_floats;
+};
+struct SegBinMulti {
+  int n;
+  int first[kSegMulti + 1];    // items [first[q], first[q + 1]) of an XCD serve source q
+  int cfirst[kSegMulti + 1];   // workgroups of the kernel that adds the runs ...
+  int range_blocks[kSegMulti];   // ... and how many of them serve a range
+  SegBin s[kSegMulti];
+};
+
 struct ColredArgs {
   const float* D;
   int64_t rows;
@@ -395,6 +436,9 @@ hipError_t launch_sort_by_source_row(const int32_t* idx, int64_t r_T, int64_t r_
                                      int32_t* vals_a, int32_t* keys_b, int32_t* vals_b, int32_t* hist,
                                      int32_t* rowptr, int32_t* perm, hipStream_t st);
 size_t sort_hist_ints(int64_t r_T);
+// One stable pass of the sort over the low eight bits of the keys; hist is left as the digit-major start offsets.
+hipError_t launch_radix_digit(const int32_t* keys_in, const int32_t* vals_in, int64_t n, int32_t* keys_out, int32_t* vals_out,
+                              int32_t* hist, hipStream_t st);
 // In-place exclusive prefix sum of n integers on the device; `totals` is scratch of ceil(n / 1024) integers.
 void launch_exclusive_scan(int32_t* a, int64_t n, int32_t* totals, hipStream_t st);
 
@@ -457,6 +501,18 @@ int64_t segsum_sliced_chunk_cap(int64_t nnz);
 // n <= kSegMulti sources with the same number of operand columns; their sums and the sums over slices run as one
 // launch each.
 hipError_t launch_segsum_sliced(const SegArgs* a, int n, hipStream_t st);
+// Segment sums in LDS: the split of a source's keys into ranges, the runs of windows of sources that share a launch, the
+// index of a source, and the sums of n <= kSegMulti sources.
+int segbin_ranges(int64_t rows);
+int segbin_win_log(int64_t r_T, int64_t rows);
+inline int64_t segbin_windows(int64_t r_T, int64_t rows) { const int64_t w = 1ll << segbin_win_log(r_T, rows); return (r_T + w - 1) / w; }
+void segbin_layout(const std::vector<int32_t>& rowptr, std::vector<uint32_t>& keyinfo, std::vector<int32_t>& heavy, std::vector<BinRange>& ranges);
+void segbin_share(int64_t r_T, std::vector<BinRange>* const* ranges, const int64_t* rows, int n);   // sets nsub
+void segbin_items(std::vector<BinRange>& ranges, std::vector<BinItem>& items, int64_t* partial_floats);
+// sortbuf: four arrays of sort_n integers, hist: sort_hist_ints(r_T); both are scratch
+hipError_t launch_build_segbin(const int32_t* idx, int64_t r_T, int64_t nnz, int n_ranges, int n_win, int win_log, const uint32_t* keyinfo,
+                               int32_t* sortbuf, int64_t sort_n, int32_t* hist, int32_t* off, uint32_t* entries, hipStream_t st);
+hipError_t launch_segbin(const SegBin* a, int n, float* scratch, int64_t scratch_floats, hipStream_t st);
 hipError_t launch_colred(const ColredArgs& a, int nblocks, hipStream_t st);
 bool lmm_flat_supported(const LmmArgs& a, int vec, bool fuseg);
 hipError_t launch_lmm_flat(const LmmArgs& a, int mode, bool fuseg, hipStream_t st, int* grid_out);

@@ -720,3 +720,80 @@ def test_values_that_are_not_finite_stay_in_their_rows_and_columns(il, widths, s
         for j in range(5):                       # centroids in the other columns: means of the rows that were assigned
             if np.any(a == j):
                 assert rel(Cd.cpu().numpy()[ok, j], T0[a == j].mean(0)[ok]) < 1e-4
+
+
+def _keyed(seed, r_T, dims, missing=0.0, sparse=False):
+    """Tables of small whole numbers: every sum of the transposed multiply is a whole number below 2^24, exact in any order."""
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    sources, at = [], 0
+    for rows, skew in dims:
+        if skew:                                                  # a power law over shuffled keys
+            u = torch.rand(r_T, generator=gen, device="cuda", dtype=torch.float64)
+            rank = (rows * u ** skew).long().clamp_(max=rows - 1)
+            idx = torch.randperm(rows, generator=gen, device="cuda")[rank].int()
+        else:
+            idx = torch.randint(0, rows, (r_T,), generator=gen, device="cuda", dtype=torch.int32)
+        idx[torch.rand(r_T, generator=gen, device="cuda") < missing] = -1
+        D = torch.randint(0, 2, (rows, 3), generator=gen, device="cuda").float()
+        sources.append((D, idx, [at, at + 1, at + 2]))
+        at += 3
+    y = torch.randint(-3, 4, (r_T + 1,), generator=gen, device="cuda").float()
+    return sources, at, y
+
+
+@pytest.mark.parametrize("r_T,dims,missing", [
+    (1_500_000, [(20_480, 0)], 0.0),                              # one full range of keys
+    (1_500_001, [(20_481, 0)], 0.1),                              # two ranges, a last window of one row
+    (1_500_033, [(1, 0)], 0.0),                                   # a single key
+    (1_507_327, [(187_500, 0)], 0.0),                             # as many ranges as keys per target row allow; a whole window less a row
+    (2_000_003, [(40_000, 6), (61_441, 12), (17, 0), (100_000, 0), (5_000, 3)], 0.3),   # hot keys; sources of two launches
+    (500_003, [(1_000, 9), (300, 0), (60_000, 0)], 0.0),          # the smallest target table
+    (750_000, [(2_049, 40), (2, 0)], 0.9),                        # nearly every row of a few keys, most rows of none
+    (3_000_001, [(30_000, 2), (1_000, 200)], 0.0),                # windows of all three lengths; all entries on a few keys
+])
+def test_segment_sums_in_lds(il, r_T, dims, missing):
+    # one operand column: segment sums in LDS; a plan for several columns takes the gathering form.  Whole numbers: same bits.
+    sources, c_T, y = _keyed(9 + r_T, r_T, dims, missing)
+    one = il.ilargi_plan_create(sources, r_T, c_T, max_cx=1)
+    several = il.ilargi_plan_create(sources, r_T, c_T, max_cx=4)
+    for Y in (y[:r_T].clone().reshape(-1, 1), y[1:].reshape(-1, 1)):          # aligned and not
+        got = il.ilargi_tmm(one, Y).cpu()
+        want = torch.cat([D.cpu().double().t() @ torch.zeros(len(D), 1, dtype=torch.float64).index_add_(
+            0, idx.cpu()[idx.cpu() >= 0].long(), Y.cpu()[idx.cpu() >= 0].double()) for D, idx, _ in sources])
+        assert torch.equal(got.double(), want)
+        assert torch.equal(il.ilargi_tmm(several, Y).cpu(), got)
+    # values of no special kind: the same bits on every run
+    Y = torch.randn(r_T, 1, device="cuda")
+    got = il.ilargi_tmm(one, Y)
+    for _ in range(3):
+        assert torch.equal(got, il.ilargi_tmm(one, Y))
+    # a value that is not finite reaches its own keys' columns only
+    Y[r_T // 2] = float("inf")
+    finite = il.ilargi_tmm(one, Y).isfinite()
+    at = 0
+    for D, idx, _ in sources:
+        key = int(idx[r_T // 2])
+        if key >= 0:
+            assert not bool(finite[at:at + 3, 0][D[key] != 0].any())
+        else:
+            assert bool(finite[at:at + 3].all())
+        at += 3
+
+
+def test_segment_sums_in_lds_without_room(il):
+    # a workspace too small for the extra index of a mid-sized plan still gets a plan, without it
+    import ctypes
+    r_T, dims = 800_000, [(3_000, 0), (500, 3)]
+    sources, c_T, y = _keyed(5, r_T, dims)
+    Y = y[:r_T].clone().reshape(-1, 1)
+    want = il.ilargi_tmm(il.ilargi_plan_create(sources, r_T, c_T, max_cx=1), Y).cpu()
+    tuples, borrowed, shapes = il._marshal_sources(sources, r_T)
+    arr, keep = il.make_source_array(tuples)
+    room = il.ilargi_plan_workspace_bytes(tuples, r_T, c_T, 1) - (6 << 20)    # (the indices take four bytes a row and table)
+    ws = torch.empty(room + 256, dtype=torch.uint8, device="cuda")
+    handle = ctypes.c_void_p(0)
+    base = (ws.data_ptr() + 255) // 256 * 256
+    assert il.lib.ilargi_plan_create(len(tuples), arr, r_T, c_T, 1, base, room, None, ctypes.byref(handle)) == il.OK
+    plan = il.Plan(handle.value, ws, borrowed, r_T, c_T, 1, shapes)
+    assert torch.equal(il.ilargi_tmm(plan, Y).cpu(), want)
+    del keep
