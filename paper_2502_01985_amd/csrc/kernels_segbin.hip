@@ -342,10 +342,11 @@ void segbin_layout(const std::vector<int32_t>& rowptr, std::vector<uint32_t>& ke
         light += len;
       }
     }
-    int64_t seen = 0;
+    int64_t seen = 0, next = light / kBinWaves;                   // (a wavefront's keys start below its share of the entries)
+    int wave = 0;
     for (int64_t k = k0; k < k1; ++k) {
       if (keyinfo[(size_t)k] & kBinHeavy) continue;
-      const int wave = light > 0 ? (int)std::min<int64_t>(seen * kBinWaves / light, kBinWaves - 1) : 0;
+      while (wave + 1 < kBinWaves && seen >= next && light > 0) { ++wave; next = light * (wave + 1) / kBinWaves; }
       keyinfo[(size_t)k] = (uint32_t)(k - k0) | (uint32_t)(g * kBinWaves + wave) << kBinSlotBits;
       seen += rowptr[(size_t)k + 1] - rowptr[(size_t)k];
     }
