@@ -60,7 +60,9 @@ struct SourcePlan {
          o_long_seg = 0, o_long_first = 0, o_chunk_partial = 0, o_pz = 0, o_partial = 0, o_g = 0, o_cnt = 0;
   int64_t nch_max = 0, nl_max = 0;
   int n_chunks = 0, n_long = 0;
-  int long_thr = kLongSeg;        // segments of the inverse index longer than this are summed in chunks of this length
+  int n_multi = 0;                // chunks [0, n_multi) belong to segments of several
+  int long_thr = kLongSeg;        // segments of the inverse index longer than this are summed in chunks
+  bool cut = false;               // some segment is long enough to be spread over workgroups
   bool very_long = false;         // some segment has more than kLongSeg entries: no join-order paths
   int max_row = 0, max_col = 0;   // sparse: most entries of a row, of a column
   size_t o_join_first = 0;        // join-order column reduce: first source row of every workgroup
@@ -220,9 +222,10 @@ int colred_nblocks(int64_t rows, int64_t cols, int vec) {
   return (int)((rows + rpb - 1) / rpb);
 }
 
-// Shape-only part of a plan: fills the offsets of every workspace region.  bins: with room for segment sums in LDS.
+// Shape-only part of a plan: fills the offsets of every workspace region.  roomy: with room for
+// segment sums in LDS and for more chunks of long segments; without, a plan asks for no more than plans always did.
 ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_t c_T, int64_t max_cx,
-                            std::vector<SourcePlan>& src, Layout& lay, bool bins) {
+                            std::vector<SourcePlan>& src, Layout& lay, bool roomy) {
   if (s == nullptr) return fail(ILARGI_ERR_NULL, "sources is NULL");
   if (n < 1 || n > kMaxSources) return fail(ILARGI_ERR_SHAPE, "n = %d outside [1, %d]", n, kMaxSources);
   if (r_T < 0 || r_T > 2147483646ll) return fail(ILARGI_ERR_SHAPE, "r_T = %lld out of range", (long long)r_T);
@@ -308,7 +311,7 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
   // its plans stays enough.
   auto sliced = [&](int k) { return r_T >= 1500000 && src[k].rows > 0 && src[k].rows * kSegSlices <= r_T && s[k].csr_rowptr == nullptr; };
   auto binnable = [&](int k) {
-    return bins && max_cx == 1 && src[k].has_idx && !src[k].empty && src[k].rows * kSegSlices <= r_T && segbin_ranges(src[k].rows) <= kBinMaxRanges;
+    return roomy && max_cx == 1 && src[k].has_idx && !src[k].empty && src[k].rows * kSegSlices <= r_T && segbin_ranges(src[k].rows) <= kBinMaxRanges;
   };
   int64_t n_binnable = 0, bin_bytes = 0;
   for (int k = 0; k < n; ++k) {
@@ -331,7 +334,10 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
     if (p.has_idx) {
       p.o_rowptr = take(sizeof(int32_t) * (p.rows + 1));
       p.o_perm = take(sizeof(int32_t) * std::max<int64_t>(r_T, 1));
-      p.nch_max = std::max(chunks_long, std::min(chunks_long + more, r_T / (kLongSeg / 4) + 2));
+      // (a segment of more entries than a group of lanes sums at once has a chunk of its own: twice the chunks of kSegCut
+      // entries.  400,000 rows over 9,000 Zipf and 40,000 uniform keys, room for r_T / 512 and for r_T / 128 chunks: one
+      // column 36.8 and 31.5 microseconds, 9 columns 124 and 95, the Gram matrix 286 and 211)
+      p.nch_max = std::max(chunks_long, std::min(chunks_long + more, r_T / (roomy ? kSegCut / 2 : kLongSeg / 4) + 2));
       p.nl_max = p.nch_max / 2;                       // (a long segment is cut in two at least)
       p.o_chunk_seg = take(sizeof(int32_t) * p.nch_max);
       p.o_chunk_beg = take(sizeof(int32_t) * p.nch_max);
@@ -429,21 +435,29 @@ int32_t longest_segment(const std::vector<int32_t>& rowptr) {
   return longest;
 }
 
-// Splits the segments longer than thr into chunks of thr entries (host side, once per plan).
-void build_long_tables(const std::vector<int32_t>& rowptr, int32_t thr, std::vector<int32_t>& chunk_seg,
+// Lists the segments longer than thr in chunks of len entries, len >= thr (host side, once per plan): first those of more
+// than one chunk, which long_seg and long_first name, then the others, a chunk each.
+void build_long_tables(const std::vector<int32_t>& rowptr, int32_t thr, int32_t len, std::vector<int32_t>& chunk_seg,
                        std::vector<int32_t>& chunk_beg, std::vector<int32_t>& chunk_end,
                        std::vector<int32_t>& long_seg, std::vector<int32_t>& long_first) {
+  std::vector<int32_t> single;
   long_first.push_back(0);
   for (size_t j = 0; j + 1 < rowptr.size(); ++j) {
     int32_t b = rowptr[j], e = rowptr[j + 1];
     if (e - b <= thr) continue;
+    if (e - b <= len) { single.push_back((int32_t)j); continue; }
     long_seg.push_back((int32_t)j);
-    for (int32_t c = b; c < e; c += thr) {
+    for (int32_t c = b; c < e; c += len) {
       chunk_seg.push_back((int32_t)j);
       chunk_beg.push_back(c);
-      chunk_end.push_back(std::min(e, c + thr));
+      chunk_end.push_back(std::min(e, c + len));
     }
     long_first.push_back((int32_t)chunk_seg.size());
+  }
+  for (int32_t j : single) {
+    chunk_seg.push_back(j);
+    chunk_beg.push_back(rowptr[(size_t)j]);
+    chunk_end.push_back(rowptr[(size_t)j + 1]);
   }
 }
 
@@ -460,6 +474,7 @@ SegArgs seg_args(const ilargi_plan* pl, int k) {
   a.long_first = pl->at<int32_t>(p.o_long_first);
   a.n_chunks = p.n_chunks;
   a.n_long = p.n_long;
+  a.n_multi = p.n_multi;
   a.long_thr = p.long_thr;
   a.r_k = p.rows;
   a.gidx = nullptr;
@@ -1205,7 +1220,7 @@ bool kmeans_fused_ok(const ilargi_plan* pl, int64_t k) {
   for (int q = 0; q < pl->n; ++q) {
     const SourcePlan& p = pl->src[q];
     if (p.empty || q == pl->fused) continue;
-    if (p.ident || p.n_long > 0) return false;     // (a cut segment is spread over workgroups)
+    if (p.ident || p.cut) return false;
   }
   return true;
 }
@@ -1308,7 +1323,7 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
   std::vector<SourcePlan> src;
   Layout lay;
   ilargi_status_t rc = make_layout(n, sources, r_T, c_T, max_cx, src, lay, true);
-  if (rc == ILARGI_OK && workspace_bytes < lay.total) {      // no room for every index: the plan works without
+  if (rc == ILARGI_OK && workspace_bytes < lay.total) {      // sized for less: the plan works without
     lay = Layout();
     rc = make_layout(n, sources, r_T, c_T, max_cx, src, lay, false);
   }
@@ -1402,25 +1417,27 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     p.nnz = rowptr[(size_t)p.rows];
     const int64_t avg = p.rows > 0 ? (p.nnz + p.rows - 1) / p.rows : 1;
     // lanes per segment of the narrow segment sum: about four entries each, a lane per entry while that leaves the chip
-    // room.  A segment is cut when it is longer than 16 entries a lane and than kSegCut, later if the tables have no room
-    // for its chunks
+    // room.  A longer segment than such a group sums in one go (eight entries a lane) is a wavefront's: in a chunk of its
+    // own, or in several from 256 entries (or what a group sums) on.  Both limits double until the tables have room.
     p.logG = std::min(6, ilog2_ceil(std::max<int64_t>((avg + 3) / 4, 1)));
     const int one_each = std::min(6, ilog2_ceil(std::max<int64_t>(avg, 1)));
     while (p.logG < one_each && p.rows << (p.logG + 1) <= 256 * 1024) ++p.logG;
     // (with hundreds of entries per segment on average, whole wavefronts serve the segments as they are: cutting a part
     // of them costs a launch, 48 against 39 microseconds for 1,000,000 rows over 1,000 uniform keys)
-    p.long_thr = std::max(kSegCut, 16 << p.logG);
-    if (2 * avg > p.long_thr) p.long_thr = kLongSeg;
+    const int32_t spread = std::max(kSegCut, 16 << p.logG);
+    p.long_thr = 2 * avg > spread ? kLongSeg : std::max((int)kWave, 8 << p.logG);
     const int32_t longest = longest_segment(rowptr);
     p.very_long = longest > kLongSeg;
+    p.cut = longest > (2 * avg > spread ? kLongSeg : spread);
     std::vector<int32_t> cs, cb, ce, ls, lf(1, 0);
     while (longest > p.long_thr) {
       lf.clear();
-      build_long_tables(rowptr, p.long_thr, cs, cb, ce, ls, lf);
+      build_long_tables(rowptr, p.long_thr, std::max(kSegCut, p.long_thr), cs, cb, ce, ls, lf);
       if ((int64_t)cs.size() <= p.nch_max || p.long_thr >= kLongSeg) break;
       p.long_thr *= 2;
       cs.clear(); cb.clear(); ce.clear(); ls.clear(); lf.clear();
     }
+    p.n_multi = ls.empty() ? 0 : lf.back();
     p.n_chunks = (int)cs.size();
     p.n_long = (int)ls.size();
     if (p.n_chunks > p.nch_max || p.n_long > p.nl_max) return fail(ILARGI_ERR_WORKSPACE, "internal: long-segment tables overflow");

@@ -158,7 +158,8 @@ struct SegArgs {
   const int32_t* chunk_seg, *chunk_beg, *chunk_end;  // long-segment chunks
   const int32_t* long_seg, *long_first;              // long segments and their chunk ranges
   int n_chunks, n_long;
-  int long_thr;            // longest segment that is summed in one go
+  int n_multi;             // chunks [0, n_multi) belong to segments of several; each of the others is a segment
+  int long_thr;            // longest segment that is summed by a group of lanes
   int64_t r_k;
   const float* Y;          // rows addressed through perm (and gidx if given)
   int ldy, col0, ncols;

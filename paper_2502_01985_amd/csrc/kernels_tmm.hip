@@ -20,6 +20,11 @@ __device__ __forceinline__ int64_t seg_row(const SegArgs& a, int64_t p) {
   return i;
 }
 
+// Where the sums of chunk c go: the chunks of one segment are added by segsum_combine_kernel, a segment of one chunk is done.
+__device__ __forceinline__ float* segsum_chunk_result(const SegArgs& a, int c) {
+  return c < a.n_multi ? a.chunk_partial + (int64_t)c * a.ncols : a.Z + (int64_t)a.chunk_seg[c] * a.ldz + a.zcol0;
+}
+
 constexpr int kSegU = 8;
 
 // Sum of the operand rows of entries [beg, end) by lanes `lig` of G: kSegU entries of a lane in flight, first their
@@ -48,23 +53,42 @@ __device__ __forceinline__ void segsum_range(const SegArgs& a, int64_t beg, int6
   }
 }
 
+// Workgroups that sum the chunks of long segments, a wavefront each: they come first, and work beside the others.
+__host__ __device__ __forceinline__ int segsum_chunk_blocks(int n_chunks) {
+  const int n = (n_chunks + kBlock / kWave - 1) / (kBlock / kWave);
+  return n < 16384 ? n : 16384;
+}
+
 // Narrow form, CT columns per lane.  Bound by the two dependent round trips (index entry, operand row) per group of
-// entries, so a lane keeps eight entries in flight.  Segments longer than a.long_thr, which the plan sets between 256 and
-// 2048 entries, are cut into chunks, which whole wavefronts sum and segsum_combine_kernel adds up; an uncut one takes a
-// group of 2^logG lanes up to long_thr / 8 / 2^logG rounds.
-// 333,333 rows over 9,001 Zipf and 41,003 uniform keys, three columns: 21 microseconds in one launch (with segments cut
-// at 2048 entries and one entry in flight: 42 and 8 in two).  What is left are 650,000 gathers from a residual of 4 MB,
-// which does not stay in an XCD's L2 beside the index.
+// entries, so a lane keeps eight entries in flight and no segment takes a second round: one that is longer than its group of
+// 2^logG lanes sums at once (a.long_thr) is a wavefront's, as a chunk of its own or, from 256 entries on, as several, which
+// segsum_combine_kernel adds up.
+// 333,333 rows over 9,001 Zipf and 41,003 uniform keys, three columns: 13 microseconds in one launch, and 4 for the chunks
+// (groups that walk segments of up to 512 entries: 20; such keys without the skew 9).  What is left are 650,000 gathers
+// from a residual of 4 MB, which does not stay in an XCD's L2 beside the index.
 template <int CT>
 __global__ __launch_bounds__(kBlock) void segsum_narrow_kernel(SegMulti m) {
   int q = 0;
   while (q + 1 < m.n && (int)blockIdx.x >= m.first[q + 1]) ++q;
   const SegArgs a = m.s[q];
-  const int bx = (int)blockIdx.x - m.first[q], gx = m.first[q + 1] - m.first[q];
+  const int bx = (int)blockIdx.x - m.first[q], chunk_blocks = segsum_chunk_blocks(a.n_chunks);
   float acc[CT];
+  if (bx < chunk_blocks) {
+    const int lane = threadIdx.x % kWave;
+    for (int c = bx * (kBlock / kWave) + threadIdx.x / kWave; c < a.n_chunks; c += chunk_blocks * (kBlock / kWave)) {
+      segsum_range<CT>(a, a.chunk_beg[c], a.chunk_end[c], lane, kWave, acc);
+      if (lane == 0) {
+#pragma unroll
+        for (int n = 0; n < CT; ++n)
+          if (n < a.ncols) segsum_chunk_result(a, c)[n] = acc[n];
+      }
+    }
+    return;
+  }
+  const int gx = m.first[q + 1] - m.first[q] - chunk_blocks;
   const int G = 1 << a.logG, lig = threadIdx.x & (G - 1);
   const int64_t gpb = kBlock >> a.logG;
-  for (int64_t base = (int64_t)bx * gpb; base < a.r_k; base += (int64_t)gx * gpb) {   // same trip count for all lanes
+  for (int64_t base = (int64_t)(bx - chunk_blocks) * gpb; base < a.r_k; base += (int64_t)gx * gpb) {   // same trip count for all lanes
     const int64_t j = base + (threadIdx.x >> a.logG);
     int64_t beg = 0, end = 0;
     if (j < a.r_k) { beg = a.rowptr[j]; end = a.rowptr[j + 1]; }
@@ -74,15 +98,6 @@ __global__ __launch_bounds__(kBlock) void segsum_narrow_kernel(SegMulti m) {
 #pragma unroll
       for (int n = 0; n < CT; ++n)
         if (n < a.ncols) a.Z[j * a.ldz + a.zcol0 + n] = acc[n];
-    }
-  }
-  const int lane = threadIdx.x % kWave;
-  for (int c = bx * (kBlock / kWave) + threadIdx.x / kWave; c < a.n_chunks; c += gx * (kBlock / kWave)) {
-    segsum_range<CT>(a, a.chunk_beg[c], a.chunk_end[c], lane, kWave, acc);
-    if (lane == 0) {
-#pragma unroll
-      for (int n = 0; n < CT; ++n)
-        if (n < a.ncols) a.chunk_partial[(int64_t)c * a.ncols + n] = acc[n];
     }
   }
 }
@@ -108,7 +123,7 @@ __global__ __launch_bounds__(kBlock) void segsum_wide_kernel(SegArgs a) {
       int c = (int)(item - a.r_k);
       beg = a.chunk_beg[c];
       end = a.chunk_end[c];
-      dst = a.chunk_partial + (int64_t)c * a.ncols;
+      dst = segsum_chunk_result(a, c);
     }
     for (int nb = 0; nb < a.ncols; nb += W) {
       const int n0 = nb + lig;
@@ -689,8 +704,7 @@ hipError_t launch_segsum_narrow(const SegArgs* a, int n, hipStream_t st) {
     if (a[q].ncols < 1 || a[q].ncols > kNarrowCT || a[q].ncols != a[0].ncols || a[q].r_k <= 0) return hipErrorInvalidValue;
     m.s[q] = a[q];
     const int64_t gpb = kBlock >> a[q].logG;
-    const int64_t grid = std::max<int64_t>((a[q].r_k + gpb - 1) / gpb, (a[q].n_chunks + kBlock / kWave - 1) / (kBlock / kWave));
-    m.first[q + 1] = m.first[q] + (int)std::min<int64_t>(grid, 65536);
+    m.first[q + 1] = m.first[q] + segsum_chunk_blocks(a[q].n_chunks) + (int)std::min<int64_t>((a[q].r_k + gpb - 1) / gpb, 65536);
   }
   const unsigned grid = (unsigned)m.first[n];
   if (a[0].ncols == 1) segsum_narrow_kernel<1><<<grid, kBlock, 0, st>>>(m);

@@ -797,3 +797,23 @@ def test_segment_sums_in_lds_without_room(il):
     plan = il.Plan(handle.value, ws, borrowed, r_T, c_T, 1, shapes)
     assert torch.equal(il.ilargi_tmm(plan, Y).cpu(), want)
     del keep
+
+
+@pytest.mark.parametrize("rows,short", [(40, 3), (3_000, 1), (3_000, 20), (20_000, 6)])
+@pytest.mark.parametrize("cx", [1, 2, 4, 5, 16, 40])
+def test_segments_around_the_lengths_of_groups_and_chunks(il, rows, short, cx):
+    # segments a lane group sums at once, a wavefront's chunk, several chunks; whole numbers, so the order does not show
+    rng = np.random.default_rng(rows + short)
+    lengths = np.full(rows, short)
+    special = [0, 7, 8, 9, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 767, 769, 2_047, 2_048, 2_049, 5_000]
+    lengths[rng.choice(rows, len(special), replace=False)] = special
+    idx = rng.permutation(np.repeat(np.arange(rows), lengths)).astype(np.int32)
+    idx = np.concatenate([idx, np.full(11, -1, np.int32)])
+    r_T = len(idx)
+    S = torch.ones((r_T, 4), device="cuda")
+    sources = [(S, None, [0, 1, 2, 3]), (torch.ones((rows, 3), device="cuda"), torch.from_numpy(idx).cuda(), [4, 5, 6])]
+    plan = il.ilargi_plan_create(sources, r_T, 7, max_cx=40)
+    Y = torch.randint(-9, 10, (r_T, cx), device="cuda").float()
+    want = torch.zeros((rows, cx), dtype=torch.float64).index_add_(0, torch.from_numpy(idx[:-11]).long(), Y[:-11].cpu().double())
+    assert torch.equal(il.ilargi_segment_sum(plan, 1, Y).cpu().double(), want)
+    assert torch.equal(il.ilargi_tmm(plan, Y)[4:].cpu().double(), want.sum(0).expand(3, cx))
