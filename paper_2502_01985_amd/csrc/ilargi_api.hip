@@ -774,6 +774,27 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
     if (rc != ILARGI_OK) return rc;
   }
   // Column reduces that share a launch: dense tables without aligned float4 rows (tiles), small sparse tables.
+  SparseFin fin;
+  memset(&fin, 0, sizeof(fin));
+  fin.mode = -1;
+  {
+    // every row of the result comes from one column of one sparse table, all of them in one launch: its sums are the result
+    int by_lanes = 0, others = 0;
+    for (int k = 0; k < pl->n; ++k) {
+      const SourcePlan& p = pl->src[k];
+      if (!p.empty) ++(k != done_k && p.sparse && sparse_cols_by_lanes(p) ? by_lanes : others);
+    }
+    if (others == 0 && by_lanes >= 1 && by_lanes <= kSparseMulti && pl->cover_disjoint && pl->cover_columns) {
+      fin.mode = mode;
+      fin.out = out; fin.ldo = ldo; fin.col0 = col0;
+      fin.lr = lr;
+      fin.inv_rT = pl->r_T > 0 ? 1.0f / (float)pl->r_T : 0.0f;
+      fin.loss_partial = pl->at<float>(pl->lay.o_loss);
+      fin.n_loss_partial = n_loss_partial;
+      fin.loss = loss;
+      fin.loss_scale = loss_scale;
+    }
+  }
   int tile_blocks[kMaxSources] = {};                   // partial blocks the tile kernel left for source k (0: not its)
   bool sparse_done[kMaxSources] = {};
   {
@@ -793,7 +814,7 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
     auto flush_sparse = [&]() -> ilargi_status_t {
       if (ns == 0) return ILARGI_OK;
       TraceScope ts(pl, "colred", first_sparse, st);
-      HIP_TRY(launch_spmm_lanes_cols(sparse, ns, st));
+      HIP_TRY(launch_spmm_lanes_cols(sparse, ns, fin, st));
       ns = 0;
       return ILARGI_OK;
     };
@@ -825,7 +846,7 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
     }
     ilargi_status_t rc = flush_tiles();
     if (rc == ILARGI_OK) rc = flush_sparse();
-    if (rc != ILARGI_OK) return rc;
+    if (rc != ILARGI_OK || fin.mode >= 0) return rc;
   }
   for (int k = 0; k < pl->n; ++k) {
     SourcePlan& p = pl->src[k];

@@ -100,10 +100,23 @@ struct SparsePart {
   const float* X; int ldx, col0, ncols;   // rows: the operand; columns: the rows of Z
   float* out; int ldo;                    // rows: P, rows x ldo; columns: [cols][kNarrowCT]
 };
+// What becomes of the transposed products: mode -1: the parts' outputs; 0: the result, row colmap[j] of column j; 1: the update
+// of Alg. 1 and the loss (one more workgroup).  For modes 0 and 1 every row of the result is fed by one column of the parts.
+struct SparseFin {
+  int mode;
+  float* out; int ldo, col0;          // c_T x ldo: the result, or the weights
+  const float* lr;
+  float inv_rT;
+  const float* loss_partial;
+  int n_loss_partial;
+  float* loss;
+  float loss_scale;
+};
 struct SparseMultiArgs {
   int n;
   int first[kSparseMulti + 1];
   SparsePart s[kSparseMulti];
+  SparseFin f;
 };
 
 // Gradient-descent pass over a two-table star join for a wide batch of models (kernels_star.hip).
@@ -488,7 +501,7 @@ hipError_t launch_spmm_rows(const SparseArgs& a, const float* X, int ldx, int co
 hipError_t launch_spmm_t(const SparseArgs& a, const float* Z, int ldz, int col0, int ncols, float* partial, float* G,
                          hipStream_t st);
 hipError_t launch_spmm_lanes_rows(const SparsePart* s, int n, hipStream_t st);
-hipError_t launch_spmm_lanes_cols(const SparsePart* s, int n, hipStream_t st);
+hipError_t launch_spmm_lanes_cols(const SparsePart* s, int n, const SparseFin& f, hipStream_t st);
 hipError_t launch_mat_scatter(const SparseArgs* sparse, const float* D, int64_t rows, int ck, const int32_t* colmap,
                               const int32_t* idx, int64_t ident_rows, float* T, int64_t r_T, int c_T, hipStream_t st);
 hipError_t launch_segsum(const SegArgs& a, hipStream_t st);
@@ -630,6 +643,44 @@ __device__ __forceinline__ float logistic_residual(float z, float y, float& loss
   const float p = fmaf(fmaf(fmaf(fmaf(0.12144784f, u, 0.10715369f), u, 0.14308299f), u, 0.19999444f), u, 0.33333337f);
   loss += fmaxf(z, 0.0f) + (t2 + fmaf(t2 * u, p, 2.0f * fmaf(t_lo, u, t_lo))) - y * z;
   return sigmoid - y;
+}
+
+// Sum of float4 records rec[b * stride4] over b < count by a whole workgroup: threads stride the records
+// (four independent loads in flight each), xor butterfly inside the wavefronts, wavefronts added in order.
+__device__ __forceinline__ float4 block_sum4(const float4* __restrict__ rec, int64_t stride4, int count,
+                                             float (*scratch)[4]) {
+  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  float4 s0 = make_float4(0.f, 0.f, 0.f, 0.f), s1 = s0, s2 = s0, s3 = s0;
+  int b = tid;
+  for (; b + 3 * kBlock < count; b += 4 * kBlock) {
+    float4 v0 = rec[(int64_t)b * stride4], v1 = rec[(int64_t)(b + kBlock) * stride4];
+    float4 v2 = rec[(int64_t)(b + 2 * kBlock) * stride4], v3 = rec[(int64_t)(b + 3 * kBlock) * stride4];
+    s0.x += v0.x; s0.y += v0.y; s0.z += v0.z; s0.w += v0.w;
+    s1.x += v1.x; s1.y += v1.y; s1.z += v1.z; s1.w += v1.w;
+    s2.x += v2.x; s2.y += v2.y; s2.z += v2.z; s2.w += v2.w;
+    s3.x += v3.x; s3.y += v3.y; s3.z += v3.z; s3.w += v3.w;
+  }
+  for (; b < count; b += kBlock) {
+    float4 v0 = rec[(int64_t)b * stride4];
+    s0.x += v0.x; s0.y += v0.y; s0.z += v0.z; s0.w += v0.w;
+  }
+  float r[4] = {(s0.x + s1.x) + (s2.x + s3.x), (s0.y + s1.y) + (s2.y + s3.y), (s0.z + s1.z) + (s2.z + s3.z),
+                (s0.w + s1.w) + (s2.w + s3.w)};
+#pragma unroll
+  for (int n = 0; n < 4; ++n)
+    for (int m = kWave / 2; m >= 1; m >>= 1) r[n] += __shfl_xor(r[n], m);
+  __syncthreads();   // scratch may still be read from a previous call
+  if (lane == 0) {
+#pragma unroll
+    for (int n = 0; n < 4; ++n) scratch[wave][n] = r[n];
+  }
+  __syncthreads();
+  float4 out;
+  out.x = ((scratch[0][0] + scratch[1][0]) + scratch[2][0]) + scratch[3][0];
+  out.y = ((scratch[0][1] + scratch[1][1]) + scratch[2][1]) + scratch[3][1];
+  out.z = ((scratch[0][2] + scratch[1][2]) + scratch[2][2]) + scratch[3][2];
+  out.w = ((scratch[0][3] + scratch[1][3]) + scratch[2][3]) + scratch[3][3];
+  return out;
 }
 
 inline int ilog2_ceil(int64_t v) { int l = 0; while ((1ll << l) < v) ++l; return l; }

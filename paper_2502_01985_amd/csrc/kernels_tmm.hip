@@ -575,44 +575,6 @@ __global__ __launch_bounds__(kBlock) void tmm_parts_kernel(TmmParts t) {
   else colred_body<4, CT>(t.c[part], bx, 0);
 }
 
-// Sum of float4 records rec[b * stride4] over b < count by a whole workgroup: threads stride the records
-// (four independent loads in flight each), xor butterfly inside the wavefronts, wavefronts added in order.
-__device__ __forceinline__ float4 block_sum4(const float4* __restrict__ rec, int64_t stride4, int count,
-                                             float (*scratch)[4]) {
-  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-  float4 s0 = make_float4(0.f, 0.f, 0.f, 0.f), s1 = s0, s2 = s0, s3 = s0;
-  int b = tid;
-  for (; b + 3 * kBlock < count; b += 4 * kBlock) {
-    float4 v0 = rec[(int64_t)b * stride4], v1 = rec[(int64_t)(b + kBlock) * stride4];
-    float4 v2 = rec[(int64_t)(b + 2 * kBlock) * stride4], v3 = rec[(int64_t)(b + 3 * kBlock) * stride4];
-    s0.x += v0.x; s0.y += v0.y; s0.z += v0.z; s0.w += v0.w;
-    s1.x += v1.x; s1.y += v1.y; s1.z += v1.z; s1.w += v1.w;
-    s2.x += v2.x; s2.y += v2.y; s2.z += v2.z; s2.w += v2.w;
-    s3.x += v3.x; s3.y += v3.y; s3.z += v3.z; s3.w += v3.w;
-  }
-  for (; b < count; b += kBlock) {
-    float4 v0 = rec[(int64_t)b * stride4];
-    s0.x += v0.x; s0.y += v0.y; s0.z += v0.z; s0.w += v0.w;
-  }
-  float r[4] = {(s0.x + s1.x) + (s2.x + s3.x), (s0.y + s1.y) + (s2.y + s3.y), (s0.z + s1.z) + (s2.z + s3.z),
-                (s0.w + s1.w) + (s2.w + s3.w)};
-#pragma unroll
-  for (int n = 0; n < 4; ++n)
-    for (int m = kWave / 2; m >= 1; m >>= 1) r[n] += __shfl_xor(r[n], m);
-  __syncthreads();   // scratch may still be read from a previous call
-  if (lane == 0) {
-#pragma unroll
-    for (int n = 0; n < 4; ++n) scratch[wave][n] = r[n];
-  }
-  __syncthreads();
-  float4 out;
-  out.x = ((scratch[0][0] + scratch[1][0]) + scratch[2][0]) + scratch[3][0];
-  out.y = ((scratch[0][1] + scratch[1][1]) + scratch[2][1]) + scratch[3][1];
-  out.z = ((scratch[0][2] + scratch[1][2]) + scratch[2][2]) + scratch[3][2];
-  out.w = ((scratch[0][3] + scratch[1][3]) + scratch[2][3]) + scratch[3][3];
-  return out;
-}
-
 // One workgroup per target column: sum each contributing source's per-workgroup partials (records of
 // kNarrowCT floats), add the sources in order.  MODE 0 stores, MODE 1 applies  W -= lr * G / r_T  and, in
 // one extra workgroup, reduces the loss partials (Alg. 1).

@@ -817,3 +817,36 @@ def test_segments_around_the_lengths_of_groups_and_chunks(il, rows, short, cx):
     want = torch.zeros((rows, cx), dtype=torch.float64).index_add_(0, torch.from_numpy(idx[:-11]).long(), Y[:-11].cpu().double())
     assert torch.equal(il.ilargi_segment_sum(plan, 1, Y).cpu().double(), want)
     assert torch.equal(il.ilargi_tmm(plan, Y)[4:].cpu().double(), want.sum(0).expand(3, cx))
+
+
+@pytest.mark.parametrize("n,ncols,c_T_more,drop", [(1, 1, 0, False), (4, 3, 0, False), (5, 1, 0, False), (2, 2, 3, False), (2, 4, 0, True)])
+def test_sparse_products_are_the_result(il, n, ncols, c_T_more, drop):
+    # sparse tables alone, disjoint and covering: the transposed products update the weights in their launch (up to four
+    # tables); with columns nobody feeds, or dropped ones, and with more tables the usual sequence does
+    rng = datagen.rng_for(600 + 10 * n + ncols)
+    r_T, sources, at = 700, [], 0
+    for k in range(n):
+        rows, cols = 60 + 7 * k, 33 + 5 * k
+        D = np.where(rng.random((rows, cols)) < 0.15, rng.standard_normal((rows, cols)), 0.0).astype(np.float32)
+        cm = np.arange(at, at + cols, dtype=np.int32)
+        if drop:
+            cm[3::9] = -1
+        sources.append(datagen.Source(D, rng.integers(-1, rows, r_T).astype(np.int32), cm))
+        at += cols
+    sch = datagen.Schema(sources, r_T, at + c_T_more)
+    tg = oracle.Target(sch)
+    dev = [(il.CSR.from_dense(s.D), torch.from_numpy(s.row_idx).cuda(), s.col_map) for s in sources]
+    plan = il.ilargi_plan_create(dev, r_T, sch.c_T, max_cx=ncols)
+    Y = rng.standard_normal((r_T, ncols)).astype(np.float32)
+    got = il.ilargi_tmm(plan, torch.from_numpy(Y).cuda()).cpu().numpy()
+    want = oracle.tmm(tg, Y)
+    assert np.abs(got - want).max() <= 2e-6 * max(1.0, np.abs(want).max())     # sums of about a hundred terms of order one
+    y = (rng.random(r_T) < 0.5).astype(np.float64)
+    W0, lr = rng.standard_normal((sch.c_T, ncols)), [0.5 / (j + 1) for j in range(ncols)]
+    W = torch.from_numpy(W0.astype(np.float32)).cuda()
+    losses = torch.empty((4, ncols), device="cuda")
+    for t in range(4):
+        il.ilargi_gd_step(plan, il.LOGISTIC, W, torch.from_numpy(y.astype(np.float32)).cuda(), torch.tensor(lr, device="cuda"), losses[t])
+    W_ref, L_ref = oracle.gd(tg, "logistic", y, W0.astype(np.float32).astype(np.float64), lr, 4)
+    assert np.linalg.norm(W.cpu().numpy() - W_ref) <= 1e-6 * np.linalg.norm(W_ref)
+    np.testing.assert_allclose(losses.cpu().numpy(), np.asarray(L_ref).reshape(4, ncols), rtol=2e-6)
