@@ -936,8 +936,10 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
 // Runs the matrix-core transposed reduction in row chunks and adds the chunk results in order.
 // transposed: block receives the cb x ca transpose of the product.
 // part / part_floats: the partial-block space of this call (default: all of the plan's).
+// nparts: if not NULL, the chunk results may be left in part for the caller to add (*nparts of them; 0: they are in block).
 ilargi_status_t run_tred(ilargi_plan* pl, TredArgs& g, float* block, const char* tag, int tag_k, bool bf16,
-                         hipStream_t st, bool transposed = false, float* part = nullptr, int64_t part_floats = 0) {
+                         hipStream_t st, bool transposed = false, float* part = nullptr, int64_t part_floats = 0,
+                         int* nparts = nullptr) {
   int64_t elems = (int64_t)g.ca * g.cb;
   if (elems <= 0) return ILARGI_OK;
   if (part == nullptr) { part = pl->at<float>(pl->lay.o_gpartial); part_floats = pl->lay.gpartial_floats; }
@@ -988,6 +990,7 @@ ilargi_status_t run_tred(ilargi_plan* pl, TredArgs& g, float* block, const char*
     TraceScope ts(pl, tag, tag_k, st);
     HIP_TRY(launch_tred(g, (int)nch, bf16, st));
   }
+  if (nparts != nullptr) { *nparts = (int)nch; return ILARGI_OK; }
   HIP_TRY(launch_tred_reduce(g.partial, (int)nch, elems, block, st, transposed ? g.cb : 0));
   return ILARGI_OK;
 }
@@ -1246,8 +1249,7 @@ bool kmeans_fused_ok(const ilargi_plan* pl, int64_t k) {
   return true;
 }
 
-ilargi_status_t kmeans_fused(ilargi_plan* pl, const float* C, int k, const float* cn, int32_t* assign, float* G, int32_t* cnt,
-                             hipStream_t st) {
+ilargi_status_t kmeans_fused(ilargi_plan* pl, float* C, int k, int32_t* assign, int32_t* counts, hipStream_t st) {
   LmmArgs a;
   memset(&a, 0, sizeof(a));
   const SourcePlan& f = pl->src[pl->fused];
@@ -1264,9 +1266,11 @@ ilargi_status_t kmeans_fused(ilargi_plan* pl, const float* C, int k, const float
   int32_t* sizes = pl->at<int32_t>(pl->lay.o_loss);
   {
     TraceScope ts(pl, "kmeans_assign", -1, st);
-    HIP_TRY(launch_kmeans_tile(a, cn, assign, sizes, sums, grid, logR, st));
+    HIP_TRY(launch_kmeans_tile(a, pl->c_T, assign, sizes, sums, grid, logR, st));
   }
-  HIP_TRY(launch_kmeans_counts(sizes, grid, k, cnt, st));
+  // the blocks of all sources stay until the last launch adds them: the room left is shared out
+  int64_t used = (int64_t)grid * f.cols * k;
+  const int64_t share = (pl->lay.gpartial_floats - used) / std::max(pl->n - 1, 1);
   ColAsmArgs c;
   memset(&c, 0, sizeof(c));
   for (int q = 0; q < pl->n; ++q) {
@@ -1288,17 +1292,19 @@ ilargi_status_t kmeans_fused(ilargi_plan* pl, const float* C, int k, const float
       g.A = p.D; g.lda = (int)p.cols; g.ca = (int)p.cols; g.a_rows = p.rows;
       g.B = pl->at<float>(p.o_pz); g.ldb = k; g.cb = k; g.b_rows = p.rows;
       g.n_rows = p.rows;
-      const int64_t room = (int64_t)grid * f.cols * k;
-      const ilargi_status_t rc = run_tred(pl, g, pl->at<float>(p.o_g), "colred", q, false, st, false, sums + room,
-                                          pl->lay.gpartial_floats - room);
+      int nparts = 0;
+      const ilargi_status_t rc = run_tred(pl, g, pl->at<float>(p.o_g), "colred", q, false, st, false, sums + used, share, &nparts);
       if (rc != ILARGI_OK) return rc;
-      c.G[c.n] = pl->at<float>(p.o_g);
+      c.G[c.n] = nparts > 0 ? sums + used : pl->at<float>(p.o_g);
+      c.nparts[c.n] = nparts;
+      used += (int64_t)nparts * p.cols * k;
     }
     ++c.n;
   }
-  c.c_T = (int)pl->c_T; c.cx = k; c.out = G;
-  TraceScope ts(pl, "finalize", -1, st);
-  HIP_TRY(launch_colasm(c, 0, st));
+  c.c_T = (int)pl->c_T; c.cx = k; c.out = C;
+  c.sizes = sizes; c.n_sizes = grid; c.counts = counts;
+  TraceScope ts(pl, "kmeans_update", -1, st);
+  HIP_TRY(launch_colasm(c, 2, st));
   return ILARGI_OK;
 }
 
@@ -2164,14 +2170,13 @@ ilargi_status_t ilargi_kmeans_step(ilargi_plan_t* plan, float* C, int64_t k, int
   float* cn = plan->at<float>(plan->lay.o_cn);
   int32_t* cnt = plan->at<int32_t>(plan->lay.o_counts);
   if (plan->r_T > 0) {
-    {
-      TraceScope ts(plan, "centroid_norm", -1, st);
-      HIP_TRY(launch_centroid_norm(C, plan->c_T, (int)k, cn, st));
-    }
     if (kmeans_fused_ok(plan, k)) {
-      const ilargi_status_t rc = kmeans_fused(plan, C, (int)k, cn, assign != nullptr ? assign : reinterpret_cast<int32_t*>(P), G, cnt, st);
-      if (rc != ILARGI_OK) return rc;
+      return kmeans_fused(plan, C, (int)k, assign != nullptr ? assign : reinterpret_cast<int32_t*>(P), counts, st);
     } else {
+      {
+        TraceScope ts(plan, "centroid_norm", -1, st);
+        HIP_TRY(launch_centroid_norm(C, plan->c_T, (int)k, cn, st));
+      }
       ilargi_status_t rc = ilargi_lmm(plan, C, k, P, ILARGI_F32, stream);
       if (rc != ILARGI_OK) return rc;
       {

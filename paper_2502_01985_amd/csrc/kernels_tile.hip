@@ -362,8 +362,41 @@ __global__ __launch_bounds__(kBlock, 4) void asm_tile_kernel(LmmArgs a, int logR
 // 1,000,000 x 20 joined with 100,000 rows, 10 centroids: 58 microseconds; T C (65), the assignment (21) and S^T A (38)
 // by themselves took 124.  Of the 58, 8 are the gathers, 8 the cluster sums and most of the rest the operand's way
 // through LDS to every lane (smaller tiles, which spread a row over lanes, measure 3 to 26 % slower).
+// The squared norm of every centroid, by every workgroup: C is a few kilobytes, and a launch for it takes as long as this.
+// Added in the order of centroid_norm_kernel, so that both forms of a Lloyd iteration see the same bits.  red: k x kBlock.
+template <int KC>
+__device__ __forceinline__ void centroid_norms(const float* __restrict__ C, int ldc, int c_T, int k, float* red, float* cns) {
+  const int tid = threadIdx.x;
+  float s[KC];
+#pragma unroll
+  for (int n = 0; n < KC; ++n) s[n] = 0.0f;
+  for (int t = tid; t < c_T; t += kBlock) {
+#pragma unroll
+    for (int n = 0; n < KC; ++n) {
+      const float v = n < k ? C[(int64_t)t * ldc + n] : 0.0f;
+      s[n] = fmaf(v, v, s[n]);
+    }
+  }
+#pragma unroll
+  for (int n = 0; n < KC; ++n)
+    if (n < k) red[n * kBlock + tid] = s[n];
+  __syncthreads();
+  static_assert(kBlock == 4 * kWave, "two steps of the tree before a wavefront's");
+  const int lane = tid % kWave;
+  for (int n = tid / kWave; n < KC; n += kBlock / kWave) {        // the tree of that kernel, a wavefront per centroid
+    float v = 0.0f;
+    if (n < k) {
+      const float* r = red + n * kBlock + lane;
+      v = (r[0] + r[2 * kWave]) + (r[kWave] + r[3 * kWave]);
+      for (int w = kWave / 2; w > 0; w >>= 1) v += __shfl_down(v, w);
+    }
+    if (lane == 0) cns[n] = v;
+  }
+  __syncthreads();
+}
+
 template <int KC, bool AL>
-__global__ __launch_bounds__(kBlock, 4) void kmeans_tile_kernel(LmmArgs a, const float* __restrict__ cn, int32_t* __restrict__ assign,
+__global__ __launch_bounds__(kBlock, 4) void kmeans_tile_kernel(LmmArgs a, int c_T, int32_t* __restrict__ assign,
                                                              int32_t* __restrict__ counts_partial, float* __restrict__ sum_partial,
                                                              int logR) {
   extern __shared__ v4f tile_lds4[];
@@ -380,9 +413,9 @@ __global__ __launch_bounds__(kBlock, 4) void kmeans_tile_kernel(LmmArgs a, const
     const int t = a.colmap[j];
     Xs[e] = (t >= 0 && n < k) ? a.X[(int64_t)t * a.ldx + n] : 0.0f;
   }
-  for (int e = tid; e < k * kBlock; e += kBlock) acc[e] = 0.0f;
-  if (tid < KC) cns[tid] = tid < k ? cn[tid] : 0.0f;
   if (tid < k) hist[tid] = 0;
+  centroid_norms<KC>(a.X, a.ldx, c_T, k, acc, cns);      // (acc is scratch until here)
+  for (int e = tid; e < k * kBlock; e += kBlock) acc[e] = 0.0f;
   const int Rt = 1 << logR, logL = 8 - logR;
   const int row = tid >> logL, l = tid & ((1 << logL) - 1);
   const bool rotate = ((ck >> logL) & 1) == 0;
@@ -779,7 +812,7 @@ int kmeans_tile_grid(const LmmArgs& a, int* logR) {
 }
 
 // counts_partial: grid x k integers, sum_partial: grid x ck x k floats.
-hipError_t launch_kmeans_tile(const LmmArgs& a, const float* cn, int32_t* assign, int32_t* counts_partial, float* sum_partial,
+hipError_t launch_kmeans_tile(const LmmArgs& a, int64_t c_T, int32_t* assign, int32_t* counts_partial, float* sum_partial,
                               int grid, int logR, hipStream_t st) {
   if (!kmeans_tile_supported(a.ck, a.ncols) || a.D == nullptr || a.r_out <= 0) return hipErrorInvalidValue;
   const int kc = (a.ncols + 3) / 4 * 4;
@@ -787,8 +820,8 @@ hipError_t launch_kmeans_tile(const LmmArgs& a, const float* cn, int32_t* assign
   const bool al = reinterpret_cast<uintptr_t>(a.D) % 16 == 0;
 #define ILARGI_KMEANS(C)                                                                                               \
   do {                                                                                                                 \
-    if (al) kmeans_tile_kernel<C, true><<<grid, kBlock, lds, st>>>(a, cn, assign, counts_partial, sum_partial, logR);  \
-    else kmeans_tile_kernel<C, false><<<grid, kBlock, lds, st>>>(a, cn, assign, counts_partial, sum_partial, logR);    \
+    if (al) kmeans_tile_kernel<C, true><<<grid, kBlock, lds, st>>>(a, (int)c_T, assign, counts_partial, sum_partial, logR);  \
+    else kmeans_tile_kernel<C, false><<<grid, kBlock, lds, st>>>(a, (int)c_T, assign, counts_partial, sum_partial, logR);    \
   } while (0)
   if (kc == 4) ILARGI_KMEANS(4);
   else if (kc == 8) ILARGI_KMEANS(8);

@@ -454,16 +454,19 @@ __global__ __launch_bounds__(kBlock) void colasm_kernel(ColAsmArgs a) {
 // The same with sources that still hold per-workgroup partial blocks (nparts[k] blocks of c_k x cx): one workgroup
 // per target column; thread (n, slice) adds the blocks slice, slice + S, ... of operand column n, the slices are
 // added in order through LDS, the sources in source order.  For operands of at most 64 columns.
+// MODE 2: the means of KMeans, from about a thousand blocks of a source and as many shares of the sizes: 1024 threads (9
+// microseconds, 14 with 256); the others have a few hundred blocks and no more to gain.
 template <int MODE>
-__global__ __launch_bounds__(kBlock) void colasm_parts_kernel(ColAsmArgs a, int nw) {
-  __shared__ float part[kBlock];
+__global__ __launch_bounds__(MODE == 2 ? 1024 : kBlock) void colasm_parts_kernel(ColAsmArgs a, int nw) {
+  constexpr int kPartsBlock = MODE == 2 ? 1024 : kBlock;
+  __shared__ float part[kPartsBlock];
   const int t = blockIdx.x;
   if (t >= a.c_T) {
     if constexpr (MODE == 1) {
       // one extra workgroup: loss[n] = scale * sum of the per-workgroup partials, wavefront per column
       if (a.loss != nullptr) {
         const int lane = threadIdx.x % kWave;
-        for (int n = threadIdx.x / kWave; n < a.cx; n += kBlock / kWave) {
+        for (int n = threadIdx.x / kWave; n < a.cx; n += kPartsBlock / kWave) {
           float s = 0.0f;
           for (int b = lane; b < a.n_loss_partial; b += kWave) s += a.loss_partial[(int64_t)b * a.cx + n];
           for (int m = kWave / 2; m >= 1; m >>= 1) s += __shfl_xor(s, m);
@@ -473,7 +476,28 @@ __global__ __launch_bounds__(kBlock) void colasm_parts_kernel(ColAsmArgs a, int 
     }
     return;
   }
-  const int n = threadIdx.x % nw, sl = threadIdx.x / nw, ns = kBlock / nw;
+  const int n = threadIdx.x % nw, sl = threadIdx.x / nw, ns = kPartsBlock / nw;
+  int members = 0;
+  if constexpr (MODE == 2) {
+    // the cluster's size, which every workgroup adds up for itself: a launch for it takes as long as its share of this one
+    __shared__ int ipart[kPartsBlock];
+    int c = 0;
+    if (n < a.cx) {
+      for (int b = sl; b < a.n_sizes; b += 8 * ns) {
+        int v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = b + u * ns < a.n_sizes ? a.sizes[(int64_t)(b + u * ns) * a.cx + n] : 0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) c += v[u];
+      }
+    }
+    ipart[threadIdx.x] = c;
+    __syncthreads();
+    if (sl == 0) {
+      for (int q = 0; q < ns; ++q) members += ipart[q * nw + n];
+      if (t == 0 && a.counts != nullptr && n < a.cx) a.counts[n] = members;
+    }
+  }
   float acc = 0.0f;
   for (int k = 0; k < a.n; ++k) {
     const int j = a.tcol2src[k][t];
@@ -482,19 +506,23 @@ __global__ __launch_bounds__(kBlock) void colasm_parts_kernel(ColAsmArgs a, int 
     if (j >= 0 && n < a.cx) {
       const float* g = a.G[k] + (int64_t)j * a.cx + n;
       const int64_t stride = (int64_t)a.ck[k] * a.cx;
-      float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
-      int b = sl;
-      for (; b + 3 * ns < np; b += 4 * ns) {
-        s0 += g[(int64_t)b * stride]; s1 += g[(int64_t)(b + ns) * stride];
-        s2 += g[(int64_t)(b + 2 * ns) * stride]; s3 += g[(int64_t)(b + 3 * ns) * stride];
+      for (int b = sl; b < np; b += 8 * ns) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = b + u * ns < np ? g[(int64_t)(b + u * ns) * stride] : 0.0f;
+        s += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
       }
-      for (; b < np; b += ns) s0 += g[(int64_t)b * stride];
-      s = (s0 + s1) + (s2 + s3);
     }
     __syncthreads();                                   // the previous source's sums are consumed
     part[threadIdx.x] = s;
     __syncthreads();
-    if (sl == 0) {
+    if constexpr (MODE == 2) {
+      for (int w = ns / 2; w >= 1; w >>= 1) {
+        if (sl < w) part[threadIdx.x] += part[threadIdx.x + w * nw];
+        __syncthreads();
+      }
+      if (sl == 0) acc += part[n];
+    } else if (sl == 0) {
       float v = 0.0f;
       for (int q = 0; q < ns; ++q) v += part[q * nw + n];
       acc += v;
@@ -503,7 +531,8 @@ __global__ __launch_bounds__(kBlock) void colasm_parts_kernel(ColAsmArgs a, int 
   if (sl == 0 && n < a.cx) {
     float* o = a.out + (int64_t)t * a.cx + n;
     if constexpr (MODE == 0) *o = acc;
-    else *o = *o - a.lr[n] * (acc * a.inv_rT);
+    else if constexpr (MODE == 1) *o = *o - a.lr[n] * (acc * a.inv_rT);
+    else if (members > 0) *o = acc / (float)members;
   }
 }
 
@@ -625,10 +654,12 @@ hipError_t launch_colasm(const ColAsmArgs& a, int mode, hipStream_t st) {
   if (total <= 0) return hipSuccess;
   bool parts = false;
   for (int k = 0; k < a.n; ++k) parts = parts || a.nparts[k] > 1;
-  if (parts && a.cx <= 64) {
+  if (mode == 2 && a.cx > 64) return hipErrorInvalidValue;
+  if ((parts || mode == 2) && a.cx <= 64) {
     const int nw = a.cx <= 16 ? 16 : (a.cx <= 32 ? 32 : 64);
     const int grid = a.c_T + ((mode == 1 && a.loss != nullptr) ? 1 : 0);
     if (mode == 0) colasm_parts_kernel<0><<<grid, kBlock, 0, st>>>(a, nw);
+    else if (mode == 2) colasm_parts_kernel<2><<<grid, 1024, 0, st>>>(a, nw);
     else colasm_parts_kernel<1><<<grid, kBlock, 0, st>>>(a, nw);
     return hipGetLastError();
   }
