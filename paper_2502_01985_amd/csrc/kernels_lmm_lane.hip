@@ -30,7 +30,7 @@ namespace {
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kLaneGather = 3;                 // gathered sources
-constexpr int kLaneWaves = kBlock / kWave;
+constexpr int kLaneBlockWaves = kBlock / kWave;
 
 __device__ __forceinline__ void lane_wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -42,10 +42,21 @@ __device__ __forceinline__ float lane_uniform(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
 }
 
+// The first n[s] products of source s in LDS, from float off[s] on.
+struct LaneLds { int n[kLaneGather], off[kLaneGather]; };
+constexpr int kLaneLdsWaves = 16, kLaneLdsBytes = 156 << 10;
+
 // RPL rows per lane (1: rows of whole float4, 2: rows of an odd number of float2), NV float4 per unit.
-template <int RPL, int NV, int MODE, bool NT>
-__global__ __launch_bounds__(kBlock) void lmm_lane_kernel(LmmArgs a) {
+// WAVES: wavefronts of a workgroup.  With kLaneLdsWaves of them a workgroup has a compute unit for itself, and what its LDS
+// holds beside the tiles takes products of the smaller tables: a gather from there costs an eighteenth of one that goes to
+// the L2, whose request rate bounds this kernel.  The lanes that find theirs in LDS request the first product of the table
+// instead, one line for all of them.  5,000,000 x 10 with three joined tables of 100,000, 50,000 and 10,000 rows, all of the
+// last and 10,000 products of the second in LDS: 81 microseconds, 89 without.
+template <int RPL, int NV, int MODE, bool NT, int WAVES>
+__global__ __launch_bounds__(WAVES * kWave) void lmm_lane_kernel(LmmArgs a, LaneLds pl) {
   constexpr int CK = 4 * NV / RPL;                              // columns of the table
+  constexpr int kLaneWaves = WAVES;
+  constexpr bool LDSP = WAVES == kLaneLdsWaves;
   extern __shared__ v4f lds4[];
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
   v4f* tile = lds4 + (size_t)wave * kWave * NV;
@@ -111,7 +122,8 @@ __global__ __launch_bounds__(kBlock) void lmm_lane_kernel(LmmArgs a) {
       for (int h = 0; h < RPL; ++h) y[h] = 0.0f;
     }
   };
-  // a missing key reads row 0; its value is dropped when it is used
+  const float* prod = reinterpret_cast<const float*>(lds4 + (size_t)WAVES * kWave * NV);
+  // a missing key reads row 0; its value is dropped when it is used, like that of a product that is in LDS
   auto gather = [&](const int (&j)[kLaneGather][RPL], float (&p)[kLaneGather][RPL]) {
 #pragma unroll
     for (int s = 0; s < kLaneGather; ++s) {
@@ -119,7 +131,10 @@ __global__ __launch_bounds__(kBlock) void lmm_lane_kernel(LmmArgs a) {
       for (int h = 0; h < RPL; ++h) p[s][h] = 0.0f;
       if (s < ng) {
 #pragma unroll
-        for (int h = 0; h < RPL; ++h) p[s][h] = gP[s][(int64_t)max(j[s][h], 0) * ldp];
+        for (int h = 0; h < RPL; ++h) {
+          const int row = LDSP && j[s][h] < pl.n[s] ? 0 : max(j[s][h], 0);
+          p[s][h] = gP[s][(int64_t)row * ldp];
+        }
       }
     }
   };
@@ -127,7 +142,7 @@ __global__ __launch_bounds__(kBlock) void lmm_lane_kernel(LmmArgs a) {
   float gacc[CK];
 #pragma unroll
   for (int j = 0; j < CK; ++j) gacc[j] = 0.0f;
-  float loss_local = 0.0f;
+  float loss_local = 0.0f, loss_lost = 0.0f;
 
   v4f vn[NV];
   int jc[kLaneGather][RPL], jn[kLaneGather][RPL];
@@ -137,13 +152,29 @@ __global__ __launch_bounds__(kBlock) void lmm_lane_kernel(LmmArgs a) {
   load_y(chunk, yn);
   load_idx(chunk + cstride, jn);
   gather(jc, pn);
+  if constexpr (LDSP) {
+    float* to = reinterpret_cast<float*>(lds4 + (size_t)WAVES * kWave * NV);
+#pragma unroll
+    for (int s = 0; s < kLaneGather; ++s)
+      if (s < ng)
+        for (int k = tid; k < pl.n[s]; k += WAVES * kWave) to[pl.off[s] + k] = gP[s][(int64_t)k * ldp];
+    __syncthreads();
+  }
   for (; chunk < nchunks; chunk += cstride) {
     // this step's values (all requested a step ago) leave the request registers
     float pc[kLaneGather][RPL], yc[RPL];
 #pragma unroll
     for (int s = 0; s < kLaneGather; ++s)
 #pragma unroll
-      for (int h = 0; h < RPL; ++h) pc[s][h] = jc[s][h] >= 0 ? pn[s][h] : 0.0f;
+      for (int h = 0; h < RPL; ++h) {
+        float v = pn[s][h];
+        if constexpr (LDSP) {
+          const bool in = jc[s][h] < pl.n[s];
+          const float w = prod[in ? pl.off[s] + max(jc[s][h], 0) : 0];
+          v = in ? w : v;
+        }
+        pc[s][h] = jc[s][h] >= 0 ? v : 0.0f;
+      }
 #pragma unroll
     for (int h = 0; h < RPL; ++h) yc[h] = yn[h];
     lane_wave_sync();                                           // the previous step's tile is consumed
@@ -186,12 +217,12 @@ __global__ __launch_bounds__(kBlock) void lmm_lane_kernel(LmmArgs a) {
         r[h] = live ? zz - yc[h] : 0.0f;
         loss_local = fmaf(r[h], r[h], loss_local);
       } else {
-        // one exponential serves the sigmoid and the softplus: e = exp(-|z|)
-        const float e = __expf(-fabsf(zz));
-        const float inv = __builtin_amdgcn_rcpf(1.0f + e);
-        const float sg = zz >= 0.0f ? inv : e * inv;
-        r[h] = live ? sg - yc[h] : 0.0f;
-        loss_local += live ? fmaxf(zz, 0.0f) + __logf(1.0f + e) - yc[h] * zz : 0.0f;
+        float loss = 0.0f;
+        r[h] = logistic_residual(zz, yc[h], loss);
+        if (!live) r[h] = loss = 0.0f;
+        const float add = loss - loss_lost, sum = loss_local + add;   // compensated: with zero weights every row adds log 2,
+        loss_lost = (sum - loss_local) - add;                         // and the roundings of a lane's sum all go one way
+        loss_local = sum;
       }
     }
     if (live) {
@@ -229,35 +260,40 @@ __global__ __launch_bounds__(kBlock) void lmm_lane_kernel(LmmArgs a) {
     }
     __syncthreads();
     if (tid <= CK) {
-      float s = 0.0f;
-      for (int wv = 0; wv < kLaneWaves; ++wv) s += red[wv * (CK + 1) + tid];
+      float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};                  // (four at a time: sixteen in a row would round more often)
+#pragma unroll
+      for (int wv = 0; wv < kLaneWaves; ++wv) part[wv / 4] += red[wv * (CK + 1) + tid];
+      const float s = (part[0] + part[1]) + (part[2] + part[3]);
       if (tid < CK) a.grad_partial[((int64_t)blockIdx.x * CK + tid) * kNarrowCT] = s;
       else a.loss_partial[(int64_t)blockIdx.x * kNarrowCT] = s;
     }
   }
 }
 
-typedef void (*LaneFn)(LmmArgs);
+typedef void (*LaneFn)(LmmArgs, LaneLds);
 
 template <int RPL, int NV, bool NT>
-LaneFn pick_lane(int mode) {
-  return mode == 0 ? lmm_lane_kernel<RPL, NV, 0, NT> : (mode == 1 ? lmm_lane_kernel<RPL, NV, 1, NT> : lmm_lane_kernel<RPL, NV, 2, NT>);
+LaneFn pick_lane(int mode, bool in_lds) {
+  if constexpr (NT && NV <= 5)
+    if (in_lds) return mode == 1 ? lmm_lane_kernel<RPL, NV, 1, NT, kLaneLdsWaves> : lmm_lane_kernel<RPL, NV, 2, NT, kLaneLdsWaves>;
+  return mode == 0 ? lmm_lane_kernel<RPL, NV, 0, NT, kLaneBlockWaves>
+                   : (mode == 1 ? lmm_lane_kernel<RPL, NV, 1, NT, kLaneBlockWaves> : lmm_lane_kernel<RPL, NV, 2, NT, kLaneBlockWaves>);
 }
 
 // Built for rows of 6, 10 and 14 columns (pairs of 8-byte aligned rows).  For rows of whole float4 the same kernel
 // (RPL = 1) measured 2 us faster than the flat-stream assembly on tables that sit in the last-level cache and 2 us
 // slower on tables that come from memory, so those keep the flat-stream kernel.
-LaneFn lane_fn(int rpl, int nv, int mode, bool nt) {
+LaneFn lane_fn(int rpl, int nv, int mode, bool nt, bool in_lds = false) {
   if (rpl != 2) return nullptr;
   switch (nv) {
-    case 3: return nt ? pick_lane<2, 3, true>(mode) : pick_lane<2, 3, false>(mode);
-    case 5: return nt ? pick_lane<2, 5, true>(mode) : pick_lane<2, 5, false>(mode);
-    case 7: return nt ? pick_lane<2, 7, true>(mode) : pick_lane<2, 7, false>(mode);
+    case 3: return nt ? pick_lane<2, 3, true>(mode, in_lds) : pick_lane<2, 3, false>(mode, in_lds);
+    case 5: return nt ? pick_lane<2, 5, true>(mode, in_lds) : pick_lane<2, 5, false>(mode, in_lds);
+    case 7: return nt ? pick_lane<2, 7, true>(mode, in_lds) : pick_lane<2, 7, false>(mode, in_lds);
     default: return nullptr;
   }
 }
 
-int lane_slots(LaneFn fn, size_t lds_bytes) {
+int lane_slots(LaneFn fn, size_t lds_bytes, int threads) {
   static std::mutex cache_mutex;
   std::lock_guard<std::mutex> lock(cache_mutex);
   static LaneFn seen_fn[64];
@@ -269,7 +305,7 @@ int lane_slots(LaneFn fn, size_t lds_bytes) {
   hipDeviceProp_t prop;
   if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0)
     cus = prop.multiProcessorCount;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(fn), kBlock, lds_bytes) != hipSuccess ||
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(fn), threads, lds_bytes) != hipSuccess ||
       per_cu < 1)
     per_cu = 1;
   if (n_seen < 64) { seen_fn[n_seen] = fn; seen_slots[n_seen] = per_cu * cus; ++n_seen; }
@@ -279,6 +315,29 @@ int lane_slots(LaneFn fn, size_t lds_bytes) {
 void lane_shape(const LmmArgs& a, int vec, int* rpl, int* nv) {
   *rpl = (vec == 2 && a.ck % 4 == 2) ? 2 : 1;
   *nv = *rpl * a.ck / 4;
+}
+
+// The products a workgroup of kLaneLdsWaves wavefronts keeps in LDS, the smallest tables first; whether that pays: with a
+// residual (without one the chip holds more wavefronts), rows of 6 or 10 columns (wider ones would spill registers), at least
+// half of a source's gathers from LDS in all, and an entity table that is read past the caches.  Iterations in microseconds,
+// without / with, rows of 10 columns: 20,000 products, 5,000,000 rows 96.0 / 86.9, 3,400,000 75.5 / 71.4, and read through the
+// caches 3,000,000 64.7 / 67.2, 1,000,000 38.3 / 41.7; three tables 174.9 / 166.2, 135.5 / 132.3, 129.8 / 127.3, 77.3 / 79.9.
+bool lane_lds(const LmmArgs& a, int mode, int nv, LaneLds* pl) {
+  memset(pl, 0, sizeof(*pl));
+  if (mode == 0 || nv > 5 || a.nt_in == 0) return false;
+  int order[kLaneGather];
+  for (int s = 0; s < a.g.n; ++s) order[s] = s;
+  std::sort(order, order + a.g.n, [&](int x, int y) { return a.g.rows[x] < a.g.rows[y]; });
+  int at = 0;
+  double share = 0.0;
+  for (int i = 0; i < a.g.n; ++i) {
+    const int s = order[i], room = kLaneLdsBytes / 4 - kLaneLdsWaves * kWave * nv * 4 - at;
+    pl->n[s] = (int)std::min<int64_t>(a.g.rows[s], room);
+    pl->off[s] = at;
+    at += pl->n[s];
+    share += a.g.rows[s] > 0 ? (double)pl->n[s] / (double)a.g.rows[s] : 1.0;
+  }
+  return 2.0 * share >= 1.0;
 }
 
 }  // namespace
@@ -310,16 +369,20 @@ hipError_t launch_lmm_lane(const LmmArgs& a, int vec, int mode, hipStream_t st, 
   if (!lmm_lane_supported(a, vec, mode, mode != 0)) return hipErrorInvalidValue;
   int rpl, nv;
   lane_shape(a, vec, &rpl, &nv);
-  LaneFn fn = lane_fn(rpl, nv, mode, a.nt_in != 0);
-  size_t lds_bytes = (size_t)kLaneWaves * kWave * nv * sizeof(v4f);
-  lds_bytes = std::max(lds_bytes, (size_t)kLaneWaves * (a.ck + 1) * sizeof(float));
+  LaneLds pl;
+  const bool in_lds = lane_lds(a, mode, nv, &pl);
+  const int waves = in_lds ? kLaneLdsWaves : kLaneBlockWaves;
+  LaneFn fn = lane_fn(rpl, nv, mode, a.nt_in != 0, in_lds);
+  size_t lds_bytes = (size_t)waves * kWave * nv * sizeof(v4f);
+  lds_bytes = std::max(lds_bytes, (size_t)waves * (a.ck + 1) * sizeof(float));
+  if (in_lds) lds_bytes = kLaneLdsBytes;
   const int64_t nchunks = (a.r_out / rpl + kWave - 1) / kWave;
-  int64_t grid = (nchunks + kLaneWaves - 1) / kLaneWaves;
-  int64_t cap = lane_slots(fn, lds_bytes);
+  int64_t grid = (nchunks + waves - 1) / waves;
+  int64_t cap = lane_slots(fn, lds_bytes, waves * kWave);
   if (mode != 0) cap = std::min<int64_t>(cap, kColredBlocks);
   if (grid > cap) grid = cap;
   if (grid_out) *grid_out = (int)grid;
-  hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kBlock), lds_bytes, st, a);
+  hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3((unsigned)(waves * kWave)), lds_bytes, st, a, pl);
   return hipGetLastError();
 }
 

@@ -850,3 +850,39 @@ def test_sparse_products_are_the_result(il, n, ncols, c_T_more, drop):
     W_ref, L_ref = oracle.gd(tg, "logistic", y, W0.astype(np.float32).astype(np.float64), lr, 4)
     assert np.linalg.norm(W.cpu().numpy() - W_ref) <= 1e-6 * np.linalg.norm(W_ref)
     np.testing.assert_allclose(losses.cpu().numpy(), np.asarray(L_ref).reshape(4, ncols), rtol=2e-6)
+
+
+@pytest.mark.parametrize("r_T,c,dims,missing", [
+    (3_355_444, 10, [20_479], 0.0),                # a whole table in LDS, the least rows that are read past the caches
+    (3_355_500, 10, [19_000, 1, 70_000], 0.2),     # two tables and a part of the third; a table of one row; missing keys
+    (5_592_406, 6, [26_000], 0.1),
+])
+@pytest.mark.parametrize("model", ["linear", "logistic"])
+def test_products_in_lds_beside_a_streamed_entity_table(il, r_T, c, dims, missing, model):
+    gen = torch.Generator(device="cuda").manual_seed(r_T + c)
+    S = torch.randn((r_T, c), generator=gen, device="cuda")
+    sources, at = [(S, None, list(range(c)))], c
+    for rows in dims:
+        idx = torch.randint(0, rows, (r_T,), generator=gen, device="cuda", dtype=torch.int32)
+        idx[torch.rand(r_T, generator=gen, device="cuda") < missing] = -1
+        idx[:2] = torch.tensor([rows - 1, 0], dtype=torch.int32)
+        sources.append((torch.randn((rows, 4), generator=gen, device="cuda"), idx, list(range(at, at + 4))))
+        at += 4
+    y = (torch.rand(r_T, generator=gen, device="cuda") < 0.5).float()
+    w = torch.randn((at, 1), generator=gen, device="cuda", dtype=torch.float64) / at ** 0.5
+    z = S.double() @ w[:c]
+    for D, idx, cm in sources[1:]:
+        z += torch.where(idx >= 0, (D.double() @ w[cm[0]:cm[-1] + 1])[idx.long().clamp(min=0), 0], 0.0).unsqueeze(1)
+    e = (torch.sigmoid(z) if model == "logistic" else z) - y.double().unsqueeze(1)
+    grads = [S.double().t() @ e]
+    for D, idx, cm in sources[1:]:
+        Z = torch.zeros((len(D), 1), dtype=torch.float64).index_add_(0, idx.cpu()[idx.cpu() >= 0].long(), e.cpu()[idx.cpu() >= 0])
+        grads.append(D.double().t() @ Z.cuda())
+    loss = (torch.nn.functional.softplus(z) - y.double().unsqueeze(1) * z).mean() if model == "logistic" else (e * e).mean() / 2
+    plan = il.ilargi_plan_create(sources, r_T, at, max_cx=1)
+    W, got = w.float(), torch.empty(1, device="cuda")
+    il.ilargi_gd_step(plan, il.LOGISTIC if model == "logistic" else il.LINEAR, W, y, torch.full((1,), 0.5, device="cuda"), got)
+    want = w.float().double() - 0.5 * torch.cat(grads) / r_T
+    # float32 products of ten to twenty terms: residuals to some 1e-6, gradients averaged over millions of them
+    assert float((W.double() - want).norm() / want.norm()) < 1e-6
+    assert abs(float(got) - float(loss)) < 2e-6 * abs(float(loss))
