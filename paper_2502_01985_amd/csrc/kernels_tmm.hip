@@ -66,14 +66,15 @@ __host__ __device__ __forceinline__ int segsum_chunk_blocks(int n_chunks) {
 // 333,333 rows over 9,001 Zipf and 41,003 uniform keys, three columns: 13 microseconds in one launch, and 4 for the chunks
 // (groups that walk segments of up to 512 entries: 20; such keys without the skew 9).  What is left are 650,000 gathers
 // from a residual of 4 MB, which does not stay in an XCD's L2 beside the index.
-template <int CT>
+// CHUNKS: some source has chunks.
+template <int CT, bool CHUNKS>
 __global__ __launch_bounds__(kBlock) void segsum_narrow_kernel(SegMulti m) {
   int q = 0;
   while (q + 1 < m.n && (int)blockIdx.x >= m.first[q + 1]) ++q;
   const SegArgs a = m.s[q];
-  const int bx = (int)blockIdx.x - m.first[q], chunk_blocks = segsum_chunk_blocks(a.n_chunks);
+  const int bx = (int)blockIdx.x - m.first[q], chunk_blocks = CHUNKS ? segsum_chunk_blocks(a.n_chunks) : 0;
   float acc[CT];
-  if (bx < chunk_blocks) {
+  if (CHUNKS && bx < chunk_blocks) {
     const int lane = threadIdx.x % kWave;
     for (int c = bx * (kBlock / kWave) + threadIdx.x / kWave; c < a.n_chunks; c += chunk_blocks * (kBlock / kWave)) {
       segsum_range<CT>(a, a.chunk_beg[c], a.chunk_end[c], lane, kWave, acc);
@@ -662,16 +663,24 @@ hipError_t launch_segsum_narrow(const SegArgs* a, int n, hipStream_t st) {
   SegMulti m;
   memset(&m, 0, sizeof(m));
   m.n = n;
+  bool chunks = false;
   for (int q = 0; q < n; ++q) {
     if (a[q].ncols < 1 || a[q].ncols > kNarrowCT || a[q].ncols != a[0].ncols || a[q].r_k <= 0) return hipErrorInvalidValue;
     m.s[q] = a[q];
     const int64_t gpb = kBlock >> a[q].logG;
+    chunks = chunks || a[q].n_chunks > 0;
     m.first[q + 1] = m.first[q] + segsum_chunk_blocks(a[q].n_chunks) + (int)std::min<int64_t>((a[q].r_k + gpb - 1) / gpb, 65536);
   }
   const unsigned grid = (unsigned)m.first[n];
-  if (a[0].ncols == 1) segsum_narrow_kernel<1><<<grid, kBlock, 0, st>>>(m);
-  else if (a[0].ncols == 2) segsum_narrow_kernel<2><<<grid, kBlock, 0, st>>>(m);
-  else segsum_narrow_kernel<4><<<grid, kBlock, 0, st>>>(m);
+#define ILARGI_SEGSUM(C)                                                          \
+  do {                                                                            \
+    if (chunks) segsum_narrow_kernel<C, true><<<grid, kBlock, 0, st>>>(m);        \
+    else segsum_narrow_kernel<C, false><<<grid, kBlock, 0, st>>>(m);              \
+  } while (0)
+  if (a[0].ncols == 1) ILARGI_SEGSUM(1);
+  else if (a[0].ncols == 2) ILARGI_SEGSUM(2);
+  else ILARGI_SEGSUM(4);
+#undef ILARGI_SEGSUM
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_combine(m, st);
