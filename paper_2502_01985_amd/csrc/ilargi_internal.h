@@ -25,7 +25,7 @@ constexpr int kSlLong = 256;         // ... runs of a (slice, source row) longer
 constexpr int kSlChunk = 1024;       // ... of this many entries, each summed by a whole workgroup
 constexpr int kLongSeg = 2048;       // inverse-index segments longer than this keep a plan off the join-order paths, and
                                      // the most entries of a segment that the segment sums leave uncut
-constexpr int kSegCut = 256;         // the least (a plan picks its own threshold between the two)
+constexpr int kSegCut = 256;         // least entries of a chunk of a longer segment (a plan picks its own length between the two)
 constexpr int kSortChunk = 2048;     // keys per workgroup in one radix pass
 constexpr int kMaxLdsFloats = 4096;  // 16 KiB of LDS for the staged operand rows (also the column limit of a source)
 constexpr int64_t kGramPartialFloats = 16ll << 20;
