@@ -110,10 +110,11 @@ __device__ __forceinline__ void segbin_windows_sum(const SegBin& a, const float*
     const uint32_t t0 = (uint32_t)w * WIN;                  // (32 bits throughout, which scalar instructions compare)
     const uint32_t left = w < w1 ? min(rT - t0, (uint32_t)WIN) : 0u;
     const __amdgpu_buffer_rsrc_t rows = bin_buffer(Y + (uint64_t)t0 * ldy, left * ldy * 4u);
+    // (all of an offset goes into the lane's: the scalar one has no part in the check against the buffer's length)
     if constexpr (PLAIN) {
 #pragma unroll
       for (int u = 0; u < RV / 4; ++u) {
-        const u4 v = __builtin_amdgcn_raw_buffer_load_b128(rows, tid * 16, u * kBinThreads * 16, 0);
+        const u4 v = __builtin_amdgcn_raw_buffer_load_b128(rows, tid * 16 + u * kBinThreads * 16, 0, 0);
 #pragma unroll
         for (int c = 0; c < 4; ++c) r[4 * u + c] = __uint_as_float(v[c]);
       }

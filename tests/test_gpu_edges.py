@@ -886,3 +886,16 @@ def test_products_in_lds_beside_a_streamed_entity_table(il, r_T, c, dims, missin
     # float32 products of ten to twenty terms: residuals to some 1e-6, gradients averaged over millions of them
     assert float((W.double() - want).norm() / want.norm()) < 1e-6
     assert abs(float(got) - float(loss)) < 2e-6 * abs(float(loss))
+
+
+@pytest.mark.parametrize("rows", [1_000, 30_000, 100_000])        # windows of 2^12, 2^13, 2^14 rows
+@pytest.mark.parametrize("short", [0, 4, 16_380, 1, 4_099])       # on 16 bytes; on any float
+def test_segment_sums_in_lds_of_an_operand_that_ends_with_its_allocation(il, rows, short):
+    # the windows requested ahead and the rest of the last one lie past the operand's end
+    whole = torch.randint(-3, 4, ((14 << 20) // 4,), device="cuda").float()
+    Y = whole[short:].reshape(-1, 1)
+    sources, c_T, _ = _keyed(31 + rows, len(Y), [(rows, 0)])
+    plan = il.ilargi_plan_create(sources, len(Y), c_T, max_cx=1)
+    D, idx, _ = sources[0]
+    z = torch.zeros(rows, 1, dtype=torch.float64).index_add_(0, idx.cpu().long(), Y.cpu().double())
+    assert torch.equal(il.ilargi_tmm(plan, Y).cpu().double(), D.cpu().double().t() @ z)
