@@ -435,9 +435,9 @@ int32_t longest_segment(const std::vector<int32_t>& rowptr) {
   return longest;
 }
 
-// Lists the segments longer than thr in chunks of len entries, len >= thr (host side, once per plan): first those of more
-// than one chunk, which long_seg and long_first name, then the others, a chunk each.
-void build_long_tables(const std::vector<int32_t>& rowptr, int32_t thr, int32_t len, std::vector<int32_t>& chunk_seg,
+// Lists the segments longer than thr in chunks (host side, once per plan): first those longer than whole, in chunks of len
+// entries each, len <= whole, which long_seg and long_first name, then the others, a chunk each.
+void build_long_tables(const std::vector<int32_t>& rowptr, int32_t thr, int32_t whole, int32_t len, std::vector<int32_t>& chunk_seg,
                        std::vector<int32_t>& chunk_beg, std::vector<int32_t>& chunk_end,
                        std::vector<int32_t>& long_seg, std::vector<int32_t>& long_first) {
   std::vector<int32_t> single;
@@ -445,7 +445,7 @@ void build_long_tables(const std::vector<int32_t>& rowptr, int32_t thr, int32_t 
   for (size_t j = 0; j + 1 < rowptr.size(); ++j) {
     int32_t b = rowptr[j], e = rowptr[j + 1];
     if (e - b <= thr) continue;
-    if (e - b <= len) { single.push_back((int32_t)j); continue; }
+    if (e - b <= whole) { single.push_back((int32_t)j); continue; }
     long_seg.push_back((int32_t)j);
     for (int32_t c = b; c < e; c += len) {
       chunk_seg.push_back((int32_t)j);
@@ -1445,7 +1445,7 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     const int64_t avg = p.rows > 0 ? (p.nnz + p.rows - 1) / p.rows : 1;
     // lanes per segment of the narrow segment sum: about four entries each, a lane per entry while that leaves the chip
     // room.  A longer segment than such a group sums in one go (eight entries a lane) is a wavefront's: in a chunk of its
-    // own, or in several from 256 entries (or what a group sums) on.  Both limits double until the tables have room.
+    // own up to 256 entries (or twice what a group sums), in several beyond.  The limits double until the tables have room.
     p.logG = std::min(6, ilog2_ceil(std::max<int64_t>((avg + 3) / 4, 1)));
     const int one_each = std::min(6, ilog2_ceil(std::max<int64_t>(avg, 1)));
     while (p.logG < one_each && p.rows << (p.logG + 1) <= 256 * 1024) ++p.logG;
@@ -1459,7 +1459,9 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     std::vector<int32_t> cs, cb, ce, ls, lf(1, 0);
     while (longest > p.long_thr) {
       lf.clear();
-      build_long_tables(rowptr, p.long_thr, std::max(kSegCut, p.long_thr), cs, cb, ce, ls, lf);
+      // (a segment in several chunks costs a launch, one of two rounds does not: 500,000 rows over 1,000 uniform keys, whose
+      // segments have 500 entries and lane groups sum 512)
+      build_long_tables(rowptr, p.long_thr, std::max(spread, p.long_thr), std::max(kSegCut, p.long_thr), cs, cb, ce, ls, lf);
       if ((int64_t)cs.size() <= p.nch_max || p.long_thr >= kLongSeg) break;
       p.long_thr *= 2;
       cs.clear(); cb.clear(); ce.clear(); ls.clear(); lf.clear();

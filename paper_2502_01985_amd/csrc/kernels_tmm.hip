@@ -60,9 +60,10 @@ __host__ __device__ __forceinline__ int segsum_chunk_blocks(int n_chunks) {
 }
 
 // Narrow form, CT columns per lane.  Bound by the two dependent round trips (index entry, operand row) per group of
-// entries, so a lane keeps eight entries in flight and no segment takes a second round: one that is longer than its group of
-// 2^logG lanes sums at once (a.long_thr) is a wavefront's, as a chunk of its own or, from 256 entries on, as several, which
-// segsum_combine_kernel adds up.
+// entries, so a lane keeps eight entries in flight.  A group of 2^logG lanes takes segments of up to max(64, 8 << logG)
+// entries (a.long_thr; more if the chunk tables have no room for the others, 2048 where segments have hundreds of entries
+// on average).  A longer one is a wavefront's: as a chunk of its own up to max(256, 16 << logG) entries, whose sum goes
+// straight to the result, and beyond that as several, which segsum_combine_kernel adds up.
 // 333,333 rows over 9,001 Zipf and 41,003 uniform keys, three columns: 13 microseconds in one launch, and 4 for the chunks
 // (groups that walk segments of up to 512 entries: 20; such keys without the skew 9).  What is left are 650,000 gathers
 // from a residual of 4 MB, which does not stay in an XCD's L2 beside the index.

@@ -899,3 +899,34 @@ def test_segment_sums_in_lds_of_an_operand_that_ends_with_its_allocation(il, row
     D, idx, _ = sources[0]
     z = torch.zeros(rows, 1, dtype=torch.float64).index_add_(0, idx.cpu().long(), Y.cpu().double())
     assert torch.equal(il.ilargi_tmm(plan, Y).cpu().double(), D.cpu().double().t() @ z)
+
+
+def _launches(fn):
+    """Kernels of one call, counted in a captured graph."""
+    import ctypes
+    fn()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        fn()
+    hip, count = ctypes.CDLL("libamdhip64.so"), ctypes.c_size_t(0)
+    hip.hipGraphGetNodes.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]
+    assert hip.hipGraphGetNodes(graph.raw_cuda_graph(), None, ctypes.byref(count)) == 0
+    return count.value
+
+
+@pytest.mark.parametrize("rows,lengths", [(1_000, range(440, 561)), (1_000, range(200, 601)), (5_000, [60] * 9 + [400])])
+@pytest.mark.parametrize("cx", [1, 4])
+def test_segments_around_a_group_of_lanes_cost_no_launch_of_their_own(il, rows, lengths, cx):
+    # lengths on both sides of what a group of lanes sums at once, none beyond twice that
+    rng = np.random.default_rng(rows)
+    idx = torch.from_numpy(rng.permutation(np.repeat(np.arange(rows, dtype=np.int32), rng.choice(list(lengths), rows)))).cuda()
+    even = torch.arange(len(idx), device="cuda", dtype=torch.int32) % rows
+    D = torch.randint(0, 3, (rows, 7), device="cuda").float()
+    Y = torch.randint(-3, 4, (len(idx), cx), device="cuda").float()
+    plan = il.ilargi_plan_create([(D, idx, list(range(7)))], len(idx), 7, max_cx=4)
+    level = il.ilargi_plan_create([(D, even, list(range(7)))], len(idx), 7, max_cx=4)
+    z = torch.zeros(rows, cx, dtype=torch.float64).index_add_(0, idx.cpu().long(), Y.cpu().double())
+    out = il.ilargi_tmm(plan, Y)
+    assert torch.equal(out.cpu().double(), D.cpu().double().t() @ z)
+    assert _launches(lambda: il.ilargi_tmm(plan, Y, out)) == _launches(lambda: il.ilargi_tmm(level, Y, out))
