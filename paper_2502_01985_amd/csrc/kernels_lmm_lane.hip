@@ -51,7 +51,8 @@ constexpr int kLaneLdsWaves = 16, kLaneLdsBytes = 156 << 10;
 // holds beside the tiles takes products of the smaller tables: a gather from there costs an eighteenth of one that goes to
 // the L2, whose request rate bounds this kernel.  The lanes that find theirs in LDS request the first product of the table
 // instead, one line for all of them.  5,000,000 x 10 with three joined tables of 100,000, 50,000 and 10,000 rows, all of the
-// last and 10,000 products of the second in LDS: 81 microseconds, 89 without.
+// last and 9,456 products of the second in LDS (19,456 are room beside tiles of 10 columns, 27,648 beside 6): 81 microseconds,
+// 89 without.
 template <int RPL, int NV, int MODE, bool NT, int WAVES>
 __global__ __launch_bounds__(WAVES * kWave) void lmm_lane_kernel(LmmArgs a, LaneLds pl) {
   constexpr int CK = 4 * NV / RPL;                              // columns of the table
@@ -169,8 +170,8 @@ __global__ __launch_bounds__(WAVES * kWave) void lmm_lane_kernel(LmmArgs a, Lane
       for (int h = 0; h < RPL; ++h) {
         float v = pn[s][h];
         if constexpr (LDSP) {
-          const bool in = jc[s][h] < pl.n[s];
-          const float w = prod[in ? pl.off[s] + max(jc[s][h], 0) : 0];
+          const bool in = (uint32_t)jc[s][h] < (uint32_t)pl.n[s];       // (not a missing key, whose place may be past the end)
+          const float w = prod[in ? pl.off[s] + jc[s][h] : 0];
           v = in ? w : v;
         }
         pc[s][h] = jc[s][h] >= 0 ? v : 0.0f;
@@ -320,7 +321,7 @@ void lane_shape(const LmmArgs& a, int vec, int* rpl, int* nv) {
 // The products a workgroup of kLaneLdsWaves wavefronts keeps in LDS, the smallest tables first; whether that pays: with a
 // residual (without one the chip holds more wavefronts), rows of 6 or 10 columns (wider ones would spill registers), at least
 // half of a source's gathers from LDS in all, and an entity table that is read past the caches.  Iterations in microseconds,
-// without / with, rows of 10 columns: 20,000 products, 5,000,000 rows 96.0 / 86.9, 3,400,000 75.5 / 71.4, and read through the
+// without / with, rows of 10 columns: one table of 20,000 rows, all but 544 in LDS, 5,000,000 rows 96.0 / 86.9, 3,400,000 75.5 / 71.4, and read through the
 // caches 3,000,000 64.7 / 67.2, 1,000,000 38.3 / 41.7; three tables 174.9 / 166.2, 135.5 / 132.3, 129.8 / 127.3, 77.3 / 79.9.
 bool lane_lds(const LmmArgs& a, int mode, int nv, LaneLds* pl) {
   memset(pl, 0, sizeof(*pl));

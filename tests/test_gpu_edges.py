@@ -853,7 +853,13 @@ def test_sparse_products_are_the_result(il, n, ncols, c_T_more, drop):
 
 
 @pytest.mark.parametrize("r_T,c,dims,missing", [
-    (3_355_444, 10, [20_479], 0.0),                # a whole table in LDS, the least rows that are read past the caches
+    (3_355_444, 10, [20_479], 0.0),                # nearly all of a table in LDS, the least rows that are read past the caches
+    (3_355_444, 10, [19_456], 0.1),                # the longest table that is in LDS as a whole, missing keys
+    (3_355_446, 10, [19_457], 0.0),                # one row too many
+    (3_355_444, 10, [19_456, 25_000], 0.3),        # no room for the second table, whose place is the end of the LDS
+    (3_355_444, 10, [19_500, 19_501, 60_000], 0.3),
+    (5_592_406, 6, [27_648, 30_000], 0.3),
+    (5_592_406, 6, [27_649], 0.1),
     (3_355_500, 10, [19_000, 1, 70_000], 0.2),     # two tables and a part of the third; a table of one row; missing keys
     (5_592_406, 6, [26_000], 0.1),
 ])
