@@ -222,7 +222,8 @@ __global__ __launch_bounds__(WAVES * kWave) void lmm_lane_kernel(LmmArgs a, Lane
         r[h] = logistic_residual(zz, yc[h], loss);
         if (!live) r[h] = loss = 0.0f;
         const float add = loss - loss_lost, sum = loss_local + add;   // compensated: with zero weights every row adds log 2,
-        loss_lost = (sum - loss_local) - add;                         // and the roundings of a lane's sum all go one way
+        // and the roundings of a lane's sum all go one way; what is infinite stays so
+        loss_lost = fabsf(sum) <= __FLT_MAX__ ? (sum - loss_local) - add : 0.0f;
         loss_local = sum;
       }
     }
@@ -321,8 +322,9 @@ void lane_shape(const LmmArgs& a, int vec, int* rpl, int* nv) {
 // The products a workgroup of kLaneLdsWaves wavefronts keeps in LDS, the smallest tables first; whether that pays: with a
 // residual (without one the chip holds more wavefronts), rows of 6 or 10 columns (wider ones would spill registers), at least
 // half of a source's gathers from LDS in all, and an entity table that is read past the caches.  Iterations in microseconds,
-// without / with, rows of 10 columns: one table of 20,000 rows, all but 544 in LDS, 5,000,000 rows 96.0 / 86.9, 3,400,000 75.5 / 71.4, and read through the
-// caches 3,000,000 64.7 / 67.2, 1,000,000 38.3 / 41.7; three tables 174.9 / 166.2, 135.5 / 132.3, 129.8 / 127.3, 77.3 / 79.9.
+// without / with, rows of 10 columns: one table of 20,000 rows, all but 544 in LDS, 5,000,000 target rows 96.0 / 86.9,
+// 3,400,000 75.5 / 71.4, and read through the caches 3,000,000 64.7 / 67.2, 1,000,000 38.3 / 41.7; three tables 174.9 / 166.2,
+// 135.5 / 132.3, 129.8 / 127.3, 77.3 / 79.9.
 bool lane_lds(const LmmArgs& a, int mode, int nv, LaneLds* pl) {
   memset(pl, 0, sizeof(*pl));
   if (mode == 0 || nv > 5 || a.nt_in == 0) return false;

@@ -936,3 +936,21 @@ def test_segments_around_a_group_of_lanes_cost_no_launch_of_their_own(il, rows, 
     out = il.ilargi_tmm(plan, Y)
     assert torch.equal(out.cpu().double(), D.cpu().double().t() @ z)
     assert _launches(lambda: il.ilargi_tmm(plan, Y, out)) == _launches(lambda: il.ilargi_tmm(level, Y, out))
+
+
+@pytest.mark.parametrize("c,r_T", [(6, 3_001 * 2), (10, 200_000), (14, 50_000), (6, 5_592_406), (10, 3_355_444), (14, 2_396_746)])
+@pytest.mark.parametrize("at", ["first", "middle", "last", "sum"])
+def test_logistic_loss_beyond_the_range_is_infinite(il, c, r_T, at):
+    # entity tables read through the caches and past them; a row whose own loss is infinite, and rows whose sum is
+    S = torch.full((r_T, c), 0.25, device="cuda")
+    idx = torch.arange(r_T, device="cuda", dtype=torch.int32) % 100
+    y = torch.ones(r_T, device="cuda")
+    W = torch.full((c + 1, 1), 1.0, device="cuda")
+    if at == "sum":
+        S[:, 0] = -2e38                                           # (z = -2e38 in every row, the loss of each is its negative)
+    else:
+        S[{"first": 0, "middle": r_T // 2, "last": r_T - 1}[at], :2] = -3e38
+    plan = il.ilargi_plan_create([(S, None, list(range(c))), (torch.ones(100, 1, device="cuda"), idx, [c])], r_T, c + 1, max_cx=1)
+    loss = torch.zeros(1, device="cuda")
+    il.ilargi_gd_step(plan, il.LOGISTIC, W, y, torch.zeros(1, device="cuda"), loss)
+    assert float(loss) == float("inf")
