@@ -67,11 +67,13 @@ struct SourcePlan {
   int max_row = 0, max_col = 0;   // sparse: most entries of a row, of a column
   size_t o_join_first = 0;        // join-order column reduce: first source row of every workgroup
   int n_join_blocks = 0;
-  bool sliced = false;            // the inverse index is also split by slice of target rows (large target tables)
+  // the inverse index is also split by slice of target rows (large target tables); a layout says that there is room for it
+  bool sliced = false;
   size_t o_sl_rowptr = 0, o_sl_perm = 0, o_sl_chunk0 = 0, o_sl_ch_beg = 0, o_sl_ch_end = 0, o_sl_nchunk = 0,
          o_sl_ch_partial = 0, o_zslice = 0;
   int sl_cap = 0, sl_logG = 0;
-  bool binned = false;            // the segment sums run in LDS over windows of target rows (large target tables)
+  // the segment sums run in LDS over windows of target rows (large target tables); a layout says that there is room for it
+  bool binned = false;
   size_t o_bin_entries = 0, o_bin_off = 0, o_bin_keyinfo = 0, o_bin_ranges = 0, o_bin_items = 0, o_bin_heavy = 0;
   int bin_items = 0, bin_heavy = 0, bin_slots = 0;
   int64_t bin_partial = 0;
@@ -222,10 +224,14 @@ int colred_nblocks(int64_t rows, int64_t cols, int vec) {
   return (int)((rows + rpb - 1) / rpb);
 }
 
-// Shape-only part of a plan: fills the offsets of every workspace region.  roomy: with room for
-// segment sums in LDS and for more chunks of long segments; without, a plan asks for no more than plans always did.
+// Room of a plan: with segment sums in LDS, more chunks of long segments and the sliced index for tables that turn out not
+// to gain in LDS; the same without that; or none of them.
+enum { kRoomBare, kRoomBins, kRoomFull };
+
+// Shape-only part of a plan: fills the offsets of every workspace region.
 ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_t c_T, int64_t max_cx,
-                            std::vector<SourcePlan>& src, Layout& lay, bool roomy) {
+                            std::vector<SourcePlan>& src, Layout& lay, int room) {
+  const bool roomy = room != kRoomBare;
   if (s == nullptr) return fail(ILARGI_ERR_NULL, "sources is NULL");
   if (n < 1 || n > kMaxSources) return fail(ILARGI_ERR_SHAPE, "n = %d outside [1, %d]", n, kMaxSources);
   if (r_T < 0 || r_T > 2147483646ll) return fail(ILARGI_ERR_SHAPE, "r_T = %lld out of range", (long long)r_T);
@@ -303,12 +309,10 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
   int64_t n_indexed = 0;
   for (int k = 0; k < n; ++k) n_indexed += src[k].has_idx ? 1 : 0;
   const int64_t chunks_long = 2 * (r_T / kLongSeg) + 2;
-  // Segment sums in LDS (kernels_segbin.hip) for one operand column: their two launches cost about 20 microseconds before
-  // they gain.  Iterations with one model, gathering / in LDS: 5,000,000 rows and three tables 205 / 175, 2,000,000 121 / 101,
-  // 1,600,000 130 / 93; 1,000,000 and three tables 74 / 63, two sparse ones 39 / 34, one 37..45 / 39..45; 500,000 and three
-  // 58 / 53, one 33 / 36; 250,000 and three 50 / 51.  Several columns would take a pass each: 418 / 520 for three models.
-  // Their index takes the place of the sliced one, or of what the plan saves elsewhere: room that a caller set aside for
-  // its plans stays enough.
+  // Segment sums in LDS (kernels_segbin.hip) for one operand column: room where they may gain, which segbin_gain decides when
+  // the plan knows its keys.  Several columns would take a pass each: 418 / 520 microseconds for three models.  Their index
+  // lies where the sliced one does, or takes the place of what the plan saves elsewhere: room that a caller set aside for its
+  // plans stays enough.
   auto sliced = [&](int k) { return r_T >= 1500000 && src[k].rows > 0 && src[k].rows * kSegSlices <= r_T && s[k].csr_rowptr == nullptr; };
   auto binnable = [&](int k) {
     return roomy && max_cx == 1 && src[k].has_idx && !src[k].empty && src[k].rows * kSegSlices <= r_T && segbin_ranges(src[k].rows) <= kBinMaxRanges;
@@ -323,8 +327,7 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
                    (int64_t)sizeof(BinRange) * n_ranges + (int64_t)sizeof(BinItem) * 2 * kBinPerXcd + 6 * (int64_t)kAlign;
   }
   const int64_t spare = lay.max_entries > 0 ? 4 * n_indexed * chunks_long * (widest - wmax) : shared_bytes;
-  const bool use_bins = bin_bytes <= spare &&
-                        (r_T >= 1500000 || (n_binnable >= 2 && r_T >= 500000 && n_binnable * r_T >= 1500000));
+  const bool use_bins = bin_bytes <= spare && segbin_enough(r_T, (int)n_binnable);
   const int64_t chunk_bytes = shared_bytes - (use_bins && lay.max_entries == 0 ? bin_bytes : 0);
   const int64_t more = std::max<int64_t>(chunk_bytes / std::max<int64_t>(n_indexed, 1) - 6 * (int64_t)kAlign, 0) / (4 * wmax + 16);
   for (int k = 0; k < n; ++k) {
@@ -348,10 +351,10 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
       p.o_join_first = take(sizeof(int32_t) * (kColredBlocks + 1));
       // a residual of 6 MB or more does not stay in an XCD's 4 MB of L2: segments are then also split by slice
       // of target rows (worth it when a source row still has entries in most slices)
-      p.sliced = sliced(k);
       p.binned = use_bins && binnable(k);
+      p.sliced = sliced(k) && (!p.binned || room == kRoomFull);
+      const size_t index = off;                       // (a plan keeps one of the two)
       if (p.binned) {
-        p.sliced = false;
         const int n_ranges = segbin_ranges(p.rows);
         p.o_bin_entries = take(sizeof(uint32_t) * (r_T + kBinPad));
         p.o_bin_off = take(sizeof(int32_t) * n_ranges * kBinWaves * (segbin_windows(r_T, p.rows) + 1));
@@ -360,7 +363,9 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
         p.o_bin_items = take(sizeof(BinItem) * 2 * kBinPerXcd);
         p.o_bin_heavy = take(sizeof(int32_t) * kBinHeavyShare * n_ranges);
       }
+      const size_t bins_end = off;
       if (p.sliced) {
+        off = index;
         p.sl_cap = (int)segsum_sliced_chunk_cap(r_T);
         p.o_sl_rowptr = take(sizeof(int32_t) * (kSegSlices * p.rows + 1));
         p.o_sl_perm = take(sizeof(int32_t) * std::max<int64_t>(r_T, 1));
@@ -371,6 +376,7 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
         p.o_sl_ch_partial = take(sizeof(float) * kSegSlices * p.sl_cap * kNarrowCT);
         p.o_zslice = take(sizeof(float) * kSegSlices * p.rows * kNarrowCT);
       }
+      off = std::max(off, bins_end);
     }
     p.o_pz = take(sizeof(float) * std::max<int64_t>(p.rows, 1) * max_cx);
     // (a sparse source's transposed product leaves a single block of partials)
@@ -1331,7 +1337,7 @@ ilargi_status_t ilargi_plan_workspace_bytes(int n, const ilargi_source_t* source
   if (bytes == nullptr) return fail(ILARGI_ERR_NULL, "bytes is NULL");
   std::vector<SourcePlan> src;
   Layout lay;
-  ilargi_status_t st = make_layout(n, sources, r_T, c_T, max_cx, src, lay, true);
+  ilargi_status_t st = make_layout(n, sources, r_T, c_T, max_cx, src, lay, kRoomFull);
   if (st != ILARGI_OK) return st;
   *bytes = lay.total;
   return ILARGI_OK;
@@ -1349,11 +1355,12 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
   if (plan == nullptr) return fail(ILARGI_ERR_NULL, "plan is NULL");
   std::vector<SourcePlan> src;
   Layout lay;
-  ilargi_status_t rc = make_layout(n, sources, r_T, c_T, max_cx, src, lay, true);
-  if (rc == ILARGI_OK && workspace_bytes < lay.total) {      // sized for less: the plan works without
-    lay = Layout();
-    rc = make_layout(n, sources, r_T, c_T, max_cx, src, lay, false);
-  }
+  ilargi_status_t rc = make_layout(n, sources, r_T, c_T, max_cx, src, lay, kRoomFull);
+  for (const int room : {kRoomBins, kRoomBare})
+    if (rc == ILARGI_OK && workspace_bytes < lay.total) {      // sized for less: the plan works without
+      lay = Layout();
+      rc = make_layout(n, sources, r_T, c_T, max_cx, src, lay, room);
+    }
   if (rc != ILARGI_OK) return rc;
   // column maps (Def. 1): entries in [-1, c_T), no target column hit twice by one source
   std::vector<std::vector<int32_t>> tcol(n, std::vector<int32_t>((size_t)c_T, -1));
@@ -1429,7 +1436,7 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     if (p.ident) p.nnz = p.rows;
   }
   // inverse index of every non-identity source (Def. 2, transposed): stable sort by source row
-  std::vector<std::vector<BinRange>> bin_ranges((size_t)n);
+  std::vector<SegBinPlan> bin((size_t)n);
   for (int k = 0; k < n; ++k) {
     SourcePlan& p = pl->src[k];
     if (p.ident) continue;
@@ -1479,38 +1486,9 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
       HIP_TRY(hipStreamSynchronize(st));
     }
     if (p.binned) {
-      std::vector<uint32_t> keyinfo;
-      std::vector<int32_t> heavy;
-      segbin_layout(rowptr, keyinfo, heavy, bin_ranges[k]);
-      p.bin_heavy = (int)heavy.size();
-      for (const BinRange& r : bin_ranges[k]) p.bin_slots = std::max(p.bin_slots, r.slots);
-      if (heavy.size() > kBinHeavyShare * bin_ranges[k].size() || p.bin_slots > kBinSlots)
-        return fail(ILARGI_ERR_WORKSPACE, "internal: tables of the segment sums overflow");
-      HIP_TRY(hipMemcpyAsync(pl->at<uint32_t>(p.o_bin_keyinfo), keyinfo.data(), sizeof(uint32_t) * keyinfo.size(), hipMemcpyHostToDevice, st));
-      if (!heavy.empty())
-        HIP_TRY(hipMemcpyAsync(pl->at<int32_t>(p.o_bin_heavy), heavy.data(), sizeof(int32_t) * heavy.size(), hipMemcpyHostToDevice, st));
-      HIP_TRY(launch_build_segbin(p.idx, r_T, p.nnz, (int)bin_ranges[k].size(), (int)segbin_windows(r_T, p.rows), segbin_win_log(r_T, p.rows),
-                                  pl->at<uint32_t>(p.o_bin_keyinfo), sortbuf, rr, pl->at<int32_t>(lay.o_hist), pl->at<int32_t>(p.o_bin_off),
-                                  pl->at<uint32_t>(p.o_bin_entries), st));
-      HIP_TRY(hipStreamSynchronize(st));
-    }
-    if (p.sliced) {
-      int64_t slice_rows = (r_T + kSegSlices - 1) / kSegSlices;
-      slice_rows = (slice_rows + 63) / 64 * 64;
-      HIP_TRY(hipMemsetAsync(pl->at<int32_t>(p.o_sl_nchunk), 0, sizeof(int32_t) * kSegSlices, st));
-      // (the sort's buffers are free again: scratch for the runs' positions and for the scan)
-      HIP_TRY(launch_build_sliced_index(pl->at<int32_t>(p.o_rowptr), pl->at<int32_t>(p.o_perm), p.rows, p.nnz, slice_rows,
-                                        pl->at<int32_t>(p.o_sl_rowptr), pl->at<int32_t>(p.o_sl_perm),
-                                        pl->at<int32_t>(p.o_sl_chunk0), pl->at<int32_t>(p.o_sl_ch_beg),
-                                        pl->at<int32_t>(p.o_sl_ch_end), pl->at<int32_t>(p.o_sl_nchunk), p.sl_cap,
-                                        pl->at<int32_t>(lay.o_sort), pl->at<int32_t>(lay.o_hist), st));
-      int32_t nch[kSegSlices];
-      HIP_TRY(hipMemcpyAsync(nch, pl->at<int32_t>(p.o_sl_nchunk), sizeof(nch), hipMemcpyDeviceToHost, st));
-      HIP_TRY(hipStreamSynchronize(st));
-      for (int x = 0; x < kSegSlices; ++x)
-        if (nch[x] > p.sl_cap) return fail(ILARGI_ERR_WORKSPACE, "internal: chunk table of the sliced index overflows");
-      // lanes per (slice, source row) run: about four entries per lane, which it keeps in flight together
-      p.sl_logG = std::min(6, ilog2_ceil(std::max<int64_t>((avg + 4 * kSegSlices - 1) / (4 * kSegSlices), 1)));
+      segbin_layout(rowptr, bin[k]);
+      bin[k].entries = p.nnz;
+      bin[k].very_long = p.very_long;
     }
     if (!p.very_long && p.rows > 0 && !p.sparse && p.nnz <= 32 * p.rows && p.nnz >= 4 * p.rows) {
       // (with more index entries per row the gathers dominate and the segment-sum kernel, which spreads a
@@ -1537,23 +1515,71 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
       }
     }
   }
-  // the runs of windows of the segment sums in LDS: kSegMulti sources, in order, share a launch
-  for (int k = 0; k < n;) {
-    std::vector<BinRange>* shared[kSegMulti];
-    int64_t rows[kSegMulti];
-    int ks[kSegMulti], m = 0;
-    for (; k < n && m < kSegMulti; ++k)
-      if (!bin_ranges[k].empty()) { shared[m] = &bin_ranges[k]; rows[m] = pl->src[k].rows; ks[m] = k; ++m; }
-    segbin_share(r_T, shared, rows, m);
-    for (int i = 0; i < m; ++i) {
-      SourcePlan& p = pl->src[ks[i]];
+  // The sources whose segment sums run in LDS: those that gain by it, judged by the lengths of the segments first and, once the index is there, by how the entries lie in it.
+  {
+    std::vector<int> in_bins;
+    bool gathers = false;                             // some source's segment sums gather in any case
+    for (int k = 0; k < n; ++k) {
+      SourcePlan& p = pl->src[k];
+      if (p.empty || p.ident) continue;
+      if (p.binned) in_bins.push_back(k);
+      else gathers = true;
+    }
+    segbin_choose(r_T, bin, in_bins, gathers);
+    for (int k : in_bins) {
+      SourcePlan& p = pl->src[k];
+      SegBinPlan& b = bin[k];
+      if (b.heavy.size() > kBinHeavyShare * b.ranges.size() || b.max_slots() > kBinSlots)
+        return fail(ILARGI_ERR_WORKSPACE, "internal: tables of the segment sums overflow");
+      int32_t* sortbuf = pl->at<int32_t>(lay.o_sort);
+      HIP_TRY(hipMemcpyAsync(pl->at<uint32_t>(p.o_bin_keyinfo), b.keyinfo.data(), sizeof(uint32_t) * b.keyinfo.size(), hipMemcpyHostToDevice, st));
+      if (!b.heavy.empty())
+        HIP_TRY(hipMemcpyAsync(pl->at<int32_t>(p.o_bin_heavy), b.heavy.data(), sizeof(int32_t) * b.heavy.size(), hipMemcpyHostToDevice, st));
+      const int n_win = (int)segbin_windows(r_T, p.rows);
+      HIP_TRY(launch_build_segbin(p.idx, r_T, p.nnz, (int)b.ranges.size(), n_win, segbin_win_log(r_T, p.rows),
+                                  pl->at<uint32_t>(p.o_bin_keyinfo), sortbuf, std::max<int64_t>(r_T, 1), pl->at<int32_t>(lay.o_hist),
+                                  pl->at<int32_t>(p.o_bin_off), pl->at<uint32_t>(p.o_bin_entries), sortbuf, st));
+      b.groups.resize(b.ranges.size() * (size_t)n_win);
+      HIP_TRY(hipMemcpyAsync(b.groups.data(), sortbuf, sizeof(int32_t) * b.groups.size(), hipMemcpyDeviceToHost, st));
+      HIP_TRY(hipStreamSynchronize(st));
+    }
+    segbin_choose(r_T, bin, in_bins, gathers);
+    for (int k = 0; k < n; ++k) pl->src[k].binned = false;
+    for (int k : in_bins) {
+      SourcePlan& p = pl->src[k];
+      SegBinPlan& b = bin[k];
+      p.binned = true;
+      p.sliced = false;
+      p.bin_heavy = (int)b.heavy.size();
+      p.bin_slots = b.max_slots();
       std::vector<BinItem> items;
-      segbin_items(*shared[i], items, &p.bin_partial);
+      segbin_items(b.ranges, items, &p.bin_partial);
       p.bin_items = (int)items.size();
-      HIP_TRY(hipMemcpyAsync(pl->at<BinRange>(p.o_bin_ranges), shared[i]->data(), sizeof(BinRange) * shared[i]->size(), hipMemcpyHostToDevice, st));
+      HIP_TRY(hipMemcpyAsync(pl->at<BinRange>(p.o_bin_ranges), b.ranges.data(), sizeof(BinRange) * b.ranges.size(), hipMemcpyHostToDevice, st));
       HIP_TRY(hipMemcpyAsync(pl->at<BinItem>(p.o_bin_items), items.data(), sizeof(BinItem) * items.size(), hipMemcpyHostToDevice, st));
       HIP_TRY(hipStreamSynchronize(st));
     }
+  }
+  for (int k = 0; k < n; ++k) {
+    SourcePlan& p = pl->src[k];
+    if (!p.sliced || p.ident) continue;
+    int64_t slice_rows = (r_T + kSegSlices - 1) / kSegSlices;
+    slice_rows = (slice_rows + 63) / 64 * 64;
+    HIP_TRY(hipMemsetAsync(pl->at<int32_t>(p.o_sl_nchunk), 0, sizeof(int32_t) * kSegSlices, st));
+    // (the sort's buffers are free again: scratch for the runs' positions and for the scan)
+    HIP_TRY(launch_build_sliced_index(pl->at<int32_t>(p.o_rowptr), pl->at<int32_t>(p.o_perm), p.rows, p.nnz, slice_rows,
+                                      pl->at<int32_t>(p.o_sl_rowptr), pl->at<int32_t>(p.o_sl_perm),
+                                      pl->at<int32_t>(p.o_sl_chunk0), pl->at<int32_t>(p.o_sl_ch_beg),
+                                      pl->at<int32_t>(p.o_sl_ch_end), pl->at<int32_t>(p.o_sl_nchunk), p.sl_cap,
+                                      pl->at<int32_t>(lay.o_sort), pl->at<int32_t>(lay.o_hist), st));
+    int32_t nch[kSegSlices];
+    HIP_TRY(hipMemcpyAsync(nch, pl->at<int32_t>(p.o_sl_nchunk), sizeof(nch), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    for (int x = 0; x < kSegSlices; ++x)
+      if (nch[x] > p.sl_cap) return fail(ILARGI_ERR_WORKSPACE, "internal: chunk table of the sliced index overflows");
+    // lanes per (slice, source row) run: about four entries per lane, which it keeps in flight together
+    const int64_t avg = p.rows > 0 ? (p.nnz + p.rows - 1) / p.rows : 1;
+    p.sl_logG = std::min(6, ilog2_ceil(std::max<int64_t>((avg + 4 * kSegSlices - 1) / (4 * kSegSlices), 1)));
   }
   // column-sorted view of every sparse source: the same stable sort, keyed by column index
   for (int k = 0; k < n; ++k) {

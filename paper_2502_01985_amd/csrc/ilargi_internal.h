@@ -233,6 +233,16 @@ constexpr uint32_t kBinHeavy = 1u << 31;  // ... and whether the key has a slot 
 static_assert(kBinSlots <= 1 << kBinSlotBits && kBinSlotBits + kBinRowBits <= 32 && kBinSlotBits + 8 < 31, "packed fields");
 struct BinRange { int key0, slots, nsub, partial0, entries; };   // first key, sums, runs of windows per XCD, first partial, index entries
 struct BinItem { int range, sub; };
+// What a plan knows of a source's segment sums in LDS while it is made.
+struct SegBinPlan {
+  std::vector<BinRange> ranges;
+  std::vector<uint32_t> keyinfo;
+  std::vector<int32_t> heavy;
+  std::vector<int32_t> groups;   // [range][window]: groups of 64 entries of the wavefront with the most; empty: not known yet
+  int64_t entries = 0;
+  bool very_long = false;        // some segment has more than kLongSeg entries
+  int max_slots() const { int m = 0; for (const BinRange& r : ranges) m = r.slots > m ? r.slots : m; return m; }
+};
 struct SegBin {
   const uint32_t* entries;
   const int32_t* off;        // [ranges x 16][n_win + 1]
@@ -519,17 +529,21 @@ int64_t segsum_sliced_chunk_cap(int64_t nnz);
 // n <= kSegMulti sources with the same number of operand columns; their sums and the sums over slices run as one
 // launch each.
 hipError_t launch_segsum_sliced(const SegArgs* a, int n, hipStream_t st);
-// Segment sums in LDS: the split of a source's keys into ranges, the runs of windows of sources that share a launch, the
-// index of a source, and the sums of n <= kSegMulti sources.
+// Segment sums in LDS: the split of a source's keys into ranges, the choice of the sources that gain by them, the runs of
+// windows of sources that share a launch, the index of a source, and the sums of n <= kSegMulti sources.
 int segbin_ranges(int64_t rows);
 int segbin_win_log(int64_t r_T, int64_t rows);
 inline int64_t segbin_windows(int64_t r_T, int64_t rows) { const int64_t w = 1ll << segbin_win_log(r_T, rows); return (r_T + w - 1) / w; }
-void segbin_layout(const std::vector<int32_t>& rowptr, std::vector<uint32_t>& keyinfo, std::vector<int32_t>& heavy, std::vector<BinRange>& ranges);
-void segbin_share(int64_t r_T, std::vector<BinRange>* const* ranges, const int64_t* rows, int n);   // sets nsub
+void segbin_layout(const std::vector<int32_t>& rowptr, SegBinPlan& plan);
+bool segbin_enough(int64_t r_T, int n);            // whether n sources over so many target rows may gain at all
+// in_bins: the sources that may run in LDS; on return those that do, with the runs of windows in their ranges.  gathers: some
+// source of the plan gathers; set when one is dropped.
+void segbin_choose(int64_t r_T, std::vector<SegBinPlan>& plans, std::vector<int>& in_bins, bool& gathers);
 void segbin_items(std::vector<BinRange>& ranges, std::vector<BinItem>& items, int64_t* partial_floats);
-// sortbuf: four arrays of sort_n integers, hist: sort_hist_ints(r_T); both are scratch
+// sortbuf: four arrays of sort_n integers, hist: sort_hist_ints(r_T); both are scratch.  groups: SegBinPlan::groups, may lie
+// in the first of the four arrays.
 hipError_t launch_build_segbin(const int32_t* idx, int64_t r_T, int64_t nnz, int n_ranges, int n_win, int win_log, const uint32_t* keyinfo,
-                               int32_t* sortbuf, int64_t sort_n, int32_t* hist, int32_t* off, uint32_t* entries, hipStream_t st);
+                               int32_t* sortbuf, int64_t sort_n, int32_t* hist, int32_t* off, uint32_t* entries, int32_t* groups, hipStream_t st);
 hipError_t launch_segbin(const SegBin* a, int n, float* scratch, int64_t scratch_floats, hipStream_t st);
 hipError_t launch_colred(const ColredArgs& a, int nblocks, hipStream_t st);
 bool lmm_flat_supported(const LmmArgs& a, int vec, bool fuseg);

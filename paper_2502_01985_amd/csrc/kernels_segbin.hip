@@ -163,6 +163,13 @@ __device__ __forceinline__ void segbin_windows_sum(const SegBin& a, const float*
   if (w < w1) step(w, r0, e0);
 }
 
+// Run `sub` of the nsub runs of windows of XCD x.
+struct BinRun { int w0, w1; };
+__host__ __device__ __forceinline__ BinRun segbin_run(int n_win, int x, int sub, int nsub) {
+  const int wx0 = (int)((int64_t)n_win * x / kSegSlices), wx1 = (int)((int64_t)n_win * (x + 1) / kSegSlices);
+  return BinRun{wx0 + (int)((int64_t)(wx1 - wx0) * sub / nsub), wx0 + (int)((int64_t)(wx1 - wx0) * (sub + 1) / nsub)};
+}
+
 // PLAIN: the operand is one column of 16-byte aligned floats.
 template <bool PLAIN>
 __global__ __launch_bounds__(kBinThreads, 4) void segbin_kernel(SegBinMulti m) {
@@ -177,8 +184,8 @@ __global__ __launch_bounds__(kBinThreads, 4) void segbin_kernel(SegBinMulti m) {
   it.range = __builtin_amdgcn_readfirstlane(it.range); it.sub = __builtin_amdgcn_readfirstlane(it.sub);
   BinRange rg = a.ranges[it.range];
   rg.slots = __builtin_amdgcn_readfirstlane(rg.slots); rg.nsub = __builtin_amdgcn_readfirstlane(rg.nsub);
-  const int wx0 = (int)((int64_t)a.n_win * x / kSegSlices), wx1 = (int)((int64_t)a.n_win * (x + 1) / kSegSlices);
-  const int w0 = wx0 + (int)((int64_t)(wx1 - wx0) * it.sub / rg.nsub), w1 = wx0 + (int)((int64_t)(wx1 - wx0) * (it.sub + 1) / rg.nsub);
+  const BinRun run = segbin_run(a.n_win, x, it.sub, rg.nsub);
+  const int w0 = run.w0, w1 = run.w1;
   const int tid = (int)threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   for (int s = tid; s < rg.slots; s += kBinThreads) acc[s] = 0.0f;
   __syncthreads();
@@ -288,6 +295,20 @@ __global__ __launch_bounds__(kBlock) void bin_offsets_kernel(const int32_t* __re
   }
 }
 
+// groups[range][w]: groups of 64 entries in window w of the wavefront of the range that has the most.
+__global__ __launch_bounds__(kBlock) void bin_groups_kernel(const int32_t* __restrict__ off, int n_ranges, int n_win, int32_t* __restrict__ groups) {
+  const int64_t total = (int64_t)n_ranges * n_win;
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t range = e / n_win, w = e - range * n_win;
+    int most = 0;
+    for (int v = 0; v < kBinWaves; ++v) {
+      const int32_t* o = off + (range * kBinWaves + v) * (n_win + 1) + w;
+      most = max(most, (o[1] - o[0] + kWave - 1) / kWave);
+    }
+    groups[e] = most;
+  }
+}
+
 // Packs the entries of every wavefront's windows, 64 at a time in order of their slot (a bitonic sort across the lanes).
 __global__ __launch_bounds__(kBlock) void bin_pack_kernel(const int32_t* __restrict__ keys, const int32_t* __restrict__ rows,
                                                           const int32_t* __restrict__ off, int n_digits, int n_win, int win_log,
@@ -324,7 +345,9 @@ int segbin_win_log(int64_t r_T, int64_t rows) {
 
 int segbin_ranges(int64_t rows) { return (int)((rows + kBinKeys - 1) / kBinKeys); }
 
-void segbin_layout(const std::vector<int32_t>& rowptr, std::vector<uint32_t>& keyinfo, std::vector<int32_t>& heavy, std::vector<BinRange>& ranges) {
+void segbin_layout(const std::vector<int32_t>& rowptr, SegBinPlan& plan) {
+  std::vector<uint32_t>& keyinfo = plan.keyinfo;
+  std::vector<int32_t>& heavy = plan.heavy;
   const int64_t rows = (int64_t)rowptr.size() - 1;
   const int n_ranges = segbin_ranges(rows);
   keyinfo.assign((size_t)rows, 0);
@@ -351,32 +374,107 @@ void segbin_layout(const std::vector<int32_t>& rowptr, std::vector<uint32_t>& ke
       keyinfo[(size_t)k] = (uint32_t)(k - k0) | (uint32_t)(g * kBinWaves + wave) << kBinSlotBits;
       seen += rowptr[(size_t)k + 1] - rowptr[(size_t)k];
     }
-    ranges.push_back(BinRange{(int)k0, slots, 1, 0, (int)entries});
+    plan.ranges.push_back(BinRange{(int)k0, slots, 1, 0, (int)entries});
   }
 }
 
+namespace {
+
+struct BinPart { BinRange* r; const int32_t* groups; double window; int windows, n_win, source, log; };
+
+// Instructions of a wavefront in a window: its rows, and its groups of 64 entries.
+double window_cost(int log, double groups) { return 60.0 + (1 << log) / 400.0 + 40.0 * groups; }
+
 // Shares the workgroups of an XCD out to the ranges of the sources of a launch: one more run of windows for the range whose
-// runs are the longest, until the XCD is full.  A window costs its rows and its groups of 64 entries a wavefront, counted in
-// instructions of a wavefront.
-void segbin_share(int64_t r_T, std::vector<BinRange>* const* ranges, const int64_t* rows, int n) {
-  struct Part { BinRange* r; double window; int windows; };
-  std::vector<Part> parts;
-  for (int q = 0; q < n; ++q) {
-    const int log = segbin_win_log(r_T, rows[q]);
-    const double n_win = (double)segbin_windows(r_T, rows[q]);
-    for (BinRange& r : *ranges[q]) {
-      const double groups = std::max(1.0, r.entries / n_win / kBinWaves / kWave + 0.5);
-      parts.push_back(Part{&r, 60.0 + (1 << log) / 400.0 + 40.0 * groups, (int)std::max<int64_t>(1, segbin_windows(r_T, rows[q]) / kSegSlices)});
-    }
-  }
-  auto cost = [](const Part& p) { return p.window * ((p.windows + p.r->nsub - 1) / p.r->nsub); };
+// runs are the longest, until the XCD is full.
+void segbin_share(std::vector<BinPart>& parts) {
+  auto cost = [](const BinPart& p) { return p.window * ((p.windows + p.r->nsub - 1) / p.r->nsub); };
   const int room = ((int)parts.size() + kBinPerXcd - 1) / kBinPerXcd * kBinPerXcd;
+  for (BinPart& p : parts) p.r->nsub = 1;
   for (int used = (int)parts.size(); used < room; ++used) {
-    Part* most = nullptr;
-    for (Part& p : parts)
+    BinPart* most = nullptr;
+    for (BinPart& p : parts)
       if (p.r->nsub < p.windows && (most == nullptr || cost(p) > cost(*most))) most = &p;
     if (most == nullptr) break;
     ++most->r->nsub;
+  }
+}
+
+// Microseconds that the sources ks[0 .. n) gain by a launch in LDS over gathering, and the source whose entries lie the
+// least evenly (-1: they lie evenly, or it is not known).
+// In LDS: the longest run of windows, had every wavefront of a workgroup the same number of entries in every window; what it
+// is longer because they have not (then one wavefront works and its requests are not hidden: 13 microseconds per 1000
+// instructions instead of 6), as where the rows of a key lie together; and the runs' sums, a microsecond per million.
+// Gathering: the entries; keys of thousands of rows, which are summed in chunks.  Iterations of one model, gathering / in LDS:
+//   rows        tables                  keys                                                              this rule
+//   5,000,000   100,000, 50,000, 10,000 uniform                                       205 / 175            in LDS
+//   5,000,000   30,000 and 5000         uniform; sorted by the first                  153 / 112; 105 / 645 in LDS; gathers
+//   5,000,000   180,000                 uniform                                       111 / 109            in LDS
+//   5,000,000   50,000                  each key's rows together                      97 / 99              gathers
+//   2,000,000   20,000; 50,000; 180,000 uniform                                       51 / 53; 53 / 55; 58 / 63   gathers
+//   1,500,000   50,000                  uniform; a power law                          47 / 52; 93 / 51     gathers; in LDS
+//   1,000,000   20,000 twice; 3000 twice uniform                                      49 / 50; 43 / 41     gathers; in LDS
+//   1,000,000   30,000 and 5000         the first of slowly moving keys               48 / 100             gathers
+//   500,000     60,000; 3000; three of each uniform                                   47 / 54; 39 / 38     gathers; in LDS
+double segbin_gain(int64_t r_T, std::vector<SegBinPlan>& plans, const int* ks, int n, bool gathers, int* uneven) {
+  std::vector<BinPart> parts;
+  double gather = gathers ? 0.0 : 8.0;              // (a launch, unless there is one in any case)
+  for (int q = 0; q < n; ++q) {
+    SegBinPlan& s = plans[(size_t)ks[q]];
+    const int64_t rows = (int64_t)s.keyinfo.size();
+    const int log = segbin_win_log(r_T, rows), n_win = (int)segbin_windows(r_T, rows);
+    for (size_t g = 0; g < s.ranges.size(); ++g) {
+      BinRange& r = s.ranges[g];
+      const double groups = std::max(1.0, r.entries / (double)n_win / kBinWaves / kWave + 0.5);
+      parts.push_back(BinPart{&r, s.groups.empty() ? nullptr : s.groups.data() + g * (size_t)n_win, window_cost(log, groups),
+                              std::max(1, n_win / kSegSlices), n_win, ks[q], log});
+    }
+    gather += 6.2e-6 * (double)s.entries;
+  }
+  for (int q = 0; q < n; ++q)
+    if (plans[(size_t)ks[q]].very_long) { gather += 10.0; break; }
+  segbin_share(parts);
+  double even = 0.0, longest = 0.0, sums = 0.0, most = 0.0;
+  *uneven = -1;
+  for (const BinPart& p : parts) {
+    sums += (double)p.r->nsub * kSegSlices * p.r->slots;
+    double p_even = 0.0, p_longest = 0.0;
+    for (int x = 0; x < kSegSlices; ++x)
+      for (int sub = 0; sub < p.r->nsub; ++sub) {
+        const BinRun run = segbin_run(p.n_win, x, sub, p.r->nsub);
+        double c = p.window * (run.w1 - run.w0);
+        p_even = std::max(p_even, c);
+        if (p.groups != nullptr) {
+          c = 0.0;
+          for (int w = run.w0; w < run.w1; ++w) c += window_cost(p.log, p.groups[w]);
+        }
+        p_longest = std::max(p_longest, c);
+      }
+    if (p_longest > 1.5 * p_even && p_longest - p_even > most) { most = p_longest - p_even; *uneven = p.source; }
+    even = std::max(even, p_even);
+    longest = std::max(longest, p_longest);
+  }
+  return gather - (12.2 + 6e-3 * even + 13e-3 * std::max(longest - even, 0.0) + 1e-6 * sums);
+}
+
+}  // namespace
+
+// Below these sizes the two launches cost more than the gathers: 250,000 rows and three tables 50 / 51 microseconds an
+// iteration (gathering / in LDS), 500,000 and one 33 / 36, 1,000,000 and one 37..45 / 39..45.
+bool segbin_enough(int64_t r_T, int n) { return n > 0 && (r_T >= 1500000 || (n >= 2 && r_T >= 500000 && n * r_T >= 1500000)); }
+
+void segbin_choose(int64_t r_T, std::vector<SegBinPlan>& plans, std::vector<int>& in_bins, bool& gathers) {
+  for (bool again = true; again;) {
+    again = false;
+    if (!segbin_enough(r_T, (int)in_bins.size())) in_bins.clear();
+    for (size_t i = 0; i < in_bins.size() && !again; i += kSegMulti) {       // (the sources of a launch, as they are called)
+      const int n = (int)std::min<size_t>(kSegMulti, in_bins.size() - i);
+      int uneven = -1;
+      if (segbin_gain(r_T, plans, in_bins.data() + i, n, gathers, &uneven) > 0.0) continue;
+      if (uneven >= 0) in_bins.erase(std::find(in_bins.begin() + i, in_bins.begin() + i + n, uneven));
+      else in_bins.erase(in_bins.begin() + i, in_bins.begin() + i + n);
+      gathers = again = true;
+    }
   }
 }
 
@@ -391,7 +489,7 @@ void segbin_items(std::vector<BinRange>& ranges, std::vector<BinItem>& items, in
 }
 
 hipError_t launch_build_segbin(const int32_t* idx, int64_t r_T, int64_t nnz, int n_ranges, int n_win, int win_log, const uint32_t* keyinfo,
-                               int32_t* sortbuf, int64_t sort_n, int32_t* hist, int32_t* off, uint32_t* entries, hipStream_t st) {
+                               int32_t* sortbuf, int64_t sort_n, int32_t* hist, int32_t* off, uint32_t* entries, int32_t* groups, hipStream_t st) {
   if (r_T <= 0) return hipSuccess;
   const int nchunks = (int)((r_T + kSortChunk - 1) / kSortChunk);
   int32_t* keys_a = sortbuf, *vals_a = sortbuf + sort_n, *keys_b = sortbuf + 2 * sort_n, *vals_b = sortbuf + 3 * sort_n;
@@ -402,6 +500,8 @@ hipError_t launch_build_segbin(const int32_t* idx, int64_t r_T, int64_t nnz, int
   const int64_t n_off = (int64_t)n_ranges * kBinWaves * (n_win + 1);
   bin_offsets_kernel<<<(int)std::min<int64_t>((n_off + kBlock - 1) / kBlock, 8192), kBlock, 0, st>>>(vals_b, hist, nchunks, n_ranges * kBinWaves,
                                                                                                    n_win, win_log, off);
+  const int64_t n_groups = (int64_t)n_ranges * n_win;
+  bin_groups_kernel<<<(int)std::min<int64_t>((n_groups + kBlock - 1) / kBlock, 8192), kBlock, 0, st>>>(off, n_ranges, n_win, groups);
   if (nnz > 0) {
     const int64_t lists = (int64_t)n_ranges * kBinWaves * n_win;
     bin_pack_kernel<<<(int)std::min<int64_t>((lists + 3) / 4, 16384), kBlock, 0, st>>>(keys_b, vals_b, off, n_ranges * kBinWaves, n_win, win_log, entries);

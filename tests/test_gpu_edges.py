@@ -954,3 +954,72 @@ def test_logistic_loss_beyond_the_range_is_infinite(il, c, r_T, at):
     loss = torch.zeros(1, device="cuda")
     il.ilargi_gd_step(plan, il.LOGISTIC, W, y, torch.zeros(1, device="cuda"), loss)
     assert float(loss) == float("inf")
+
+
+def _ordered(kind, rows, r_T, gen):
+    """Keys whose target rows do not lie evenly."""
+    u = torch.randint(0, rows, (r_T,), generator=gen, device="cuda")
+    at = torch.arange(r_T, device="cuda").double() / r_T
+    if kind == "sorted":
+        u = u.sort()[0]
+    elif kind == "together":                                       # each key's rows lie together, the keys in no order
+        u = torch.randperm(rows, generator=gen, device="cuda")[u.sort()[0]]
+    elif kind == "blocks":                                         # a twentieth of the keys in every twentieth of the rows
+        u = (at * 20).long() * (rows // 20) + u % (rows // 20)
+    elif kind == "moving":
+        u = ((at + 0.02 * torch.randn(r_T, generator=gen, device="cuda", dtype=torch.float64)).clamp(0, 0.999999) * rows).long()
+    elif kind == "new":                                            # keys numbered as they first appear
+        u = (torch.rand(r_T, generator=gen, device="cuda", dtype=torch.float64) * (at + 1.0 / r_T) * rows).long().clamp(max=rows - 1)
+    return u.int()
+
+
+_ORDERS = ["sorted", "together", "blocks", "moving", "new"]
+
+
+@pytest.mark.parametrize("kind", _ORDERS)
+@pytest.mark.parametrize("r_T,dims", [(750_001, [30_000, 5_000]), (1_600_000, [50_000]), (3_200_001, [100_000, 3_000, 50_000])])
+def test_segment_sums_over_keys_in_some_order(il, kind, r_T, dims):
+    # whichever index a plan keeps for them: whole numbers, the same bits as a plan for several columns, and on every run
+    gen = torch.Generator(device="cuda").manual_seed(r_T)
+    sources, c_T, y = _keyed(3, r_T, [(rows, 0) for rows in dims])
+    for first in (True, False):                                    # one table in that order, then all of them
+        sources = [(D, _ordered(kind, len(D), r_T, gen) if k == 0 or not first else idx, cm) for k, (D, idx, cm) in enumerate(sources)]
+        one = il.ilargi_plan_create(sources, r_T, c_T, max_cx=1)
+        several = il.ilargi_plan_create(sources, r_T, c_T, max_cx=4)
+        Y = y[:r_T].clone().reshape(-1, 1)
+        got = il.ilargi_tmm(one, Y)
+        want = torch.cat([D.double().t() @ torch.zeros(len(D), 1, dtype=torch.float64, device="cuda").index_add_(
+            0, idx.long(), Y.double()) for D, idx, _ in sources])
+        assert torch.equal(got.double(), want) and torch.equal(il.ilargi_tmm(several, Y), got)
+        Y = torch.randn(r_T, 1, device="cuda")
+        got = il.ilargi_tmm(one, Y)
+        assert all(torch.equal(got, il.ilargi_tmm(one, Y)) for _ in range(3))
+
+
+def _one_model_ms(il, r_T, dims, kind):
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    sources, at = [(torch.randn(r_T, 10, generator=gen, device="cuda"), None, list(range(10)))], 10
+    for k, rows in enumerate(dims):
+        idx = _ordered(kind if k == 0 else "", rows, r_T, gen)
+        sources.append((torch.randn(rows, 7, generator=gen, device="cuda"), idx, list(range(at, at + 7))))
+        at += 7
+    plan = il.ilargi_plan_create(sources, r_T, at, max_cx=1)
+    W, y, lr, loss = torch.zeros(at, 1, device="cuda"), torch.ones(r_T, device="cuda"), torch.full((1,), 0.1, device="cuda"), torch.zeros(1, device="cuda")
+    step = lambda: il.ilargi_gd_step(plan, il.LOGISTIC, W, y, lr, loss)  # noqa: E731
+    for _ in range(3):
+        step()
+    begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    begin.record()
+    for _ in range(10):
+        step()
+    end.record()
+    torch.cuda.synchronize()
+    return begin.elapsed_time(end) / 10
+
+
+@pytest.mark.parametrize("kind", _ORDERS)
+@pytest.mark.parametrize("r_T,dims", [(1_000_000, [30_000, 5_000]), (2_000_000, [50_000]), (3_000_000, [3_000, 20_000])])
+def test_iteration_over_keys_in_some_order_costs_no_more_than_over_keys_in_none(il, kind, r_T, dims):
+    # the segment sums in LDS go by windows of target rows, where such keys leave all but a few wavefronts without work:
+    # 1.9 to 6 times the time of keys in no order; gathered, "new" keys take up to 1.5 times as long, the others 1.2
+    assert _soon(lambda: _one_model_ms(il, r_T, dims, kind) < (1.7 if kind == "new" else 1.35) * _one_model_ms(il, r_T, dims, ""))
