@@ -1515,13 +1515,20 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
       }
     }
   }
-  // The sources whose segment sums run in LDS: those that gain by it, judged by the lengths of the segments first and, once the index is there, by how the entries lie in it.
+  // The sources whose segment sums run in LDS: those that have them at all (a table in join order has none) and gain by
+  // it, judged by the lengths of the segments first and, once the index is there, by how the entries lie in it.
   {
     std::vector<int> in_bins;
     bool gathers = false;                             // some source's segment sums gather in any case
     for (int k = 0; k < n; ++k) {
       SourcePlan& p = pl->src[k];
       if (p.empty || p.ident) continue;
+      ColredArgs c;
+      memset(&c, 0, sizeof(c));
+      c.rows = p.rows; c.ck = (int)p.cols; c.vec = p.vec; c.ncols = 1;
+      SegArgs sg = seg_args(pl, k);
+      sg.ncols = 1;
+      if (!p.sparse && tmm_part_supported(c, &sg)) continue;
       if (p.binned) in_bins.push_back(k);
       else gathers = true;
     }

@@ -1023,3 +1023,32 @@ def test_iteration_over_keys_in_some_order_costs_no_more_than_over_keys_in_none(
     # the segment sums in LDS go by windows of target rows, where such keys leave all but a few wavefronts without work:
     # 1.9 to 6 times the time of keys in no order; gathered, "new" keys take up to 1.5 times as long, the others 1.2
     assert _soon(lambda: _one_model_ms(il, r_T, dims, kind) < (1.7 if kind == "new" else 1.35) * _one_model_ms(il, r_T, dims, ""))
+
+
+def test_sources_in_join_order_leave_the_segment_sums_to_the_others(il):
+    # tables with float4 rows and few entries a row have no segment sums, and the launches hold four of the others
+    r_T = 2_457_600
+    sources, c_T, y = _keyed(77, r_T, [(300_000, 0), (300_000, 0), (300_000, 0), (307_200, 0)] * 4)
+    wide = []
+    for k, (D, idx, _) in enumerate(sources):
+        c = 3 if k % 4 == 3 else 4
+        wide.append((D[:, :3].contiguous() if c == 3 else torch.cat([D, D[:, :1]], 1).contiguous(), idx, list(range(4 * k, 4 * k + c))))
+    plan = il.ilargi_plan_create(wide, r_T, 64, max_cx=1)
+    Y = y[:r_T].clone().reshape(-1, 1)
+    got = il.ilargi_tmm(plan, Y)
+    for D, idx, cm in wide:
+        want = D.double().t() @ torch.zeros(len(D), 1, dtype=torch.float64, device="cuda").index_add_(0, idx.long(), Y.double())
+        assert torch.equal(got[cm].double(), want)
+
+
+def test_one_source_left_by_the_join_order_is_too_few_for_sums_in_lds(il):
+    # over 1,000,000 rows the sums in LDS take two tables to gain; the first of these two has no segment sums
+    sources, c_T, y = _keyed(13, 1_000_000, [(62_500, 0), (20_000, 0)])
+    D, idx, _ = sources[0]
+    sources = [(torch.cat([D, D[:, :1]], 1).contiguous(), idx, [0, 1, 2, 6]), sources[1]]
+    one = il.ilargi_plan_create(sources, 1_000_000, 7, max_cx=1)
+    several = il.ilargi_plan_create(sources, 1_000_000, 7, max_cx=4)
+    Y = y[:1_000_000].clone().reshape(-1, 1)
+    out = il.ilargi_tmm(one, Y)
+    assert torch.equal(out, il.ilargi_tmm(several, Y))
+    assert _launches(lambda: il.ilargi_tmm(one, Y, out)) == _launches(lambda: il.ilargi_tmm(several, Y, out))
