@@ -1519,7 +1519,7 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
   // it, judged by the lengths of the segments first and, once the index is there, by how the entries lie in it.
   {
     std::vector<int> in_bins;
-    bool gathers = false;                             // some source's segment sums gather in any case
+    bool gathers[2] = {};                             // some source's segment sums gather in any case: as they are, by slices
     for (int k = 0; k < n; ++k) {
       SourcePlan& p = pl->src[k];
       if (p.empty || p.ident) continue;
@@ -1530,9 +1530,10 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
       sg.ncols = 1;
       if (!p.sparse && tmm_part_supported(c, &sg)) continue;
       if (p.binned) in_bins.push_back(k);
-      else gathers = true;
+      else gathers[p.sliced] = true;
     }
-    segbin_choose(r_T, bin, in_bins, gathers);
+    for (int k : in_bins) bin[k].joins_launch = gathers[pl->src[k].sliced];
+    segbin_choose(r_T, bin, in_bins);
     for (int k : in_bins) {
       SourcePlan& p = pl->src[k];
       SegBinPlan& b = bin[k];
@@ -1550,7 +1551,7 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
       HIP_TRY(hipMemcpyAsync(b.groups.data(), sortbuf, sizeof(int32_t) * b.groups.size(), hipMemcpyDeviceToHost, st));
       HIP_TRY(hipStreamSynchronize(st));
     }
-    segbin_choose(r_T, bin, in_bins, gathers);
+    segbin_choose(r_T, bin, in_bins);
     for (int k = 0; k < n; ++k) pl->src[k].binned = false;
     for (int k : in_bins) {
       SourcePlan& p = pl->src[k];

@@ -241,6 +241,7 @@ struct SegBinPlan {
   std::vector<int32_t> groups;   // [range][window]: groups of 64 entries of the wavefront with the most; empty: not known yet
   int64_t entries = 0;
   bool very_long = false;        // some segment has more than kLongSeg entries
+  bool joins_launch = false;     // another source gathers in the launch that this one would gather in
   int max_slots() const { int m = 0; for (const BinRange& r : ranges) m = r.slots > m ? r.slots : m; return m; }
 };
 struct SegBin {
@@ -536,9 +537,8 @@ int segbin_win_log(int64_t r_T, int64_t rows);
 inline int64_t segbin_windows(int64_t r_T, int64_t rows) { const int64_t w = 1ll << segbin_win_log(r_T, rows); return (r_T + w - 1) / w; }
 void segbin_layout(const std::vector<int32_t>& rowptr, SegBinPlan& plan);
 bool segbin_enough(int64_t r_T, int n);            // whether n sources over so many target rows may gain at all
-// in_bins: the sources that may run in LDS; on return those that do, with the runs of windows in their ranges.  gathers: some
-// source of the plan gathers; set when one is dropped.
-void segbin_choose(int64_t r_T, std::vector<SegBinPlan>& plans, std::vector<int>& in_bins, bool& gathers);
+// in_bins: the sources that may run in LDS; on return those that do, with the runs of windows in their ranges.
+void segbin_choose(int64_t r_T, std::vector<SegBinPlan>& plans, std::vector<int>& in_bins);
 void segbin_items(std::vector<BinRange>& ranges, std::vector<BinItem>& items, int64_t* partial_floats);
 // sortbuf: four arrays of sort_n integers, hist: sort_hist_ints(r_T); both are scratch.  groups: SegBinPlan::groups, may lie
 // in the first of the four arrays.

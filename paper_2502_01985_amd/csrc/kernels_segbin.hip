@@ -380,7 +380,7 @@ void segbin_layout(const std::vector<int32_t>& rowptr, SegBinPlan& plan) {
 
 namespace {
 
-struct BinPart { BinRange* r; const int32_t* groups; double window; int windows, n_win, source, log; };
+struct BinPart { BinRange* r; const int32_t* groups; double window; int windows, n_win, log; };
 
 // Instructions of a wavefront in a window: its rows, and its groups of 64 entries.
 double window_cost(int log, double groups) { return 60.0 + (1 << log) / 400.0 + 40.0 * groups; }
@@ -400,25 +400,25 @@ void segbin_share(std::vector<BinPart>& parts) {
   }
 }
 
-// Microseconds that the sources ks[0 .. n) gain by a launch in LDS over gathering, and the source whose entries lie the
-// least evenly (-1: they lie evenly, or it is not known).
+// Microseconds that the sources ks[0 .. n) gain by a launch in LDS over gathering.
 // In LDS: the longest run of windows, had every wavefront of a workgroup the same number of entries in every window; what it
 // is longer because they have not (then one wavefront works and its requests are not hidden: 13 microseconds per 1000
 // instructions instead of 6), as where the rows of a key lie together; and the runs' sums, a microsecond per million.
-// Gathering: the entries; keys of thousands of rows, which are summed in chunks.  Iterations of one model, gathering / in LDS:
-//   rows        tables                  keys                                                              this rule
-//   5,000,000   100,000, 50,000, 10,000 uniform                                       205 / 175            in LDS
-//   5,000,000   30,000 and 5000         uniform; sorted by the first                  153 / 112; 105 / 645 in LDS; gathers
-//   5,000,000   180,000                 uniform                                       111 / 109            in LDS
-//   5,000,000   50,000                  each key's rows together                      97 / 99              gathers
-//   2,000,000   20,000; 50,000; 180,000 uniform                                       51 / 53; 53 / 55; 58 / 63   gathers
-//   1,500,000   50,000                  uniform; a power law                          47 / 52; 93 / 51     gathers; in LDS
-//   1,000,000   20,000 twice; 3000 twice uniform                                      49 / 50; 43 / 41     gathers; in LDS
-//   1,000,000   30,000 and 5000         the first of slowly moving keys               48 / 100             gathers
-//   500,000     60,000; 3000; three of each uniform                                   47 / 54; 39 / 38     gathers; in LDS
-double segbin_gain(int64_t r_T, std::vector<SegBinPlan>& plans, const int* ks, int n, bool gathers, int* uneven) {
+// Gathering: the entries; keys of thousands of rows, which are summed in chunks; and the launch, unless another source takes
+// one in any case.  All sources of a launch or none: where one gathers it costs the others little to join it (3,000,000 rows
+// over 100,000 sorted and twice 20,000 keys: 122 with the two in LDS, 110 without).  Iterations of one model, gathering / in LDS:
+//   5,000,000 rows   100,000, 50,000 and 10,000 uniform keys     205 / 175   in LDS
+//                    180,000 uniform keys                        111 / 109   in LDS
+//                    50,000 keys, the rows of each together       97 / 99    gathers
+//                    30,000 sorted and 5000 uniform keys         105 / 645   gathers
+//   2,000,000 rows   20,000, 50,000 or 180,000 uniform keys       51 / 53, 53 / 55, 58 / 63   gathers
+//   1,500,000 rows   50,000 uniform keys; by a power law          47 / 52; 93 / 51            gathers; in LDS
+//   1,000,000 rows   twice 20,000 or twice 3000 uniform keys      49 / 50; 43 / 41            gathers; in LDS
+//                    30,000 slowly moving and 5000 uniform keys   48 / 100  gathers
+//     500,000 rows   three times 60,000 or 3000 uniform keys      47 / 54; 39 / 38            gathers; in LDS
+double segbin_gain(int64_t r_T, std::vector<SegBinPlan>& plans, const int* ks, int n) {
   std::vector<BinPart> parts;
-  double gather = gathers ? 0.0 : 8.0;              // (a launch, unless there is one in any case)
+  double gather = 0.0, launch = 0.0, chunks = 0.0;
   for (int q = 0; q < n; ++q) {
     SegBinPlan& s = plans[(size_t)ks[q]];
     const int64_t rows = (int64_t)s.keyinfo.size();
@@ -427,34 +427,29 @@ double segbin_gain(int64_t r_T, std::vector<SegBinPlan>& plans, const int* ks, i
       BinRange& r = s.ranges[g];
       const double groups = std::max(1.0, r.entries / (double)n_win / kBinWaves / kWave + 0.5);
       parts.push_back(BinPart{&r, s.groups.empty() ? nullptr : s.groups.data() + g * (size_t)n_win, window_cost(log, groups),
-                              std::max(1, n_win / kSegSlices), n_win, ks[q], log});
+                              std::max(1, n_win / kSegSlices), n_win, log});
     }
     gather += 6.2e-6 * (double)s.entries;
+    if (!s.joins_launch) launch = 8.0;
+    if (s.very_long) chunks = 10.0;
   }
-  for (int q = 0; q < n; ++q)
-    if (plans[(size_t)ks[q]].very_long) { gather += 10.0; break; }
   segbin_share(parts);
-  double even = 0.0, longest = 0.0, sums = 0.0, most = 0.0;
-  *uneven = -1;
+  double even = 0.0, longest = 0.0, sums = 0.0;
   for (const BinPart& p : parts) {
     sums += (double)p.r->nsub * kSegSlices * p.r->slots;
-    double p_even = 0.0, p_longest = 0.0;
     for (int x = 0; x < kSegSlices; ++x)
       for (int sub = 0; sub < p.r->nsub; ++sub) {
         const BinRun run = segbin_run(p.n_win, x, sub, p.r->nsub);
         double c = p.window * (run.w1 - run.w0);
-        p_even = std::max(p_even, c);
+        even = std::max(even, c);
         if (p.groups != nullptr) {
           c = 0.0;
           for (int w = run.w0; w < run.w1; ++w) c += window_cost(p.log, p.groups[w]);
         }
-        p_longest = std::max(p_longest, c);
+        longest = std::max(longest, c);
       }
-    if (p_longest > 1.5 * p_even && p_longest - p_even > most) { most = p_longest - p_even; *uneven = p.source; }
-    even = std::max(even, p_even);
-    longest = std::max(longest, p_longest);
   }
-  return gather - (12.2 + 6e-3 * even + 13e-3 * std::max(longest - even, 0.0) + 1e-6 * sums);
+  return gather + launch + chunks - (12.2 + 6e-3 * even + 13e-3 * std::max(longest - even, 0.0) + 1e-6 * sums);
 }
 
 }  // namespace
@@ -463,17 +458,16 @@ double segbin_gain(int64_t r_T, std::vector<SegBinPlan>& plans, const int* ks, i
 // iteration (gathering / in LDS), 500,000 and one 33 / 36, 1,000,000 and one 37..45 / 39..45.
 bool segbin_enough(int64_t r_T, int n) { return n > 0 && (r_T >= 1500000 || (n >= 2 && r_T >= 500000 && n * r_T >= 1500000)); }
 
-void segbin_choose(int64_t r_T, std::vector<SegBinPlan>& plans, std::vector<int>& in_bins, bool& gathers) {
+void segbin_choose(int64_t r_T, std::vector<SegBinPlan>& plans, std::vector<int>& in_bins) {
   for (bool again = true; again;) {
     again = false;
     if (!segbin_enough(r_T, (int)in_bins.size())) in_bins.clear();
     for (size_t i = 0; i < in_bins.size() && !again; i += kSegMulti) {       // (the sources of a launch, as they are called)
       const int n = (int)std::min<size_t>(kSegMulti, in_bins.size() - i);
-      int uneven = -1;
-      if (segbin_gain(r_T, plans, in_bins.data() + i, n, gathers, &uneven) > 0.0) continue;
-      if (uneven >= 0) in_bins.erase(std::find(in_bins.begin() + i, in_bins.begin() + i + n, uneven));
-      else in_bins.erase(in_bins.begin() + i, in_bins.begin() + i + n);
-      gathers = again = true;
+      if (segbin_gain(r_T, plans, in_bins.data() + i, n) > 0.0) continue;
+      in_bins.erase(in_bins.begin() + i, in_bins.begin() + i + n);
+      for (int k : in_bins) plans[(size_t)k].joins_launch = true;
+      again = true;
     }
   }
 }
