@@ -742,14 +742,19 @@ def _keyed(seed, r_T, dims, missing=0.0, sparse=False):
 
 
 @pytest.mark.parametrize("r_T,dims,missing", [
-    (1_500_000, [(20_480, 0)], 0.0),                              # one full range of keys
-    (1_500_001, [(20_481, 0)], 0.1),                              # two ranges, a last window of one row
+    (4_000_000, [(20_480, 0)], 0.0),                              # one full range of keys
+    (5_000_001, [(20_481, 0)], 0.1),                              # two ranges
+    (3_002_369, [(1_000, 0)], 0.0),                               # windows of 2^12 rows, the last of one row
+    (4_005_889, [(1_000, 0), (40_960, 0)], 0.1),                  # ... and of 2^13, two full ranges
+    (6_291_457, [(100_000, 2), (61_441, 9)], 0.0),                # windows of 2^14 rows, the last of one row; hot keys
+    (12_000_001, [(307_200, 0), (250_000, 1), (225_281, 1)], 0.0),   # 15, 13 and 12 ranges in one launch
     (1_500_033, [(1, 0)], 0.0),                                   # a single key
-    (1_507_327, [(187_500, 0)], 0.0),                             # as many ranges as keys per target row allow; a whole window less a row
+    (1_507_327, [(187_500, 0)], 0.0),                             # as many keys as rows allow: gathers
+    (4_005_887, [(40_961, 0), (5, 0)], 0.0),                      # a whole window less a row
     (2_000_003, [(40_000, 6), (61_441, 12), (17, 0), (100_000, 0), (5_000, 3)], 0.3),   # hot keys; sources of two launches
     (500_003, [(1_000, 9), (300, 0), (60_000, 0)], 0.0),          # the smallest target table
     (750_000, [(2_049, 40), (2, 0)], 0.9),                        # nearly every row of a few keys, most rows of none
-    (3_000_001, [(30_000, 2), (1_000, 200)], 0.0),                # windows of all three lengths; all entries on a few keys
+    (3_000_001, [(30_000, 2), (1_000, 200)], 0.0),                # all entries on a few keys
 ])
 def test_segment_sums_in_lds(il, r_T, dims, missing):
     # one operand column: segment sums in LDS; a plan for several columns takes the gathering form.  Whole numbers: same bits.
@@ -780,16 +785,22 @@ def test_segment_sums_in_lds(il, r_T, dims, missing):
         at += 3
 
 
-def test_segment_sums_in_lds_without_room(il):
-    # a workspace too small for the extra index of a mid-sized plan still gets a plan, without it
+@pytest.mark.parametrize("r_T,dims,less,ordered", [
+    (800_000, [(3_000, 0), (500, 3)], 6 << 20, False),            # without the index (four bytes a row and table)
+    (5_000_000, [(100_000, 0)], 10 << 20, False),                 # with it, but without room for the sliced one beside it ...
+    (5_000_000, [(100_000, 0)], 10 << 20, True),                  # ... which keys in order would take
+])
+def test_segment_sums_in_lds_without_room(il, r_T, dims, less, ordered):
+    # a workspace too small for what a plan would like to keep still gets a plan, without it
     import ctypes
-    r_T, dims = 800_000, [(3_000, 0), (500, 3)]
     sources, c_T, y = _keyed(5, r_T, dims)
+    if ordered:
+        sources = [(D, idx.sort()[0], cm) for D, idx, cm in sources]
     Y = y[:r_T].clone().reshape(-1, 1)
     want = il.ilargi_tmm(il.ilargi_plan_create(sources, r_T, c_T, max_cx=1), Y).cpu()
     tuples, borrowed, shapes = il._marshal_sources(sources, r_T)
     arr, keep = il.make_source_array(tuples)
-    room = il.ilargi_plan_workspace_bytes(tuples, r_T, c_T, 1) - (6 << 20)    # (the indices take four bytes a row and table)
+    room = il.ilargi_plan_workspace_bytes(tuples, r_T, c_T, 1) - less
     ws = torch.empty(room + 256, dtype=torch.uint8, device="cuda")
     handle = ctypes.c_void_p(0)
     base = (ws.data_ptr() + 255) // 256 * 256
