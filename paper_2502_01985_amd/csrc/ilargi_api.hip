@@ -1230,7 +1230,7 @@ ilargi_status_t gd_star_step(ilargi_plan* pl, int mode, float* W, int m, const f
 
 // One Lloyd iteration in one pass over the identity source (kernels_tile.hip): the assignments come out of the assembly
 // of T C, with the identity source's cluster sums; a joined source's sums are its table times the cluster counts of its
-// rows.  G (c_T x k) receives the per-cluster sums, cnt the cluster sizes.
+// rows.
 // Widest identity source that the one pass serves faster than the separate ones.  Its operand and cluster sums grow with
 // columns times centroids in LDS, until three workgroups, then two, share a compute unit; the separate passes take operands
 // of 5 to 7 columns in two rounds.  Time of an iteration over 20,000 to 1,000,000 rows, one pass over separate passes:
@@ -1255,7 +1255,21 @@ bool kmeans_fused_ok(const ilargi_plan* pl, int64_t k) {
   return true;
 }
 
+// Most cells of C whose norms every workgroup of the pass forms for itself, while every workgroup of the last launch (one per
+// column) adds up the cluster sizes and divides; beyond, launches of their own do so once.  Iterations in microseconds,
+// launches / merged: 200,000 rows joined with 2000 x c, 10 centroids: c = 200 52 / 47, 500 65 / 65, 1000 81 / 91, 4000 140 / 191;
+// 3 centroids: 500 55 / 47, 1000 62 / 58, 2000 72 / 79; 16 centroids: 200 58 / 55, 500 71 / 80, 4000 145 / 268.
+constexpr int64_t kKmeansMergedCells = 4096;
+
 ilargi_status_t kmeans_fused(ilargi_plan* pl, float* C, int k, int32_t* assign, int32_t* counts, hipStream_t st) {
+  const bool merged = pl->c_T * k <= kKmeansMergedCells;
+  float* G = pl->at<float>(pl->lay.o_rmm);              // c_T x k: per-cluster sums
+  float* cn = merged ? nullptr : pl->at<float>(pl->lay.o_cn);
+  int32_t* cnt = pl->at<int32_t>(pl->lay.o_counts);
+  if (!merged) {
+    TraceScope ts(pl, "centroid_norm", -1, st);
+    HIP_TRY(launch_centroid_norm(C, pl->c_T, k, cn, st));
+  }
   LmmArgs a;
   memset(&a, 0, sizeof(a));
   const SourcePlan& f = pl->src[pl->fused];
@@ -1272,9 +1286,10 @@ ilargi_status_t kmeans_fused(ilargi_plan* pl, float* C, int k, int32_t* assign, 
   int32_t* sizes = pl->at<int32_t>(pl->lay.o_loss);
   {
     TraceScope ts(pl, "kmeans_assign", -1, st);
-    HIP_TRY(launch_kmeans_tile(a, pl->c_T, assign, sizes, sums, grid, logR, st));
+    HIP_TRY(launch_kmeans_tile(a, cn, pl->c_T, assign, sizes, sums, grid, logR, st));
   }
-  // the blocks of all sources stay until the last launch adds them: the room left is shared out
+  if (!merged) HIP_TRY(launch_kmeans_counts(sizes, grid, k, cnt, st));
+  // merged: the blocks of all sources stay until the last launch adds them, and the room left is shared out
   int64_t used = (int64_t)grid * f.cols * k;
   const int64_t share = (pl->lay.gpartial_floats - used) / std::max(pl->n - 1, 1);
   ColAsmArgs c;
@@ -1299,7 +1314,8 @@ ilargi_status_t kmeans_fused(ilargi_plan* pl, float* C, int k, int32_t* assign, 
       g.B = pl->at<float>(p.o_pz); g.ldb = k; g.cb = k; g.b_rows = p.rows;
       g.n_rows = p.rows;
       int nparts = 0;
-      const ilargi_status_t rc = run_tred(pl, g, pl->at<float>(p.o_g), "colred", q, false, st, false, sums + used, share, &nparts);
+      const ilargi_status_t rc = run_tred(pl, g, pl->at<float>(p.o_g), "colred", q, false, st, false, sums + used,
+                                          merged ? share : pl->lay.gpartial_floats - used, merged ? &nparts : nullptr);
       if (rc != ILARGI_OK) return rc;
       c.G[c.n] = nparts > 0 ? sums + used : pl->at<float>(p.o_g);
       c.nparts[c.n] = nparts;
@@ -1307,7 +1323,18 @@ ilargi_status_t kmeans_fused(ilargi_plan* pl, float* C, int k, int32_t* assign, 
     }
     ++c.n;
   }
-  c.c_T = (int)pl->c_T; c.cx = k; c.out = C;
+  c.c_T = (int)pl->c_T; c.cx = k;
+  if (!merged) {
+    c.out = G;
+    {
+      TraceScope ts(pl, "finalize", -1, st);
+      HIP_TRY(launch_colasm(c, 0, st));
+    }
+    TraceScope ts(pl, "kmeans_update", -1, st);
+    HIP_TRY(launch_kmeans_update(C, G, cnt, pl->c_T, k, counts, st));
+    return ILARGI_OK;
+  }
+  c.out = C;
   c.sizes = sizes; c.n_sizes = grid; c.counts = counts;
   TraceScope ts(pl, "kmeans_update", -1, st);
   HIP_TRY(launch_colasm(c, 2, st));

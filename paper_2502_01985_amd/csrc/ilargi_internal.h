@@ -614,8 +614,9 @@ hipError_t launch_kmeans_assign(float* P, const float* cn, int64_t r_T, int k, i
 constexpr int kKmeansTileK = 16;     // most centroids of the one-pass assignment (kernels_tile.hip)
 bool kmeans_tile_supported(int ck, int k);
 int kmeans_tile_grid(const LmmArgs& a, int* logR);
-hipError_t launch_kmeans_tile(const LmmArgs& a, int64_t c_T, int32_t* assign, int32_t* counts_partial, float* sum_partial,
-                              int grid, int logR, hipStream_t st);
+hipError_t launch_kmeans_tile(const LmmArgs& a, const float* cn, int64_t c_T, int32_t* assign, int32_t* counts_partial,
+                              float* sum_partial, int grid, int logR, hipStream_t st);   // cn: centroid norms, NULL: formed there
+hipError_t launch_kmeans_counts(const int32_t* partial, int nparts, int k, int32_t* counts, hipStream_t st);
 hipError_t launch_kmeans_segcount(const int32_t* rowptr, const int32_t* perm, const int32_t* assign, int64_t r_k, int k,
                                   int logG, float* Z, hipStream_t st);
 hipError_t launch_kmeans_update(float* C, const float* G, const int32_t* counts, int64_t c_T, int k,

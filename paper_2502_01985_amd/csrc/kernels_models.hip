@@ -360,6 +360,11 @@ hipError_t launch_kmeans_assign(float* P, const float* cn, int64_t r_T, int k, i
   return hipGetLastError();
 }
 
+hipError_t launch_kmeans_counts(const int32_t* partial, int nparts, int k, int32_t* counts, hipStream_t st) {
+  kmeans_counts_kernel<<<k, kBlock, 0, st>>>(partial, nparts, k, counts);
+  return hipGetLastError();
+}
+
 hipError_t launch_kmeans_segcount(const int32_t* rowptr, const int32_t* perm, const int32_t* assign, int64_t r_k, int k,
                                   int logG, float* Z, hipStream_t st) {
   if (r_k <= 0) return hipSuccess;

@@ -355,15 +355,8 @@ __global__ __launch_bounds__(kBlock, 4) void asm_tile_kernel(LmmArgs a, int logR
   if constexpr (FUSEG) tile_grad_store<CT>(tile, g, ck, nsub, a.grad_partial + (int64_t)blockIdx.x * ck * kNarrowCT);
 }
 
-// KMeans (at most 16 centroids): the assembly of T C, the nearest centroid of every row and the identity source's share
-// of the per-cluster sums in one pass over its tiles.  Neither T C nor the 0/1 assignment matrix is written: the rows'
-// products stay in registers (KC of them, KC = k rounded up to a multiple of four), and a thread owns a column of the
-// tile and every nsub-th of its rows and adds each value to its sum for the row's cluster, kept in LDS.
-// 1,000,000 x 20 joined with 100,000 rows, 10 centroids: 58 microseconds; T C (65), the assignment (21) and S^T A (38)
-// by themselves took 124.  Of the 58, 8 are the gathers, 8 the cluster sums and most of the rest the operand's way
-// through LDS to every lane (smaller tiles, which spread a row over lanes, measure 3 to 26 % slower).
-// The squared norm of every centroid, by every workgroup: C is a few kilobytes, and a launch for it takes as long as this.
-// Added in the order of centroid_norm_kernel, so that both forms of a Lloyd iteration see the same bits.  red: k x kBlock.
+// The squared norm of every centroid, by every workgroup of a kernel: while C is a few kilobytes, a launch for it takes as
+// long as this.  Added in the order of centroid_norm_kernel, so that both ways give the same bits.  red: k x kBlock.
 template <int KC>
 __device__ __forceinline__ void centroid_norms(const float* __restrict__ C, int ldc, int c_T, int k, float* red, float* cns) {
   const int tid = threadIdx.x;
@@ -395,8 +388,16 @@ __device__ __forceinline__ void centroid_norms(const float* __restrict__ C, int 
   __syncthreads();
 }
 
+// KMeans (at most 16 centroids): the assembly of T C, the nearest centroid of every row and the identity source's share
+// of the per-cluster sums in one pass over its tiles.  Neither T C nor the 0/1 assignment matrix is written: the rows'
+// products stay in registers (KC of them, KC = k rounded up to a multiple of four), and a thread owns a column of the
+// tile and every nsub-th of its rows and adds each value to its sum for the row's cluster, kept in LDS.
+// 1,000,000 x 20 joined with 100,000 rows, 10 centroids: 60 microseconds, 2 of them the norms; T C (65), the assignment (21)
+// and S^T A (38) by themselves took 124.  Of the 60, 8 are the gathers, 8 the cluster sums and most of the rest the operand's
+// way through LDS to every lane (smaller tiles, which spread a row over lanes, measure 3 to 26 % slower).
+// cn: the norms of the centroids, or NULL.
 template <int KC, bool AL>
-__global__ __launch_bounds__(kBlock, 4) void kmeans_tile_kernel(LmmArgs a, int c_T, int32_t* __restrict__ assign,
+__global__ __launch_bounds__(kBlock, 4) void kmeans_tile_kernel(LmmArgs a, const float* __restrict__ cn, int c_T, int32_t* __restrict__ assign,
                                                              int32_t* __restrict__ counts_partial, float* __restrict__ sum_partial,
                                                              int logR) {
   extern __shared__ v4f tile_lds4[];
@@ -414,7 +415,8 @@ __global__ __launch_bounds__(kBlock, 4) void kmeans_tile_kernel(LmmArgs a, int c
     Xs[e] = (t >= 0 && n < k) ? a.X[(int64_t)t * a.ldx + n] : 0.0f;
   }
   if (tid < k) hist[tid] = 0;
-  centroid_norms<KC>(a.X, a.ldx, c_T, k, acc, cns);      // (acc is scratch until here)
+  if (cn == nullptr) centroid_norms<KC>(a.X, a.ldx, c_T, k, acc, cns);      // (acc is scratch until here)
+  else if (tid < KC) cns[tid] = tid < k ? cn[tid] : 0.0f;
   for (int e = tid; e < k * kBlock; e += kBlock) acc[e] = 0.0f;
   const int Rt = 1 << logR, logL = 8 - logR;
   const int row = tid >> logL, l = tid & ((1 << logL) - 1);
@@ -812,7 +814,7 @@ int kmeans_tile_grid(const LmmArgs& a, int* logR) {
 }
 
 // counts_partial: grid x k integers, sum_partial: grid x ck x k floats.
-hipError_t launch_kmeans_tile(const LmmArgs& a, int64_t c_T, int32_t* assign, int32_t* counts_partial, float* sum_partial,
+hipError_t launch_kmeans_tile(const LmmArgs& a, const float* cn, int64_t c_T, int32_t* assign, int32_t* counts_partial, float* sum_partial,
                               int grid, int logR, hipStream_t st) {
   if (!kmeans_tile_supported(a.ck, a.ncols) || a.D == nullptr || a.r_out <= 0) return hipErrorInvalidValue;
   const int kc = (a.ncols + 3) / 4 * 4;
@@ -820,8 +822,8 @@ hipError_t launch_kmeans_tile(const LmmArgs& a, int64_t c_T, int32_t* assign, in
   const bool al = reinterpret_cast<uintptr_t>(a.D) % 16 == 0;
 #define ILARGI_KMEANS(C)                                                                                               \
   do {                                                                                                                 \
-    if (al) kmeans_tile_kernel<C, true><<<grid, kBlock, lds, st>>>(a, (int)c_T, assign, counts_partial, sum_partial, logR);  \
-    else kmeans_tile_kernel<C, false><<<grid, kBlock, lds, st>>>(a, (int)c_T, assign, counts_partial, sum_partial, logR);    \
+    if (al) kmeans_tile_kernel<C, true><<<grid, kBlock, lds, st>>>(a, cn, (int)c_T, assign, counts_partial, sum_partial, logR);  \
+    else kmeans_tile_kernel<C, false><<<grid, kBlock, lds, st>>>(a, cn, (int)c_T, assign, counts_partial, sum_partial, logR);    \
   } while (0)
   if (kc == 4) ILARGI_KMEANS(4);
   else if (kc == 8) ILARGI_KMEANS(8);
