@@ -63,6 +63,7 @@ struct SourcePlan {
   int n_multi = 0;                // chunks [0, n_multi) belong to segments of several
   int long_thr = kLongSeg;        // segments of the inverse index longer than this are summed in chunks
   bool cut = false;               // some segment is long enough to be spread over workgroups
+  float lines = 0.0f;             // lines of a product that 64 target rows in a row read (0: not asked for)
   bool very_long = false;         // some segment has more than kLongSeg entries: no join-order paths
   int max_row = 0, max_col = 0;   // sparse: most entries of a row, of a column
   size_t o_join_first = 0;        // join-order column reduce: first source row of every workgroup
@@ -263,7 +264,7 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
   }
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
-  lay.o_flags = take(sizeof(int32_t) * 3 * n);
+  lay.o_flags = take(sizeof(int32_t) * 4 * n);
   lay.o_tcol_table = take(sizeof(void*) * n);
   lay.o_pairs = take(sizeof(GramAsmPair) * n * (n + 1) / 2);
   lay.o_gslot = take(sizeof(int32_t) * c_T);
@@ -636,6 +637,7 @@ ilargi_status_t lmm_products(ilargi_plan* pl, const float* X, int ldx, int col0,
     g.idx[g.n] = p.ident ? nullptr : p.idx;
     g.P[g.n] = pl->at<float>(p.o_pz);
     g.rows[g.n] = p.rows;
+    g.lines[g.n] = p.lines;
     ++g.n;
   }
   return ILARGI_OK;
@@ -1431,7 +1433,9 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
   pl->src = std::move(src); pl->lay = lay;
   hipStream_t st = static_cast<hipStream_t>(stream);
 
-  HIP_TRY(hipMemsetAsync(pl->at<int32_t>(lay.o_flags), 0, sizeof(int32_t) * 3 * n, st));
+  HIP_TRY(hipMemsetAsync(pl->at<int32_t>(lay.o_flags), 0, sizeof(int32_t) * 4 * n, st));
+  bool count_lines = false;
+  for (const SourcePlan& p : pl->src) count_lines = count_lines || (!p.sparse && p.rows == r_T && lmm_lane_wants_lines(p.rows, p.cols));
   std::vector<const int32_t*> tcol_ptrs(n);
   for (int k = 0; k < n; ++k) {
     SourcePlan& p = pl->src[k];
@@ -1439,6 +1443,7 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     HIP_TRY(hipMemcpyAsync(pl->at<int32_t>(p.o_tcol), tcol[k].data(), sizeof(int32_t) * c_T, hipMemcpyHostToDevice, st));
     tcol_ptrs[k] = pl->at<int32_t>(p.o_tcol);
     if (p.has_idx) HIP_TRY(launch_check_idx(p.idx, r_T, p.rows, pl->at<int32_t>(lay.o_flags) + 2 * k, st));
+    if (p.has_idx && count_lines) HIP_TRY(launch_count_lines(p.idx, r_T, pl->at<int32_t>(lay.o_flags) + 3 * n + k, st));
     if (p.sparse) {
       pl->any_sparse = true;
       SparseArgs sa;
@@ -1448,8 +1453,8 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     }
   }
   HIP_TRY(hipMemcpyAsync(pl->at<void*>(lay.o_tcol_table), tcol_ptrs.data(), sizeof(void*) * n, hipMemcpyHostToDevice, st));
-  std::vector<int32_t> flags(3 * n, 0);
-  HIP_TRY(hipMemcpyAsync(flags.data(), pl->at<int32_t>(lay.o_flags), sizeof(int32_t) * 3 * n, hipMemcpyDeviceToHost, st));
+  std::vector<int32_t> flags(4 * n, 0);
+  HIP_TRY(hipMemcpyAsync(flags.data(), pl->at<int32_t>(lay.o_flags), sizeof(int32_t) * 4 * n, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   for (int k = 0; k < n; ++k)
     if (flags[2 * n + k] != 0)
@@ -1459,6 +1464,7 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     SourcePlan& p = pl->src[k];
     if (!p.has_idx) { p.ident = true; p.nnz = p.rows; continue; }
     if (flags[2 * k] != 0) return fail(ILARGI_ERR_INDEX_RANGE, "source %d: row_idx has an entry outside [-1, %lld)", k, (long long)p.rows);
+    p.lines = (float)flags[3 * n + k] / kLineSamples;
     p.ident = flags[2 * k + 1] == 0 && p.rows <= r_T;
     if (p.ident) p.nnz = p.rows;
   }

@@ -37,6 +37,7 @@ struct GatherArgs {
   const float* P[kMaxSources];
   int64_t rows[kMaxSources];
   int ldp;
+  float lines[kMaxSources];         // 128-byte lines of a column P_s that 64 target rows in a row read (0: not measured)
 };
 
 struct LmmArgs {
@@ -460,6 +461,9 @@ hipError_t launch_cluster_rows(const float* S, int cs, const int32_t* perm, cons
 hipError_t launch_gd_cluster(const ClusterArgs& a, int mode, int max_grid, hipStream_t st, int* grid_out);
 
 // ---- launchers (each enqueues on `st`; returns the HIP error of the launch) ----
+// *lines += lines of 32 keys that 64 consecutive entries hold, summed over kLineSamples places spread over the r_T >= 64 entries.
+constexpr int kLineSamples = 256;
+hipError_t launch_count_lines(const int32_t* idx, int64_t r_T, int32_t* lines, hipStream_t st);
 hipError_t launch_check_idx(const int32_t* idx, int64_t r_T, int64_t r_k, int32_t* flags, hipStream_t st);
 hipError_t launch_sort_by_source_row(const int32_t* idx, int64_t r_T, int64_t r_k, int32_t* keys_a,
                                      int32_t* vals_a, int32_t* keys_b, int32_t* vals_b, int32_t* hist,
@@ -546,6 +550,7 @@ hipError_t launch_build_segbin(const int32_t* idx, int64_t r_T, int64_t nnz, int
                                int32_t* sortbuf, int64_t sort_n, int32_t* hist, int32_t* off, uint32_t* entries, int32_t* groups, hipStream_t st);
 hipError_t launch_segbin(const SegBin* a, int n, float* scratch, int64_t scratch_floats, hipStream_t st);
 hipError_t launch_colred(const ColredArgs& a, int nblocks, hipStream_t st);
+bool lmm_lane_wants_lines(int64_t rows, int64_t cols);   // whether the choice of the assembly over such a table asks for `lines`
 bool lmm_flat_supported(const LmmArgs& a, int vec, bool fuseg);
 hipError_t launch_lmm_flat(const LmmArgs& a, int mode, bool fuseg, hipStream_t st, int* grid_out);
 hipError_t launch_finalize(const FinArgs& a, int c_T, int mode, hipStream_t st);

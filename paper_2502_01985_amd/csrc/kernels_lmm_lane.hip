@@ -320,11 +320,14 @@ void lane_shape(const LmmArgs& a, int vec, int* rpl, int* nv) {
 }
 
 // The products a workgroup of kLaneLdsWaves wavefronts keeps in LDS, the smallest tables first; whether that pays: with a
-// residual (without one the chip holds more wavefronts), rows of 6 or 10 columns (wider ones would spill registers), at least
-// half of a source's gathers from LDS in all, and an entity table that is read past the caches.  Iterations in microseconds,
-// without / with, rows of 10 columns: one table of 20,000 rows, all but 544 in LDS, 5,000,000 target rows 96.0 / 86.9,
-// 3,400,000 75.5 / 71.4, and read through the caches 3,000,000 64.7 / 67.2, 1,000,000 38.3 / 41.7; three tables 174.9 / 166.2,
-// 135.5 / 132.3, 129.8 / 127.3, 77.3 / 79.9.
+// residual (without one the chip holds more wavefronts), rows of 6 or 10 columns (wider ones would spill registers), an entity
+// table that is read past the caches, and gathers that go to many lines: what 64 target rows in a row read beyond 30 lines,
+// weighted with the part of the table in LDS, has to be a quarter of the most there could be.
+// Iterations in microseconds, without / with, 5,000,000 x 10 and one table of 20,000 rows: uniform keys (61 lines) 94 / 86, by a
+// power law whose first key has a fifth of the rows (48) 98 / 94, in blocks of 1000 (28) 99 / 102, sorted (1) 84 / 90; 38,000
+// uniform keys, half of them in LDS, 97 / 96; 300 keys (10) 78 / 79.  By rows, uniform keys: 3,400,000 75.5 / 71.4; read through
+// the caches 3,000,000 64.7 / 67.2, 1,000,000 38.3 / 41.7; three tables 5,000,000 174.9 / 166.2, 3,800,000 135.5 / 132.3; through
+// the caches 3,000,000 129.8 / 127.3, 1,000,000 77.3 / 79.9.
 bool lane_lds(const LmmArgs& a, int mode, int nv, LaneLds* pl) {
   memset(pl, 0, sizeof(*pl));
   if (mode == 0 || nv > 5 || a.nt_in == 0) return false;
@@ -332,18 +335,20 @@ bool lane_lds(const LmmArgs& a, int mode, int nv, LaneLds* pl) {
   for (int s = 0; s < a.g.n; ++s) order[s] = s;
   std::sort(order, order + a.g.n, [&](int x, int y) { return a.g.rows[x] < a.g.rows[y]; });
   int at = 0;
-  double share = 0.0;
+  double gain = 0.0;
   for (int i = 0; i < a.g.n; ++i) {
     const int s = order[i], room = kLaneLdsBytes / 4 - kLaneLdsWaves * kWave * nv * 4 - at;
     pl->n[s] = (int)std::min<int64_t>(a.g.rows[s], room);
     pl->off[s] = at;
     at += pl->n[s];
-    share += a.g.rows[s] > 0 ? (double)pl->n[s] / (double)a.g.rows[s] : 1.0;
+    if (a.g.rows[s] > 0) gain += std::max(a.g.lines[s] - 30.0, 0.0) / (kWave - 30) * pl->n[s] / (double)a.g.rows[s];
   }
-  return 2.0 * share >= 1.0;
+  return gain >= 0.25;
 }
 
 }  // namespace
+
+bool lmm_lane_wants_lines(int64_t rows, int64_t cols) { return (cols == 6 || cols == 10) && stream_past_caches(rows * cols) != 0; }
 
 // One operand column; the identity source covers every target row (d_rows == r_out, an even number); rows of 6, 10
 // or 14 columns (vec 2) on a 16-byte aligned base; one to three

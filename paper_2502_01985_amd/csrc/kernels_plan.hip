@@ -26,6 +26,26 @@ __global__ __launch_bounds__(kBlock) void check_idx_kernel(const int32_t* __rest
   }
 }
 
+// A wavefront per place: the lanes with the line of the first remaining one are counted once and leave.
+__global__ __launch_bounds__(kBlock) void count_lines_kernel(const int32_t* __restrict__ idx, int64_t r_T, int32_t* __restrict__ lines) {
+  const int lane = threadIdx.x % kWave, at = (int)(blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave);
+  const int32_t j = idx[(r_T - kWave) * at / (kLineSamples - 1) + lane];
+  const int line = j / 32;
+  int count = 0;
+  for (uint64_t left = __ballot(j >= 0); left != 0;) {
+    left &= ~__ballot(line == __builtin_amdgcn_readlane(line, __builtin_ctzll(left)));
+    ++count;
+  }
+  if (lane == 0) atomicAdd(lines, count);
+}
+
+hipError_t launch_count_lines(const int32_t* idx, int64_t r_T, int32_t* lines, hipStream_t st) {
+  if (r_T < kWave) return hipErrorInvalidValue;
+  static_assert(kLineSamples % (kBlock / kWave) == 0, "whole workgroups");
+  count_lines_kernel<<<kLineSamples / (kBlock / kWave), kBlock, 0, st>>>(idx, r_T, lines);
+  return hipGetLastError();
+}
+
 hipError_t launch_check_idx(const int32_t* idx, int64_t r_T, int64_t r_k, int32_t* flags, hipStream_t st) {
   if (r_T == 0) return hipSuccess;
   int grid = (int)((r_T + kBlock - 1) / kBlock);

@@ -1090,3 +1090,26 @@ def test_one_source_left_by_the_join_order_is_too_few_for_sums_in_lds(il):
     out = il.ilargi_tmm(one, Y)
     assert torch.equal(out, il.ilargi_tmm(several, Y))
     assert _launches(lambda: il.ilargi_tmm(one, Y, out)) == _launches(lambda: il.ilargi_tmm(several, Y, out))
+
+
+@pytest.mark.parametrize("kind", _ORDERS)
+@pytest.mark.parametrize("r_T,c,rows", [(3_355_444, 10, 20_000), (5_592_406, 6, 27_000)])
+def test_products_in_lds_only_for_keys_in_no_order(il, kind, r_T, c, rows):
+    # gathers that find their lines in the caches are faster from there; either way against float64
+    gen = torch.Generator(device="cuda").manual_seed(rows)
+    idx = _ordered(kind, rows, r_T, gen)
+    sources = [(torch.randn(r_T, c, generator=gen, device="cuda"), None, list(range(c))),
+               (torch.randn(rows, 7, generator=gen, device="cuda"), idx, list(range(c, c + 7)))]
+    plan = il.ilargi_plan_create(sources, r_T, c + 7, max_cx=1)
+    w = torch.randn(c + 7, 1, generator=gen, device="cuda") / 4
+    y = (torch.rand(r_T, generator=gen, device="cuda") < 0.5).float()
+    (S, _, _), (R, _, _) = sources
+    z = S.double() @ w[:c].double() + (R.double() @ w[c:].double())[idx.long()]
+    e = torch.sigmoid(z) - y.double().unsqueeze(1)
+    Z = torch.zeros(rows, 1, dtype=torch.float64, device="cuda").index_add_(0, idx.long(), e)
+    want = w.double() - 0.5 * torch.cat([S.double().t() @ e, R.double().t() @ Z]) / r_T
+    W, loss = w.clone(), torch.zeros(1, device="cuda")
+    il.ilargi_gd_step(plan, il.LOGISTIC, W, y, torch.full((1,), 0.5, device="cuda"), loss)
+    # float32 products of seventeen terms: residuals to some 1e-6, gradients averaged over millions of them
+    assert float((W.double() - want).norm() / want.norm()) < 1e-6
+    assert abs(float(loss) / float((torch.nn.functional.softplus(z) - y.double().unsqueeze(1) * z).mean()) - 1) < 2e-6
