@@ -1567,6 +1567,9 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     }
     for (int k : in_bins) bin[k].joins_launch = gathers[pl->src[k].sliced];
     segbin_choose(r_T, bin, in_bins);
+    // (the counts lie where the residual will: a small part of it)
+    int32_t* counts = pl->at<int32_t>(lay.o_E);
+    std::vector<int32_t> groups;
     for (int k : in_bins) {
       SourcePlan& p = pl->src[k];
       SegBinPlan& b = bin[k];
@@ -1579,10 +1582,15 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
       const int n_win = (int)segbin_windows(r_T, p.rows);
       HIP_TRY(launch_build_segbin(p.idx, r_T, p.nnz, (int)b.ranges.size(), n_win, segbin_win_log(r_T, p.rows),
                                   pl->at<uint32_t>(p.o_bin_keyinfo), sortbuf, std::max<int64_t>(r_T, 1), pl->at<int32_t>(lay.o_hist),
-                                  pl->at<int32_t>(p.o_bin_off), pl->at<uint32_t>(p.o_bin_entries), sortbuf, st));
-      b.groups.resize(b.ranges.size() * (size_t)n_win);
-      HIP_TRY(hipMemcpyAsync(b.groups.data(), sortbuf, sizeof(int32_t) * b.groups.size(), hipMemcpyDeviceToHost, st));
+                                  pl->at<int32_t>(p.o_bin_off), pl->at<uint32_t>(p.o_bin_entries), counts + groups.size(), st));
+      groups.resize(groups.size() + b.ranges.size() * (size_t)n_win);
+    }
+    if (!in_bins.empty()) {
+      if ((int64_t)groups.size() > r_T * max_cx) return fail(ILARGI_ERR_WORKSPACE, "internal: counts of the segment sums overflow");
+      HIP_TRY(hipMemcpyAsync(groups.data(), counts, sizeof(int32_t) * groups.size(), hipMemcpyDeviceToHost, st));
       HIP_TRY(hipStreamSynchronize(st));
+      const int32_t* g = groups.data();
+      for (int k : in_bins) { bin[k].groups = g; g += bin[k].ranges.size() * (size_t)segbin_windows(r_T, pl->src[k].rows); }
     }
     segbin_choose(r_T, bin, in_bins);
     for (int k = 0; k < n; ++k) pl->src[k].binned = false;
@@ -1593,13 +1601,12 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
       p.sliced = false;
       p.bin_heavy = (int)b.heavy.size();
       p.bin_slots = b.max_slots();
-      std::vector<BinItem> items;
-      segbin_items(b.ranges, items, &p.bin_partial);
-      p.bin_items = (int)items.size();
+      segbin_items(b.ranges, b.items, &p.bin_partial);
+      p.bin_items = (int)b.items.size();
       HIP_TRY(hipMemcpyAsync(pl->at<BinRange>(p.o_bin_ranges), b.ranges.data(), sizeof(BinRange) * b.ranges.size(), hipMemcpyHostToDevice, st));
-      HIP_TRY(hipMemcpyAsync(pl->at<BinItem>(p.o_bin_items), items.data(), sizeof(BinItem) * items.size(), hipMemcpyHostToDevice, st));
-      HIP_TRY(hipStreamSynchronize(st));
+      HIP_TRY(hipMemcpyAsync(pl->at<BinItem>(p.o_bin_items), b.items.data(), sizeof(BinItem) * b.items.size(), hipMemcpyHostToDevice, st));
     }
+    if (!in_bins.empty()) HIP_TRY(hipStreamSynchronize(st));
   }
   for (int k = 0; k < n; ++k) {
     SourcePlan& p = pl->src[k];

@@ -239,7 +239,8 @@ struct SegBinPlan {
   std::vector<BinRange> ranges;
   std::vector<uint32_t> keyinfo;
   std::vector<int32_t> heavy;
-  std::vector<int32_t> groups;   // [range][window]: groups of 64 entries of the wavefront with the most; empty: not known yet
+  std::vector<BinItem> items;
+  const int32_t* groups = nullptr;   // [range][window]: groups of 64 entries of the wavefront with the most; NULL: not known yet
   int64_t entries = 0;
   bool very_long = false;        // some segment has more than kLongSeg entries
   bool joins_launch = false;     // another source gathers in the launch that this one would gather in
@@ -544,8 +545,7 @@ bool segbin_enough(int64_t r_T, int n);            // whether n sources over so 
 // in_bins: the sources that may run in LDS; on return those that do, with the runs of windows in their ranges.
 void segbin_choose(int64_t r_T, std::vector<SegBinPlan>& plans, std::vector<int>& in_bins);
 void segbin_items(std::vector<BinRange>& ranges, std::vector<BinItem>& items, int64_t* partial_floats);
-// sortbuf: four arrays of sort_n integers, hist: sort_hist_ints(r_T); both are scratch.  groups: SegBinPlan::groups, may lie
-// in the first of the four arrays.
+// sortbuf: four arrays of sort_n integers, hist: sort_hist_ints(r_T); both are scratch.  groups: SegBinPlan::groups
 hipError_t launch_build_segbin(const int32_t* idx, int64_t r_T, int64_t nnz, int n_ranges, int n_win, int win_log, const uint32_t* keyinfo,
                                int32_t* sortbuf, int64_t sort_n, int32_t* hist, int32_t* off, uint32_t* entries, int32_t* groups, hipStream_t st);
 hipError_t launch_segbin(const SegBin* a, int n, float* scratch, int64_t scratch_floats, hipStream_t st);

@@ -426,7 +426,7 @@ double segbin_gain(int64_t r_T, std::vector<SegBinPlan>& plans, const int* ks, i
     for (size_t g = 0; g < s.ranges.size(); ++g) {
       BinRange& r = s.ranges[g];
       const double groups = std::max(1.0, r.entries / (double)n_win / kBinWaves / kWave + 0.5);
-      parts.push_back(BinPart{&r, s.groups.empty() ? nullptr : s.groups.data() + g * (size_t)n_win, window_cost(log, groups),
+      parts.push_back(BinPart{&r, s.groups == nullptr ? nullptr : s.groups + g * (size_t)n_win, window_cost(log, groups),
                               std::max(1, n_win / kSegSlices), n_win, log});
     }
     gather += 6.2e-6 * (double)s.entries;
