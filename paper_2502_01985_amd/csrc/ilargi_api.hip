@@ -769,9 +769,10 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
       }
       if (nm == 0) first_k = k;
       if (kind == kBinned) {
-        bins[nm] = bin_args(pl, k);
-        bins[nm].Y = Y; bins[nm].ldy = ldy; bins[nm].col0 = col0;
-        bins[nm].Z = pl->at<float>(p.o_pz); bins[nm].ldz = ldy; bins[nm].zcol0 = col0;
+        if (ldy != 1) return fail(ILARGI_ERR_WORKSPACE, "internal: segment sums of several columns in LDS");
+        bins[nm] = bin_args(pl, k);                                                // (such plans are for one operand column)
+        bins[nm].Y = Y;
+        bins[nm].Z = pl->at<float>(p.o_pz);
       } else {
         multi[nm] = segsum_args(k);
       }

@@ -255,10 +255,8 @@ struct SegBin {
   const int32_t* heavy;      // keys with a slot per wavefront
   int n_items, n_heavy, n_ranges, n_win, win_log, max_slots;
   int64_t r_T, r_k;
-  const float* Y;
-  int ldy, col0;
-  float* Z;
-  int ldz, zcol0;
+  const float* Y;            // r_T
+  float* Z;                  // r_k
   float* partial;            // set by the launcher
   int64_t partial_floats;
 };

@@ -1,4 +1,4 @@
-// Segment sums  Z_k = I_k^T Y  for narrow operands over large target tables, summed in LDS in target-row order.
+// Segment sums  Z_k = I_k^T Y  for one operand column over large target tables, summed in LDS in target-row order.
 //
 // The gathering forms of kernels_tmm.hip pay one L2 request per index entry, and a residual of megabytes does not stay
 // in the 32 KB next to a compute unit: 265 G entries a second on this device, whatever the kernel looks like.  Here the
@@ -89,11 +89,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t bin_buffer(const void* p, uint
 // the compiler wait for all of them.
 // U: groups of 64 entries a wavefront requests ahead (the array is padded for reading past its end); what a window has
 // beyond them is loaded when it is its turn.
-template <int RV, int U, bool PLAIN>
+// ALIGNED: the operand starts on 16 bytes.
+template <int RV, int U, bool ALIGNED>
 __device__ __forceinline__ void segbin_windows_sum(const SegBin& a, const float* Y, const int32_t* off, int w0, int w1, float* win, float* acc) {
   constexpr int WIN = RV * kBinThreads;
   const int tid = (int)threadIdx.x, lane = tid % kWave;
-  const uint32_t lane4 = (uint32_t)lane * 4, rT = (uint32_t)a.r_T, ldy = PLAIN ? 1u : (uint32_t)a.ldy;
+  const uint32_t lane4 = (uint32_t)lane * 4, rT = (uint32_t)a.r_T;
   const char* entries = reinterpret_cast<const char*>(a.entries);
   const int n_win = a.n_win;
   float r0[RV], r1[RV];
@@ -109,9 +110,9 @@ __device__ __forceinline__ void segbin_windows_sum(const SegBin& a, const float*
   auto rows_of = [&](int w, float (&r)[RV]) {
     const uint32_t t0 = (uint32_t)w * WIN;                  // (32 bits throughout, which scalar instructions compare)
     const uint32_t left = w < w1 ? min(rT - t0, (uint32_t)WIN) : 0u;
-    const __amdgpu_buffer_rsrc_t rows = bin_buffer(Y + (uint64_t)t0 * ldy, left * ldy * 4u);
+    const __amdgpu_buffer_rsrc_t rows = bin_buffer(Y + t0, left * 4u);
     // (all of an offset goes into the lane's: the scalar one has no part in the check against the buffer's length)
-    if constexpr (PLAIN) {
+    if constexpr (ALIGNED) {
 #pragma unroll
       for (int u = 0; u < RV / 4; ++u) {
         const u4 v = __builtin_amdgcn_raw_buffer_load_b128(rows, tid * 16 + u * kBinThreads * 16, 0, 0);
@@ -121,7 +122,7 @@ __device__ __forceinline__ void segbin_windows_sum(const SegBin& a, const float*
     } else {
 #pragma unroll
       for (int u = 0; u < RV; ++u)
-        r[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, (u / 4 * kBinThreads * 4 + u % 4 + tid * 4) * (int)ldy * 4, 0, 0));
+        r[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, (u / 4 * kBinThreads * 4 + u % 4 + tid * 4) * 4, 0, 0));
     }
   };
   int p0 = __builtin_amdgcn_readlane(offs, 0), p1 = __builtin_amdgcn_readlane(offs, 1), p2 = __builtin_amdgcn_readlane(offs, min(2, w1 - w0));
@@ -170,8 +171,7 @@ __host__ __device__ __forceinline__ BinRun segbin_run(int n_win, int x, int sub,
   return BinRun{wx0 + (int)((int64_t)(wx1 - wx0) * sub / nsub), wx0 + (int)((int64_t)(wx1 - wx0) * (sub + 1) / nsub)};
 }
 
-// PLAIN: the operand is one column of 16-byte aligned floats.
-template <bool PLAIN>
+template <bool ALIGNED>
 __global__ __launch_bounds__(kBinThreads, 4) void segbin_kernel(SegBinMulti m) {
   extern __shared__ float lds[];
   float* win = lds;                               // the residual of a window
@@ -190,11 +190,10 @@ __global__ __launch_bounds__(kBinThreads, 4) void segbin_kernel(SegBinMulti m) {
   for (int s = tid; s < rg.slots; s += kBinThreads) acc[s] = 0.0f;
   __syncthreads();
   if (w0 < w1) {
-    const float* Y = a.Y + a.col0;
     const int32_t* off = a.off + (int64_t)(it.range * kBinWaves + wave) * (a.n_win + 1);
-    if (a.win_log == 12) segbin_windows_sum<4, 5, PLAIN>(a, Y, off, w0, w1, win, acc);
-    else if (a.win_log == 13) segbin_windows_sum<8, 5, PLAIN>(a, Y, off, w0, w1, win, acc);
-    else segbin_windows_sum<16, 5, PLAIN>(a, Y, off, w0, w1, win, acc);
+    if (a.win_log == 12) segbin_windows_sum<4, 5, ALIGNED>(a, a.Y, off, w0, w1, win, acc);
+    else if (a.win_log == 13) segbin_windows_sum<8, 5, ALIGNED>(a, a.Y, off, w0, w1, win, acc);
+    else segbin_windows_sum<16, 5, ALIGNED>(a, a.Y, off, w0, w1, win, acc);
   }
   float* out = a.partial + rg.partial0 + (int64_t)(x * rg.nsub + it.sub) * rg.slots;
   for (int s = tid; s < rg.slots; s += kBinThreads) out[s] = acc[s];
@@ -210,7 +209,6 @@ __global__ __launch_bounds__(kBlock) void segbin_combine_kernel(SegBinMulti m) {
   const SegBin& a = m.s[q];
   const int b = (int)blockIdx.x - m.cfirst[q];
   const int key_blocks = a.n_ranges * m.range_blocks[q];
-  float* Z = a.Z + a.zcol0;
   if (b < key_blocks) {
     const int range = b / m.range_blocks[q];
     const BinRange rg = a.ranges[range];
@@ -233,7 +231,7 @@ __global__ __launch_bounds__(kBlock) void segbin_combine_kernel(SegBinMulti m) {
     __syncthreads();
     if (g == 0 && s < keys && !(a.keyinfo[rg.key0 + s] & kBinHeavy)) {
       for (int c = 1; c < kBinCombineParts; ++c) z += part[c * kBinCombineKeys + l];
-      Z[(int64_t)(rg.key0 + s) * a.ldz] = z;
+      a.Z[rg.key0 + s] = z;
     }
     return;
   }
@@ -256,7 +254,7 @@ __global__ __launch_bounds__(kBlock) void segbin_combine_kernel(SegBinMulti m) {
     for (int u = 0; u < 8; ++u) z += v[u];
   }
   for (int k = kWave / 2; k >= 1; k >>= 1) z += __shfl_xor(z, k);
-  if (lane == 0) Z[(int64_t)j * a.ldz] = z;
+  if (lane == 0) a.Z[j] = z;
 }
 
 // ---- the index, built with the plan ----
@@ -510,7 +508,7 @@ hipError_t launch_segbin(const SegBin* a, int n, float* scratch, int64_t scratch
   m.n = n;
   int64_t at = 0;
   size_t slots = 0;
-  bool plain = true;
+  bool aligned = true;
   for (int q = 0; q < n; ++q) {
     SegBin& s = m.s[q];
     s = a[q];
@@ -521,12 +519,12 @@ hipError_t launch_segbin(const SegBin* a, int n, float* scratch, int64_t scratch
     m.first[q + 1] = m.first[q] + s.n_items;
     m.range_blocks[q] = (int)((s.r_k + s.n_ranges - 1) / s.n_ranges + kBinCombineKeys - 1) / kBinCombineKeys;
     m.cfirst[q + 1] = m.cfirst[q] + s.n_ranges * m.range_blocks[q] + (s.n_heavy + kBlock / kWave - 1) / (kBlock / kWave);
-    plain = plain && s.ldy == 1 && reinterpret_cast<uintptr_t>(s.Y) % 16 == 0;
+    aligned = aligned && reinterpret_cast<uintptr_t>(s.Y) % 16 == 0;
   }
   if (at > scratch_floats) return hipErrorInvalidValue;
   const size_t lds = sizeof(float) * (kBinWinFloats + slots);
   const unsigned grid = (unsigned)m.first[n] * kSegSlices;
-  if (plain) segbin_kernel<true><<<grid, kBinThreads, lds, st>>>(m);
+  if (aligned) segbin_kernel<true><<<grid, kBinThreads, lds, st>>>(m);
   else segbin_kernel<false><<<grid, kBinThreads, lds, st>>>(m);
   segbin_combine_kernel<<<(unsigned)m.cfirst[n], kBlock, 0, st>>>(m);
   return hipGetLastError();
