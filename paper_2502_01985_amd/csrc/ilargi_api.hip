@@ -567,7 +567,7 @@ int pass_width(const ilargi_plan* pl) {
 // The products P_k = D_k (M_k^T X) of every source but the fused one, operand columns [col0, col0 + ncols), and the
 // gathers that add them up.
 ilargi_status_t lmm_products(ilargi_plan* pl, const float* X, int ldx, int col0, int ncols, bool wide, bool bf16, hipStream_t st,
-                             GatherArgs& g) {
+                             GatherArgs& g, float* lines = nullptr) {
   memset(&g, 0, sizeof(g));
   g.ldp = ldx;
   auto product_args = [&](int k) {
@@ -637,7 +637,7 @@ ilargi_status_t lmm_products(ilargi_plan* pl, const float* X, int ldx, int col0,
     g.idx[g.n] = p.ident ? nullptr : p.idx;
     g.P[g.n] = pl->at<float>(p.o_pz);
     g.rows[g.n] = p.rows;
-    g.lines[g.n] = p.lines;
+    if (lines != nullptr) lines[g.n] = p.lines;
     ++g.n;
   }
   return ILARGI_OK;
@@ -649,8 +649,9 @@ ilargi_status_t lmm_pass(ilargi_plan* pl, const float* X, int ldx, int col0, int
                          bool* fused_gradient = nullptr, bool bf16 = false) {
   if (fused_gradient) *fused_gradient = false;
   GatherArgs g;
+  float lines[kMaxSources] = {};
   {
-    const ilargi_status_t rc = lmm_products(pl, X, ldx, col0, ncols, wide, bf16, st, g);
+    const ilargi_status_t rc = lmm_products(pl, X, ldx, col0, ncols, wide, bf16, st, g, lines);
     if (rc != ILARGI_OK) return rc;
   }
   LmmArgs a;
@@ -668,6 +669,7 @@ ilargi_status_t lmm_pass(ilargi_plan* pl, const float* X, int ldx, int col0, int
   a.nt_in = stream_past_caches(a.d_rows * a.ck);
   a.nt_out = (int64_t)pl->r_T * ldo * (int64_t)sizeof(float) >= (64ll << 20);
   a.g = g;
+  a.lds_products = lmm_lane_lds_pays(a, lines) ? 1 : 0;
   a.y = y;
   a.loss_partial = pl->at<float>(pl->lay.o_loss);
   a.ld_loss = ldx;

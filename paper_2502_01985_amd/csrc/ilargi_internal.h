@@ -37,7 +37,6 @@ struct GatherArgs {
   const float* P[kMaxSources];
   int64_t rows[kMaxSources];
   int ldp;
-  float lines[kMaxSources];         // 128-byte lines of a column P_s that 64 target rows in a row read (0: not measured)
 };
 
 struct LmmArgs {
@@ -58,6 +57,7 @@ struct LmmArgs {
   int ld_loss;
   int nt_in;              // read the table past the caches (see stream_past_caches)
   int nt_out;             // store the output with non-temporal stores (large results nobody re-reads soon)
+  int lds_products;       // the gathers are worth products in LDS (lmm_lane_lds_pays)
   float* scratch;         // optional device scratch of scratch_floats floats (the caller's, free for the launch)
   int64_t scratch_floats;
   float* grad_partial;    // optional partials of D^T e: narrow kernel [gridDim.x][ck][kNarrowCT],
@@ -548,7 +548,10 @@ hipError_t launch_build_segbin(const int32_t* idx, int64_t r_T, int64_t nnz, int
                                int32_t* sortbuf, int64_t sort_n, int32_t* hist, int32_t* off, uint32_t* entries, int32_t* groups, hipStream_t st);
 hipError_t launch_segbin(const SegBin* a, int n, float* scratch, int64_t scratch_floats, hipStream_t st);
 hipError_t launch_colred(const ColredArgs& a, int nblocks, hipStream_t st);
-bool lmm_lane_wants_lines(int64_t rows, int64_t cols);   // whether the choice of the assembly over such a table asks for `lines`
+// Whether the choice of the assembly over such a table asks for the lines that gathers go to, and the choice.  lines[s]: 128-byte
+// lines of a column P_s that 64 target rows in a row read.
+bool lmm_lane_wants_lines(int64_t rows, int64_t cols);
+bool lmm_lane_lds_pays(const LmmArgs& a, const float* lines);
 bool lmm_flat_supported(const LmmArgs& a, int vec, bool fuseg);
 hipError_t launch_lmm_flat(const LmmArgs& a, int mode, bool fuseg, hipStream_t st, int* grid_out);
 hipError_t launch_finalize(const FinArgs& a, int c_T, int mode, hipStream_t st);

@@ -319,36 +319,43 @@ void lane_shape(const LmmArgs& a, int vec, int* rpl, int* nv) {
   *nv = *rpl * a.ck / 4;
 }
 
-// The products a workgroup of kLaneLdsWaves wavefronts keeps in LDS, the smallest tables first; whether that pays: with a
-// residual (without one the chip holds more wavefronts), rows of 6 or 10 columns (wider ones would spill registers), an entity
-// table that is read past the caches, and gathers that go to many lines: what 64 target rows in a row read beyond 30 lines,
-// weighted with the part of the table in LDS, has to be a quarter of the most there could be.
-// Iterations in microseconds, without / with, 5,000,000 x 10 and one table of 20,000 rows: uniform keys (61 lines) 94 / 86, by a
-// power law whose first key has a fifth of the rows (48) 98 / 94, in blocks of 1000 (28) 99 / 102, sorted (1) 84 / 90; 38,000
-// uniform keys, half of them in LDS, 97 / 96; 300 keys (10) 78 / 79.  By rows, uniform keys: 3,400,000 75.5 / 71.4; read through
-// the caches 3,000,000 64.7 / 67.2, 1,000,000 38.3 / 41.7; three tables 5,000,000 174.9 / 166.2, 3,800,000 135.5 / 132.3; through
-// the caches 3,000,000 129.8 / 127.3, 1,000,000 77.3 / 79.9.
-bool lane_lds(const LmmArgs& a, int mode, int nv, LaneLds* pl) {
-  memset(pl, 0, sizeof(*pl));
-  if (mode == 0 || nv > 5 || a.nt_in == 0) return false;
+// The products a workgroup of kLaneLdsWaves wavefronts keeps in LDS beside its tiles, the smallest tables first.
+LaneLds lane_lds(const LmmArgs& a, int nv) {
+  LaneLds pl;
+  memset(&pl, 0, sizeof(pl));
   int order[kLaneGather];
   for (int s = 0; s < a.g.n; ++s) order[s] = s;
   std::sort(order, order + a.g.n, [&](int x, int y) { return a.g.rows[x] < a.g.rows[y]; });
   int at = 0;
-  double gain = 0.0;
   for (int i = 0; i < a.g.n; ++i) {
     const int s = order[i], room = kLaneLdsBytes / 4 - kLaneLdsWaves * kWave * nv * 4 - at;
-    pl->n[s] = (int)std::min<int64_t>(a.g.rows[s], room);
-    pl->off[s] = at;
-    at += pl->n[s];
-    if (a.g.rows[s] > 0) gain += std::max(a.g.lines[s] - 30.0, 0.0) / (kWave - 30) * pl->n[s] / (double)a.g.rows[s];
+    pl.n[s] = (int)std::min<int64_t>(a.g.rows[s], room);
+    pl.off[s] = at;
+    at += pl.n[s];
   }
-  return gain >= 0.25;
+  return pl;
 }
 
 }  // namespace
 
 bool lmm_lane_wants_lines(int64_t rows, int64_t cols) { return (cols == 6 || cols == 10) && stream_past_caches(rows * cols) != 0; }
+
+// Whether products in LDS pay: with a residual (without one the chip holds more wavefronts), rows of 6 or 10 columns (wider ones
+// would spill registers), an entity table that is read past the caches, and gathers that go to many lines: what 64 target rows
+// in a row read beyond 30 lines, weighted with the part of the table in LDS, has to be a quarter of the most there could be.
+// Iterations in microseconds, without / with, 5,000,000 x 10 and one table of 20,000 rows: uniform keys (61 lines) 94 / 86, by a
+// power law whose first key has a fifth of the rows (48) 98 / 94, in blocks of 1000 (28) 99 / 102, sorted (1) 84 / 90; 38,000
+// uniform keys, half of them in LDS, 97 / 96; 300 keys (10) 78 / 79.  By rows, uniform keys: 3,400,000 75.5 / 71.4; read through
+// the caches 3,000,000 64.7 / 67.2, 1,000,000 38.3 / 41.7; three tables 5,000,000 174.9 / 166.2, 3,400,000 135.5 / 132.3; through
+// the caches 3,000,000 129.8 / 127.3, 1,000,000 77.3 / 79.9.
+bool lmm_lane_lds_pays(const LmmArgs& a, const float* lines) {
+  if (a.D == nullptr || a.nt_in == 0 || !lmm_lane_wants_lines(a.d_rows, a.ck) || a.g.n < 1 || a.g.n > kLaneGather) return false;
+  const LaneLds pl = lane_lds(a, a.ck / 2);
+  double gain = 0.0;
+  for (int s = 0; s < a.g.n; ++s)
+    if (a.g.rows[s] > 0) gain += std::max(lines[s] - 30.0, 0.0) / (kWave - 30) * pl.n[s] / (double)a.g.rows[s];
+  return gain >= 0.25;
+}
 
 // One operand column; the identity source covers every target row (d_rows == r_out, an even number); rows of 6, 10
 // or 14 columns (vec 2) on a 16-byte aligned base; one to three
@@ -377,8 +384,10 @@ hipError_t launch_lmm_lane(const LmmArgs& a, int vec, int mode, hipStream_t st, 
   if (!lmm_lane_supported(a, vec, mode, mode != 0)) return hipErrorInvalidValue;
   int rpl, nv;
   lane_shape(a, vec, &rpl, &nv);
+  const bool in_lds = mode != 0 && a.lds_products != 0 && rpl == 2 && nv <= 5;
   LaneLds pl;
-  const bool in_lds = lane_lds(a, mode, nv, &pl);
+  memset(&pl, 0, sizeof(pl));
+  if (in_lds) pl = lane_lds(a, nv);
   const int waves = in_lds ? kLaneLdsWaves : kLaneBlockWaves;
   LaneFn fn = lane_fn(rpl, nv, mode, a.nt_in != 0, in_lds);
   size_t lds_bytes = (size_t)waves * kWave * nv * sizeof(v4f);

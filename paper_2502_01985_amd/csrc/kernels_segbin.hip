@@ -209,6 +209,7 @@ __global__ __launch_bounds__(kBlock) void segbin_combine_kernel(SegBinMulti m) {
   const SegBin& a = m.s[q];
   const int b = (int)blockIdx.x - m.cfirst[q];
   const int key_blocks = a.n_ranges * m.range_blocks[q];
+  float* Z = a.Z;
   if (b < key_blocks) {
     const int range = b / m.range_blocks[q];
     const BinRange rg = a.ranges[range];
@@ -231,7 +232,7 @@ __global__ __launch_bounds__(kBlock) void segbin_combine_kernel(SegBinMulti m) {
     __syncthreads();
     if (g == 0 && s < keys && !(a.keyinfo[rg.key0 + s] & kBinHeavy)) {
       for (int c = 1; c < kBinCombineParts; ++c) z += part[c * kBinCombineKeys + l];
-      a.Z[rg.key0 + s] = z;
+      Z[rg.key0 + s] = z;
     }
     return;
   }
@@ -254,7 +255,7 @@ __global__ __launch_bounds__(kBlock) void segbin_combine_kernel(SegBinMulti m) {
     for (int u = 0; u < 8; ++u) z += v[u];
   }
   for (int k = kWave / 2; k >= 1; k >>= 1) z += __shfl_xor(z, k);
-  if (lane == 0) a.Z[j] = z;
+  if (lane == 0) Z[j] = z;
 }
 
 // ---- the index, built with the plan ----

@@ -180,8 +180,8 @@ __device__ __forceinline__ void store_loss(const float (&loss)[CT], float (*lsum
 
 // Assembly without an identity source (every table is joined): a thread takes kGatherRows rows, 256 apart, with the
 // row numbers and then the gathered values of all of them in flight.  1,000,000 rows over two tables with the logistic
-// residual: 10 microseconds (four rows a thread leave half of the wavefront slots empty: 11), of which 3 are its bytes; the rest is the chain row
-// number -> value -> store of a kernel this short.
+// residual: 8 microseconds (four rows a thread leave half of the wavefront slots empty: 0.7 more), of which 3 are its bytes; the
+// rest is the chain row number -> value -> store of a kernel this short.
 constexpr int kGatherRows = 2;
 
 template <int CT, int MODE>
