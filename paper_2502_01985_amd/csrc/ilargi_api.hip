@@ -1583,13 +1583,14 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
       if (!b.heavy.empty())
         HIP_TRY(hipMemcpyAsync(pl->at<int32_t>(p.o_bin_heavy), b.heavy.data(), sizeof(int32_t) * b.heavy.size(), hipMemcpyHostToDevice, st));
       const int n_win = (int)segbin_windows(r_T, p.rows);
+      const size_t counted = groups.size();
+      groups.resize(counted + b.ranges.size() * (size_t)n_win);
+      if ((int64_t)groups.size() > r_T * max_cx) return fail(ILARGI_ERR_WORKSPACE, "internal: counts of the segment sums overflow");
       HIP_TRY(launch_build_segbin(p.idx, r_T, p.nnz, (int)b.ranges.size(), n_win, segbin_win_log(r_T, p.rows),
                                   pl->at<uint32_t>(p.o_bin_keyinfo), sortbuf, std::max<int64_t>(r_T, 1), pl->at<int32_t>(lay.o_hist),
-                                  pl->at<int32_t>(p.o_bin_off), pl->at<uint32_t>(p.o_bin_entries), counts + groups.size(), st));
-      groups.resize(groups.size() + b.ranges.size() * (size_t)n_win);
+                                  pl->at<int32_t>(p.o_bin_off), pl->at<uint32_t>(p.o_bin_entries), counts + counted, st));
     }
     if (!in_bins.empty()) {
-      if ((int64_t)groups.size() > r_T * max_cx) return fail(ILARGI_ERR_WORKSPACE, "internal: counts of the segment sums overflow");
       HIP_TRY(hipMemcpyAsync(groups.data(), counts, sizeof(int32_t) * groups.size(), hipMemcpyDeviceToHost, st));
       HIP_TRY(hipStreamSynchronize(st));
       const int32_t* g = groups.data();

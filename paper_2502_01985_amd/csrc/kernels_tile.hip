@@ -178,22 +178,20 @@ __device__ __forceinline__ void store_loss(const float (&loss)[CT], float (*lsum
   }
 }
 
-// Assembly without an identity source (every table is joined): a thread takes kGatherRows rows, 256 apart, with the
-// row numbers and then the gathered values of all of them in flight.  1,000,000 rows over two tables with the logistic
-// residual: 8 microseconds (four rows a thread leave half of the wavefront slots empty: 0.7 more), of which 3 are its bytes; the
-// rest is the chain row number -> value -> store of a kernel this short.
-constexpr int kGatherRows = 2;
-
-template <int CT, int MODE>
+// Assembly without an identity source (every table is joined): a thread takes ROWS rows, 256 apart, with the row numbers and
+// then the gathered values of all of them in flight.  1,000,000 rows over two tables with the logistic residual: 8
+// microseconds (four rows a thread leave half of the wavefront slots empty: 0.7 more), of which 3 are its bytes; the rest is
+// the chain row number -> value -> store of a kernel this short.
+template <int CT, int MODE, int ROWS>
 __global__ __launch_bounds__(kBlock) void asm_gather_kernel(LmmArgs a) {
   float loss_local[CT];
 #pragma unroll
   for (int n = 0; n < CT; ++n) loss_local[n] = 0.0f;
-  constexpr int64_t step = (int64_t)kBlock * kGatherRows;
+  constexpr int64_t step = (int64_t)kBlock * ROWS;
   for (int64_t base = (int64_t)blockIdx.x * step + threadIdx.x; base < a.r_out + threadIdx.x; base += (int64_t)gridDim.x * step) {
-    float z[kGatherRows][CT], y[kGatherRows];
+    float z[ROWS][CT], y[ROWS];
 #pragma unroll
-    for (int u = 0; u < kGatherRows; ++u) {
+    for (int u = 0; u < ROWS; ++u) {
       const int64_t i = base + u * kBlock;
 #pragma unroll
       for (int n = 0; n < CT; ++n) z[u][n] = 0.0f;
@@ -201,33 +199,33 @@ __global__ __launch_bounds__(kBlock) void asm_gather_kernel(LmmArgs a) {
       if constexpr (MODE != 0) y[u] = i < a.r_out ? a.y[i] : 0.0f;
     }
     for (int s0 = 0; s0 < a.g.n; s0 += 2) {
-      int j[2][kGatherRows];
+      int j[2][ROWS];
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int u = 0; u < kGatherRows; ++u) {
+        for (int u = 0; u < ROWS; ++u) {
           const int64_t i = base + u * kBlock;
           j[h][u] = -1;
           if (s0 + h < a.g.n && i < a.r_out)
             j[h][u] = a.g.idx[s0 + h] != nullptr ? (int)a.g.idx[s0 + h][i] : (i < a.g.rows[s0 + h] ? (int)i : -1);
         }
-      float p[2][kGatherRows][CT];
+      float p[2][ROWS][CT];
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int u = 0; u < kGatherRows; ++u)
+        for (int u = 0; u < ROWS; ++u)
 #pragma unroll
           for (int n = 0; n < CT; ++n)
             p[h][u][n] = (j[h][u] >= 0 && n < a.ncols) ? a.g.P[s0 + h][(int64_t)j[h][u] * a.g.ldp + a.col0 + n] : 0.0f;
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int u = 0; u < kGatherRows; ++u)
+        for (int u = 0; u < ROWS; ++u)
 #pragma unroll
           for (int n = 0; n < CT; ++n) z[u][n] += p[h][u][n];
     }
 #pragma unroll
-    for (int u = 0; u < kGatherRows; ++u) {
+    for (int u = 0; u < ROWS; ++u) {
       const int64_t i = base + u * kBlock;
       if (i >= a.r_out) break;
 #pragma unroll
@@ -695,18 +693,39 @@ bool asm_tile_supported(const LmmArgs& a, int vec, bool fuseg) {
   return vec != 4 || a.ck <= 256;
 }
 
+namespace {
+
+// Rows of a thread of asm_gather_kernel: two fill more wavefront slots, four have more in flight.  Iterations of one logistic
+// model, two rows / four, by target rows: one table 100,000 to 1,000,000 0.96 to 0.99, 1,500,000 and 2,000,000 1.02, 3,000,000
+// 0.99, 5,000,000 and 10,000,000 1.00; several tables to 1,000,000 0.96 to 0.99, 1,500,000 1.02, 3,000,000 0.99, 5,000,000 1.01,
+// 10,000,000 1.01 to 1.04.  Three models: one table 0.93 to 0.99 (10,000,000 1.01), several to 300,000 0.92 to 0.96, 500,000 1.01,
+// 10,000,000 1.03 to 1.05; their products alone 1.05 from 500,000 on.
+int gather_rows(const LmmArgs& a) {
+  if (a.ncols > 1) return a.g.n > 1 && a.r_out >= 400000 ? 4 : 2;
+  return a.r_out >= 1250000 && (a.g.n > 1 || a.r_out < 2500000) ? 4 : 2;
+}
+
+template <int CT, int MODE>
+void launch_asm_gather(const LmmArgs& a, int rows, int grid, hipStream_t st) {
+  if (rows == 2) asm_gather_kernel<CT, MODE, 2><<<grid, kBlock, 0, st>>>(a);
+  else asm_gather_kernel<CT, MODE, 4><<<grid, kBlock, 0, st>>>(a);
+}
+
+}  // namespace
+
 hipError_t launch_asm_tile(const LmmArgs& a, int mode, hipStream_t st, int* grid_out) {
   const bool fuseg = a.grad_partial != nullptr && mode != 0;
   if (!asm_tile_supported(a, 1, fuseg)) return hipErrorInvalidValue;
   if (a.D == nullptr) {
-    int64_t grid = (a.r_out + kBlock * kGatherRows - 1) / (kBlock * kGatherRows);
+    const int rows = gather_rows(a);
+    int64_t grid = (a.r_out + kBlock * rows - 1) / (kBlock * rows);
     if (grid > 4096) grid = 4096;
     if (grid_out) *grid_out = (int)grid;
 #define ILARGI_GATHER(C)                                                                  \
   do {                                                                                    \
-    if (mode == 0) asm_gather_kernel<C, 0><<<(int)grid, kBlock, 0, st>>>(a);              \
-    else if (mode == 1) asm_gather_kernel<C, 1><<<(int)grid, kBlock, 0, st>>>(a);         \
-    else asm_gather_kernel<C, 2><<<(int)grid, kBlock, 0, st>>>(a);                        \
+    if (mode == 0) launch_asm_gather<C, 0>(a, rows, (int)grid, st);                       \
+    else if (mode == 1) launch_asm_gather<C, 1>(a, rows, (int)grid, st);                  \
+    else launch_asm_gather<C, 2>(a, rows, (int)grid, st);                                 \
   } while (0)
     if (a.ncols <= 1) ILARGI_GATHER(1);
     else if (a.ncols <= 2) ILARGI_GATHER(2);

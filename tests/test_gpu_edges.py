@@ -1113,3 +1113,73 @@ def test_products_in_lds_only_for_keys_in_no_order(il, kind, r_T, c, rows):
     # float32 products of seventeen terms: residuals to some 1e-6, gradients averaged over millions of them
     assert float((W.double() - want).norm() / want.norm()) < 1e-6
     assert abs(float(loss) / float((torch.nn.functional.softplus(z) - y.double().unsqueeze(1) * z).mean()) - 1) < 2e-6
+
+
+@pytest.mark.parametrize("what", ["sums and products in LDS", "sums gathered by slices", "sparse products", "kmeans", "kmeans, large centroids"])
+def test_replayed_from_a_graph(il, what):
+    # every replay continues the eager iterations bit for bit, with eager work between the replays
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    if what.startswith("s") and "sparse" not in what:
+        sources, c_T, _ = _keyed(8, 3_355_444, [(20_000, 0), (3_000, 0)])
+        if "slices" in what:
+            sources = [(D, idx.sort()[0], cm) for D, idx, cm in sources]
+        sources = [(D, idx, [j + 10 for j in cm]) for D, idx, cm in sources]
+        sources.insert(0, (torch.randn(3_355_444, 10, generator=gen, device="cuda"), None, list(range(10))))
+        r_T, c_T, k = 3_355_444, c_T + 10, 1
+    elif what == "sparse products":
+        r_T, c_T, k, sources = 1_000_000, 300, 1, []
+        for t in range(2):
+            D = (torch.rand(4_000, 150, generator=gen, device="cuda") < 0.02).float()
+            sources.append((il.CSR.from_dense(D.cpu().numpy()), torch.randint(0, 4_000, (r_T,), generator=gen, device="cuda", dtype=torch.int32), list(range(150 * t, 150 * t + 150))))
+    else:
+        wide = 400 if "large" not in what else 900
+        r_T, c_T, k = 20_000, 20 + wide, 8
+        sources = [(torch.randn(r_T, 20, generator=gen, device="cuda"), None, list(range(20))),
+                   (torch.randn(300, wide, generator=gen, device="cuda"), torch.randint(0, 300, (r_T,), generator=gen, device="cuda", dtype=torch.int32), list(range(20, c_T)))]
+    plan = il.ilargi_plan_create(sources, r_T, c_T, max_cx=k)
+    start = torch.randn(c_T, k, generator=gen, device="cuda") / 10
+    y, lr, loss = (torch.rand(r_T, generator=gen, device="cuda") < 0.5).float(), torch.full((1,), 0.1, device="cuda"), torch.zeros(1, device="cuda")
+    counts = torch.zeros(k, dtype=torch.int32, device="cuda")
+
+    def step(W):
+        if k > 1:
+            il.ilargi_kmeans_step(plan, W, None, counts)
+        else:
+            il.ilargi_gd_step(plan, il.LOGISTIC, W, y, lr, loss)
+
+    W, want = start.clone(), []
+    for _ in range(6):
+        step(W)
+        want.append((W.clone(), loss.clone(), counts.clone()))
+    W = start.clone()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(2):
+            step(W)
+    W.copy_(start)
+    for t in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip((W, loss, counts), want[2 * t + 1]))
+        assert np.isfinite(torch.randn(1 << 20, device="cuda").sum().item())
+
+
+@pytest.mark.parametrize("r_T,tables,cx", [(399_999, 2, 3), (400_000, 2, 3), (400_001, 3, 2), (1_249_999, 1, 1), (1_250_000, 1, 1), (1_250_001, 2, 1),
+                                           (2_499_999, 1, 1), (2_500_000, 1, 1), (2_500_003, 3, 1), (2_500_001, 1, 4)])
+def test_gathers_alone_with_two_and_four_rows_a_thread(il, r_T, tables, cx):
+    # whole numbers: products, residuals and squared sums exact in any order
+    sources, c_T, _ = _keyed(r_T + tables, r_T, [(3_000, 0), (700, 3), (50_000, 0)][:tables], missing=0.1)
+    plan = il.ilargi_plan_create(sources, r_T, c_T, max_cx=4)
+    W = torch.randint(-2, 3, (c_T, cx), device="cuda").float()
+    z = sum(torch.where(idx[:, None] >= 0, (D.double() @ W[cm].double())[idx.long().clamp(min=0)], 0.0) for D, idx, cm in sources)
+    assert torch.equal(il.ilargi_lmm(plan, W).double(), z)
+    y = torch.randint(0, 2, (r_T,), device="cuda").float()
+    e = z - y.double()[:, None]
+    G = torch.cat([D.double().t() @ torch.zeros(len(D), cx, dtype=torch.float64, device="cuda").index_add_(
+        0, idx[idx >= 0].long(), e[idx >= 0]) for D, idx, _ in sources])
+    want = W.double() - 0.25 * G / r_T
+    loss = torch.zeros(cx, device="cuda")
+    il.ilargi_gd_step(plan, il.LINEAR, W, y, torch.full((cx,), 0.25, device="cuda"), loss)
+    assert float((W.double() - want).abs().max()) <= 1e-6 * float(want.abs().max())      # one rounding of the mean and of the update each
+    assert torch.allclose(loss.double(), (e * e).sum(0) / (2 * r_T), rtol=1e-5)
