@@ -769,6 +769,8 @@ def _keyed(seed, r_T, dims, missing=0.0, sparse=False):
 
 
 @pytest.mark.parametrize("r_T,dims,missing", [
+    (1_500_000, [(20_480, 0)], 0.0),                              # as many keys as one range holds, too few rows to gain
+    (1_500_001, [(20_481, 0)], 0.1),
     (4_000_000, [(20_480, 0)], 0.0),                              # one full range of keys
     (5_000_001, [(20_481, 0)], 0.1),                              # two ranges
     (3_002_369, [(1_000, 0)], 0.0),                               # windows of 2^12 rows, the last of one row
