@@ -73,11 +73,6 @@ struct SourcePlan {
   size_t o_sl_rowptr = 0, o_sl_perm = 0, o_sl_chunk0 = 0, o_sl_ch_beg = 0, o_sl_ch_end = 0, o_sl_nchunk = 0,
          o_sl_ch_partial = 0, o_zslice = 0;
   int sl_cap = 0, sl_logG = 0;
-  // the segment sums run in LDS over windows of target rows (large target tables); a layout says that there is room for it
-  bool binned = false;
-  size_t o_bin_entries = 0, o_bin_off = 0, o_bin_keyinfo = 0, o_bin_ranges = 0, o_bin_items = 0, o_bin_heavy = 0;
-  int bin_items = 0, bin_heavy = 0, bin_slots = 0;
-  int64_t bin_partial = 0;
   int64_t nnz = 0;
   int logG = 0;
 };
@@ -131,6 +126,7 @@ struct ilargi_plan {
   bool cover_full = false;      // every target column is fed and every source reaches every target row
   bool mat_flat = false;  // every aligned group of four target columns is an aligned float4 of one source, or unfed
   bool cover_columns = false;   // every target column is fed by some source
+  bool fix_cols[kNarrowCT + 1] = {};   // segment sums of so many operand columns run in LDS (segfix_pays)
   int npairs = 0;
   int64_t pairlist_n[kMaxPairLists] = {};   // entries of the pair lists of the layout
   bool small_gd = false;  // the schema is small enough for the single-workgroup gradient-descent iteration
@@ -225,14 +221,14 @@ int colred_nblocks(int64_t rows, int64_t cols, int vec) {
   return (int)((rows + rpb - 1) / rpb);
 }
 
-// Room of a plan: with segment sums in LDS, more chunks of long segments and the sliced index for tables that turn out not
-// to gain in LDS; the same without that; or none of them.
-enum { kRoomBare, kRoomBins, kRoomFull };
+// Room of a plan: with more chunks of long segments; without; or without the sliced index too, and with half the space for
+// partial blocks.
+enum { kRoomTight, kRoomBare, kRoomFull };
 
 // Shape-only part of a plan: fills the offsets of every workspace region.
 ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_t c_T, int64_t max_cx,
                             std::vector<SourcePlan>& src, Layout& lay, int room) {
-  const bool roomy = room != kRoomBare;
+  const bool roomy = room == kRoomFull;
   if (s == nullptr) return fail(ILARGI_ERR_NULL, "sources is NULL");
   if (n < 1 || n > kMaxSources) return fail(ILARGI_ERR_SHAPE, "n = %d outside [1, %d]", n, kMaxSources);
   if (r_T < 0 || r_T > 2147483646ll) return fail(ILARGI_ERR_SHAPE, "r_T = %lld out of range", (long long)r_T);
@@ -276,7 +272,7 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
   lay.o_rr = take(sizeof(float) * 2 * kGnmfMaxRank * kGnmfMaxRank);
   // Gram scratch: summed rows for the "via sums" route, chunk partials, the (k,l) blocks
   lay.zc_floats = 1;
-  lay.gpartial_floats = kGramPartialFloats;
+  lay.gpartial_floats = room == kRoomTight ? kGramPartialFloats / 2 : kGramPartialFloats;
   lay.blocks_floats = 0;
   for (int k = 0; k < n && lay.max_entries == 0; ++k)    // (plans with sparse sources have no Gram matrix)
     for (int l = k; l < n; ++l) {
@@ -310,27 +306,8 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
   int64_t n_indexed = 0;
   for (int k = 0; k < n; ++k) n_indexed += src[k].has_idx ? 1 : 0;
   const int64_t chunks_long = 2 * (r_T / kLongSeg) + 2;
-  // Segment sums in LDS (kernels_segbin.hip) for one operand column: room where they may gain, which segbin_gain decides when
-  // the plan knows its keys.  Several columns would take a pass each: 418 / 520 microseconds for three models.  Their index
-  // lies where the sliced one does, or takes the place of what the plan saves elsewhere: room that a caller set aside for its
-  // plans stays enough.
-  auto sliced = [&](int k) { return r_T >= 1500000 && src[k].rows > 0 && src[k].rows * kSegSlices <= r_T && s[k].csr_rowptr == nullptr; };
-  auto binnable = [&](int k) {
-    return roomy && max_cx == 1 && src[k].has_idx && !src[k].empty && src[k].rows * kSegSlices <= r_T && segbin_ranges(src[k].rows) <= kBinMaxRanges;
-  };
-  int64_t n_binnable = 0, bin_bytes = 0;
-  for (int k = 0; k < n; ++k) {
-    if (!binnable(k)) continue;
-    ++n_binnable;
-    const int64_t n_ranges = segbin_ranges(src[k].rows);
-    if (!sliced(k))
-      bin_bytes += 4 * (r_T + kBinPad + n_ranges * kBinWaves * (segbin_windows(r_T, src[k].rows) + 1) + src[k].rows + n_ranges * kBinHeavyShare) +
-                   (int64_t)sizeof(BinRange) * n_ranges + (int64_t)sizeof(BinItem) * 2 * kBinPerXcd + 6 * (int64_t)kAlign;
-  }
-  const int64_t spare = lay.max_entries > 0 ? 4 * n_indexed * chunks_long * (widest - wmax) : shared_bytes;
-  const bool use_bins = bin_bytes <= spare && segbin_enough(r_T, (int)n_binnable);
-  const int64_t chunk_bytes = shared_bytes - (use_bins && lay.max_entries == 0 ? bin_bytes : 0);
-  const int64_t more = std::max<int64_t>(chunk_bytes / std::max<int64_t>(n_indexed, 1) - 6 * (int64_t)kAlign, 0) / (4 * wmax + 16);
+  auto sliced = [&](int k) { return room != kRoomTight && r_T >= 1500000 && src[k].rows > 0 && src[k].rows * kSegSlices <= r_T && s[k].csr_rowptr == nullptr; };
+  const int64_t more = std::max<int64_t>(shared_bytes / std::max<int64_t>(n_indexed, 1) - 6 * (int64_t)kAlign, 0) / (4 * wmax + 16);
   for (int k = 0; k < n; ++k) {
     SourcePlan& p = src[k];
     p.o_colmap = take(sizeof(int32_t) * std::max<int64_t>(p.cols, 1));
@@ -352,21 +329,8 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
       p.o_join_first = take(sizeof(int32_t) * (kColredBlocks + 1));
       // a residual of 6 MB or more does not stay in an XCD's 4 MB of L2: segments are then also split by slice
       // of target rows (worth it when a source row still has entries in most slices)
-      p.binned = use_bins && binnable(k);
-      p.sliced = sliced(k) && (!p.binned || room == kRoomFull);
-      const size_t index = off;                       // (a plan keeps one of the two)
-      if (p.binned) {
-        const int n_ranges = segbin_ranges(p.rows);
-        p.o_bin_entries = take(sizeof(uint32_t) * (r_T + kBinPad));
-        p.o_bin_off = take(sizeof(int32_t) * n_ranges * kBinWaves * (segbin_windows(r_T, p.rows) + 1));
-        p.o_bin_keyinfo = take(sizeof(uint32_t) * p.rows);
-        p.o_bin_ranges = take(sizeof(BinRange) * n_ranges);
-        p.o_bin_items = take(sizeof(BinItem) * 2 * kBinPerXcd);
-        p.o_bin_heavy = take(sizeof(int32_t) * kBinHeavyShare * n_ranges);
-      }
-      const size_t bins_end = off;
+      p.sliced = sliced(k);
       if (p.sliced) {
-        off = index;
         p.sl_cap = (int)segsum_sliced_chunk_cap(r_T);
         p.o_sl_rowptr = take(sizeof(int32_t) * (kSegSlices * p.rows + 1));
         p.o_sl_perm = take(sizeof(int32_t) * std::max<int64_t>(r_T, 1));
@@ -377,7 +341,6 @@ ilargi_status_t make_layout(int n, const ilargi_source_t* s, int64_t r_T, int64_
         p.o_sl_ch_partial = take(sizeof(float) * kSegSlices * p.sl_cap * kNarrowCT);
         p.o_zslice = take(sizeof(float) * kSegSlices * p.rows * kNarrowCT);
       }
-      off = std::max(off, bins_end);
     }
     p.o_pz = take(sizeof(float) * std::max<int64_t>(p.rows, 1) * max_cx);
     // (a sparse source's transposed product leaves a single block of partials)
@@ -497,21 +460,6 @@ SegArgs seg_args(const ilargi_plan* pl, int k) {
     a.sl_cap = p.sl_cap; a.sl_logG = p.sl_logG;
     a.Zs = pl->at<float>(p.o_zslice);
   }
-  return a;
-}
-
-// Arguments of the segment sums in LDS of source k; the caller adds operand and result.
-SegBin bin_args(const ilargi_plan* pl, int k) {
-  const SourcePlan& p = pl->src[k];
-  SegBin a;
-  memset(&a, 0, sizeof(a));
-  a.entries = pl->at<uint32_t>(p.o_bin_entries); a.off = pl->at<int32_t>(p.o_bin_off);
-  a.ranges = pl->at<BinRange>(p.o_bin_ranges); a.items = pl->at<BinItem>(p.o_bin_items);
-  a.keyinfo = pl->at<uint32_t>(p.o_bin_keyinfo); a.heavy = pl->at<int32_t>(p.o_bin_heavy);
-  a.n_items = p.bin_items; a.n_heavy = p.bin_heavy; a.n_ranges = segbin_ranges(p.rows); a.max_slots = p.bin_slots;
-  a.n_win = (int)segbin_windows(pl->r_T, p.rows); a.win_log = segbin_win_log(pl->r_T, p.rows);
-  a.r_T = pl->r_T; a.r_k = p.rows;
-  a.partial_floats = p.bin_partial;
   return a;
 }
 
@@ -745,22 +693,23 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
   // table's are summed by slice (and then over the slices).  The sources then take part in the column reduce with Z_k
   // as a plain operand.
   bool z_ready[kMaxSources] = {};
-  enum { kBinned, kSliced, kPlain };
-  for (const int kind : {kBinned, kSliced, kPlain}) {
+  enum { kFixed, kSliced, kPlain };
+  const bool fixed = Y != nullptr && ldy == ncols && pl->fix_cols[ncols];
+  for (const int kind : {kFixed, kSliced, kPlain}) {
     SegArgs multi[kSegMulti];
-    SegBin bins[kSegMulti];
+    SegFix fix[kSegMulti];
     int nm = 0, first_k = -1;
     auto flush_multi = [&]() -> ilargi_status_t {
       if (nm == 0) return ILARGI_OK;
       TraceScope ts(pl, "segsum", first_k, st);
-      if (kind == kBinned) HIP_TRY(launch_segbin(bins, nm, pl->at<float>(pl->lay.o_gpartial), pl->lay.gpartial_floats, st));
+      if (kind == kFixed) HIP_TRY(launch_segfix(fix, nm, ncols, pl->at<float>(pl->lay.o_gpartial), pl->lay.gpartial_floats, st));
       else HIP_TRY(kind == kSliced ? launch_segsum_sliced(multi, nm, st) : launch_segsum_narrow(multi, nm, st));
       nm = 0; first_k = -1;
       return ILARGI_OK;
     };
     for (int k = 0; k < pl->n && Y != nullptr; ++k) {
       const SourcePlan& p = pl->src[k];
-      if (p.empty || k == done_k || p.ident || kind != (p.binned ? kBinned : p.sliced ? kSliced : kPlain)) continue;
+      if (p.empty || k == done_k || p.ident || kind != (fixed ? kFixed : p.sliced ? kSliced : kPlain)) continue;
       if (!p.sparse) {
         SegArgs sg = segsum_args(k);
         if (tmm_part_supported(colred_args(k, nullptr, 0, 0), &sg)) continue;      // join-order form: no Z_k
@@ -770,11 +719,11 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
         if (rc != ILARGI_OK) return rc;
       }
       if (nm == 0) first_k = k;
-      if (kind == kBinned) {
-        if (ldy != 1) return fail(ILARGI_ERR_WORKSPACE, "internal: segment sums of several columns in LDS");
-        bins[nm] = bin_args(pl, k);                                                // (such plans are for one operand column)
-        bins[nm].Y = Y;
-        bins[nm].Z = pl->at<float>(p.o_pz);
+      if (kind == kFixed) {
+        SegFix& f = fix[nm];
+        memset(&f, 0, sizeof(f));
+        f.idx = p.idx; f.Y = Y; f.r_T = pl->r_T; f.r_k = p.rows;
+        f.Z = pl->at<float>(p.o_pz); f.ldz = ldy; f.zcol0 = col0;
       } else {
         multi[nm] = segsum_args(k);
       }
@@ -1388,7 +1337,7 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
   std::vector<SourcePlan> src;
   Layout lay;
   ilargi_status_t rc = make_layout(n, sources, r_T, c_T, max_cx, src, lay, kRoomFull);
-  for (const int room : {kRoomBins, kRoomBare})
+  for (const int room : {kRoomBare, kRoomTight})
     if (rc == ILARGI_OK && workspace_bytes < lay.total) {      // sized for less: the plan works without
       lay = Layout();
       rc = make_layout(n, sources, r_T, c_T, max_cx, src, lay, room);
@@ -1472,7 +1421,6 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     if (p.ident) p.nnz = p.rows;
   }
   // inverse index of every non-identity source (Def. 2, transposed): stable sort by source row
-  std::vector<SegBinPlan> bin((size_t)n);
   for (int k = 0; k < n; ++k) {
     SourcePlan& p = pl->src[k];
     if (p.ident) continue;
@@ -1521,11 +1469,6 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
       HIP_TRY(hipMemcpyAsync(pl->at<int32_t>(p.o_long_first), lf.data(), sizeof(int32_t) * lf.size(), hipMemcpyHostToDevice, st));
       HIP_TRY(hipStreamSynchronize(st));
     }
-    if (p.binned) {
-      segbin_layout(rowptr, bin[k]);
-      bin[k].entries = p.nnz;
-      bin[k].very_long = p.very_long;
-    }
     if (!p.very_long && p.rows > 0 && !p.sparse && p.nnz <= 32 * p.rows && p.nnz >= 4 * p.rows) {
       // (with more index entries per row the gathers dominate and the segment-sum kernel, which spreads a
       // segment over a group of lanes, serves them better; with about one entry per row the gathers of a round
@@ -1551,66 +1494,28 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
       }
     }
   }
-  // The sources whose segment sums run in LDS: those that have them at all (a table in join order has none) and gain by
-  // it, judged by the lengths of the segments first and, once the index is there, by how the entries lie in it.
+  // Segment sums in LDS: of the sources that have them at all (a table in join order has none).
   {
-    std::vector<int> in_bins;
-    bool gathers[2] = {};                             // some source's segment sums gather in any case: as they are, by slices
-    for (int k = 0; k < n; ++k) {
-      SourcePlan& p = pl->src[k];
+    std::vector<int64_t> rows;
+    bool cut = false;
+    for (const SourcePlan& p : pl->src) {
       if (p.empty || p.ident) continue;
       ColredArgs c;
       memset(&c, 0, sizeof(c));
       c.rows = p.rows; c.ck = (int)p.cols; c.vec = p.vec; c.ncols = 1;
-      SegArgs sg = seg_args(pl, k);
+      SegArgs sg = seg_args(pl, (int)(&p - pl->src.data()));
       sg.ncols = 1;
       if (!p.sparse && tmm_part_supported(c, &sg)) continue;
-      if (p.binned) in_bins.push_back(k);
-      else gathers[p.sliced] = true;
+      rows.push_back(p.rows);
+      cut = cut || p.cut;
     }
-    for (int k : in_bins) bin[k].joins_launch = gathers[pl->src[k].sliced];
-    segbin_choose(r_T, bin, in_bins);
-    // (the counts lie where the residual will: a small part of it)
-    int32_t* counts = pl->at<int32_t>(lay.o_E);
-    std::vector<int32_t> groups;
-    for (int k : in_bins) {
-      SourcePlan& p = pl->src[k];
-      SegBinPlan& b = bin[k];
-      if (b.heavy.size() > kBinHeavyShare * b.ranges.size() || b.max_slots() > kBinSlots)
-        return fail(ILARGI_ERR_WORKSPACE, "internal: tables of the segment sums overflow");
-      int32_t* sortbuf = pl->at<int32_t>(lay.o_sort);
-      HIP_TRY(hipMemcpyAsync(pl->at<uint32_t>(p.o_bin_keyinfo), b.keyinfo.data(), sizeof(uint32_t) * b.keyinfo.size(), hipMemcpyHostToDevice, st));
-      if (!b.heavy.empty())
-        HIP_TRY(hipMemcpyAsync(pl->at<int32_t>(p.o_bin_heavy), b.heavy.data(), sizeof(int32_t) * b.heavy.size(), hipMemcpyHostToDevice, st));
-      const int n_win = (int)segbin_windows(r_T, p.rows);
-      const size_t counted = groups.size();
-      groups.resize(counted + b.ranges.size() * (size_t)n_win);
-      if ((int64_t)groups.size() > r_T * max_cx) return fail(ILARGI_ERR_WORKSPACE, "internal: counts of the segment sums overflow");
-      HIP_TRY(launch_build_segbin(p.idx, r_T, p.nnz, (int)b.ranges.size(), n_win, segbin_win_log(r_T, p.rows),
-                                  pl->at<uint32_t>(p.o_bin_keyinfo), sortbuf, std::max<int64_t>(r_T, 1), pl->at<int32_t>(lay.o_hist),
-                                  pl->at<int32_t>(p.o_bin_off), pl->at<uint32_t>(p.o_bin_entries), counts + counted, st));
+    for (int cx = 1; cx <= std::min<int64_t>(max_cx, kNarrowCT); ++cx) {
+      pl->fix_cols[cx] = !rows.empty();
+      for (size_t i = 0; i < rows.size(); i += kSegMulti)
+        if (!segfix_pays(r_T, rows.data() + i, (int)std::min<size_t>(kSegMulti, rows.size() - i), cx, cut)) pl->fix_cols[cx] = false;
     }
-    if (!in_bins.empty()) {
-      HIP_TRY(hipMemcpyAsync(groups.data(), counts, sizeof(int32_t) * groups.size(), hipMemcpyDeviceToHost, st));
-      HIP_TRY(hipStreamSynchronize(st));
-      const int32_t* g = groups.data();
-      for (int k : in_bins) { bin[k].groups = g; g += bin[k].ranges.size() * (size_t)segbin_windows(r_T, pl->src[k].rows); }
-    }
-    segbin_choose(r_T, bin, in_bins);
-    for (int k = 0; k < n; ++k) pl->src[k].binned = false;
-    for (int k : in_bins) {
-      SourcePlan& p = pl->src[k];
-      SegBinPlan& b = bin[k];
-      p.binned = true;
-      p.sliced = false;
-      p.bin_heavy = (int)b.heavy.size();
-      p.bin_slots = b.max_slots();
-      segbin_items(b.ranges, b.items, &p.bin_partial);
-      p.bin_items = (int)b.items.size();
-      HIP_TRY(hipMemcpyAsync(pl->at<BinRange>(p.o_bin_ranges), b.ranges.data(), sizeof(BinRange) * b.ranges.size(), hipMemcpyHostToDevice, st));
-      HIP_TRY(hipMemcpyAsync(pl->at<BinItem>(p.o_bin_items), b.items.data(), sizeof(BinItem) * b.items.size(), hipMemcpyHostToDevice, st));
-    }
-    if (!in_bins.empty()) HIP_TRY(hipStreamSynchronize(st));
+    if (pl->fix_cols[1] && max_cx == 1)
+      for (SourcePlan& p : pl->src) p.sliced = false;
   }
   for (int k = 0; k < n; ++k) {
     SourcePlan& p = pl->src[k];

@@ -219,53 +219,24 @@ struct SegMulti {
   SegArgs s[kSegMulti];
 };
 
-// Segment sums in LDS over large target tables, one operand column (kernels_segbin.hip).
-constexpr int kBinWaves = 16;             // wavefronts of a workgroup
-constexpr int kBinKeys = 20480;           // most source rows of a range: 80 KB of sums ...
-constexpr int kBinHeavyShare = 128;       // ... and a slot per wavefront for keys with more than this part of its entries
-constexpr int kBinSlots = kBinKeys + kBinHeavyShare * kBinWaves;
-constexpr int kBinWinFloats = 16384;      // the longest window: 64 KB, so that one workgroup fills a compute unit's LDS
-constexpr int kBinMaxRanges = 15;         // ranges x wavefronts are one digit of the sort, 255 stands for no entry
-constexpr int kBinPerXcd = 32;            // workgroups an XCD holds
-constexpr int kBinPad = 512;              // index entries that may be read past the end
-constexpr int kBinRowBits = 14;           // an index entry: row within the window, above it the slot
-constexpr int kBinSlotBits = 15;          // keyinfo: (first) slot, above it the wavefront (range x 16 + wavefront) ...
-constexpr uint32_t kBinHeavy = 1u << 31;  // ... and whether the key has a slot in every wavefront
-static_assert(kBinSlots <= 1 << kBinSlotBits && kBinSlotBits + kBinRowBits <= 32 && kBinSlotBits + 8 < 31, "packed fields");
-struct BinRange { int key0, slots, nsub, partial0, entries; };   // first key, sums, runs of windows per XCD, first partial, index entries
-struct BinItem { int range, sub; };
-// What a plan knows of a source's segment sums in LDS while it is made.
-struct SegBinPlan {
-  std::vector<BinRange> ranges;
-  std::vector<uint32_t> keyinfo;
-  std::vector<int32_t> heavy;
-  std::vector<BinItem> items;
-  const int32_t* groups = nullptr;   // [range][window]: groups of 64 entries of the wavefront with the most; NULL: not known yet
-  int64_t entries = 0;
-  bool very_long = false;        // some segment has more than kLongSeg entries
-  bool joins_launch = false;     // another source gathers in the launch that this one would gather in
-  int max_slots() const { int m = 0; for (const BinRange& r : ranges) m = r.slots > m ? r.slots : m; return m; }
-};
-struct SegBin {
-  const uint32_t* entries;
-  const int32_t* off;        // [ranges x 16][n_win + 1]
-  const BinRange* ranges;
-  const BinItem* items;
-  const uint32_t* keyinfo;   // r_k
-  const int32_t* heavy;      // keys with a slot per wavefront
-  int n_items, n_heavy, n_ranges, n_win, win_log, max_slots;
+// Segment sums in fixed point in LDS (kernels_segfix.hip).
+constexpr int kFixThreads = 1024;
+constexpr int kFixSlots = 20416;          // sums of 64 bits a workgroup holds
+constexpr int kFixHead = 6;               // factor (log2) that values may exceed the first ones of a run by
+constexpr int kFixPerXcd = 32;            // workgroups an XCD holds
+struct SegFix {
+  const int32_t* idx;        // r_T
+  const float* Y;            // r_T x ncols
   int64_t r_T, r_k;
-  const float* Y;            // r_T
-  float* Z;                  // r_k
-  float* partial;            // set by the launcher
-  int64_t partial_floats;
+  float* Z;                  // r_k x ldz, columns [zcol0, zcol0 + ncols)
+  int ldz, zcol0;
+  int n_ranges, nsub, runs, bits, stride;   // set by the launcher
+  float* partial;
 };
-struct SegBinMulti {
+struct SegFixMulti {
   int n;
-  int first[kSegMulti + 1];    // items [first[q], first[q + 1]) of an XCD serve source q
-  int cfirst[kSegMulti + 1];   // workgroups of the kernel that adds the runs ...
-  int range_blocks[kSegMulti];   // ... and how many of them serve a range
-  SegBin s[kSegMulti];
+  int first[kSegMulti + 1], cfirst[kSegMulti + 1], range_blocks[kSegMulti];
+  SegFix s[kSegMulti];
 };
 
 struct ColredArgs {
@@ -533,20 +504,9 @@ int64_t segsum_sliced_chunk_cap(int64_t nnz);
 // n <= kSegMulti sources with the same number of operand columns; their sums and the sums over slices run as one
 // launch each.
 hipError_t launch_segsum_sliced(const SegArgs* a, int n, hipStream_t st);
-// Segment sums in LDS: the split of a source's keys into ranges, the choice of the sources that gain by them, the runs of
-// windows of sources that share a launch, the index of a source, and the sums of n <= kSegMulti sources.
-int segbin_ranges(int64_t rows);
-int segbin_win_log(int64_t r_T, int64_t rows);
-inline int64_t segbin_windows(int64_t r_T, int64_t rows) { const int64_t w = 1ll << segbin_win_log(r_T, rows); return (r_T + w - 1) / w; }
-void segbin_layout(const std::vector<int32_t>& rowptr, SegBinPlan& plan);
-bool segbin_enough(int64_t r_T, int n);            // whether n sources over so many target rows may gain at all
-// in_bins: the sources that may run in LDS; on return those that do, with the runs of windows in their ranges.
-void segbin_choose(int64_t r_T, std::vector<SegBinPlan>& plans, std::vector<int>& in_bins);
-void segbin_items(std::vector<BinRange>& ranges, std::vector<BinItem>& items, int64_t* partial_floats);
-// sortbuf: four arrays of sort_n integers, hist: sort_hist_ints(r_T); both are scratch.  groups: SegBinPlan::groups
-hipError_t launch_build_segbin(const int32_t* idx, int64_t r_T, int64_t nnz, int n_ranges, int n_win, int win_log, const uint32_t* keyinfo,
-                               int32_t* sortbuf, int64_t sort_n, int32_t* hist, int32_t* off, uint32_t* entries, int32_t* groups, hipStream_t st);
-hipError_t launch_segbin(const SegBin* a, int n, float* scratch, int64_t scratch_floats, hipStream_t st);
+// Segment sums in fixed point in LDS of n <= kSegMulti sources.
+bool segfix_pays(int64_t r_T, const int64_t* rows, int n, int ncols, bool cut);
+hipError_t launch_segfix(const SegFix* a, int n, int ncols, float* scratch, int64_t scratch_floats, hipStream_t st);
 hipError_t launch_colred(const ColredArgs& a, int nblocks, hipStream_t st);
 // Whether the choice of the assembly over such a table asks for the lines that gathers go to, and the choice.  lines[s]: 128-byte
 // lines of a column P_s that 64 target rows in a row read.

@@ -1,0 +1,79 @@
+"""Segment sums in fixed point in LDS, against 64-bit sums."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+# A run's sums are rounded to float32 once, up to 256 of them are added in pairs of parts, and the table's product adds
+# thousands of rows in float32: a few units of 2^-24 by the 2-norm.
+REL = 1e-6
+
+
+@pytest.fixture(scope="module")
+def il():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2502_01985_amd as mod
+    return mod
+
+
+def _sources(r_T, rows, kinds, missing, gen, shift=0):
+    sources, at = [], 0
+    for r, kind in zip(rows, kinds):
+        idx = torch.randint(0, r, (r_T + shift,), generator=gen, device="cuda", dtype=torch.int32)
+        if kind == "sorted":
+            idx = idx.sort()[0]
+        elif kind == "hot":
+            idx[torch.rand(r_T + shift, generator=gen, device="cuda") < 0.7] = r // 2
+        idx[torch.rand(r_T + shift, generator=gen, device="cuda") < missing] = -1
+        sources.append((torch.randn(r, 5, generator=gen, device="cuda"), idx[shift:], list(range(at, at + 5))))
+        at += 5
+    return sources, at
+
+
+def _exact_tmm(sources, Y):
+    # (on the CPU: atomic additions of doubles to one popular row take seconds on the GPU)
+    out, Y = [], Y.double().cpu()
+    for D, idx, _ in sources:
+        idx = idx.cpu().long()
+        ok = idx >= 0
+        Z = torch.zeros(len(D), Y.shape[1], dtype=torch.float64).index_add_(0, idx[ok], Y[ok])
+        out.append((D.double().cpu().unsqueeze(2) * Z.unsqueeze(1)).sum(0))
+    return torch.cat(out).cuda()
+
+
+def _close(got, want):
+    assert torch.equal(got.isfinite(), want.isfinite())
+    ok = want.isfinite()
+    assert (got.double() - want)[ok].norm() <= REL * want[ok].norm()
+
+
+@pytest.mark.parametrize("r_T,rows,kinds,cx", [
+    (2_500_000, [20_416], ["uniform"], 1),                            # one full range ...
+    (2_500_003, [20_417], ["uniform"], 1),                            # ... and a key more, rows beyond the last four
+    (2_500_001, [2_000, 3], ["uniform", "hot"], 1),
+    (1_500_002, [100_000, 50_001, 9_999], ["uniform", "hot", "uniform"], 1),
+    (2_500_001, [30_000, 20_000], ["sorted", "uniform"], 1),          # four rows of a key side by side
+    (1_500_003, [10_208, 5_000], ["uniform", "sorted"], 2),
+    (2_500_001, [3_000, 6_806], ["hot", "uniform"], 3),
+    (1_500_001, [3_000, 5_105, 1], ["sorted", "uniform", "uniform"], 4),
+])
+@pytest.mark.parametrize("values", ["normal", "late", "outlier", "odd", "tiny"])
+def test_segment_sums_in_fixed_point(il, r_T, rows, kinds, cx, values):
+    gen = torch.Generator(device="cuda").manual_seed(r_T + cx)
+    shift = 1 if values == "late" else 0                              # row indices and operand off a multiple of 16 bytes
+    sources, c_T = _sources(r_T, rows, kinds, 0.1, gen, shift)
+    Y = torch.randn(r_T * cx + shift, generator=gen, device="cuda")[shift:].reshape(r_T, cx)
+    if values == "late":
+        Y[: r_T // 2] = 0.0                                           # nothing to see in a run's first rows
+    elif values == "outlier":
+        Y[r_T // 3, 0] = 3e9
+    elif values == "odd":
+        Y[r_T // 3, 0], Y[7, cx - 1], Y[r_T - 1, 0] = float("inf"), float("nan"), float("-inf")
+    elif values == "tiny":
+        Y *= 1e-36
+    plan = il.ilargi_plan_create(sources, r_T, c_T, max_cx=cx)
+    got = il.ilargi_tmm(plan, Y)
+    _close(got, _exact_tmm(sources, Y))
+    assert torch.equal(il.ilargi_tmm(plan, Y).view(torch.int32), got.view(torch.int32))
