@@ -594,8 +594,9 @@ ilargi_status_t lmm_products(ilargi_plan* pl, const float* X, int ldx, int col0,
 // out (or the residual E) for operand columns [col0, col0 + ncols):  per-source products, then the assembly.
 ilargi_status_t lmm_pass(ilargi_plan* pl, const float* X, int ldx, int col0, int ncols, float* out, int ldo,
                          int mode, const float* y, int* loss_grid, bool wide, hipStream_t st,
-                         bool* fused_gradient = nullptr, bool bf16 = false) {
+                         bool* fused_gradient = nullptr, bool bf16 = false, bool* summed = nullptr) {
   if (fused_gradient) *fused_gradient = false;
+  if (summed) *summed = false;
   GatherArgs g;
   float lines[kMaxSources] = {};
   {
@@ -621,6 +622,17 @@ ilargi_status_t lmm_pass(ilargi_plan* pl, const float* X, int ldx, int col0, int
   a.y = y;
   a.loss_partial = pl->at<float>(pl->lay.o_loss);
   a.ld_loss = ldx;
+  if (!wide && summed != nullptr && pl->fused < 0 && asm_fix_supported(a, mode) && asm_fix_pays(a, lines)) {
+    // (no residual, and every source's segment sums are formed here)
+    float* Z[kAsmFixSources];
+    int n = 0;
+    for (int k = 0; k < pl->n; ++k)
+      if (!pl->src[k].empty) Z[n++] = pl->at<float>(pl->src[k].o_pz);
+    TraceScope ts(pl, "lmm_assemble", -1, st);
+    HIP_TRY(launch_asm_fix(a, mode, Z, pl->at<float>(pl->lay.o_gpartial), pl->lay.gpartial_floats, st, loss_grid));
+    *summed = true;
+    return ILARGI_OK;
+  }
   if (!wide && mode != 0 && fused_gradient != nullptr && pl->fused >= 0 &&
       (lmm_can_fuse_gradient(a.ck, vec, a.logL) || asm_tile_supported(a, vec, true))) {
     // the fused source's share of the gradient comes out of the same pass over its rows
@@ -651,7 +663,7 @@ ilargi_status_t lmm_pass(ilargi_plan* pl, const float* X, int ldx, int col0, int
 // T^T Y for operand columns [col0, col0 + ncols); mode 1 turns the finalize step into the update of Alg. 1.
 ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int ncols, float* out, int ldo,
                          int mode, const float* lr, float* loss, int n_loss_partial, float loss_scale,
-                         hipStream_t st, int done_k = -1, int done_blocks = 0) {
+                         hipStream_t st, int done_k = -1, int done_blocks = 0, bool summed = false) {
   FinArgs f;
   memset(&f, 0, sizeof(f));
   auto colred_args = [&](int k, const float* Z, int ldz, int zcol0) {
@@ -694,6 +706,7 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
   // as a plain operand.
   bool z_ready[kMaxSources] = {};
   enum { kFixed, kSliced, kPlain };
+  for (int k = 0; k < pl->n && summed; ++k) z_ready[k] = !pl->src[k].empty;
   const bool fixed = Y != nullptr && ldy == ncols && pl->fix_cols[ncols];
   for (const int kind : {kFixed, kSliced, kPlain}) {
     SegArgs multi[kSegMulti];
@@ -707,7 +720,7 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
       nm = 0; first_k = -1;
       return ILARGI_OK;
     };
-    for (int k = 0; k < pl->n && Y != nullptr; ++k) {
+    for (int k = 0; k < pl->n && Y != nullptr && !summed; ++k) {
       const SourcePlan& p = pl->src[k];
       if (p.empty || k == done_k || p.ident || kind != (fixed ? kFixed : p.sliced ? kSliced : kPlain)) continue;
       if (!p.sparse) {
@@ -1388,6 +1401,11 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
   HIP_TRY(hipMemsetAsync(pl->at<int32_t>(lay.o_flags), 0, sizeof(int32_t) * 4 * n, st));
   bool count_lines = false;
   for (const SourcePlan& p : pl->src) count_lines = count_lines || (!p.sparse && p.rows == r_T && lmm_lane_wants_lines(p.rows, p.cols));
+  {
+    bool gathers_alone = true;
+    for (const SourcePlan& p : pl->src) gathers_alone = gathers_alone && p.has_idx;
+    count_lines = count_lines || (gathers_alone && r_T >= 100000);
+  }
   std::vector<const int32_t*> tcol_ptrs(n);
   for (int k = 0; k < n; ++k) {
     SourcePlan& p = pl->src[k];
@@ -2130,11 +2148,12 @@ ilargi_status_t ilargi_gd_step(ilargi_plan_t* plan, ilargi_model_t model, float*
     int ncols = (int)std::min<int64_t>(w, m - col0);
     int loss_grid = 0;
     bool fusedg = false;
+    bool summed = false;
     rc = lmm_pass(plan, W, (int)m, (int)col0, ncols, E, (int)m, model == ILARGI_LINEAR ? 1 : 2, y, &loss_grid, false, st,
-                  &fusedg);
+                  &fusedg, false, &summed);
     if (rc != ILARGI_OK) return rc;
     rc = tmm_pass(plan, E, (int)m, (int)col0, ncols, W, (int)m, 1, lr, loss, loss_grid, loss_scale, st,
-                  fusedg ? plan->fused : -1, loss_grid);
+                  fusedg ? plan->fused : -1, loss_grid, summed);
     if (rc != ILARGI_OK) return rc;
   }
   return ILARGI_OK;

@@ -239,6 +239,21 @@ struct SegFixMulti {
   SegFix s[kSegMulti];
 };
 
+// The assembly of gathered products alone with the segment sums of its residual (kernels_segfix.hip).
+constexpr int kAsmFixSources = 4;
+constexpr int kAsmFixSlots = 13568;       // sums of 64 bits and products of 32 a workgroup holds
+struct AsmFix {
+  int n;
+  const int32_t* idx[kAsmFixSources];
+  const float* P[kAsmFixSources];
+  int keys[kAsmFixSources], off[kAsmFixSources];
+  int ldp, col0, slots, bits;
+  const float* y;
+  int64_t r_T;
+  float* loss_partial;       // [gridDim.x][kNarrowCT]
+  float* partial;            // [gridDim.x][slots]
+};
+
 struct ColredArgs {
   const float* D;
   int64_t rows;
@@ -504,9 +519,12 @@ int64_t segsum_sliced_chunk_cap(int64_t nnz);
 // n <= kSegMulti sources with the same number of operand columns; their sums and the sums over slices run as one
 // launch each.
 hipError_t launch_segsum_sliced(const SegArgs* a, int n, hipStream_t st);
-// Segment sums in fixed point in LDS of n <= kSegMulti sources.
+// Segment sums in fixed point in LDS of n <= kSegMulti sources, and the assembly of gathered products with them.
 bool segfix_pays(int64_t r_T, const int64_t* rows, int n, int ncols, bool cut);
 hipError_t launch_segfix(const SegFix* a, int n, int ncols, float* scratch, int64_t scratch_floats, hipStream_t st);
+bool asm_fix_supported(const LmmArgs& a, int mode);
+bool asm_fix_pays(const LmmArgs& a, const float* lines);
+hipError_t launch_asm_fix(const LmmArgs& a, int mode, float* const* Z, float* scratch, int64_t scratch_floats, hipStream_t st, int* grid_out);
 hipError_t launch_colred(const ColredArgs& a, int nblocks, hipStream_t st);
 // Whether the choice of the assembly over such a table asks for the lines that gathers go to, and the choice.  lines[s]: 128-byte
 // lines of a column P_s that 64 target rows in a row read.

@@ -1,5 +1,5 @@
 // Segment sums  Z_k = I_k^T Y  of one to four operand columns over large target tables, summed in LDS in fixed point, in
-// target-row order.
+// target-row order; and the assembly of gathered products alone with the segment sums of its residual.
 //
 // The gathering forms of kernels_tmm.hip pay one L2 request per index entry and operand: 265 G entries a second on this device,
 // whatever the kernel looks like.  Here a workgroup of 16 wavefronts holds the sums of a range of source rows (at most 20,416
@@ -18,7 +18,9 @@
 // Bound by instructions: nine ranges look at 5,000,000 rows each, about ten vector instructions a row, two of them in 64 bits.
 // Two more rows a thread in flight, or the conversion ahead of the test for the range (42), gain nothing.
 #include <algorithm>
+#include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "ilargi_internal.h"
 
@@ -66,6 +68,17 @@ __device__ __forceinline__ uint32_t largest_of_wave(uint32_t v) {
   v = max(v, dpp<kRowBcast15, 0xa>(v));
   v = max(v, dpp<kRowBcast31, 0xc>(v));
   return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+}
+
+// Sum of a wavefront's values, in its last lane.
+__device__ __forceinline__ float sum_of_wave(float v) {
+  v += __uint_as_float(dpp<kRowShr + 1>(__float_as_uint(v)));
+  v += __uint_as_float(dpp<kRowShr + 2>(__float_as_uint(v)));
+  v += __uint_as_float(dpp<kRowShr + 4>(__float_as_uint(v)));
+  v += __uint_as_float(dpp<kRowShr + 8>(__float_as_uint(v)));
+  v += __uint_as_float(dpp<kRowBcast15, 0xa>(__float_as_uint(v)));
+  v += __uint_as_float(dpp<kRowBcast31, 0xc>(__float_as_uint(v)));
+  return v;
 }
 
 // Largest of the threads' values, in every thread (one barrier).
@@ -240,6 +253,213 @@ __global__ __launch_bounds__(kFixThreads, 4) void segfix_kernel(SegFixMulti m) {
       phase = kOdd;
     }
     request(u0, g0);
+  }
+}
+
+// The assembly of gathered products alone, with residual and loss, and the segment sums of the residual: products and sums of
+// all tables in LDS, the residual never written.  MODE 1 linear, 2 logistic.  NS: tables.
+// 1,000,000 rows over 6040 and 3710 keys, one logistic model: 12.5 microseconds and 4 for the workgroups' sums, where assembly,
+// segment sums and their runs' sums took 8, 10 and 4.5 (an iteration with 250,000 sparse cells 30 -> 24).  About 9 of the 12.5
+// are there with any number of rows: the launch, the round trips for indices and products, the sums' way out.  Hence few
+// workgroups: 64 to 256 take 13.8, 12.0 (128), 13.1, and the sums of 256 take a microsecond longer to add up.
+// A row without a key takes the place after its table's last: a product of zero, and a sum that nobody reads.
+template <int NS, int CT, int MODE>
+__global__ __launch_bounds__(kFixThreads, 4) void asm_fix_kernel(AsmFix a) {
+  extern __shared__ __align__(16) u64 acc[];
+  __shared__ uint32_t most[kFixThreads / kWave];
+  __shared__ uint32_t found;
+  __shared__ float lsum[kFixThreads / kWave][CT];
+  float* prod = reinterpret_cast<float*>(acc + (size_t)a.slots);
+  const int tid = (int)threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const int units = (int)(a.r_T / 4);                    // groups of four rows
+  const int u0 = (int)((int64_t)units * blockIdx.x / gridDim.x), u1 = (int)((int64_t)units * (blockIdx.x + 1) / gridDim.x);
+  const int steps = (u1 - u0 + kFixThreads - 1) / kFixThreads;
+  const int tail = blockIdx.x + 1 == gridDim.x ? (int)(a.r_T % 4) : 0;         // rows beyond the last group
+
+  struct Group { i4 j[NS]; f4 y; };
+  auto request = [&](int u, Group& g) {                  // (see segfix_kernel)
+    const int64_t at = min(u, u1 - 1);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) g.j[s] = reinterpret_cast<const i4*>(a.idx[s])[at];
+    g.y = reinterpret_cast<const f4*>(a.y)[at];
+  };
+  auto clear = [&]() {
+    for (int s = 2 * tid; s < a.slots; s += 2 * kFixThreads) *reinterpret_cast<ulonglong2*>(acc + s) = ulonglong2{0, 0};
+  };
+
+  Group g;
+  request(u0 + tid, g);
+  // (the products of all tables are requested together: one after the other they cost a round trip each)
+  constexpr int kAhead = CT == 1 ? 4 : 2;
+  int most_keys = a.keys[0];
+#pragma unroll
+  for (int s = 1; s < NS; ++s) most_keys = max(most_keys, a.keys[s]);
+  for (int k0 = tid; k0 < most_keys; k0 += kAhead * kFixThreads) {
+    float p[NS][kAhead][CT];
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const float* from = a.P[s] + (uint32_t)(min(k0 + u * kFixThreads, a.keys[s] - 1) * a.ldp) + a.col0;
+#pragma unroll
+        for (int c = 0; c < CT; ++c) p[s][u][c] = from[c];
+      }
+    if (k0 == tid) clear();
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u)
+        if (k0 + u * kFixThreads < a.keys[s]) {
+#pragma unroll
+          for (int c = 0; c < CT; ++c) prod[(a.off[s] + k0 + u * kFixThreads) * CT + c] = p[s][u][c];
+        }
+  }
+  if (tid >= most_keys) clear();                         // (a thread without a product)
+  if (tid < NS)
+#pragma unroll
+    for (int c = 0; c < CT; ++c) prod[(a.off[tid] + a.keys[tid]) * CT + c] = 0.0f;
+  if (tid == 0) found = 0;
+  __syncthreads();
+
+  float loss[CT], lost[CT];
+#pragma unroll
+  for (int c = 0; c < CT; ++c) loss[c] = lost[c] = 0.0f;
+  float* out = a.partial + (int64_t)blockIdx.x * a.slots;
+  FixScale sc = {0.0f, 0.0, 0.0};
+  uint32_t beyond = 0, largest = 0;
+  // The rows are walked once, in kSum.  Where a value is beyond the limit that the first rows gave, again: for the largest
+  // finite one, for the sums with that limit, and for what is not finite, which makes the same of a sum in any order.
+  enum { kSum, kLargest, kSumAgain, kOdd };
+  for (int phase = kSum;;) {
+    int u = u0 + tid;
+    for (int it = 0; it < steps + (tail > 0 ? 1 : 0); ++it, u += kFixThreads) {
+      Group now = g;
+      if (it + 1 < steps) request(u + kFixThreads, g);
+      bool live = u < u1;
+      if (it == steps) {
+        live = tid == 0;
+        for (int r = 0; r < tail; ++r) {
+          const int64_t t = a.r_T - tail + r;
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (q == r) {
+#pragma unroll
+              for (int s = 0; s < NS; ++s) now.j[s][q] = a.idx[s][t];
+              now.y[q] = a.y[t];
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0x0f70);              // vmcnt(0) here, not where the ways meet
+      }
+      float e[4][CT];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) e[r][c] = 0.0f;
+      if (live) {
+        float add[4][CT];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+#pragma unroll
+          for (int s = 0; s < NS; ++s) now.j[s][r] = (int)min((uint32_t)now.j[s][r], (uint32_t)a.keys[s]) + a.off[s];
+#pragma unroll
+          for (int c = 0; c < CT; ++c) {
+            float z = 0.0f;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) z += prod[now.j[s][r] * CT + c];
+            add[r][c] = 0.0f;
+            if constexpr (MODE == 1) {
+              e[r][c] = z - now.y[r];
+              add[r][c] = e[r][c] * e[r][c];
+            } else {
+              e[r][c] = logistic_residual(z, now.y[r], add[r][c]);
+            }
+          }
+        }
+        if (it == steps) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+              if (r >= tail) e[r][c] = add[r][c] = 0.0f;
+        }
+        if (phase == kSum) {
+#pragma unroll
+          for (int c = 0; c < CT; ++c) {                 // compensated; what is infinite stays so
+            const float t = ((add[0][c] + add[1][c]) + (add[2][c] + add[3][c])) - lost[c], sum = loss[c] + t;
+            lost[c] = fabsf(sum) <= __FLT_MAX__ ? (sum - loss[c]) - t : 0.0f;
+            loss[c] = sum;
+          }
+        }
+      }
+      if (phase == kSum && it == 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) { const uint32_t b = magnitude(e[r][c]); largest = b < kFixInf ? max(largest, b) : largest; }
+        sc = fix_scale(largest_of(largest, most), kFixHead, a.bits);
+      }
+      if (!live) continue;
+      if (phase == kSum || phase == kSumAgain) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) {
+            const bool in = fabsf(e[r][c]) < sc.limit;   // (below the largest finite limit: finite)
+            beyond |= in ? 0u : 1u;
+            e[r][c] = in ? e[r][c] : 0.0f;
+          }
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const uint32_t at[4] = {(uint32_t)now.j[s][0], (uint32_t)now.j[s][1], (uint32_t)now.j[s][2], (uint32_t)now.j[s][3]};
+          add_four<CT>(acc, at, [](int) { return true; }, [&](int r, int c) { return to_fixed(e[r][c], sc.up); });
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) {
+            const uint32_t b = magnitude(e[r][c]);
+            if (phase == kLargest) {
+              largest = b < kFixInf ? max(largest, b) : largest;
+            } else if (b >= kFixInf) {
+#pragma unroll
+              for (int s = 0; s < NS; ++s) atomicAdd(&out[now.j[s][r] * CT + c], e[r][c]);
+            }
+          }
+      }
+    }
+    if (phase == kSum) {
+      if (beyond) atomicOr(&found, 1u);
+#pragma unroll
+      for (int c = 0; c < CT; ++c) {
+        const float t = sum_of_wave(loss[c]);
+        if (lane == kWave - 1) lsum[wave][c] = t;
+      }
+    }
+    __syncthreads();
+    if (phase == kOdd) break;
+    if (phase == kSum && tid < CT) {
+      float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int w = 0; w < kFixThreads / kWave; ++w) part[w / 4] += lsum[w][tid];
+      a.loss_partial[(int64_t)blockIdx.x * kNarrowCT + tid] = (part[0] + part[1]) + (part[2] + part[3]);
+    }
+    const bool again = phase == kSum && found != 0;
+    if (!again && phase != kLargest) {
+      for (int s = tid; s < a.slots; s += kFixThreads) out[s] = from_fixed(acc[s], sc.down);
+      if (phase == kSum || !__syncthreads_or((int)beyond)) break;       // (beyond the largest finite one: not finite)
+      __threadfence();
+      __syncthreads();
+      phase = kOdd;
+    } else if (again) {
+      phase = kLargest;
+    } else {
+      clear();
+      sc = fix_scale(largest_of(largest, most), 0, a.bits);             // (its barrier stands between clearing and adding)
+      beyond = 0;
+      phase = kSumAgain;
+    }
+    request(u0 + tid, g);
   }
 }
 
@@ -425,6 +645,92 @@ hipError_t launch_segfix(const SegFix* a, int n, int ncols, float* scratch, int6
   }
 #undef ILARGI_SEGFIX
   return launch_combine(m, ncols, st);
+}
+
+// Where the tables lie in the products and sums of a workgroup; the number of sums, or 0 if they do not fit.
+static int asm_fix_places(const GatherArgs& g, int ncols, int (&off)[kAsmFixSources]) {
+  if (g.n < 1 || g.n > kAsmFixSources) return 0;
+  int64_t at = 0;
+  for (int s = 0; s < g.n; ++s) {
+    if (g.idx[s] == nullptr || g.rows[s] < 1 || g.rows[s] > kAsmFixSlots || g.rows[s] * g.ldp > (1 << 28)) return 0;
+    off[s] = (int)at;
+    at += (g.rows[s] + 4) / 4 * 4;                       // (a place for rows without a key)
+  }
+  return at * ncols <= kAsmFixSlots ? (int)at * ncols : 0;
+}
+
+bool asm_fix_supported(const LmmArgs& a, int mode) {
+  int off[kAsmFixSources];
+  for (int s = 0; s < a.g.n; ++s)
+    if (reinterpret_cast<uintptr_t>(a.g.idx[s]) % 16 != 0) return false;
+  return a.D == nullptr && reinterpret_cast<uintptr_t>(a.y) % 16 == 0 && (mode == 1 || mode == 2) && a.ncols >= 1 && a.ncols <= kNarrowCT && a.y != nullptr && a.loss_partial != nullptr &&
+         a.r_out >= 4096 && a.r_out < 2147483647ll && asm_fix_places(a.g, a.ncols, off) > 0;
+}
+
+// Whether it pays: the more sums there are, the more rows it takes to make up for clearing and adding up the workgroups' copies.
+// lines[s]: lines of a product that 64 target rows in a row read; keys in order (one or two lines) gather well, so they ask for
+// more rows.  Iterations of one to four logistic models, separate launches / one: 1,000,000 rows over 300 keys 42 / 20, over 3000
+// 31 / 23 (four models 55 / 40), over 12,000 32 / 27, over twice 6000 38 / 28, over 3000 in order 22 / 24; 300,000 over 3000
+// 21 / 22, over twice 300 and more 24 / 19; 100,000 over 3000 19 / 20 (four models 24 / 29); 3,000,000 over three times 2000
+// 74 / 33, over 3000 in order 38 / 27.
+bool asm_fix_pays(const LmmArgs& a, const float* lines) {
+  int64_t keys = 0;
+  int in_order = 0;
+  for (int s = 0; s < a.g.n; ++s) {
+    keys += a.g.rows[s];
+    in_order += lines[s] < 2.5f && a.g.rows[s] > 64 ? 1 : 0;
+  }
+  const int64_t rows = in_order == 0 ? 40 : in_order < a.g.n ? 100 : 700;
+  return a.r_out >= 100000 && a.r_out >= rows * keys * a.ncols;
+}
+
+hipError_t launch_asm_fix(const LmmArgs& a, int mode, float* const* Z, float* scratch, int64_t scratch_floats, hipStream_t st, int* grid_out) {
+  if (!asm_fix_supported(a, mode)) return hipErrorInvalidValue;
+  AsmFix f;
+  memset(&f, 0, sizeof(f));
+  f.slots = asm_fix_places(a.g, a.ncols, f.off);
+  f.n = a.g.n;
+  f.ldp = a.g.ldp; f.col0 = a.col0;
+  f.y = a.y; f.r_T = a.r_out; f.loss_partial = a.loss_partial; f.partial = scratch;
+  SegFixMulti m;
+  memset(&m, 0, sizeof(m));
+  m.n = f.n;
+  const int64_t units = a.r_out / 4;
+  // (balances 0.9 microseconds a round of 4096 rows and workgroup, against 0.5 a megabyte of their sums)
+  const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(256.0, sqrt(440.0 * (double)units / f.slots)),
+                                                               (units + kFixThreads / 2 - 1) / (kFixThreads / 2)));
+  if ((int64_t)grid * f.slots > scratch_floats) return hipErrorInvalidValue;
+  for (int s = 0; s < f.n; ++s) {
+    f.idx[s] = a.g.idx[s]; f.P[s] = a.g.P[s]; f.keys[s] = (int)a.g.rows[s];
+    SegFix& z = m.s[s];
+    z.r_k = a.g.rows[s]; z.n_ranges = 1; z.runs = grid; z.stride = f.slots;
+    z.partial = scratch + (int64_t)f.off[s] * a.ncols;
+    z.Z = Z[s]; z.ldz = a.g.ldp; z.zcol0 = a.col0;
+  }
+  int count = 1;
+  while (((int64_t)1 << count) <= a.r_out / grid + 8) ++count;
+  f.bits = std::min(50, 62 - count);
+  if (grid_out) *grid_out = grid;
+  const size_t lds = (size_t)f.slots * (sizeof(u64) + sizeof(float));
+#define ILARGI_ASM_FIX(N, C)                                                \
+  if (mode == 1) asm_fix_kernel<N, C, 1><<<grid, kFixThreads, lds, st>>>(f); \
+  else asm_fix_kernel<N, C, 2><<<grid, kFixThreads, lds, st>>>(f);
+#define ILARGI_ASM_FIX_CT(N)                \
+  switch (a.ncols) {                        \
+    case 1: ILARGI_ASM_FIX(N, 1) break;     \
+    case 2: ILARGI_ASM_FIX(N, 2) break;     \
+    case 3: ILARGI_ASM_FIX(N, 3) break;     \
+    default: ILARGI_ASM_FIX(N, 4) break;    \
+  }
+  switch (f.n) {
+    case 1: ILARGI_ASM_FIX_CT(1) break;
+    case 2: ILARGI_ASM_FIX_CT(2) break;
+    case 3: ILARGI_ASM_FIX_CT(3) break;
+    default: ILARGI_ASM_FIX_CT(4) break;
+  }
+#undef ILARGI_ASM_FIX_CT
+#undef ILARGI_ASM_FIX
+  return launch_combine(m, a.ncols, st);
 }
 
 }  // namespace ilargi

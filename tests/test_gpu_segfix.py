@@ -1,4 +1,4 @@
-"""Segment sums in fixed point in LDS, against 64-bit sums."""
+"""Segment sums in fixed point in LDS, and the assembly of gathers alone that forms them, against 64-bit sums."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -77,3 +77,47 @@ def test_segment_sums_in_fixed_point(il, r_T, rows, kinds, cx, values):
     got = il.ilargi_tmm(plan, Y)
     _close(got, _exact_tmm(sources, Y))
     assert torch.equal(il.ilargi_tmm(plan, Y).view(torch.int32), got.view(torch.int32))
+
+
+@pytest.mark.parametrize("r_T,rows,kinds,m", [
+    (100_000, [250], ["uniform"], 1),
+    (100_003, [40, 30], ["hot", "uniform"], 4),
+    (600_001, [13_560], ["uniform"], 1),                              # as many keys as LDS holds
+    (540_002, [6_780, 6_776], ["uniform", "hot"], 1),
+    (600_003, [1_500, 3_000, 10], ["uniform", "uniform", "uniform"], 3),
+    (300_001, [1_000, 400, 3, 1], ["uniform", "hot", "uniform", "uniform"], 2),
+    (2_600_001, [300], ["sorted"], 4),
+    (700_000, [5_000, 300], ["sorted", "uniform"], 1),
+])
+@pytest.mark.parametrize("model", ["linear", "logistic"])
+@pytest.mark.parametrize("values", ["normal", "outlier", "odd"])
+def test_assembly_of_gathers_with_their_segment_sums(il, r_T, rows, kinds, m, model, values):
+    gen = torch.Generator(device="cuda").manual_seed(r_T + m)
+    sources, c_T = _sources(r_T, rows, kinds, 0.1, gen)
+    W = torch.randn(c_T, m, generator=gen, device="cuda") / 4
+    y = (torch.rand(r_T, generator=gen, device="cuda") < 0.5).float()
+    if values == "outlier":
+        y[r_T // 2] = 3e5
+    elif values == "odd":
+        y[r_T // 2] = float("inf")
+    lr = torch.linspace(0.1, 0.4, m, device="cuda")
+    Wd = W.double()
+    z = torch.zeros(r_T, m, dtype=torch.float64, device="cuda")
+    for D, idx, cols in sources:
+        p = (D.double().unsqueeze(2) * Wd[cols].unsqueeze(0)).sum(1)
+        z += torch.where((idx >= 0).unsqueeze(1), p[idx.clamp(min=0).long()], 0.0)
+    e = (z if model == "linear" else z.sigmoid()) - y.double().unsqueeze(1)
+    want = Wd - lr.double() / r_T * _exact_tmm(sources, e)
+    per_row = 0.5 * e * e if model == "linear" else torch.nn.functional.softplus(z) - y.double().unsqueeze(1) * z
+    plan = il.ilargi_plan_create(sources, r_T, c_T, max_cx=m)
+    first, loss, again, loss2 = W.clone(), torch.empty(m, device="cuda"), W.clone(), torch.empty(m, device="cuda")
+    which = il.LINEAR if model == "linear" else il.LOGISTIC
+    il.ilargi_gd_step(plan, which, first, y, lr, loss)
+    il.ilargi_gd_step(plan, which, again, y, lr, loss2)
+    if values != "odd":
+        # the step's own error, and the rounding of the updated weight to float32
+        assert (first.double() - want).norm() <= REL * (want - Wd).norm() + 2.0 ** -24 * want.norm()
+        _close(loss, per_row.mean(0))
+    else:
+        assert torch.equal(first.isfinite(), want.isfinite())
+    assert torch.equal(first.view(torch.int32), again.view(torch.int32)) and torch.equal(loss.view(torch.int32), loss2.view(torch.int32))
