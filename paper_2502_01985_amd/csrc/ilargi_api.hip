@@ -1247,13 +1247,25 @@ ilargi_status_t kmeans_fused(ilargi_plan* pl, float* C, int k, int32_t* assign, 
   }
   a.D = f.D; a.d_rows = f.rows; a.ck = (int)f.cols; a.colmap = pl->at<int32_t>(f.o_colmap);
   a.X = C; a.ldx = k; a.ncols = k; a.r_out = pl->r_T;
-  int logR = 0;
-  const int grid = kmeans_tile_grid(a, &logR);
   float* sums = pl->at<float>(pl->lay.o_gpartial);
   int32_t* sizes = pl->at<int32_t>(pl->lay.o_loss);
+  KmeansLaneArgs la;
+  memset(&la, 0, sizeof(la));
+  la.D = f.D; la.ck = (int)f.cols; la.d_rows = f.rows;
+  la.t0 = f.colmap_h[0];
+  for (size_t j = 0; j < f.colmap_h.size(); ++j)
+    if (f.colmap_h[j] != f.colmap_h[0] + (int32_t)j) la.t0 = -1;
+  la.C = C; la.c_T = (int)pl->c_T; la.cn = cn; la.r_T = pl->r_T;
+  la.n = a.g.n;
+  for (int s = 0; s < std::min(a.g.n, kTileParts); ++s) { la.idx[s] = a.g.idx[s]; la.P[s] = a.g.P[s]; }
+  la.assign = assign; la.sizes = sizes; la.sums = sums;
+  int logR = 0;
+  const bool by_lanes = kmeans_lane_supported(la, k);
+  const int grid = by_lanes ? kmeans_lane_grid(pl->r_T) : kmeans_tile_grid(a, &logR);
   {
     TraceScope ts(pl, "kmeans_assign", -1, st);
-    HIP_TRY(launch_kmeans_tile(a, cn, pl->c_T, assign, sizes, sums, grid, logR, st));
+    if (by_lanes) HIP_TRY(launch_kmeans_lane(la, k, grid, st));
+    else HIP_TRY(launch_kmeans_tile(a, cn, pl->c_T, assign, sizes, sums, grid, logR, st));
   }
   if (!merged) HIP_TRY(launch_kmeans_counts(sizes, grid, k, cnt, st));
   // merged: the blocks of all sources stay until the last launch adds them, and the room left is shared out

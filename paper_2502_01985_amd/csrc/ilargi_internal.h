@@ -600,6 +600,23 @@ bool kmeans_tile_supported(int ck, int k);
 int kmeans_tile_grid(const LmmArgs& a, int* logR);
 hipError_t launch_kmeans_tile(const LmmArgs& a, const float* cn, int64_t c_T, int32_t* assign, int32_t* counts_partial,
                               float* sum_partial, int grid, int logR, hipStream_t st);   // cn: centroid norms, NULL: formed there
+// The same for entity tables of few columns over large target tables, a lane per row (kernels_kmeans.hip).
+struct KmeansLaneArgs {
+  const float* D; int ck; int64_t d_rows;   // the identity source: target rows [0, d_rows) take row i
+  int t0;                                   // its columns are target columns [t0, t0 + ck); -1: they are no block
+  const float* C; int c_T;                  // c_T x k
+  const float* cn;                          // centroid norms, NULL: formed there
+  int64_t r_T;
+  int n;                                    // gathered sources
+  const int32_t* idx[kTileParts];
+  const float* P[kTileParts];               // rows x k
+  int32_t* assign;                          // r_T
+  int32_t* sizes;                           // [workgroup][k]
+  float* sums;                              // [workgroup][ck][k]
+};
+bool kmeans_lane_supported(const KmeansLaneArgs& a, int k);
+int kmeans_lane_grid(int64_t r_T);
+hipError_t launch_kmeans_lane(const KmeansLaneArgs& a, int k, int grid, hipStream_t st);
 hipError_t launch_kmeans_counts(const int32_t* partial, int nparts, int k, int32_t* counts, hipStream_t st);
 hipError_t launch_kmeans_segcount(const int32_t* rowptr, const int32_t* perm, const int32_t* assign, int64_t r_k, int k,
                                   int logG, float* Z, hipStream_t st);
