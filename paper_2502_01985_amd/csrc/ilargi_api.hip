@@ -941,6 +941,7 @@ ilargi_status_t run_tred(ilargi_plan* pl, TredArgs& g, float* block, const char*
         TraceScope ts(pl, tag, tag_k, st);
         HIP_TRY(launch_tred_stream(g, grid, bf16, st));
       }
+      if (nparts != nullptr) { *nparts = g.gx; return ILARGI_OK; }
       HIP_TRY(launch_tred_reduce(g.partial, g.gx, elems, block, st, 0));
       return ILARGI_OK;
     }
@@ -1169,19 +1170,32 @@ ilargi_status_t gd_star_step(ilargi_plan* pl, int mode, float* W, int m, const f
       HIP_TRY(launch_gd_star_wide(s, f.vec, mode, bf16, (int)max_grid, st, &grid));
     else HIP_TRY(launch_gd_star(s, f.vec, mode, bf16, (int)max_grid, st, &grid));
   }
-  HIP_TRY(launch_tred_reduce(s.grad_partial, grid, (int64_t)s.cs * m, pl->at<float>(f.o_g), st));
   TredArgs g;
   memset(&g, 0, sizeof(g));
   g.A = d.D; g.lda = (int)d.cols; g.ca = (int)d.cols; g.a_rows = d.rows;
   g.B = pl->at<float>(d.o_pz); g.ldb = m; g.cb = m; g.bcol0 = 0; g.b_rows = d.rows;
   g.n_rows = d.rows;
-  ilargi_status_t rc = run_tred(pl, g, pl->at<float>(d.o_g), "colred", pl->star_k, bf16, st);
+  // Both sources' blocks stay side by side for the last launch where there is room for nine tenths of the workgroups that the
+  // column reduce would have without the star pass's.
+  float* rest = s.grad_partial + (int64_t)grid * s.cs * m;
+  const int64_t rest_floats = pl->lay.gpartial_floats - (int64_t)grid * s.cs * m;
+  const bool together = colasm_wide_supported(m) && tred_stream_supported(g) && (bf16 || ((int64_t)g.ca * g.cb >= 64 * 64 && g.n_rows >= 1024)) &&
+                        rest_floats > 0 && 10 * tred_stream_grid(g, rest_floats) >= 9 * std::max(tred_stream_grid(g, pl->lay.gpartial_floats), 1);
+  if (!together) HIP_TRY(launch_tred_reduce(s.grad_partial, grid, (int64_t)s.cs * m, pl->at<float>(f.o_g), st));
+  int blocks = 0;
+  ilargi_status_t rc = run_tred(pl, g, pl->at<float>(d.o_g), "colred", pl->star_k, bf16, st, false, together ? rest : nullptr,
+                                together ? rest_floats : 0, together ? &blocks : nullptr);
   if (rc != ILARGI_OK) return rc;
   ColAsmArgs c;
   memset(&c, 0, sizeof(c));
   for (int k : {std::min(pl->fused, pl->star_k), std::max(pl->fused, pl->star_k)}) {   // source order, as in the general path
     c.tcol2src[c.n] = pl->at<int32_t>(pl->src[k].o_tcol);
+    c.ck[c.n] = (int)pl->src[k].cols;
     c.G[c.n] = pl->at<float>(pl->src[k].o_g);
+    if (together) {
+      c.G[c.n] = k == pl->fused ? s.grad_partial : rest;
+      c.nparts[c.n] = k == pl->fused ? grid : blocks;
+    }
     ++c.n;
   }
   c.c_T = (int)pl->c_T; c.cx = m; c.out = W;

@@ -578,6 +578,8 @@ hipError_t launch_tmm_pair(const ColredFlatArgs& f, const TmmJoinArgs& j, int64_
                            hipStream_t st, int* grid_f, int* grid_j);
 // tcols > 0: the summed (elems / tcols) x tcols matrix is written transposed
 hipError_t launch_tred_reduce(const float* partial, int nchunks, int64_t elems, float* block, hipStream_t st, int tcols = 0);
+// Blocks (nparts) of more than 64 operand columns: whole float4s, in partial buffers on 16 bytes.
+inline bool colasm_wide_supported(int cx) { return cx > 64 && cx % 4 == 0; }
 hipError_t launch_colasm(const ColAsmArgs& a, int mode, hipStream_t st);
 hipError_t launch_probe(int kind, float* dst, const float* src, int64_t n_floats, int blocks, hipStream_t st);
 hipError_t launch_fill_zero(float* p, int64_t n, hipStream_t st);

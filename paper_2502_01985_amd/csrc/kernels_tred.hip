@@ -451,6 +451,76 @@ __global__ __launch_bounds__(kBlock) void colasm_kernel(ColAsmArgs a) {
   }
 }
 
+// The same for more than 64 operand columns, whole float4s, with sources that still hold per-workgroup partial blocks: a
+// workgroup per target column and 64 operand columns, sixteen groups of lanes add every sixteenth block of a source, eight in
+// flight, and the groups are added pairwise.  The loss is one row more, with a block per workgroup of the residual pass.
+// 220 x 256 over 241 and 768 blocks (65 MB): 17 microseconds; a reduction per source, the assembly and the loss in launches of
+// their own 17, 7 and 10, the last of them waiting for 768 blocks a wavefront.
+template <int MODE>
+__global__ __launch_bounds__(kBlock) void colasm_wide_kernel(ColAsmArgs a) {
+  __shared__ float4 part[16][16];
+  const int l = threadIdx.x % 16, g = threadIdx.x / 16, slabs = (a.cx + 63) / 64;
+  const int t = (int)blockIdx.x / slabs, n = (int)blockIdx.x % slabs * 64 + 4 * l;
+  const bool live = n < a.cx;
+  auto sum_blocks = [&](const float* p, int64_t stride, int blocks) {          // in group 0
+    float4 s[2] = {make_float4(0.0f, 0.0f, 0.0f, 0.0f), make_float4(0.0f, 0.0f, 0.0f, 0.0f)};
+    if (live)
+      for (int b = g; b < blocks; b += 8 * 16) {
+        float4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          v[u] = b + u * 16 < blocks ? *reinterpret_cast<const float4*>(p + (int64_t)(b + u * 16) * stride + n) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+        for (int u = 0; u < 8; u += 2) {
+          const float4 x = v[u], y = v[u + 1];
+          float4& o = s[u / 2 % 2];
+          o.x += x.x + y.x; o.y += x.y + y.y; o.z += x.z + y.z; o.w += x.w + y.w;
+        }
+      }
+    __syncthreads();
+    part[g][l] = make_float4(s[0].x + s[1].x, s[0].y + s[1].y, s[0].z + s[1].z, s[0].w + s[1].w);
+    __syncthreads();
+    float4 r = part[0][l];
+    if (g == 0) {
+      float4 q[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) q[c] = part[c][l];
+#pragma unroll
+      for (int d = 8; d >= 1; d /= 2)
+#pragma unroll
+        for (int c = 0; c < d; ++c) { q[c].x += q[c + d].x; q[c].y += q[c + d].y; q[c].z += q[c + d].z; q[c].w += q[c + d].w; }
+      r = q[0];
+    }
+    return r;
+  };
+  if (t == a.c_T) {
+    if constexpr (MODE == 1) {
+      const float4 s = sum_blocks(a.loss_partial, a.cx, a.n_loss_partial);
+      if (g == 0 && live) {
+        const float v[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) a.loss[n + c] = v[c] * a.loss_scale;
+      }
+    }
+    return;
+  }
+  float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  for (int k = 0; k < a.n; ++k) {
+    const int j = a.tcol2src[k][t];
+    if (j < 0) continue;
+    const float4 s = sum_blocks(a.G[k] + (int64_t)j * a.cx, (int64_t)a.ck[k] * a.cx, max(a.nparts[k], 1));
+    acc.x += s.x; acc.y += s.y; acc.z += s.z; acc.w += s.w;
+  }
+  if (g != 0 || !live) return;
+  float* o = a.out + (int64_t)t * a.cx + n;
+  const float v[4] = {acc.x, acc.y, acc.z, acc.w};
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    if constexpr (MODE == 0) o[c] = v[c];
+    else o[c] = o[c] - a.lr[n + c] * (v[c] * a.inv_rT);
+  }
+}
+
 // The same with sources that still hold per-workgroup partial blocks (nparts[k] blocks of c_k x cx): one workgroup
 // per target column; thread (n, slice) adds the blocks slice, slice + S, ... of operand column n, the slices are
 // added in order through LDS, the sources in source order.  For operands of at most 64 columns.
@@ -661,6 +731,13 @@ hipError_t launch_colasm(const ColAsmArgs& a, int mode, hipStream_t st) {
     if (mode == 0) colasm_parts_kernel<0><<<grid, kBlock, 0, st>>>(a, nw);
     else if (mode == 2) colasm_parts_kernel<2><<<grid, 1024, 0, st>>>(a, nw);
     else colasm_parts_kernel<1><<<grid, kBlock, 0, st>>>(a, nw);
+    return hipGetLastError();
+  }
+  if (parts) {
+    if (!colasm_wide_supported(a.cx)) return hipErrorInvalidValue;
+    const int64_t grid = (int64_t)(a.c_T + (mode == 1 && a.loss != nullptr ? 1 : 0)) * ((a.cx + 63) / 64);
+    if (mode == 0) colasm_wide_kernel<0><<<(unsigned)grid, kBlock, 0, st>>>(a);
+    else colasm_wide_kernel<1><<<(unsigned)grid, kBlock, 0, st>>>(a);
     return hipGetLastError();
   }
   int grid = (int)((total + kBlock - 1) / kBlock);
