@@ -923,6 +923,7 @@ ilargi_status_t run_tred(ilargi_plan* pl, TredArgs& g, float* block, const char*
       TraceScope ts(pl, tag, tag_k, st);
       HIP_TRY(launch_gram_narrow(g, part, part_floats, st, &nch));
     }
+    if (nparts != nullptr) { *nparts = nch; return ILARGI_OK; }
     HIP_TRY(launch_tred_reduce(part, nch, elems, block, st, 0));
     return ILARGI_OK;
   }
@@ -2452,8 +2453,32 @@ ilargi_status_t ilargi_crossprod(ilargi_plan_t* plan, float* out, void* stream) 
   bool forked = false;
   float* part_main = gpart;
   int64_t part_main_floats = gfloats;
-  auto run_gram = [&](TredArgs& g, float* block, int pair) -> ilargi_status_t {
-    return run_tred(plan, g, block, "gram", pair, false, st, false, part_main, part_main_floats);   // traced as gram:<k * n + l>
+  // The chunks' sums of several blocks wait side by side in the partial-block space for one launch that adds them, as long as
+  // half of the space is free for the next block.
+  TredReduce waiting[kTredReduceMulti];
+  int n_waiting = 0;
+  int64_t waiting_floats = 0;
+  auto add_waiting = [&]() -> ilargi_status_t {
+    HIP_TRY(launch_tred_reduce_multi(waiting, n_waiting, st));
+    n_waiting = 0; waiting_floats = 0;
+    return ILARGI_OK;
+  };
+  auto wait = [&](int chunks, int64_t elems, float* block, int tcols) {
+    waiting[n_waiting++] = TredReduce{part_main + waiting_floats, chunks, elems, block, tcols};
+    waiting_floats = (waiting_floats + chunks * elems + 3) / 4 * 4;
+  };
+  auto make_room = [&]() -> ilargi_status_t {
+    return n_waiting == kTredReduceMulti || 2 * waiting_floats > part_main_floats ? add_waiting() : ILARGI_OK;
+  };
+  auto run_gram = [&](TredArgs& g, float* block, int pair, bool transposed = false) -> ilargi_status_t {
+    ilargi_status_t rc = make_room();
+    if (rc != ILARGI_OK) return rc;
+    const int64_t elems = (int64_t)g.ca * g.cb;
+    int chunks = 0;
+    rc = run_tred(plan, g, block, "gram", pair, false, st, transposed, part_main + waiting_floats, part_main_floats - waiting_floats,
+                  &chunks);                                   // traced as gram:<k * n + l>
+    if (rc == ILARGI_OK && chunks > 0) wait(chunks, elems, block, transposed ? g.cb : 0);
+    return rc;
   };
   // two-table star join with a narrow entity table listed first: S^T S and the rows of S summed per row of R
   // (which the off-diagonal block needs) come from one pass over S in join order
@@ -2498,8 +2523,7 @@ ilargi_status_t ilargi_crossprod(ilargi_plan_t* plan, float* out, void* stream) 
         HIP_TRY(hipEventRecord(plan->ev_join, plan->side));
         forked = true;
       }
-      HIP_TRY(launch_tred_reduce(ga.ss_partial, grid, f.cols * f.cols,
-                                 blocks + plan->block_off[(size_t)plan->fused * n + plan->fused], st));
+      wait(grid, f.cols * f.cols, blocks + plan->block_off[(size_t)plan->fused * n + plan->fused], 0);
       star_done = true;
     }
   }
@@ -2540,7 +2564,7 @@ ilargi_status_t ilargi_crossprod(ilargi_plan_t* plan, float* out, void* stream) 
             // few summed columns against a wide table: the wide table takes the A role (whole rows as float4,
             // 128 columns per workgroup) and the block is written transposed, D_l^T Zc = (Zc^T D_l)^T
             std::swap(g.A, g.B); std::swap(g.lda, g.ldb); std::swap(g.ca, g.cb); std::swap(g.a_rows, g.b_rows);
-            rc = run_tred(plan, g, block, "gram", k * n + l, false, st, true, part_main, part_main_floats);
+            rc = run_gram(g, block, k * n + l, true);
             if (rc != ILARGI_OK) return rc;
             continue;
           }
@@ -2567,13 +2591,15 @@ ilargi_status_t ilargi_crossprod(ilargi_plan_t* plan, float* out, void* stream) 
               HIP_TRY(launch_fill_zero(block, (int64_t)g.ca * g.cb, st));
               continue;
             }
-            if (gram_pairs_supported(g) && gram_pairs_pay(g, plan->r_T) && (int64_t)g.ca * g.cb <= part_main_floats) {
+            if (gram_pairs_supported(g) && gram_pairs_pay(g, plan->r_T) && 2 * (int64_t)g.ca * g.cb <= part_main_floats) {
               int nch = 0;
+              rc = make_room();
+              if (rc != ILARGI_OK) return rc;
               {
                 TraceScope ts(plan, "gram", k * n + l, st);
-                HIP_TRY(launch_gram_narrow(g, part_main, part_main_floats, st, &nch));
+                HIP_TRY(launch_gram_narrow(g, part_main + waiting_floats, part_main_floats - waiting_floats, st, &nch));
               }
-              HIP_TRY(launch_tred_reduce(part_main, nch, (int64_t)g.ca * g.cb, block, st, 0));
+              wait(nch, (int64_t)g.ca * g.cb, block, 0);
               continue;
             }
           }
@@ -2585,6 +2611,10 @@ ilargi_status_t ilargi_crossprod(ilargi_plan_t* plan, float* out, void* stream) 
       }
       if (rc != ILARGI_OK) return rc;
     }
+  }
+  {
+    const ilargi_status_t rc = add_waiting();
+    if (rc != ILARGI_OK) return rc;
   }
   if (forked) HIP_TRY(hipStreamWaitEvent(st, plan->ev_join, 0));   // join
   HIP_TRY(launch_gram_assemble(plan->at<GramAsmPair>(plan->lay.o_pairs), plan->npairs,

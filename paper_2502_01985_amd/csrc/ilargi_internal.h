@@ -578,6 +578,11 @@ hipError_t launch_tmm_pair(const ColredFlatArgs& f, const TmmJoinArgs& j, int64_
                            hipStream_t st, int* grid_f, int* grid_j);
 // tcols > 0: the summed (elems / tcols) x tcols matrix is written transposed
 hipError_t launch_tred_reduce(const float* partial, int nchunks, int64_t elems, float* block, hipStream_t st, int tcols = 0);
+// The same for several matrices in one launch.
+constexpr int kTredReduceMulti = 8;
+struct TredReduce { const float* partial; int nchunks; int64_t elems; float* block; int tcols; };
+struct TredReduceMulti { int n; int first[kTredReduceMulti + 1]; TredReduce r[kTredReduceMulti]; };
+hipError_t launch_tred_reduce_multi(const TredReduce* r, int n, hipStream_t st);
 // Blocks (nparts) of more than 64 operand columns: whole float4s, in partial buffers on 16 bytes.
 inline bool colasm_wide_supported(int cx) { return cx > 64 && cx % 4 == 0; }
 hipError_t launch_colasm(const ColAsmArgs& a, int mode, hipStream_t st);
