@@ -611,6 +611,9 @@ ilargi_status_t lmm_pass(ilargi_plan* pl, const float* X, int ldx, int col0, int
     a.D = f.D; a.d_rows = f.rows; a.ck = (int)f.cols; a.colmap = pl->at<int32_t>(f.o_colmap);
     vec = f.vec;
     a.logL = pick_logL(f.cols, f.vec);
+    a.x_block = f.colmap_h[0] + 1;
+    for (size_t j = 0; j < f.colmap_h.size(); ++j)
+      if (f.colmap_h[j] != f.colmap_h[0] + (int32_t)j) a.x_block = 0;
   }
   a.X = X; a.ldx = ldx; a.col0 = col0; a.ncols = ncols;
   a.out = out; a.ldo = ldo; a.r_out = pl->r_T;
@@ -2454,7 +2457,7 @@ ilargi_status_t ilargi_crossprod(ilargi_plan_t* plan, float* out, void* stream) 
   float* part_main = gpart;
   int64_t part_main_floats = gfloats;
   // The chunks' sums of several blocks wait side by side in the partial-block space for one launch that adds them, as long as
-  // half of the space is free for the next block.
+  // the next block finds room for a thousand chunks, or for as many as the whole space holds.
   TredReduce waiting[kTredReduceMulti];
   int n_waiting = 0;
   int64_t waiting_floats = 0;
@@ -2467,13 +2470,14 @@ ilargi_status_t ilargi_crossprod(ilargi_plan_t* plan, float* out, void* stream) 
     waiting[n_waiting++] = TredReduce{part_main + waiting_floats, chunks, elems, block, tcols};
     waiting_floats = (waiting_floats + chunks * elems + 3) / 4 * 4;
   };
-  auto make_room = [&]() -> ilargi_status_t {
-    return n_waiting == kTredReduceMulti || 2 * waiting_floats > part_main_floats ? add_waiting() : ILARGI_OK;
+  auto make_room = [&](int64_t elems) -> ilargi_status_t {
+    const bool room = (part_main_floats - waiting_floats) / elems >= std::min<int64_t>(1024, part_main_floats / elems);
+    return n_waiting == kTredReduceMulti || !room ? add_waiting() : ILARGI_OK;
   };
   auto run_gram = [&](TredArgs& g, float* block, int pair, bool transposed = false) -> ilargi_status_t {
-    ilargi_status_t rc = make_room();
-    if (rc != ILARGI_OK) return rc;
     const int64_t elems = (int64_t)g.ca * g.cb;
+    ilargi_status_t rc = make_room(std::max<int64_t>(elems, 1));
+    if (rc != ILARGI_OK) return rc;
     int chunks = 0;
     rc = run_tred(plan, g, block, "gram", pair, false, st, transposed, part_main + waiting_floats, part_main_floats - waiting_floats,
                   &chunks);                                   // traced as gram:<k * n + l>
@@ -2591,9 +2595,9 @@ ilargi_status_t ilargi_crossprod(ilargi_plan_t* plan, float* out, void* stream) 
               HIP_TRY(launch_fill_zero(block, (int64_t)g.ca * g.cb, st));
               continue;
             }
-            if (gram_pairs_supported(g) && gram_pairs_pay(g, plan->r_T) && 2 * (int64_t)g.ca * g.cb <= part_main_floats) {
+            if (gram_pairs_supported(g) && gram_pairs_pay(g, plan->r_T) && (int64_t)g.ca * g.cb <= part_main_floats) {
               int nch = 0;
-              rc = make_room();
+              rc = make_room((int64_t)g.ca * g.cb);
               if (rc != ILARGI_OK) return rc;
               {
                 TraceScope ts(plan, "gram", k * n + l, st);
