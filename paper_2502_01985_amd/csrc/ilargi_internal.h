@@ -57,6 +57,7 @@ struct LmmArgs {
   int ld_loss;
   int nt_in;              // read the table past the caches (see stream_past_caches)
   int nt_out;             // store the output with non-temporal stores (large results nobody re-reads soon)
+  int x_block;            // the table's columns are target columns [x_block - 1, x_block - 1 + ck); 0: no block, or not known
   int lds_products;       // the gathers are worth products in LDS (lmm_lane_lds_pays)
   float* scratch;         // optional device scratch of scratch_floats floats (the caller's, free for the launch)
   int64_t scratch_floats;
@@ -530,6 +531,8 @@ hipError_t launch_colred(const ColredArgs& a, int nblocks, hipStream_t st);
 // lines of a column P_s that 64 target rows in a row read.
 bool lmm_lane_wants_lines(int64_t rows, int64_t cols);
 bool lmm_lane_lds_pays(const LmmArgs& a, const float* lines);
+bool asm_row_supported(const LmmArgs& a, int mode, bool fuseg);
+hipError_t launch_asm_row(const LmmArgs& a, int mode, hipStream_t st, int* grid_out);
 bool lmm_flat_supported(const LmmArgs& a, int vec, bool fuseg);
 hipError_t launch_lmm_flat(const LmmArgs& a, int mode, bool fuseg, hipStream_t st, int* grid_out);
 hipError_t launch_finalize(const FinArgs& a, int c_T, int mode, hipStream_t st);

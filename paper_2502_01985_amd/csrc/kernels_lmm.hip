@@ -477,9 +477,16 @@ hipError_t launch_lmm_rows(const LmmArgs& a, int vec, int mode, hipStream_t st, 
   if (grid_out) *grid_out = grid;
   if (a.r_out <= 0) return hipSuccess;
   if (mode == 0 && !fuseg && vec == 4 && rowdot_supported(a, 4)) return launch_rowdot_multi(&a, nullptr, 1, st);
+  // The kernel with a lane per row and the gradient on the matrix cores, against those that serve aligned rows of one operand
+  // column (two rows a lane for rows of float2, a flat stream for float4): the time of an iteration over theirs is 0.77 to 0.95
+  // at 40,000 to 333,333 rows; rows of float2 1.02 to 1.10 from 1,000,000 on, where their gathers are the bound and products in
+  // LDS help; rows of float4 0.95 to 0.99 at 1,000,000, 1.02 at 2,500,000.  Several operand columns: 0.77 to 0.97 throughout.
+  const bool by_rows = asm_row_supported(a, mode, fuseg);
+  if (by_rows && (a.ncols > 1 || a.r_out < (vec == 2 ? 700000 : 1500000))) return launch_asm_row(a, mode, st, grid_out);
   if (lmm_lane_supported(a, vec, mode, fuseg)) return launch_lmm_lane(a, vec, mode, st, grid_out);
   if (lmm_flat_supported(a, vec, fuseg)) return launch_lmm_flat(a, mode, fuseg, st, grid_out);
   if (lmm_flat_pair_supported(a, vec, fuseg)) return launch_lmm_flat_pair(a, mode, fuseg, st, grid_out);
+  if (by_rows) return launch_asm_row(a, mode, st, grid_out);    // (against tiles that workgroups share: 0.79 to 0.97 everywhere)
   if (asm_tile_supported(a, vec, fuseg)) return launch_asm_tile(a, mode, st, grid_out);
   switch (vec) {
     case 4: return launch_ct<4>(a, mode, fuseg, grid, st);
