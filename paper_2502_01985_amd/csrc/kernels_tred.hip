@@ -509,7 +509,7 @@ __global__ __launch_bounds__(kBlock) void colasm_wide_kernel(ColAsmArgs a) {
   const int t = (int)blockIdx.x / slabs, n = (int)blockIdx.x % slabs * 64 + 4 * l;
   const bool live = n < a.cx;
   auto sum_blocks = [&](const float* p, int64_t stride, int blocks) {          // in group 0
-    float4 s[2] = {make_float4(0.0f, 0.0f, 0.0f, 0.0f), make_float4(0.0f, 0.0f, 0.0f, 0.0f)};
+    float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (live)
       for (int b = g; b < blocks; b += 8 * 16) {
         float4 v[8];
@@ -517,14 +517,13 @@ __global__ __launch_bounds__(kBlock) void colasm_wide_kernel(ColAsmArgs a) {
         for (int u = 0; u < 8; ++u)
           v[u] = b + u * 16 < blocks ? *reinterpret_cast<const float4*>(p + (int64_t)(b + u * 16) * stride + n) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
-        for (int u = 0; u < 8; u += 2) {
-          const float4 x = v[u], y = v[u + 1];
-          float4& o = s[u / 2 % 2];
-          o.x += x.x + y.x; o.y += x.y + y.y; o.z += x.z + y.z; o.w += x.w + y.w;
-        }
+        for (int d = 4; d >= 1; d /= 2)
+#pragma unroll
+          for (int u = 0; u < d; ++u) { v[u].x += v[u + d].x; v[u].y += v[u + d].y; v[u].z += v[u + d].z; v[u].w += v[u + d].w; }
+        s.x += v[0].x; s.y += v[0].y; s.z += v[0].z; s.w += v[0].w;
       }
     __syncthreads();
-    part[g][l] = make_float4(s[0].x + s[1].x, s[0].y + s[1].y, s[0].z + s[1].z, s[0].w + s[1].w);
+    part[g][l] = s;
     __syncthreads();
     float4 r = part[0][l];
     if (g == 0) {
