@@ -455,9 +455,6 @@ hipError_t launch_sort_by_source_row(const int32_t* idx, int64_t r_T, int64_t r_
                                      int32_t* vals_a, int32_t* keys_b, int32_t* vals_b, int32_t* hist,
                                      int32_t* rowptr, int32_t* perm, hipStream_t st);
 size_t sort_hist_ints(int64_t r_T);
-// One stable pass of the sort over the low eight bits of the keys; hist is left as the digit-major start offsets.
-hipError_t launch_radix_digit(const int32_t* keys_in, const int32_t* vals_in, int64_t n, int32_t* keys_out, int32_t* vals_out,
-                              int32_t* hist, hipStream_t st);
 // In-place exclusive prefix sum of n integers on the device; `totals` is scratch of ceil(n / 1024) integers.
 void launch_exclusive_scan(int32_t* a, int64_t n, int32_t* totals, hipStream_t st);
 

@@ -278,16 +278,6 @@ hipError_t launch_sort_by_source_row(const int32_t* idx, int64_t r_T, int64_t r_
   return hipGetLastError();
 }
 
-hipError_t launch_radix_digit(const int32_t* keys_in, const int32_t* vals_in, int64_t n, int32_t* keys_out, int32_t* vals_out,
-                              int32_t* hist, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  const int nchunks = (int)((n + kSortChunk - 1) / kSortChunk);
-  radix_hist_kernel<false><<<nchunks, kBlock, 0, st>>>(keys_in, n, 0u, 0, nchunks, hist);
-  launch_exclusive_scan(hist, (int64_t)256 * nchunks, hist + (int64_t)256 * nchunks, st);
-  radix_scatter_kernel<false><<<nchunks, kBlock, 0, st>>>(keys_in, vals_in, n, 0u, 0, nchunks, hist, keys_out, vals_out);
-  return hipGetLastError();
-}
-
 __global__ __launch_bounds__(kBlock) void fill_zero_kernel(float* __restrict__ p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     p[i] = 0.0f;

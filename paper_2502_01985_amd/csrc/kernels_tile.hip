@@ -393,6 +393,7 @@ __device__ __forceinline__ void centroid_norms(const float* __restrict__ C, int 
 // 1,000,000 x 20 joined with 100,000 rows, 10 centroids: 60 microseconds, 2 of them the norms; T C (65), the assignment (21)
 // and S^T A (38) by themselves took 124.  Of the 60, 8 are the gathers, 8 the cluster sums and most of the rest the operand's
 // way through LDS to every lane (smaller tiles, which spread a row over lanes, measure 3 to 26 % slower).
+// (Tables of at most 20 columns over many rows take kernels_kmeans.hip: 46.)
 // cn: the norms of the centroids, or NULL.
 template <int KC, bool AL>
 __global__ __launch_bounds__(kBlock, 4) void kmeans_tile_kernel(LmmArgs a, const float* __restrict__ cn, int c_T, int32_t* __restrict__ assign,
@@ -676,6 +677,7 @@ hipError_t launch_prod_tile(const LmmArgs* a, int n, hipStream_t st) {
 //                                    (17 to 21 of 32) 0.97 / 0.76, 46 1.02 / 0.88;  18 columns of 30,000 rows 1.10
 //   a product, rows of float4        68 to 80 0.91 / 0.81, 84 to 92 1.08 / 0.98;  rows of float2  34 to 46 0.82 / 0.61
 // With several operand columns the tiles win everywhere (300,000 rows, two models: 36 columns 0.80, 46 0.82, 52 0.86).
+// (Iterations over at most 24 columns take kernels_asm_row.hip where that is the faster one.)
 bool asm_tile_supported(const LmmArgs& a, int vec, bool fuseg) {
   if (a.ncols < 1 || a.ncols > kNarrowCT || a.r_out <= 0) return false;
   if (a.D == nullptr) return !fuseg;
