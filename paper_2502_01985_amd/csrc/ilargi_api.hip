@@ -65,6 +65,7 @@ struct SourcePlan {
   bool cut = false;               // some segment is long enough to be spread over workgroups
   float lines = 0.0f;             // lines of a product that 64 target rows in a row read (0: not asked for)
   bool very_long = false;         // some segment has more than kLongSeg entries: no join-order paths
+  int64_t longest = 0;            // target rows of the source row with the most of them
   int max_row = 0, max_col = 0;   // sparse: most entries of a row, of a column
   size_t o_join_first = 0;        // join-order column reduce: first source row of every workgroup
   int n_join_blocks = 0;
@@ -738,7 +739,7 @@ ilargi_status_t tmm_pass(ilargi_plan* pl, const float* Y, int ldy, int col0, int
       if (kind == kFixed) {
         SegFix& f = fix[nm];
         memset(&f, 0, sizeof(f));
-        f.idx = p.idx; f.Y = Y; f.r_T = pl->r_T; f.r_k = p.rows;
+        f.idx = p.idx; f.Y = Y; f.r_T = pl->r_T; f.r_k = p.rows; f.longest = p.longest;
         f.Z = pl->at<float>(p.o_pz); f.ldz = ldy; f.zcol0 = col0;
       } else {
         multi[nm] = segsum_args(k);
@@ -1493,6 +1494,7 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
     const int32_t spread = std::max(kSegCut, 16 << p.logG);
     p.long_thr = 2 * avg > spread ? kLongSeg : std::max((int)kWave, 8 << p.logG);
     const int32_t longest = longest_segment(rowptr);
+    p.longest = longest;
     p.very_long = longest > kLongSeg;
     p.cut = longest > (2 * avg > spread ? kLongSeg : spread);
     std::vector<int32_t> cs, cb, ce, ls, lf(1, 0);

@@ -222,17 +222,21 @@ struct SegMulti {
 
 // Segment sums in fixed point in LDS (kernels_segfix.hip).
 constexpr int kFixThreads = 1024;
-constexpr int kFixSlots = 20416;          // sums of 64 bits a workgroup holds
-constexpr int kFixHead = 6;               // factor (log2) that values may exceed the first ones of a run by
+constexpr int kFixSlots = 20160;          // sums of 64 bits a workgroup holds
+constexpr int kFixNear = 16;              // values outside the band of a walk that a wavefront lists in LDS ...
+constexpr int kFixFar = 2048;             // ... and in memory
+constexpr int kFixHead = 2;               // binades of the band above the largest of a run's first values
 constexpr int kFixPerXcd = 32;            // workgroups an XCD holds
 struct SegFix {
   const int32_t* idx;        // r_T
   const float* Y;            // r_T x ncols
   int64_t r_T, r_k;
+  int64_t longest;           // target rows of the source row with the most of them; 0: not known
   float* Z;                  // r_k x ldz, columns [zcol0, zcol0 + ncols)
   int ldz, zcol0;
-  int n_ranges, nsub, runs, bits, stride;   // set by the launcher
+  int n_ranges, nsub, runs, bits, stride, room;   // set by the launcher
   float* partial;
+  unsigned long long* far;   // room for each wavefront
 };
 struct SegFixMulti {
   int n;
@@ -242,17 +246,18 @@ struct SegFixMulti {
 
 // The assembly of gathered products alone with the segment sums of its residual (kernels_segfix.hip).
 constexpr int kAsmFixSources = 4;
-constexpr int kAsmFixSlots = 13568;       // sums of 64 bits and products of 32 a workgroup holds
+constexpr int kAsmFixSlots = 13424;       // sums of 64 bits and products of 32 a workgroup holds
 struct AsmFix {
   int n;
   const int32_t* idx[kAsmFixSources];
   const float* P[kAsmFixSources];
   int keys[kAsmFixSources], off[kAsmFixSources];
-  int ldp, col0, slots, bits;
+  int ldp, col0, slots, bits, room;
   const float* y;
   int64_t r_T;
   float* loss_partial;       // [gridDim.x][kNarrowCT]
   float* partial;            // [gridDim.x][slots]
+  unsigned long long* far;   // [gridDim.x][wavefronts][room]
 };
 
 struct ColredArgs {

@@ -2,21 +2,27 @@
 // target-row order; and the assembly of gathered products alone with the segment sums of its residual.
 //
 // The gathering forms of kernels_tmm.hip pay one L2 request per index entry and operand: 265 G entries a second on this device,
-// whatever the kernel looks like.  Here a workgroup of 16 wavefronts holds the sums of a range of source rows (at most 20,416
+// whatever the kernel looks like.  Here a workgroup of 16 wavefronts holds the sums of a range of source rows (at most 20,160
 // of 64 bits) in LDS, walks its share of the target rows in order and adds every row whose key lies in its range: row indices
 // and operand are plain streams, and no inverse index is read or kept.  Sums are 64-bit integers: ds_add_u64 takes 13 cycles a
 // wavefront instruction with 64 different places (ds_add_f64 22, ds_add_f32 194 on this device), returns nothing that anyone
 // waits for, and whole numbers add up to the same in any order, so the result is the same on every run.
 //
-// The unit of a run's sums is a power of two: a run of 2^n rows leaves 62 - n bits (at most 50) for a value, 2^6 times the
-// largest of the run's first rows is the limit.  Float sums of the same length lose more than this keeps.  Where a value is
-// beyond the limit the run is walked again, with its own largest finite value as the limit; infinities and NaN are then added to
-// the run's sums as they are.
+// A value is either added exactly or kept aside, so every sum is as accurate as it is by itself, whatever other keys and columns
+// hold.  A run has a unit for every column, a power of two: sums of up to 2^n rows leave 62 - n bits (at most 50) for a value, and
+// a float in the upper 62 - n - 24 binades of these is a whole number of units.  What is typical of the largest of the run's first
+// rows lies two binades below their top.  Each wavefront lists what is outside, in LDS and then in memory.  Short lists (one value
+// in 100,000 is outside where all are of one kind) are added in doubles to their sums on the way out; longer ones are walked like
+// rows, with a unit for the largest that is left; where they have no room, the rows are walked again.  A sum is rounded to float
+// once for every walk that found values of its own.  Infinities and NaN are listed as they are, or added in a walk of their own.
 //
-// 5,000,000 rows over 100,000 uniform, 50,000 Zipf and 10,000 uniform keys: 33 microseconds and 6 for the runs' sums (with an
+// 5,000,000 rows over 100,000 uniform, 50,000 Zipf and 10,000 uniform keys: 32 microseconds and 6 for the runs' sums (with an
 // index by windows, float sums that belong to one wavefront each, 51 and 8; gathering, by slice of the target rows, 78 and 10).
 // Bound by instructions: nine ranges look at 5,000,000 rows each, about ten vector instructions a row, two of them in 64 bits.
-// Two more rows a thread in flight, or the conversion ahead of the test for the range (42), gain nothing.
+// Four blocks a thread requested at once instead of two, or the conversion ahead of the test for the range (42), gain nothing.
+// T^T Y with these tables takes 47 microseconds for normal or constant values, nine tenths zeros or single outliers (57 through
+// the index by windows, whatever the values), 56 for Cauchy values, 92 where one value in 70 is far below the others (logistic
+// functions of N(0, 64)), 100 for lognormal values (sigma 3) and 616 where values spread evenly over 200 binades (12 walks).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -41,23 +47,125 @@ __device__ __forceinline__ u64 to_fixed(float v, double scale) {
   return d - ((u64)kFixMagicHigh << 32);
 }
 
+constexpr int kFixWaves = kFixThreads / kWave;
+
 __device__ __forceinline__ uint32_t magnitude(float v) { return __float_as_uint(v) & 0x7fffffffu; }
 constexpr uint32_t kFixInf = 0x7f800000u;
 
-struct FixScale { float limit; double up, down; };
+// What earlier walks have summed, by column: magnitudes of the first walk's band, and finite ones from `done` up.  (In LDS.)
+// down: the walk's unit.
+struct Summed { double down; uint32_t low, high, done; };
+struct Left { uint32_t largest, others; };
 
-// The unit of a run's sums: values below 2^(e + head) in magnitude, where the largest is below 2^e, get `bits` bits.
-__device__ __forceinline__ FixScale fix_scale(uint32_t largest, int head, int bits) {
-  const int e = max((int)(largest >> 23), 1) - 126 + head;
-  return FixScale{ldexpf(1.0f, e), ldexp(1.0, bits - e), ldexp(1.0, e - bits)};
+// The magnitudes that a walk sums, by column: [low, low + span), multiples of the unit, 1 / up.
+template <int CT>
+struct Bands {
+  uint32_t low[CT], span[CT];
+  double up[CT];
+
+  // [2^(top - bits + 23), 2^top): the unit is 2^(top - bits); down to the smallest float where that is a multiple.
+  __device__ __forceinline__ void set(int c, int top, int bits) {
+    up[c] = __longlong_as_double((long long)(bits - top + 1023) << 52);
+    const int field = top - bits + 23 + 127;
+    low[c] = field <= 0 ? 1u : (uint32_t)field << 23;
+    span[c] = ((uint32_t)min(top + 127, 255) << 23) - low[c];
+  }
+  static __device__ __forceinline__ int above(uint32_t largest) { return max((int)(largest >> 23), 1) - 126; }   // largest < 2^above
+  // (a column that begins with nothing but zeros is taken for one of values about one)
+  __device__ __forceinline__ void first(int c, uint32_t largest, int bits, Summed* summed) {
+    set(c, (largest == 0 ? 1 : above(largest)) + kFixHead, bits);
+    summed[c].down = down(c);
+  }
+  // The walk after this one: for the largest that is left (0: none).
+  __device__ __forceinline__ void next(int c, uint32_t largest, int bits, Summed* summed) {
+    Summed was = summed[c];
+    if (was.done == kFixInf) { was.low = low[c]; was.high = low[c] + span[c]; }
+    if (largest == 0) {
+      low[c] = was.done = 1u;
+      span[c] = 0;
+    } else {
+      set(c, above(largest), bits);
+      const uint32_t high = low[c] + span[c];
+      if (largest >= was.high) low[c] = max(low[c], was.high);
+      span[c] = (largest >= was.high ? high : min(high, was.low)) - low[c];
+      was.done = low[c];
+    }
+    was.down = down(c);
+    __syncthreads();                                     // (all threads have read)
+    summed[c] = was;
+  }
+  // (twice the distance from the low end; twice the span and more is outside)
+  __device__ __forceinline__ uint32_t offset(float v, int c) const { return (__float_as_uint(v) << 1) - (low[c] << 1); }
+  __device__ __forceinline__ bool outside(float v, int c) const { return offset(v, c) >= span[c] << 1; }
+  // Whether some of N values a thread and column are outside and not zero, in any lane.
+  template <int N, class Value>
+  __device__ __forceinline__ bool some_outside(Value value) const {
+    uint32_t off[CT];
+    bool any = false;
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      off[c] = 0;
+#pragma unroll
+      for (int i = 0; i < N; ++i) off[c] = max(off[c], offset(value(i, c), c));
+      any = any || off[c] >= span[c] << 1;
+    }
+    if (__builtin_expect(__ballot(any) == 0, 1)) return false;
+    // (zeros come behind what is above the band, and before what is below)
+    any = false;
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      uint32_t most = 0;
+#pragma unroll
+      for (int i = 0; i < N; ++i) most = max(most, __float_as_uint(value(i, c)) << 1);
+      any = any || off[c] > 0u - (low[c] << 1) || most >= (low[c] + span[c]) << 1;
+    }
+    return __ballot(any) != 0;
+  }
+  __device__ __forceinline__ double down(int c) const { return __longlong_as_double((2046ll << 52) - __double_as_longlong(up[c])); }
+};
+
+// The state in LDS before the first walk.
+template <int CT>
+__device__ __forceinline__ void none_summed(Summed* summed, Left* left, uint32_t* counts) {
+  if (threadIdx.x <= kFixWaves) counts[threadIdx.x] = 0;
+  if (threadIdx.x < CT) {
+    summed[threadIdx.x].low = summed[threadIdx.x].high = 1;
+    summed[threadIdx.x].done = kFixInf;
+    left[threadIdx.x] = Left{0, 0};
+  }
 }
+
+// Of a value outside the band: whether it is still to be summed.
+__device__ __forceinline__ bool still_left(float v, const Summed& s) {
+  const uint32_t b = __float_as_uint(v) & 0x7fffffffu;
+  return b != 0 && b - s.low >= s.high - s.low && (b < s.done || b >= kFixInf);
+}
+
+// The values that a wavefront has kept aside, sum << 32 | value: kFixNear of them in LDS, up to `room` more in memory.
+struct Strays {
+  u64* near;
+  u64* far;
+  uint32_t room, n;                                      // (lanes that are out of rows keep an older n; lane 0 is the last of them)
+
+  // Lanes with `is`; whether their value found no room.
+  __device__ __forceinline__ bool add(bool is, uint32_t slot, float v) {
+    const uint64_t m = __ballot(is);
+    if (m == 0) return false;
+    const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, n));
+    const u64 entry = (u64)slot << 32 | __float_as_uint(v);
+    if (is && at < kFixNear) near[at] = entry;
+    else if (is && at - kFixNear < room) far[at - kFixNear] = entry;
+    n += (uint32_t)__popcll(m);
+    return is && at >= kFixNear + room;
+  }
+};
 
 // v moved across the lanes of a wavefront without LDS; lanes without a source get 0.
 template <int CTRL, int ROWS = 0xf>
 __device__ __forceinline__ uint32_t dpp(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, true);
 }
-constexpr int kRowShr = 0x110, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
+constexpr int kRowShr = 0x110, kRowRor = 0x120, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
 
 // Largest of a wavefront's values.
 __device__ __forceinline__ uint32_t largest_of_wave(uint32_t v) {
@@ -68,6 +176,14 @@ __device__ __forceinline__ uint32_t largest_of_wave(uint32_t v) {
   v = max(v, dpp<kRowBcast15, 0xa>(v));
   v = max(v, dpp<kRowBcast31, 0xc>(v));
   return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+}
+
+// Largest of sixteen lanes' values, in all of them.
+__device__ __forceinline__ uint32_t largest_of_row(uint32_t v) {
+  v = max(v, dpp<kRowRor + 1>(v));
+  v = max(v, dpp<kRowRor + 2>(v));
+  v = max(v, dpp<kRowRor + 4>(v));
+  return max(v, dpp<kRowRor + 8>(v));
 }
 
 // Sum of a wavefront's values, in its last lane.
@@ -81,17 +197,29 @@ __device__ __forceinline__ float sum_of_wave(float v) {
   return v;
 }
 
-// Largest of the threads' values, in every thread (one barrier).
-__device__ __forceinline__ uint32_t largest_of(uint32_t v, uint32_t* most) {
-  v = largest_of_wave(v);
-  if (threadIdx.x % kWave == 0) most[threadIdx.x / kWave] = v;
+// By column the second of the wavefronts' largest values (the largest where the others have nothing but zeros), in every thread (one
+// barrier): a value that stands out does not take the bits of all others.
+template <int CT>
+__device__ __forceinline__ void typical_largest(uint32_t (&v)[CT], uint32_t (*most)[kFixThreads / kWave]) {
+  constexpr int W = kFixThreads / kWave;
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    const uint32_t w = largest_of_wave(v[c]);
+    if (threadIdx.x % kWave == 0) most[c][threadIdx.x / kWave] = w;
+  }
   __syncthreads();
-  return largest_of_wave(most[threadIdx.x % (kFixThreads / kWave)]);
+  // (sixteen lanes a column; the lowest bits tell the wavefronts apart)
+  static_assert(W == 16 && CT * W <= kWave, "a row of lanes for each column");
+  const int l = (int)threadIdx.x % kWave;
+  const uint32_t x = l < CT * W ? (most[l / W % CT][l % W] & ~15u) | (uint32_t)(l % W) : 0;
+  const uint32_t first = largest_of_row(x), second = largest_of_row(x == first ? 0 : x), typical = second < 16 ? first : second;
+#pragma unroll
+  for (int c = 0; c < CT; ++c) v[c] = (uint32_t)__builtin_amdgcn_readlane((int)typical, c * W) & ~15u;
 }
 
-// A sum as a float.
-__device__ __forceinline__ float from_fixed(u64 v, double down) {
-  return (float)fma((double)(int)(v >> 32), down * 4294967296.0, (double)(uint32_t)v * down);
+// A sum in doubles.
+__device__ __forceinline__ double from_fixed(u64 v, double down) {
+  return fma((double)(int)(v >> 32), down * 4294967296.0, (double)(uint32_t)v * down);
 }
 
 __device__ __forceinline__ void add_fixed(u64* sum, u64 v) { __hip_atomic_fetch_add(sum, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
@@ -119,14 +247,170 @@ __device__ __forceinline__ void add_four(u64* acc, const uint32_t (&at)[4], In i
   }
 }
 
+// A sum that has gone out with its strays (a sum of a walk is less than 2^62).
+constexpr u64 kFixTaken = 1ull << 63;
+
+// Adds the lists of all wavefronts, which lie in LDS as a whole, to the walk's sums, in doubles.  The entries are put in order first.
+template <int CT>
+__device__ __forceinline__ void add_listed(u64* acc, u64* near, const uint32_t* listed, const Summed* summed) {
+  const int tid = (int)threadIdx.x;
+  const bool has = tid < kFixWaves * kFixNear && tid % kFixNear < (int)listed[tid / kFixNear];
+  u64 mine = 0;
+  int rank = 0, n = 0;
+  for (int w = 0; w < kFixWaves; ++w) n += (int)listed[w];
+  if (has) {
+    mine = near[tid];
+    for (int w = 0; w < kFixWaves; ++w)
+      for (int j = w * kFixNear; j < w * kFixNear + (int)listed[w]; ++j) rank += near[j] < mine || (near[j] == mine && j < tid) ? 1 : 0;
+  }
+  __syncthreads();
+  if (has) near[rank] = mine;
+  __syncthreads();
+  double t = 0.0;
+  int s = -1;
+  if (tid < n) {
+    s = (int)(near[tid] >> 32);
+    if (tid > 0 && (int)(near[tid - 1] >> 32) == s) s = -1;                // (its first entry adds them all)
+    for (int j = tid; s >= 0 && j < n && (int)(near[j] >> 32) == s; ++j) t += (double)__uint_as_float((uint32_t)near[j]);
+  }
+  __syncthreads();
+  if (s >= 0) {
+    t += from_fixed(acc[s], summed[s % CT].down);
+    near[tid] = (u64)__double_as_longlong(t);
+    acc[s] = kFixTaken | (u64)tid;
+  }
+  __syncthreads();
+}
+
+// Notes a value of column c that the walk leaves: the next one goes by the largest finite one, and by whether there are others.
+__device__ __forceinline__ void note_left(float v, int c, Left* left) {
+  const uint32_t b = magnitude(v);
+  if (b >= kFixInf) left[c].others = 1;
+  else if (b > *(volatile uint32_t*)&left[c].largest) atomicMax(&left[c].largest, b);
+}
+
+// A walk over what the wavefront has listed, or (sums: false) a look at what is left of it.
+template <int CT>
+__device__ __forceinline__ void walk_list(u64* acc, bool sums, const Bands<CT>& band, const Summed* summed, const Strays& strays, bool odd, float* out,
+                                          Left* left) {
+  const uint32_t n = min((uint32_t)__builtin_amdgcn_readfirstlane((int)strays.n), kFixNear + strays.room);
+  for (uint32_t i = threadIdx.x % kWave; i < n; i += kWave) {
+    const u64 entry = i < kFixNear ? strays.near[i] : strays.far[i - kFixNear];
+    const uint32_t s = (uint32_t)(entry >> 32);
+    const float v = __uint_as_float((uint32_t)entry);
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      if (s % CT != c) continue;
+      if (sums && !band.outside(v, c)) add_fixed(&acc[s], to_fixed(v, band.up[c]));
+      else if (!still_left(v, summed[c])) continue;
+      else if (odd) atomicAdd(out + s, v);
+      else note_left(v, c, left);
+    }
+  }
+}
+
+// What follows a walk over the rows or, once they are all there, over the lists: its sums go to out (rest: are added to what
+// earlier walks left there; by the same threads).  False: no more walks.  Else the next one's bands, and where it looks.
+template <int CT>
+__device__ __forceinline__ bool walk_done(u64* acc, int slots, int cleared, Bands<CT>& band, int bits, Summed* summed, Strays& strays, u64* near, uint32_t* counts,
+                                          Left* left, bool& lists, bool& rest, bool& odd, float* out) {
+  const int tid = (int)threadIdx.x;
+  if (!lists && tid % kWave == 0 && strays.n > 0) {
+    counts[tid / kWave] = strays.n;
+    atomicMax(&counts[kFixWaves], strays.n);
+  }
+  __syncthreads();
+  const uint32_t longest = counts[kFixWaves];            // list of a walk over the rows
+  const bool last = !lists && longest <= (uint32_t)kFixNear;
+  if (last && longest == 0 && !rest) {
+    const double d = summed[tid % CT].down;              // (of all sums of the thread, but for three columns)
+#pragma unroll 4
+    for (int s = tid; s < slots; s += kFixThreads) out[s] = (float)from_fixed(acc[s], CT == 3 ? summed[s % CT].down : d);
+    return false;
+  }
+  if (last && longest > 0) add_listed<CT>(acc, near, counts, summed);
+  for (int s = tid; s < slots; s += kFixThreads) {
+    const u64 v = acc[s];
+    if (rest && v == 0) continue;
+    double t = from_fixed(v, summed[s % CT].down);
+    if (last && longest > 0 && v >> 32 == kFixTaken >> 32) t = __longlong_as_double((long long)near[(uint32_t)v]);
+    out[s] = rest ? out[s] + (float)t : (float)t;
+  }
+  if (last) return false;
+  if (!lists) {
+    walk_list<CT>(acc, false, band, summed, strays, false, out, left);
+    lists = longest <= kFixNear + strays.room;
+    __syncthreads();
+  }
+  __builtin_amdgcn_s_waitcnt(0x0f70);                    // (vmcnt(0): other threads add infinities and NaN to out; a fence for the
+                                                         // device would write back the L2)
+  odd = true;
+  bool others = false;
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    odd = odd && left[c].largest == 0;
+    others = others || left[c].others != 0;
+    band.next(c, left[c].largest, bits, summed);
+  }
+  if (odd && !others) return false;
+  if (tid < CT) left[tid] = Left{0, 0};                  // (behind a barrier of the above)
+  for (int s = 2 * tid; s < cleared; s += 2 * kFixThreads) *reinterpret_cast<ulonglong2*>(acc + s) = ulonglong2{0, 0};
+  rest = true;
+  if (!lists) {
+    strays.n = 0;
+    if (tid <= kFixWaves) counts[tid] = 0;
+  }
+  __syncthreads();
+  return true;
+}
+
+// N rows' values of which some are outside the band: those still to be summed are listed, and all are made zero for the walk's
+// sums.  here(i): whether the thread has row i; value(i, c), clear(i, c); sum(i, s): the row's place among the sums of table s of NS,
+// or -1.  odd: a walk for infinities and NaN, which make the same of a sum in any order.
+template <int CT, int N, int NS, class Here, class Value, class Clear, class Sum>
+__device__ __forceinline__ void keep_aside(const Bands<CT>& band, const Summed* summed, Strays& strays, bool rest, bool odd, float* out, Left* left,
+                                           Here here, Value value, Clear clear, Sum sum) {
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    uint32_t mask = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (here(i) && band.outside(value(i, c), c) && value(i, c) != 0.0f && (!rest || still_left(value(i, c), summed[c]))) mask |= 1u << i;
+    while (__ballot(mask != 0) != 0) {                   // (one value of every thread at a time)
+      const int k = mask != 0 ? __builtin_ctz(mask) : -1;
+      float v = 0.0f;
+#pragma unroll
+      for (int i = 0; i < N; ++i) v = k == i ? value(i, c) : v;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        int place = -1;
+#pragma unroll
+        for (int i = 0; i < N; ++i) place = k == i ? sum(i, s) : place;
+        const uint32_t at = (uint32_t)(place * CT + c);
+        if (!odd) {
+          if (strays.add(place >= 0, at, v)) note_left(v, c, left);
+        } else if (place >= 0) {
+          atomicAdd(out + at, v);
+        }
+      }
+      mask &= mask - 1;
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (band.outside(value(i, c), c)) clear(i, c);
+  }
+}
+
 // A run's rows are blocks of 4096, every runs-th: rows in order of their keys then keep all workgroups of a range busy alike.
 // The runs of XCD x are those with run % 8 == x, whose workgroups for all ranges read the same rows at about the same time.
 template <int CT, bool ALIGNED>
 __global__ __launch_bounds__(kFixThreads, 4) void segfix_kernel(SegFixMulti m) {
   extern __shared__ __align__(16) u64 acc[];
-  __shared__ uint32_t most[kFixThreads / kWave];
-  __shared__ uint32_t found;
-  constexpr int U = CT == 1 ? 4 : CT == 2 ? 2 : 1;       // blocks a thread requests at once
+  __shared__ u64 near[kFixWaves * kFixNear];
+  __shared__ uint32_t most[CT][kFixWaves], counts[kFixWaves + 1];
+  __shared__ Summed summed[CT];
+  __shared__ Left left[CT];
+  constexpr int U = CT == 1 ? 2 : 1;       // blocks a thread requests at once
   const int x = (int)blockIdx.x % kSegSlices, i = (int)blockIdx.x / kSegSlices;
   int q = 0;
   while (q + 1 < m.n && i >= m.first[q + 1]) ++q;
@@ -166,93 +450,75 @@ __global__ __launch_bounds__(kFixThreads, 4) void segfix_kernel(SegFixMulti m) {
   Group g0, g1;
   request(u0, g0);
   clear();
-  if (tid == 0) found = 0;
+  none_summed<CT>(summed, left, counts);
   float* out = a.partial + ((int64_t)range * a.runs + run) * a.stride;
-  uint32_t beyond = 0, largest = 0;
+  uint32_t largest[CT];                                  // of the first rows
 #pragma unroll
-  for (int n = 0; n < U; ++n)
+  for (int c = 0; c < CT; ++c) {
+    largest[c] = 0;
 #pragma unroll
-    for (int c = 0; c < CT; ++c)
+    for (int n = 0; n < U; ++n)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) { const uint32_t b = magnitude(g0.y[n][c][r]); largest = b < kFixInf ? max(largest, b) : largest; }
-  FixScale sc = fix_scale(largest_of(largest, most), kFixHead, a.bits);
-  // The rows are walked once, in kSum.  Where a value is beyond the limit that the first rows gave, again: for the largest
-  // finite one, for the sums with that limit, and for what is not finite, which makes the same of a sum in any order.
-  enum { kSum, kLargest, kSumAgain, kOdd };
-  auto again = [&](int phase, uint32_t at, int c, float v) {
-    const uint32_t b = magnitude(v);
-    if (phase == kLargest) {
-      if (b < kFixInf) largest = max(largest, b); else beyond |= 2u;
-    } else if (at < keys) {
-      if (phase == kSumAgain && b < kFixInf) add_fixed(&acc[at * CT + c], to_fixed(v, sc.up));
-      if (phase == kOdd && b >= kFixInf) atomicAdd(&out[at * CT + c], v);
-    }
-  };
-  for (int phase = kSum;;) {
-    uint64_t over = 0;                                   // lanes that found a value beyond the limit
-    auto spend = [&](int64_t u, const Group& g) {
+      for (int r = 0; r < 4; ++r) {
+        const uint32_t b = magnitude(g0.y[n][(r * CT + c) / 4][(r * CT + c) % 4]);
+        largest[c] = b < kFixInf ? max(largest[c], b) : largest[c];
+      }
+  }
+  typical_largest<CT>(largest, most);
+  Bands<CT> band;
+#pragma unroll
+  for (int c = 0; c < CT; ++c) band.first(c, largest[c], a.bits, summed);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  Strays strays = {near + wave * kFixNear, a.far + ((int64_t)blockIdx.x * kFixWaves + wave) * a.room, (uint32_t)a.room, 0};
+  // a walk over the lists; one after the first; the one for infinities and NaN
+  bool lists = false, rest = false, odd = false;
+  for (;;) {
+    auto spend = [&](int64_t u, Group& g) {
+      auto value = [&](int i, int c) -> float { return g.y[i / 4][(i % 4 * CT + c) / 4][(i % 4 * CT + c) % 4]; };
+      if (__builtin_expect(band.template some_outside<4 * U>(value), 0)) {
+#pragma unroll
+        for (int n = 0; n < U; ++n)
+          keep_aside<CT, 4, 1>(
+              band, summed, strays, rest, odd, out, left,
+              [&](int r) { return u + n * stride < units && (uint32_t)(g.k[n][r] - key0) < keys; }, [&](int r, int c) { return value(4 * n + r, c); },
+              [&](int r, int c) { g.y[n][(r * CT + c) / 4][(r * CT + c) % 4] = 0.0f; }, [&](int r, int) { return g.k[n][r] - key0; });
+      }
 #pragma unroll
       for (int n = 0; n < U; ++n) {
         if (u + n * stride >= units) continue;
-        auto value = [&](int r, int c) { return g.y[n][(r * CT + c) / 4][(r * CT + c) % 4]; };
         uint32_t at[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) at[r] = (uint32_t)(g.k[n][r] - key0);
-        if (phase == kSum) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int c = 0; c < CT; ++c) over |= __ballot(!(fabsf(value(r, c)) < sc.limit));
-          add_four<CT>(acc, at, [&](int r) { return at[r] < keys; }, [&](int r, int c) { return to_fixed(value(r, c), sc.up); });
-        } else {
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int c = 0; c < CT; ++c) again(phase, at[r], c, value(r, c));
-        }
+        add_four<CT>(acc, at, [&](int r) { return at[r] < keys; }, [&](int r, int c) { return to_fixed(value(4 * n + r, c), band.up[c]); });
       }
     };
-    int64_t u = u0;
-    for (int it = 0; it < steps; it += 2) {
-      request(u + U * stride, g1);
-      spend(u, g0);
-      request(u + 2 * U * stride, g0);
-      spend(u + U * stride, g1);
-      u += 2 * U * stride;
-    }
-    if (tid < tail) {
-      const int64_t t = units * 4 + tid;
-      const uint32_t at = (uint32_t)(a.idx[t] - key0);
+    if (lists) {
+      walk_list<CT>(acc, true, band, summed, strays, odd, out, left);
+    } else {
+      int64_t u = u0;
+      for (int it = 0; it < steps; it += 2) {
+        request(u + U * stride, g1);
+        spend(u, g0);
+        request(u + 2 * U * stride, g0);
+        spend(u + U * stride, g1);
+        u += 2 * U * stride;
+      }
+      if (tail > 0) {
+        const bool has = tid < tail;
+        const int64_t t = units * 4 + (has ? tid : 0);
+        const uint32_t at = has ? (uint32_t)(a.idx[t] - key0) : keys;
+        float v[CT];
 #pragma unroll
-      for (int c = 0; c < CT; ++c) {
-        const float v = a.Y[t * CT + c];
-        if (phase != kSum) {
-          again(phase, at, c, v);
-        } else {
-          if (!(fabsf(v) < sc.limit)) beyond |= 1u;
-          else if (at < keys) add_fixed(&acc[at * CT + c], to_fixed(v, sc.up));
-        }
+        for (int c = 0; c < CT; ++c) v[c] = a.Y[t * CT + c];
+        keep_aside<CT, 1, 1>(band, summed, strays, rest, odd, out, left, [&](int) { return at < keys; },
+                             [&](int, int c) { return v[c]; }, [&](int, int c) { v[c] = 0.0f; }, [&](int, int) { return (int)at; });
+        if (at < keys)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) add_fixed(&acc[at * CT + c], to_fixed(v[c], band.up[c]));
       }
     }
-    if (over != 0) beyond |= 1u;
-    if (phase == kOdd) break;
-    if (beyond) atomicOr(&found, beyond);
-    __syncthreads();
-    if (phase == kSum && found != 0) {
-      beyond = 0;
-      phase = kLargest;
-    } else if (phase == kLargest) {
-      clear();
-      sc = fix_scale(largest_of(largest, most), 0, a.bits);             // (its barrier stands between clearing and adding)
-      phase = kSumAgain;
-    } else {
-      for (int s = tid; s < slots; s += kFixThreads) out[s] = from_fixed(acc[s], sc.down);
-      if ((found & 2u) == 0) break;
-      __threadfence();
-      __syncthreads();
-      phase = kOdd;
-    }
-    request(u0, g0);
+    if (odd || !walk_done<CT>(acc, slots, a.stride, band, a.bits, summed, strays, near, counts, left, lists, rest, odd, out)) break;
+    request(u0, g0);                                     // (also where it is not needed: else the rows live on in registers)
   }
 }
 
@@ -266,11 +532,13 @@ __global__ __launch_bounds__(kFixThreads, 4) void segfix_kernel(SegFixMulti m) {
 template <int NS, int CT, int MODE>
 __global__ __launch_bounds__(kFixThreads, 4) void asm_fix_kernel(AsmFix a) {
   extern __shared__ __align__(16) u64 acc[];
-  __shared__ uint32_t most[kFixThreads / kWave];
-  __shared__ uint32_t found;
+  __shared__ u64 near[kFixWaves * kFixNear];
+  __shared__ uint32_t most[CT][kFixWaves], counts[kFixWaves + 1];
+  __shared__ Summed summed[CT];
+  __shared__ Left left[CT];
   __shared__ float lsum[kFixThreads / kWave][CT];
   float* prod = reinterpret_cast<float*>(acc + (size_t)a.slots);
-  const int tid = (int)threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const int tid = (int)threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int units = (int)(a.r_T / 4);                    // groups of four rows
   const int u0 = (int)((int64_t)units * blockIdx.x / gridDim.x), u1 = (int)((int64_t)units * (blockIdx.x + 1) / gridDim.x);
   const int steps = (u1 - u0 + kFixThreads - 1) / kFixThreads;
@@ -318,21 +586,20 @@ __global__ __launch_bounds__(kFixThreads, 4) void asm_fix_kernel(AsmFix a) {
   if (tid < NS)
 #pragma unroll
     for (int c = 0; c < CT; ++c) prod[(a.off[tid] + a.keys[tid]) * CT + c] = 0.0f;
-  if (tid == 0) found = 0;
+  none_summed<CT>(summed, left, counts);
   __syncthreads();
 
   float loss[CT], lost[CT];
 #pragma unroll
   for (int c = 0; c < CT; ++c) loss[c] = lost[c] = 0.0f;
   float* out = a.partial + (int64_t)blockIdx.x * a.slots;
-  FixScale sc = {0.0f, 0.0, 0.0};
-  uint32_t beyond = 0, largest = 0;
-  // The rows are walked once, in kSum.  Where a value is beyond the limit that the first rows gave, again: for the largest
-  // finite one, for the sums with that limit, and for what is not finite, which makes the same of a sum in any order.
-  enum { kSum, kLargest, kSumAgain, kOdd };
-  for (int phase = kSum;;) {
+  Bands<CT> band;
+  Strays strays = {near + wave * kFixNear, a.far + ((int64_t)blockIdx.x * kFixWaves + wave) * a.room, (uint32_t)a.room, 0};
+  bool lists = false, rest = false, odd = false;         // (see segfix_kernel)
+  for (;;) {
+    if (lists) walk_list<CT>(acc, true, band, summed, strays, odd, out, left);
     int u = u0 + tid;
-    for (int it = 0; it < steps + (tail > 0 ? 1 : 0); ++it, u += kFixThreads) {
+    for (int it = lists ? steps + 1 : 0; it < steps + (tail > 0 ? 1 : 0); ++it, u += kFixThreads) {
       Group now = g;
       if (it + 1 < steps) request(u + kFixThreads, g);
       bool live = u < u1;
@@ -382,7 +649,7 @@ __global__ __launch_bounds__(kFixThreads, 4) void asm_fix_kernel(AsmFix a) {
             for (int c = 0; c < CT; ++c)
               if (r >= tail) e[r][c] = add[r][c] = 0.0f;
         }
-        if (phase == kSum) {
+        if (!rest) {
 #pragma unroll
           for (int c = 0; c < CT; ++c) {                 // compensated; what is infinite stays so
             const float t = ((add[0][c] + add[1][c]) + (add[2][c] + add[3][c])) - lost[c], sum = loss[c] + t;
@@ -391,74 +658,46 @@ __global__ __launch_bounds__(kFixThreads, 4) void asm_fix_kernel(AsmFix a) {
           }
         }
       }
-      if (phase == kSum && it == 0) {
+      if (!rest && it == 0) {
+        uint32_t largest[CT];
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+        for (int c = 0; c < CT; ++c) largest[c] = 0;
 #pragma unroll
-          for (int c = 0; c < CT; ++c) { const uint32_t b = magnitude(e[r][c]); largest = b < kFixInf ? max(largest, b) : largest; }
-        sc = fix_scale(largest_of(largest, most), kFixHead, a.bits);
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) { const uint32_t b = magnitude(e[r][c]); largest[c] = b < kFixInf ? max(largest[c], b) : largest[c]; }
+        typical_largest<CT>(largest, most);
+#pragma unroll
+        for (int c = 0; c < CT; ++c) band.first(c, largest[c], a.bits, summed);
       }
       if (!live) continue;
-      if (phase == kSum || phase == kSumAgain) {
+      if (__builtin_expect(band.template some_outside<4>([&](int r, int c) { return e[r][c]; }), 0))
+        keep_aside<CT, 4, NS>(
+            band, summed, strays, rest, odd, out, left, [](int) { return true; }, [&](int r, int c) { return e[r][c]; },
+            [&](int r, int c) { e[r][c] = 0.0f; },
+            [&](int r, int s) { return now.j[s][r] < a.off[s] + a.keys[s] ? now.j[s][r] : -1; });
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int c = 0; c < CT; ++c) {
-            const bool in = fabsf(e[r][c]) < sc.limit;   // (below the largest finite limit: finite)
-            beyond |= in ? 0u : 1u;
-            e[r][c] = in ? e[r][c] : 0.0f;
-          }
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          const uint32_t at[4] = {(uint32_t)now.j[s][0], (uint32_t)now.j[s][1], (uint32_t)now.j[s][2], (uint32_t)now.j[s][3]};
-          add_four<CT>(acc, at, [](int) { return true; }, [&](int r, int c) { return to_fixed(e[r][c], sc.up); });
-        }
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int c = 0; c < CT; ++c) {
-            const uint32_t b = magnitude(e[r][c]);
-            if (phase == kLargest) {
-              largest = b < kFixInf ? max(largest, b) : largest;
-            } else if (b >= kFixInf) {
-#pragma unroll
-              for (int s = 0; s < NS; ++s) atomicAdd(&out[now.j[s][r] * CT + c], e[r][c]);
-            }
-          }
+      for (int s = 0; s < NS; ++s) {
+        const uint32_t at[4] = {(uint32_t)now.j[s][0], (uint32_t)now.j[s][1], (uint32_t)now.j[s][2], (uint32_t)now.j[s][3]};
+        add_four<CT>(acc, at, [](int) { return true; }, [&](int r, int c) { return to_fixed(e[r][c], band.up[c]); });
       }
     }
-    if (phase == kSum) {
-      if (beyond) atomicOr(&found, 1u);
+    if (!rest) {
 #pragma unroll
       for (int c = 0; c < CT; ++c) {
         const float t = sum_of_wave(loss[c]);
         if (lane == kWave - 1) lsum[wave][c] = t;
       }
     }
-    __syncthreads();
-    if (phase == kOdd) break;
-    if (phase == kSum && tid < CT) {
+    const bool first = !rest;
+    const bool more = !odd && walk_done<CT>(acc, a.slots, a.slots, band, a.bits, summed, strays, near, counts, left, lists, rest, odd, out);
+    if (first && tid < CT) {                             // (behind a barrier of the above)
       float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-      for (int w = 0; w < kFixThreads / kWave; ++w) part[w / 4] += lsum[w][tid];
+      for (int w = 0; w < kFixWaves; ++w) part[w / 4] += lsum[w][tid];
       a.loss_partial[(int64_t)blockIdx.x * kNarrowCT + tid] = (part[0] + part[1]) + (part[2] + part[3]);
     }
-    const bool again = phase == kSum && found != 0;
-    if (!again && phase != kLargest) {
-      for (int s = tid; s < a.slots; s += kFixThreads) out[s] = from_fixed(acc[s], sc.down);
-      if (phase == kSum || !__syncthreads_or((int)beyond)) break;       // (beyond the largest finite one: not finite)
-      __threadfence();
-      __syncthreads();
-      phase = kOdd;
-    } else if (again) {
-      phase = kLargest;
-    } else {
-      clear();
-      sc = fix_scale(largest_of(largest, most), 0, a.bits);             // (its barrier stands between clearing and adding)
-      beyond = 0;
-      phase = kSumAgain;
-    }
+    if (!more) break;
     request(u0 + tid, g);
   }
 }
@@ -599,6 +838,12 @@ bool segfix_pays(int64_t r_T, const int64_t* rows, int n, int ncols, bool cut) {
   return 5.0 + segfix_share(r_T, rows, n, ncols).us < gather;
 }
 
+// Room of a wavefront's list in what is left of the scratch space.
+static int list_room(float* rest, int64_t floats, int64_t grid, unsigned long long** far) {
+  *far = reinterpret_cast<unsigned long long*>(rest);                        // (the runs' sums are whole float4s)
+  return (int)std::min<int64_t>(kFixFar, floats / 2 / (grid * kFixWaves));
+}
+
 hipError_t launch_segfix(const SegFix* a, int n, int ncols, float* scratch, int64_t scratch_floats, hipStream_t st) {
   if (n < 1 || n > kSegMulti || ncols < 1 || ncols > kNarrowCT) return hipErrorInvalidValue;
   SegFixMulti m;
@@ -623,7 +868,7 @@ hipError_t launch_segfix(const SegFix* a, int n, int ncols, float* scratch, int6
     int count = 1;
     s.runs = kSegSlices * s.nsub;
     const int64_t run = ((s.r_T + 4 * kFixThreads - 1) / (4 * kFixThreads) + s.runs - 1) / s.runs * (4 * kFixThreads);   // rows
-    while (((int64_t)1 << count) <= run) ++count;
+    while (((int64_t)1 << count) <= (s.longest > 0 ? std::min(run, s.longest) : run)) ++count;
     s.bits = std::min(50, 62 - count);
     s.partial = scratch + at;
     at += (int64_t)s.n_ranges * kSegSlices * s.nsub * s.stride;
@@ -632,6 +877,7 @@ hipError_t launch_segfix(const SegFix* a, int n, int ncols, float* scratch, int6
   if (at > scratch_floats) return hipErrorInvalidValue;
   const size_t lds = sizeof(u64) * (size_t)slots;
   const unsigned grid = (unsigned)m.first[n] * kSegSlices;
+  for (int q = 0; q < n; ++q) m.s[q].room = list_room(scratch + at, scratch_floats - at, grid, &m.s[q].far);
 #define ILARGI_SEGFIX(C)                                                              \
   {                                                                                   \
     if (aligned) segfix_kernel<C, true><<<grid, kFixThreads, lds, st>>>(m);           \
@@ -699,7 +945,9 @@ hipError_t launch_asm_fix(const LmmArgs& a, int mode, float* const* Z, float* sc
   // (balances 0.9 microseconds a round of 4096 rows and workgroup, against 0.5 a megabyte of their sums)
   const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(256.0, sqrt(440.0 * (double)units / f.slots)),
                                                                (units + kFixThreads / 2 - 1) / (kFixThreads / 2)));
-  if ((int64_t)grid * f.slots > scratch_floats) return hipErrorInvalidValue;
+  const int64_t floats = (int64_t)grid * f.slots;
+  if (floats > scratch_floats) return hipErrorInvalidValue;
+  f.room = list_room(scratch + floats, scratch_floats - floats, grid, &f.far);
   for (int s = 0; s < f.n; ++s) {
     f.idx[s] = a.g.idx[s]; f.P[s] = a.g.P[s]; f.keys[s] = (int)a.g.rows[s];
     SegFix& z = m.s[s];

@@ -121,3 +121,123 @@ def test_assembly_of_gathers_with_their_segment_sums(il, r_T, rows, kinds, m, mo
     else:
         assert torch.equal(first.isfinite(), want.isfinite())
     assert torch.equal(first.view(torch.int32), again.view(torch.int32)) and torch.equal(loss.view(torch.int32), loss2.view(torch.int32))
+
+
+def _one_hot(il, r_T, rows, kinds, gen):
+    """Tables with a column for every row: a cell of T^T Y is one key's sum."""
+    sources, c_T = _sources(r_T, rows, kinds, 0.1, gen)
+    out, at = [], 0
+    for (_, idx, _), r in zip(sources, rows):
+        ints = torch.arange(r + 1, device="cuda", dtype=torch.int32)
+        out.append((il.CSR(ints, ints[:r].contiguous(), torch.ones(r, device="cuda"), (r, r)), idx, list(range(at, at + r))))
+        at += r
+    return out, at
+
+
+def _sums_by_key(sources, Y):
+    Y, out = Y.double().cpu(), []
+    for D, idx, _ in sources:
+        idx = idx.cpu().long()
+        ok = idx >= 0
+        out.append(torch.zeros(D.shape[0], Y.shape[1], dtype=torch.float64).index_add_(0, idx[ok], Y[ok]))
+    return torch.cat(out)
+
+
+def _each_sum_close(got, want, size):
+    # a run's sum of a key is rounded a few times at most (once for each walk that found rows of it, and as often in adding
+    # these), and up to 256 runs are added in pairs of parts: sixteen roundings of what the key's values come to in magnitude
+    got = got.double().cpu()
+    assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got.isinf(), want.isinf()) and torch.equal(got[want.isinf()], want[want.isinf()])
+    ok = want.isfinite()
+    # (and where floats end, half of the smallest for each run)
+    assert bool(((got - want).abs() <= 2.0 ** -20 * size + 256 * 2.0 ** -150)[ok].all())
+
+
+@pytest.mark.parametrize("r_T,rows,kinds,cx", [
+    (2_500_001, [20_160], ["uniform"], 1),                            # one full range ...
+    (2_500_002, [20_161], ["sorted"], 1),                             # ... and a key more
+    (1_500_002, [100_000, 50_001, 9_999], ["uniform", "hot", "uniform"], 1),
+    (1_500_003, [10_208, 5_000], ["uniform", "sorted"], 2),
+    (2_500_001, [3_000, 6_806], ["hot", "uniform"], 3),
+    (1_500_001, [3_000, 5_105, 1], ["sorted", "uniform", "uniform"], 4),
+])
+@pytest.mark.parametrize("values", ["columns", "outliers", "small ones", "keys", "zeros", "wide", "smallest", "odd", "odd among small ones", "odd everywhere"])
+def test_every_sum_by_itself(il, r_T, rows, kinds, cx, values):
+    gen = torch.Generator(device="cuda").manual_seed(r_T + cx)
+    sources, c_T = _one_hot(il, r_T, rows, kinds, gen)
+    key = sources[0][1].clamp(min=0).long()
+    Y = torch.randn(r_T, cx, generator=gen, device="cuda")
+    u = torch.rand(r_T, generator=gen, device="cuda")
+    if values == "columns":
+        Y *= torch.tensor([1.0, 1e-9, 1e9, 1e-15][-cx:], device="cuda")
+    elif values == "outliers":                                        # with a key and without one
+        Y[r_T // 3], Y[r_T // 2, 0], Y[r_T - 2, cx - 1] = 1e12, 3e-20, -1e30
+        sources[0][1][r_T - 2] = -1
+    elif values in ("small ones", "odd among small ones"):            # more than a list in LDS holds, fewer than one in memory
+        Y *= torch.where(u < 0.03, 1e-12 * u, 1.0).unsqueeze(1)
+        if values != "small ones":
+            Y[(u < 0.03) & (key % 5 == 0)] = float("inf")
+            Y[(u < 0.01) & (key % 5 == 1)] = float("nan")
+    elif values == "keys":                                            # values of a size of each key's own
+        Y *= (10.0 ** (-4.0 * (key % 5))).unsqueeze(1)
+    elif values == "zeros":
+        Y[u < 0.9] = 0.0
+        Y[: r_T // 2] = 0.0
+    elif values == "wide":
+        Y *= torch.exp2(200.0 * u - 100.0).unsqueeze(1)
+    elif values == "smallest":
+        Y *= torch.where(key % 3 == 0, 1e-39, 1.0).unsqueeze(1)
+    elif values == "odd":
+        Y[r_T // 3, 0], Y[r_T // 2, cx - 1], Y[r_T - 1] = float("inf"), float("nan"), float("-inf")
+    elif values == "odd everywhere":
+        Y[(u < 0.2) & (key % 7 == 3)] = float("inf")
+        Y[(u > 0.9) & (key % 7 == 5)] = float("nan")
+        Y[(u > 0.5) & (key % 11 == 5)] = float("-inf")
+    plan = il.ilargi_plan_create(sources, r_T, c_T, max_cx=cx)
+    got = il.ilargi_tmm(plan, Y)
+    _each_sum_close(got, _sums_by_key(sources, Y), _sums_by_key(sources, Y.abs()))
+    assert torch.equal(il.ilargi_tmm(plan, Y).view(torch.int32), got.view(torch.int32))
+
+
+@pytest.mark.parametrize("r_T,rows,kinds,m", [
+    (600_001, [13_510], ["uniform"], 1),                              # as many keys as LDS holds
+    (100_003, [40, 30], ["hot", "uniform"], 4),
+    (600_003, [1_500, 3_000, 10], ["uniform", "uniform", "uniform"], 2),
+    (300_001, [1_000, 400, 3, 1], ["uniform", "hot", "uniform", "uniform"], 2),
+    (2_600_001, [300], ["sorted"], 3),
+])
+@pytest.mark.parametrize("case", ["a model that diverges", "keys", "labels of some rows", "small labels", "infinite labels"])
+def test_every_model_and_key_by_itself(il, r_T, rows, kinds, m, case):
+    gen = torch.Generator(device="cuda").manual_seed(r_T + m)
+    sources, c_T = _one_hot(il, r_T, rows, kinds, gen)
+    key = sources[0][1].clamp(min=0).long()
+    W = torch.zeros(c_T, m, device="cuda")
+    y = torch.randn(r_T, generator=gen, device="cuda")
+    if case == "a model that diverges":
+        W[:, m - 1] = 1e14 * torch.randn(c_T, generator=gen, device="cuda")
+    elif case == "keys":
+        y *= 10.0 ** (-4.0 * (key % 5))
+    elif case == "labels of some rows":
+        y[::100_000] = 1e20
+    elif case == "small labels":
+        u = torch.rand(r_T, generator=gen, device="cuda")
+        y *= torch.where(u < 0.03, 1e-15 * u, 1.0)
+        y[(u < 0.01) & (key % 5 == 0)] = float("-inf")
+    elif case == "infinite labels":
+        y[(torch.rand(r_T, generator=gen, device="cuda") < 0.2) & (key % 7 == 3)] = float("inf")
+    lr = torch.full((m,), 1e-3 * r_T, device="cuda")
+    z, size = torch.zeros(r_T, m, dtype=torch.float64, device="cuda"), y.double().abs().unsqueeze(1).expand(r_T, m).clone()
+    for D, idx, cols in sources:
+        p = torch.where((idx >= 0).unsqueeze(1), W[cols].double()[idx.clamp(min=0).long()], 0.0)
+        z += p
+        size += p.abs()
+    e = z - y.double().unsqueeze(1)
+    scale = lr.double().cpu() / r_T
+    want = W.double().cpu() - scale * _sums_by_key(sources, e)
+    plan = il.ilargi_plan_create(sources, r_T, c_T, max_cx=m)
+    got, loss, again = W.clone(), torch.empty(m, device="cuda"), W.clone()
+    il.ilargi_gd_step(plan, il.LINEAR, got, y, lr, loss)
+    il.ilargi_gd_step(plan, il.LINEAR, again, y, lr, loss)
+    # (the residual's own rounding and that of the updated weight among the sixteen)
+    _each_sum_close(got, want, scale * _sums_by_key(sources, size) + W.double().abs().cpu())
+    assert torch.equal(got.view(torch.int32), again.view(torch.int32))
