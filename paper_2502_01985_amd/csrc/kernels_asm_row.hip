@@ -153,10 +153,11 @@ __global__ __launch_bounds__(kBlock, 4) void asm_row_kernel(LmmArgs a) {
       }
     }
     float r[CT];
-    const bool live = i < a.r_out;
+    const bool live = i < a.r_out, has = i < a.d_rows;            // (a row beyond the table has no product, whatever the weights)
 #pragma unroll
     for (int n = 0; n < CT; ++n) {
       float l = 0.0f;
+      z[n] = has ? z[n] : 0.0f;
       if constexpr (MODE == 1) {
         r[n] = z[n] + more[n] - yi;
         l = r[n] * r[n];
@@ -174,7 +175,7 @@ __global__ __launch_bounds__(kBlock, 4) void asm_row_kernel(LmmArgs a) {
     // the gradient: four rows a product, 16 k + q for the lanes' groups k; what lies beyond the columns or the operand columns
     // goes to sums that nobody reads, and a row that the table does not feed has no part in it
 #pragma unroll
-    for (int n = 0; n < CT; ++n) res[lane * CT + n] = i < a.d_rows ? r[n] : 0.0f;
+    for (int n = 0; n < CT; ++n) res[lane * CT + n] = has ? r[n] : 0.0f;
     wave_sync();
     const float* ra = tile + k4 * 16 * ck + n16;
     const float* rb = res + k4 * 16 * CT + n16 % CT;

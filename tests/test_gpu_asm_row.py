@@ -14,9 +14,11 @@ def il():
     return mod
 
 
-def _step(il, sources, r_T, c_T, m, model, gen, y=None, feeds=None):
+def _step(il, sources, r_T, c_T, m, model, gen, y=None, infinite=None):
     """One step from random weights against float64; returns what it gave and what it should have."""
     W = torch.randn(c_T, m, generator=gen, device="cuda") / 4
+    if infinite is not None:
+        W[infinite] = float("inf")
     y = (torch.rand(r_T, generator=gen, device="cuda") < 0.5).float() if y is None else y
     lr = torch.linspace(0.1, 0.4, m, device="cuda")
     Wd = W.double()
@@ -68,20 +70,23 @@ def test_iteration_a_lane_per_row(il, r_T, tables, m, c, model):
 
 
 @pytest.mark.parametrize("m", [1, 3])
-@pytest.mark.parametrize("case", ["prefix", "infinite label beyond the table", "infinite value", "scattered columns", "shared columns"])
+@pytest.mark.parametrize("case", ["prefix", "infinite label beyond the table", "infinite weight", "infinite value", "scattered columns", "shared columns"])
 def test_iteration_a_lane_per_row_at_its_edges(il, case, m):
     gen = torch.Generator(device="cuda").manual_seed(3)
     r_T, c, rows = 50_001, 9, 400
     idx = torch.randint(0, rows, (r_T,), generator=gen, device="cuda", dtype=torch.int32)
     R = (torch.randn(rows, 5, generator=gen, device="cuda"), idx, list(range(c, c + 5)))
-    d_rows = 33_333 if case in ("prefix", "infinite label beyond the table") else r_T
+    d_rows = 33_333 if case in ("prefix", "infinite label beyond the table", "infinite weight") else r_T
     first = None
     if d_rows < r_T:                                       # the table feeds the first rows only
         first = torch.arange(r_T, device="cuda", dtype=torch.int32)
         first[d_rows:] = -1
     S = torch.randn(d_rows, c, generator=gen, device="cuda")
     y = (torch.rand(r_T, generator=gen, device="cuda") < 0.5).float()
-    cols = list(range(c))
+    cols, infinite = list(range(c)), None
+    if case == "infinite weight":                          # in the last model: rows that the table does not feed have no part in it
+        infinite = (4, m - 1)
+        idx[:d_rows] = -1
     if case == "infinite label beyond the table":
         y[r_T - 5] = float("inf")
     elif case == "infinite value":
@@ -90,11 +95,14 @@ def test_iteration_a_lane_per_row_at_its_edges(il, case, m):
         cols = cols[::-1]                                  # no block: another kernel
     elif case == "shared columns":
         R = (R[0], R[1], list(range(c - 2, c + 3)))
-    W, got, loss, step, want = _step(il, [(S, first, cols), R], r_T, c + 5, m, "linear", gen, y)
+    W, got, loss, step, want = _step(il, [(S, first, cols), R], r_T, c + 5, m, "linear", gen, y, infinite)
     finite = step.isfinite()
     if case == "infinite label beyond the table":          # the entity table's weights stay out of it
         assert bool(finite[:c].all()) and torch.equal(got.isfinite()[:c], finite[:c]) and not bool(got[c:].isfinite().any())
+    elif case == "infinite weight":
+        assert bool(finite[c:].all()) and bool(finite[:, :m - 1].all()) and not bool(finite[:c, m - 1].any())
+        assert torch.equal(got.isfinite(), finite)
     elif case == "infinite value":
         assert torch.equal(got.isfinite(), finite)
         return
-    assert (got.double() - (W.double() - step))[finite].norm() <= 2e-6 * step[finite].norm() + 2.0 ** -24 * W.double().norm()
+    assert (got.double() - (W.double() - step))[finite].norm() <= 2e-6 * step[finite].norm() + 2.0 ** -24 * W.double()[finite].norm()
