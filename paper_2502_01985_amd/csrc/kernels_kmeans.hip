@@ -208,6 +208,8 @@ __global__ __launch_bounds__(kLaneThreads, 3) void kmeans_lane_kernel(KmeansLane
         for (int n = 0; n < K; ++n) z[n] = fmaf(d[j], a.C[(int64_t)(a.t0 + j) * K + n], z[n]);
         j = j + 1 == ck ? 0 : j + 1;
       }
+#pragma unroll
+      for (int n = 0; n < K; ++n) z[n] = i < a.d_rows ? z[n] : 0.0f;   // (zeros beyond the table are no product)
     }
     int best = 0;
     float bv = norm[0] - 2.0f * (z[0] + g[0]);

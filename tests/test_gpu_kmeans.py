@@ -120,3 +120,25 @@ def test_kmeans_a_lane_per_row_at_its_edges(il, case):
         assert bool(cells.all())
     if case == "empty":
         assert torch.equal(Cd[:, 2], C[:, 2])
+
+
+@pytest.mark.parametrize("k", [3, 10, 16])
+def test_infinite_centroids_and_rows_that_the_table_does_not_feed(il, k):
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    r_T, c, d_rows = 140_001, 18, 70_003
+    sources, c_T = _schema(r_T, c, [(400, 11)], 0.1, gen, d_rows=d_rows)
+    T = _target(sources, r_T, c_T)
+    C = torch.randn(c_T, k, generator=gen, device="cuda")
+    C[1, 0] = float("inf")                                    # infinitely far from every row that does not have the column
+    C[2, k - 1] = float("-inf")
+    keep = list(range(1, k - 1))
+    plan = il.ilargi_plan_create(sources, r_T, c_T, max_cx=k)
+    Cd, assign, counts = C.clone(), torch.empty(r_T, device="cuda", dtype=torch.int32), torch.zeros(k, device="cuda", dtype=torch.int32)
+    il.ilargi_kmeans_step(plan, Cd, assign, counts)
+    Cn = C[:, keep].double()
+    terms = (Cn * Cn).sum(0), 2.0 * (T[d_rows:] @ Cn)
+    dist, a = terms[0] - terms[1], assign[d_rows:].long()
+    assert int(a.min()) >= 1 and int(a.max()) <= k - 2
+    # rounding of a score: 2^-24 of its terms, a few dozen of them
+    slack = 1e-5 * (terms[0].max() + 2.0 * (T[d_rows:].abs() @ Cn.abs()).max(1).values)
+    assert bool((dist.gather(1, (a - 1).unsqueeze(1)).squeeze(1) <= dist.min(1).values + slack).all())
