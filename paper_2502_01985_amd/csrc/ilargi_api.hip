@@ -1430,13 +1430,7 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
   hipStream_t st = static_cast<hipStream_t>(stream);
 
   HIP_TRY(hipMemsetAsync(pl->at<int32_t>(lay.o_flags), 0, sizeof(int32_t) * 4 * n, st));
-  bool count_lines = false;
-  for (const SourcePlan& p : pl->src) count_lines = count_lines || (!p.sparse && p.rows == r_T && lmm_lane_wants_lines(p.rows, p.cols));
-  {
-    bool gathers_alone = true;
-    for (const SourcePlan& p : pl->src) gathers_alone = gathers_alone && p.has_idx;
-    count_lines = count_lines || (gathers_alone && r_T >= 100000);
-  }
+  const bool count_lines = r_T >= 100000;     // (fewer rows: no choice asks how keys lie)
   std::vector<const int32_t*> tcol_ptrs(n);
   for (int k = 0; k < n; ++k) {
     SourcePlan& p = pl->src[k];
@@ -1546,8 +1540,9 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
   }
   // Segment sums in LDS: of the sources that have them at all (a table in join order has none).
   {
-    std::vector<int64_t> rows;
-    bool cut = false;
+    int64_t rows[kMaxSources], longest = 0;
+    bool in_order[kMaxSources], cut = false;
+    int live = 0;
     for (const SourcePlan& p : pl->src) {
       if (p.empty || p.ident) continue;
       ColredArgs c;
@@ -1556,13 +1551,15 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
       SegArgs sg = seg_args(pl, (int)(&p - pl->src.data()));
       sg.ncols = 1;
       if (!p.sparse && tmm_part_supported(c, &sg)) continue;
-      rows.push_back(p.rows);
+      rows[live] = p.rows;
+      in_order[live++] = keys_in_order(p.lines, p.rows);
+      longest = std::max<int64_t>(longest, p.longest);
       cut = cut || p.cut;
     }
     for (int cx = 1; cx <= std::min<int64_t>(max_cx, kNarrowCT); ++cx) {
-      pl->fix_cols[cx] = !rows.empty();
-      for (size_t i = 0; i < rows.size(); i += kSegMulti)
-        if (!segfix_pays(r_T, rows.data() + i, (int)std::min<size_t>(kSegMulti, rows.size() - i), cx, cut)) pl->fix_cols[cx] = false;
+      pl->fix_cols[cx] = live > 0;
+      for (int i = 0; i < live; i += kSegMulti)
+        if (!segfix_pays(r_T, rows + i, in_order + i, std::min(kSegMulti, live - i), cx, cut, longest)) pl->fix_cols[cx] = false;
     }
     if (pl->fix_cols[1] && max_cx == 1)
       for (SourcePlan& p : pl->src) p.sliced = false;

@@ -523,7 +523,9 @@ int64_t segsum_sliced_chunk_cap(int64_t nnz);
 // launch each.
 hipError_t launch_segsum_sliced(const SegArgs* a, int n, hipStream_t st);
 // Segment sums in fixed point in LDS of n <= kSegMulti sources, and the assembly of gathered products with them.
-bool segfix_pays(int64_t r_T, const int64_t* rows, int n, int ncols, bool cut);
+bool segfix_pays(int64_t r_T, const int64_t* rows, const bool* in_order, int n, int ncols, bool cut, int64_t longest);
+// lines: 128-byte lines of a column of the source that 64 target rows in a row read.
+inline bool keys_in_order(float lines, int64_t rows) { return lines < 2.5f && rows > 64; }
 hipError_t launch_segfix(const SegFix* a, int n, int ncols, float* scratch, int64_t scratch_floats, hipStream_t st);
 bool asm_fix_supported(const LmmArgs& a, int mode);
 bool asm_fix_pays(const LmmArgs& a, const float* lines);

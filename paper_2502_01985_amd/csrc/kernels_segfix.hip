@@ -815,27 +815,41 @@ FixShare segfix_share(int64_t r_T, const int64_t* rows, int n, int ncols) {
 }  // namespace
 
 // Whether the segment sums of n sources with so many rows run in LDS or gather (cut: some segment would be summed in chunks by a
-// launch of their own).  Both sides are estimates in microseconds, fitted to iterations over one to three joined tables.
-// Keys in order gain by gathering and not here, so sums in LDS are taken where evenly spread keys gain more than those lose.
+// launch of their own; longest: entries of the longest segment).  Both sides are estimates in microseconds, fitted to iterations
+// over one to three joined tables.  Keys in order gather well: by themselves for next to nothing below 1,500,000 rows, beside
+// others for less.  Rows of one key are added to one place of LDS one after the other, which costs several columns more.
 // Iterations, gathering / in LDS:
-//   one model      1,000,000 rows  20,000 uniform keys              38 / 40     gathers
-//                                  50,000 and 20,000                49 / 48     in LDS
-//                                  twice 3000                       44 / 39     in LDS
-//                  5,000,000 rows  20,000 uniform; in order         93 / 81; 77 / 79   in LDS
-//                                  180,000 uniform                  110 / 110
-//                                  100,000, 50,000 Zipf and 10,000  182 / 132   in LDS
-//   two models     1,000,000 rows  twice 3000                       62 / 47     in LDS
-//   three models   5,000,000 rows  three times 3000                 344 / 187   in LDS
-//                                  100,000, 50,000 and 10,000       377 / 417   gathers: too many ranges
-bool segfix_pays(int64_t r_T, const int64_t* rows, int n, int ncols, bool cut) {
+//   one model      1,000,000 rows  20,000 uniform keys              38 / 44     gathers
+//                                  50,000 and 20,000                49 / 49     in LDS
+//                                  three times 3000                 51 / 42     in LDS
+//                                  twice 20,000 in order            36 / 46     gathers
+//                                  50,000 in order and 20,000       42 / 46     gathers
+//                  5,000,000 rows  20,000 uniform; in order         93 / 84; 84 / 80   in LDS
+//                                  100,000, 50,000 Zipf and 10,000  178 / 132   in LDS
+//   two models     1,000,000 rows  three times 3000                 70 / 49     in LDS
+//   three models   1,000,000 rows  20,000, half of them one key     57 / 65     gathers
+//                  5,000,000 rows  three times 3000                 345 / 190   in LDS
+//                                  20,000 in order                  126 / 130   gathers
+//                                  100,000, 50,000 and 10,000       379         gathers: too many ranges
+bool segfix_pays(int64_t r_T, const int64_t* rows, const bool* in_order, int n, int ncols, bool cut, int64_t longest) {
   if (n < 1 || r_T < 100000 || n > kSegMulti) return false;
   int64_t ranges = 0;
-  for (int q = 0; q < n; ++q) ranges += (rows[q] + kFixSlots / ncols - 1) / (kFixSlots / ncols);
+  int ordered = 0;
+  for (int q = 0; q < n; ++q) {
+    ranges += (rows[q] + kFixSlots / ncols - 1) / (kFixSlots / ncols);
+    ordered += in_order[q] ? 1 : 0;
+  }
   if (ranges > 20) return false;
-  const double near = 1e-6 * n * (double)std::min<int64_t>(r_T, 1500000), far = 1e-6 * n * (double)std::max<int64_t>(r_T - 1500000, 0);
-  const double gather = 7.2 * near + 4.9 * far + (ncols - 1) * (2.6 * near + 3.6 * far) + (cut ? 5.0 : 0.0) +
-                        (r_T >= 1500000 ? std::max(0.0, 6.0 * n - 9.0) : 0.0);
-  return 5.0 + segfix_share(r_T, rows, n, ncols).us < gather;
+  const bool far_apart = r_T >= 1500000;                 // (the residual does not stay in an XCD's L2: segments are cut by slice)
+  const double all = 1e-6 * (double)r_T, near = std::min(all, 1.5), more = ncols - 1;
+  const double one = 7.2 * near + 4.9 * (all - near) + more * (2.6 * near + 3.6 * (all - near));
+  double gather = n * one + (cut ? 5.0 : 0.0) + (far_apart ? std::max(0.0, 6.0 * n - 9.0) : 0.0);
+  for (int q = 0; q < n; ++q) {
+    if (!in_order[q]) continue;
+    const double less = far_apart ? 5.0 + 1.7 * all + more * (0.8 + 0.4 * all) + 1e-3 * (double)rows[q] * (0.1 + 0.12 * ncols) : 0.0;
+    gather -= std::max(one - less, 0.0) * (ordered == n ? 1.0 : 0.4);
+  }
+  return 5.0 + segfix_share(r_T, rows, n, ncols).us + 2.2e-6 * (double)longest * ncols * more < gather;
 }
 
 // Room of a wavefront's list in what is left of the scratch space.
@@ -924,7 +938,7 @@ bool asm_fix_pays(const LmmArgs& a, const float* lines) {
   int in_order = 0;
   for (int s = 0; s < a.g.n; ++s) {
     keys += a.g.rows[s];
-    in_order += lines[s] < 2.5f && a.g.rows[s] > 64 ? 1 : 0;
+    in_order += keys_in_order(lines[s], a.g.rows[s]) ? 1 : 0;
   }
   const int64_t rows = in_order == 0 ? 40 : in_order < a.g.n ? 100 : 700;
   return a.r_out >= 100000 && a.r_out >= rows * keys * a.ncols;
