@@ -13,7 +13,11 @@
 // 256 columns (wider ones are read twice), and a gathered row narrower than 32 bytes still costs a 32-byte
 // fetch (the 4-byte gathers of a one-model pass are priced at 32 bytes each).
 // Launches are priced separately: a dependent launch costs a few microseconds whatever it moves, which decides
-// small schemas.
+// small schemas.  The pass over an identity source, whose workgroups' sums the update waits for, counts for more than one
+// (an iteration over a small joined table, pass and update: 6.1 to 7.8 microseconds).  The single-launch iteration of small
+// star joins is one workgroup: a longer launch, and what it reads at the rate of one compute unit.  Measured / predicted in
+// microseconds, one linear model: 300 x 4 alone 3.2 / 3.3, 4000 x 16 alone 6.9 / 6.2; 1000 x 4 and 1000 x 8 5.5 / 5.4,
+// 10,000 x 4 and 1000 x 8 8.4 / 8.2, 16,000 x 4 and 1000 x 16 12.7 / 11.1.
 // Stacked tables (an identity source that ends before the target table does: union-style integration) are the
 // one case where the shapes say how many target rows a gathered source reaches: at most its own row count.  If
 // fetching those rows once per target row is clearly cheaper than the factorized sequence, an iteration of one
@@ -28,6 +32,10 @@
 namespace {
 constexpr double kFusedMaxCols = 256.0;   // widest table whose product, residual and gradient share one pass
 constexpr double kMinFetch = 32.0;        // bytes a gathered row costs at least
+constexpr double kPassLaunches = 1.6;     // launches that a pass over an identity source counts for
+constexpr double kSmallLaunches = 1.3;    // launches that the single-launch iteration counts for ...
+constexpr double kSmallJoined = 0.6;      // ... and with a joined table more
+constexpr double kSmallShare = 1.0 / 55;  // share of the bandwidth that its one compute unit has
 }  // namespace
 
 extern "C" ilargi_status_t ilargi_choose(int n, const ilargi_source_t* sources, int64_t r_T, int64_t c_T,
@@ -76,7 +84,7 @@ extern "C" ilargi_status_t ilargi_choose(int n, const ilargi_source_t* sources, 
   const double passes = std::ceil((double)w.models / 4.0);
   const double vec = 4.0 * pass_models;                    // bytes of one row of an operand slice
   double b_fact = 0.0, join_fetch = 0.0;
-  int launches_fact = 2;                                   // assembly pass, update
+  double launches_fact = 2.0;                              // assembly pass, update
   for (int k = 0; k < n; ++k) {
     const double rk = (double)sources[k].rows, ck = (double)sources[k].cols;
     const bool sparse = sources[k].csr_rowptr != nullptr;
@@ -86,7 +94,7 @@ extern "C" ilargi_status_t ilargi_choose(int n, const ilargi_source_t* sources, 
     if (k == fused && !sparse) {
       const bool one_pass = ck <= kFusedMaxCols;
       b_fact += one_pass ? cells : 2.0 * cells;
-      launches_fact += one_pass ? 0 : 1;
+      launches_fact += one_pass ? kPassLaunches - 1.0 : 1.0;
       join_fetch += cells;
       continue;
     }
@@ -121,7 +129,17 @@ extern "C" ilargi_status_t ilargi_choose(int n, const ilargi_source_t* sources, 
     }
     return true;
   };
-  if (small_star(n, sources, r_T)) launches_fact = 1;
+  const bool small_fact = small_star(n, sources, r_T);
+  // seconds of such an iteration of one model: tables, labels, row index and inverse index, each once
+  const auto small_seconds = [&](int ns, const ilargi_source_t* s) {
+    double bytes = 4.0 * rT, more = 0.0;
+    for (int k = 0; k < ns; ++k) {
+      if (s[k].rows == 0 || s[k].cols == 0) continue;
+      bytes += 4.0 * (double)s[k].rows * (double)s[k].cols;
+      if (s[k].row_idx != nullptr) { bytes += 8.0 * rT; more = kSmallJoined; }
+    }
+    return bytes / (kSmallShare * bw) + (kSmallLaunches + more) * launch;
+  };
   {
     bool stacked = false, ok = w.models == 1;
     for (int k = 0; k < n; ++k)
@@ -138,9 +156,9 @@ extern "C" ilargi_status_t ilargi_choose(int n, const ilargi_source_t* sources, 
       fetch += 4.0 * (ident ? rk : std::min(rT, rk)) * ck;
       seq += (k == fused ? 4.0 : 8.0) * rk * ck + (ident ? 0.0 : 24.0 * rT);
     }
-    if (ok && stacked && live >= 2 && launches_fact != 1 && fetch <= 0.85 * seq) {
+    if (ok && stacked && live >= 2 && !small_fact && fetch <= 0.85 * seq) {
       b_fact = fetch + 4.0 * rT * (double)gathered + 4.0 * rT + 2.0 * vec * cT;
-      launches_fact = 2;
+      launches_fact = 2.0;
     }
   }
   const bool mat_one_pass = cT <= kFusedMaxCols;
@@ -148,16 +166,18 @@ extern "C" ilargi_status_t ilargi_choose(int n, const ilargi_source_t* sources, 
   ilargi_source_t joined_table;
   memset(&joined_table, 0, sizeof(joined_table));
   joined_table.rows = r_T; joined_table.cols = c_T;
-  const double launches_mat = small_star(1, &joined_table, r_T) ? 1.0 : (mat_one_pass ? 2.0 : 3.0);
   const double b_join = 4.0 * mT + join_fetch;
   out->bytes_factorized = b_fact * passes;
   out->bytes_materialized = b_mat * passes;
   out->bytes_join = b_join;
   const double it = (double)w.iterations;
   // (the single-launch iteration serves one model per launch)
-  const double fact_launches = launches_fact == 1 ? (double)w.models / passes : (double)launches_fact;
-  out->seconds_factorized = it * passes * (b_fact / bw + fact_launches * launch);
-  out->seconds_materialized = b_join / bw + launch + it * passes * (b_mat / bw + launches_mat * launch);
+  const double models = (double)w.models;
+  const double t_fact = small_fact ? models * small_seconds(n, sources) : passes * (b_fact / bw + launches_fact * launch);
+  const double t_mat = small_star(1, &joined_table, r_T) ? models * small_seconds(1, &joined_table)
+                                                         : passes * (b_mat / bw + (mat_one_pass ? 1.0 + kPassLaunches : 3.0) * launch);
+  out->seconds_factorized = it * t_fact;
+  out->seconds_materialized = b_join / bw + launch + it * t_mat;
   out->factorize = out->seconds_factorized <= out->seconds_materialized ? 1 : 0;
   return ILARGI_OK;
 }

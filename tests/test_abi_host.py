@@ -144,11 +144,22 @@ def test_choose_decision_follows_its_byte_model():
     # the join is paid once: a single iteration never repays it when the per-iteration times are close
     few = il.ilargi_choose(thin, 1_000_000, 50, iterations=1)
     assert few["factorize"] == 1 and few["bytes_join"] > few["bytes_materialized"] * 0.9
-    # tiny tables are decided by launches: a two-table star join with short rows runs an iteration as one launch
-    # against two for its joined table (whose 12-column rows are too many for the single-launch form) ...
+    # tiny tables are decided by launches.  A two-table star join with short rows runs an iteration as one launch of one
+    # workgroup, which reads what many of them share in the two launches of a joined table outside that form: 8.4 against 6.5
+    # microseconds for 10,000 x 4 and 1000 x 8, 10.7 against 7.7 with 16 columns joined ...
     tiny = il.ilargi_choose([(10_000, 4, False), (1_000, 8, True)], 10_000, 12)
-    assert tiny["factorize"] == 1
-    # ... while a tiny schema outside that form takes its several dependent launches against two
+    assert tiny["factorize"] == 0
+    assert il.ilargi_choose([(10_000, 4, False), (1_000, 16, True)], 10_000, 20)["factorize"] == 0
+    # ... 5.3 against 7.0 for 300 x 16 and 100 x 8, 6.3 against 7.5 for 1000 rows ...
+    assert il.ilargi_choose([(300, 16, False), (100, 8, True)], 300, 24)["factorize"] == 1
+    assert il.ilargi_choose([(1_000, 16, False), (100, 8, True)], 1_000, 24)["factorize"] == 1
+    # ... and 5.3 against 3.6 where the joined table runs as one launch too
+    assert il.ilargi_choose([(1_000, 4, False), (100, 8, True)], 1_000, 12)["factorize"] == 0
+    # a table alone costs the same on both sides, with several models too, and the join on top
+    for models in (1, 3):
+        alone = il.ilargi_choose([(1_000, 8, False)], 1_000, 8, models=models)
+        assert alone["factorize"] == 1 and alone["seconds_factorized"] == pytest.approx(alone["seconds_materialized"], rel=0.01)
+    # a tiny schema outside that form takes its several dependent launches against two
     tiny3 = il.ilargi_choose([(10_000, 4, False), (1_000, 8, True), (500, 4, True)], 10_000, 16)
     assert tiny3["factorize"] == 0
     # a small schema with a wide dimension table moves fewer bytes factorized but needs more launches: the
