@@ -297,7 +297,7 @@ bool kmeans_lane_supported(const KmeansLaneArgs& a, int k) {
   return true;
 }
 
-// Two workgroups a compute unit: every workgroup leaves a block of sums that a later launch adds up.
+// Three workgroups a compute unit (256 of them), as many as fit; each leaves a block of sums that a later launch adds up.
 int kmeans_lane_grid(int64_t r_T) { return (int)std::min<int64_t>(768, (r_T + kLaneThreads - 1) / kLaneThreads); }
 
 hipError_t launch_kmeans_lane(const KmeansLaneArgs& a, int k, int grid, hipStream_t st) {

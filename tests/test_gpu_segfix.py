@@ -44,20 +44,22 @@ def _exact_tmm(sources, Y):
 
 
 def _close(got, want):
+    """Each operand column by itself: what is large in one does not hide the others."""
     assert torch.equal(got.isfinite(), want.isfinite())
-    ok = want.isfinite()
-    assert (got.double() - want)[ok].norm() <= REL * want[ok].norm()
+    for g, w in zip(got.double().reshape(-1, got.shape[-1]).t(), want.reshape(-1, got.shape[-1]).t()):
+        ok = w.isfinite()
+        assert (g - w)[ok].norm() <= REL * w[ok].norm()
 
 
 @pytest.mark.parametrize("r_T,rows,kinds,cx", [
-    (2_500_000, [20_416], ["uniform"], 1),                            # one full range ...
-    (2_500_003, [20_417], ["uniform"], 1),                            # ... and a key more, rows beyond the last four
+    (2_500_000, [20_160], ["uniform"], 1),                            # one full range ...
+    (2_500_003, [20_161], ["uniform"], 1),                            # ... and a key more, rows beyond the last four
     (2_500_001, [2_000, 3], ["uniform", "hot"], 1),
     (1_500_002, [100_000, 50_001, 9_999], ["uniform", "hot", "uniform"], 1),
     (2_500_001, [30_000, 20_000], ["sorted", "uniform"], 1),          # four rows of a key side by side
-    (1_500_003, [10_208, 5_000], ["uniform", "sorted"], 2),
-    (2_500_001, [3_000, 6_806], ["hot", "uniform"], 3),
-    (1_500_001, [3_000, 5_105, 1], ["sorted", "uniform", "uniform"], 4),
+    (1_500_003, [10_080, 5_000], ["uniform", "sorted"], 2),
+    (2_500_001, [3_000, 6_721], ["hot", "uniform"], 3),
+    (1_500_001, [3_000, 5_041, 1], ["sorted", "uniform", "uniform"], 4),
 ])
 @pytest.mark.parametrize("values", ["normal", "late", "outlier", "odd", "tiny"])
 def test_segment_sums_in_fixed_point(il, r_T, rows, kinds, cx, values):
@@ -82,8 +84,8 @@ def test_segment_sums_in_fixed_point(il, r_T, rows, kinds, cx, values):
 @pytest.mark.parametrize("r_T,rows,kinds,m", [
     (100_000, [250], ["uniform"], 1),
     (100_003, [40, 30], ["hot", "uniform"], 4),
-    (600_001, [13_560], ["uniform"], 1),                              # as many keys as LDS holds
-    (540_002, [6_780, 6_776], ["uniform", "hot"], 1),
+    (600_001, [13_423], ["uniform"], 1),                              # as many keys as LDS holds
+    (540_002, [6_711, 6_711], ["uniform", "hot"], 1),
     (600_003, [1_500, 3_000, 10], ["uniform", "uniform", "uniform"], 3),
     (300_001, [1_000, 400, 3, 1], ["uniform", "hot", "uniform", "uniform"], 2),
     (2_600_001, [300], ["sorted"], 4),
@@ -116,7 +118,8 @@ def test_assembly_of_gathers_with_their_segment_sums(il, r_T, rows, kinds, m, mo
     il.ilargi_gd_step(plan, which, again, y, lr, loss2)
     if values != "odd":
         # the step's own error, and the rounding of the updated weight to float32
-        assert (first.double() - want).norm() <= REL * (want - Wd).norm() + 2.0 ** -24 * want.norm()
+        for got, w, w0 in zip(first.double().t(), want.t(), Wd.t()):                 # each model by itself
+            assert (got - w).norm() <= REL * (w - w0).norm() + 2.0 ** -24 * w.norm()
         _close(loss, per_row.mean(0))
     else:
         assert torch.equal(first.isfinite(), want.isfinite())
@@ -157,9 +160,9 @@ def _each_sum_close(got, want, size):
     (2_500_001, [20_160], ["uniform"], 1),                            # one full range ...
     (2_500_002, [20_161], ["sorted"], 1),                             # ... and a key more
     (1_500_002, [100_000, 50_001, 9_999], ["uniform", "hot", "uniform"], 1),
-    (1_500_003, [10_208, 5_000], ["uniform", "sorted"], 2),
-    (2_500_001, [3_000, 6_806], ["hot", "uniform"], 3),
-    (1_500_001, [3_000, 5_105, 1], ["sorted", "uniform", "uniform"], 4),
+    (1_500_003, [10_080, 5_000], ["uniform", "sorted"], 2),
+    (2_500_001, [3_000, 6_721], ["hot", "uniform"], 3),
+    (1_500_001, [3_000, 5_041, 1], ["sorted", "uniform", "uniform"], 4),
 ])
 @pytest.mark.parametrize("values", ["columns", "outliers", "small ones", "keys", "zeros", "wide", "smallest", "odd", "odd among small ones", "odd everywhere"])
 def test_every_sum_by_itself(il, r_T, rows, kinds, cx, values):
@@ -200,7 +203,7 @@ def test_every_sum_by_itself(il, r_T, rows, kinds, cx, values):
 
 
 @pytest.mark.parametrize("r_T,rows,kinds,m", [
-    (600_001, [13_510], ["uniform"], 1),                              # as many keys as LDS holds
+    (600_001, [13_423], ["uniform"], 1),                              # as many keys as LDS holds
     (100_003, [40, 30], ["hot", "uniform"], 4),
     (600_003, [1_500, 3_000, 10], ["uniform", "uniform", "uniform"], 2),
     (300_001, [1_000, 400, 3, 1], ["uniform", "hot", "uniform", "uniform"], 2),
