@@ -464,6 +464,21 @@ SegArgs seg_args(const ilargi_plan* pl, int k) {
   return a;
 }
 
+// Whether the segment sums of one of the sources, or of all, might run in LDS: known before the keys are looked at.
+bool segfix_may_pay(const ilargi_plan* pl) {
+  int64_t rows[kMaxSources];
+  const bool in_order[kMaxSources] = {};
+  int n = 0;
+  for (const SourcePlan& p : pl->src)
+    if (!p.empty && p.has_idx) rows[n++] = p.rows;
+  for (int cx = 1; cx <= std::min<int64_t>(pl->max_cx, kNarrowCT); ++cx) {
+    if (segfix_pays(pl->r_T, rows, in_order, n, cx, true, 0)) return true;
+    for (int k = 0; k < n; ++k)
+      if (segfix_pays(pl->r_T, rows + k, in_order, 1, cx, true, 0)) return true;
+  }
+  return false;
+}
+
 // Lanes (log2) that share a row or column of a sparse table in the lane-group products: about four entries each.
 int sparse_lanes(int64_t entries, int64_t n) {
   const int64_t avg = n > 0 ? (entries + n - 1) / n : 1;
@@ -1430,7 +1445,11 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
   hipStream_t st = static_cast<hipStream_t>(stream);
 
   HIP_TRY(hipMemsetAsync(pl->at<int32_t>(lay.o_flags), 0, sizeof(int32_t) * 4 * n, st));
-  const bool count_lines = r_T >= 100000;     // (fewer rows: no choice asks how keys lie)
+  // (how the keys lie matters to three choices; the segment sums ask where they may run in LDS)
+  bool count_lines = false, gathers_alone = true;
+  for (const SourcePlan& p : pl->src) count_lines = count_lines || (!p.sparse && p.rows == r_T && lmm_lane_wants_lines(p.rows, p.cols));
+  for (const SourcePlan& p : pl->src) gathers_alone = gathers_alone && p.has_idx;
+  count_lines = count_lines || (gathers_alone && r_T >= 100000) || segfix_may_pay(pl);
   std::vector<const int32_t*> tcol_ptrs(n);
   for (int k = 0; k < n; ++k) {
     SourcePlan& p = pl->src[k];
@@ -1552,7 +1571,7 @@ ilargi_status_t plan_create_impl(int n, const ilargi_source_t* sources, int64_t 
       sg.ncols = 1;
       if (!p.sparse && tmm_part_supported(c, &sg)) continue;
       rows[live] = p.rows;
-      in_order[live++] = keys_in_order(p.lines, p.rows);
+      in_order[live++] = count_lines && keys_in_order(p.lines, p.rows);
       longest = std::max<int64_t>(longest, p.longest);
       cut = cut || p.cut;
     }
