@@ -524,8 +524,8 @@ __global__ __launch_bounds__(kFixThreads, 4) void segfix_kernel(SegFixMulti m) {
 
 // The assembly of gathered products alone, with residual and loss, and the segment sums of the residual: products and sums of
 // all tables in LDS, the residual never written.  MODE 1 linear, 2 logistic.  NS: tables.
-// 1,000,000 rows over 6040 and 3710 keys, one logistic model: 12.5 microseconds and 4 for the workgroups' sums, where assembly,
-// segment sums and their runs' sums took 8, 10 and 4.5 (an iteration with 250,000 sparse cells 30 -> 24).  About 9 of the 12.5
+// 1,000,000 rows over 6040 and 3710 keys, one logistic model: 12.9 microseconds and 4 for the workgroups' sums, where assembly,
+// segment sums and their runs' sums took 8, 10 and 4.5 (an iteration with 250,000 sparse cells 30 -> 24).  About 9 of the 12.9
 // are there with any number of rows: the launch, the round trips for indices and products, the sums' way out.  Hence few
 // workgroups: 64 to 256 take 13.8, 12.0 (128), 13.1, and the sums of 256 take a microsecond longer to add up.
 // A row without a key takes the place after its table's last: a product of zero, and a sum that nobody reads.
@@ -929,9 +929,9 @@ bool asm_fix_supported(const LmmArgs& a, int mode) {
 
 // Whether it pays: the more sums there are, the more rows it takes to make up for clearing and adding up the workgroups' copies.
 // lines[s]: lines of a product that 64 target rows in a row read; keys in order (one or two lines) gather well, so they ask for
-// more rows.  Iterations of one to four logistic models, separate launches / one: 1,000,000 rows over 300 keys 42 / 20, over 3000
-// 31 / 23 (four models 55 / 40), over 12,000 32 / 27, over twice 6000 38 / 28, over 3000 in order 22 / 24; 300,000 over 3000
-// 21 / 22, over twice 300 and more 24 / 19; 100,000 over 3000 19 / 20 (four models 24 / 29); 3,000,000 over three times 2000
+// more rows.  Iterations of one to four logistic models, separate launches / one: 1,000,000 rows over 300 keys 42 / 19, over 3000
+// 31 / 23 (four models 56 / 42), over 12,000 32 / 27, over twice 6000 38 / 27, over 3000 in order 23 / 23; 300,000 over 3000
+// 22 / 20, over 300 25 / 18; 100,000 over 3000 19 / 20 (four models 24 / 29); 3,000,000 over three times 2000
 // 74 / 33, over 3000 in order 38 / 27.
 bool asm_fix_pays(const LmmArgs& a, const float* lines) {
   int64_t keys = 0;
