@@ -246,7 +246,7 @@ struct SegFixMulti {
 
 // The assembly of gathered products alone with the segment sums of its residual (kernels_segfix.hip).
 constexpr int kAsmFixSources = 4;
-constexpr int kAsmFixSlots = 13424;       // sums of 64 bits and products of 32 a workgroup holds
+constexpr int kAsmFixSlots = 13420;       // sums of 64 bits and products of 32 a workgroup holds
 struct AsmFix {
   int n;
   const int32_t* idx[kAsmFixSources];

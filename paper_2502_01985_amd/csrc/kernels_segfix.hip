@@ -57,6 +57,14 @@ constexpr uint32_t kFixInf = 0x7f800000u;
 struct Summed { double down; uint32_t low, high, done; };
 struct Left { uint32_t largest, others; };
 
+// What the kernels of up to four operand columns hold in LDS beside their sums (loss: the assembly's), and that there is room for it.
+constexpr size_t lds_beside(bool loss) {
+  const size_t column = sizeof(uint32_t) * kFixWaves + sizeof(Summed) + sizeof(Left) + (loss ? sizeof(float) * kFixWaves : 0);
+  return (sizeof(u64) * kFixWaves * kFixNear + sizeof(uint32_t) * (kFixWaves + 1) + kNarrowCT * column + 15) / 16 * 16;
+}
+static_assert(lds_beside(false) + sizeof(u64) * kFixSlots <= 160 * 1024, "sums in LDS");
+static_assert(lds_beside(true) + (sizeof(u64) + sizeof(float)) * kAsmFixSlots <= 160 * 1024, "sums and products in LDS");
+
 // The magnitudes that a walk sums, by column: [low, low + span), multiples of the unit, 1 / up.
 template <int CT>
 struct Bands {

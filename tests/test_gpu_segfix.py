@@ -84,8 +84,10 @@ def test_segment_sums_in_fixed_point(il, r_T, rows, kinds, cx, values):
 @pytest.mark.parametrize("r_T,rows,kinds,m", [
     (100_000, [250], ["uniform"], 1),
     (100_003, [40, 30], ["hot", "uniform"], 4),
-    (600_001, [13_423], ["uniform"], 1),                              # as many keys as LDS holds
-    (540_002, [6_711, 6_711], ["uniform", "hot"], 1),
+    (600_001, [13_419], ["uniform"], 1),                              # as many keys as LDS holds ...
+    (540_002, [6_711, 6_707], ["uniform", "hot"], 1),
+    (600_001, [3_351], ["uniform"], 4),                               # ... of four models
+    (600_001, [3_355], ["uniform"], 4),                               # ... and a few more
     (600_003, [1_500, 3_000, 10], ["uniform", "uniform", "uniform"], 3),
     (300_001, [1_000, 400, 3, 1], ["uniform", "hot", "uniform", "uniform"], 2),
     (2_600_001, [300], ["sorted"], 4),
@@ -203,7 +205,7 @@ def test_every_sum_by_itself(il, r_T, rows, kinds, cx, values):
 
 
 @pytest.mark.parametrize("r_T,rows,kinds,m", [
-    (600_001, [13_423], ["uniform"], 1),                              # as many keys as LDS holds
+    (600_001, [13_419], ["uniform"], 1),                              # as many keys as LDS holds
     (100_003, [40, 30], ["hot", "uniform"], 4),
     (600_003, [1_500, 3_000, 10], ["uniform", "uniform", "uniform"], 2),
     (300_001, [1_000, 400, 3, 1], ["uniform", "hot", "uniform", "uniform"], 2),
